@@ -22,8 +22,8 @@ int make_plan(const tc_params* p, Plan* pl) {
       p->eig_method < TC_EIG_AUTO || p->eig_method > TC_EIG_TRIDIAGONAL || p->n_prompt_queries < 0 ||
       (int64_t)p->vis_start + p->n_vis + p->n_prompt_queries > p->seq_len)
     return TC_ERR_PARAM;
-  // the tridiagonal route works in float64 and keeps its panels in the LDS of one compute unit
-  const bool direct_ok = p->eig_dtype == TC_EIG_F64 && p->n_vis <= 1024 && tridiag_panel_width(p->n_vis) >= 4;
+  // the tridiagonal route works in float64
+  const bool direct_ok = p->eig_dtype == TC_EIG_F64 && p->n_vis <= 1024 && tridiag_fits(p->n_vis);
   if (p->eig_method == TC_EIG_TRIDIAGONAL && !direct_ok) return TC_ERR_PARAM;
   if (p->k_final < 1 || p->k_final > p->k_prune || p->k_prune > p->n_vis) return TC_ERR_PARAM;
   const int nA = p->k_prune / 2, nB = p->k_prune - nA;
@@ -83,7 +83,9 @@ int make_plan(const tc_params* p, Plan* pl) {
     q.off_td_tw = take(B * Np * Np * 16);      // pivots and multipliers of the twisted factorisations
     q.off_td_Cpart = take(B * nstrip * Np * 8);
     q.off_td_Tf = take(B * ((N + 15) / 16) * 256 * 4);   // T factors of the blocks of 16 reflectors
-    q.off_td_tab = take(B * Np * 24 * 4);                // wavefront assignments of the reduction, one table per image slot
+    q.td_sync_bytes = tridiag_sync_bytes(q.N, q.batch_call);
+    q.off_td_sync = take(B * q.td_sync_bytes);           // exchange memory of the reduction
+    q.off_td_fail = take(B * 4);
   }
   q.total = off > 0 ? off : 256;
   return TC_OK;
@@ -101,25 +103,24 @@ static int direct_chain(const Plan& pl, const Plan& sub, int img0, const tc_para
   float* tauv = at<float>(ws, pl.off_td_tau) + i0 * Np;
   float* Vc = at<float>(ws, pl.off_U) + i0 * Np * Np;
   double* tw = at<double>(ws, pl.off_td_tw);
-  // (the panels of the reduction pass through the start of the image's pivot scratch, which is idle until stage 2)
-  int rc = launch_tridiag(sub, G, dvec, evec, tauv, Vc, tw + i0 * Np * Np, Np * Np, at<int>(ws, pl.off_td_tab) + i0 * Np * 24, st);
+  int32_t* fail = at<int32_t>(ws, pl.off_td_fail) + i0;
+  int rc = launch_tridiag(sub, G, dvec, evec, tauv, Vc, at<char>(ws, pl.off_td_sync) + i0 * pl.td_sync_bytes, pl.td_sync_bytes, fail, st);
   if (rc != TC_OK) return rc;
   return launch_td_eigen(sub, dvec, evec, tauv, Vc, at<double>(ws, pl.off_td_lam) + i0 * Np, at<int2>(ws, pl.off_td_blk) + i0 * Np,
                          at<double>(ws, pl.off_td_tnorm) + i0, tw + i0 * Np * Np, tw + ((size_t)pl.B + i0) * Np * Np,
                          at<float>(ws, pl.off_td_W) + i0 * Np * Np, at<double>(ws, pl.off_td_rn) + i0 * Np,
-                         at<int32_t>(ws, pl.off_td_bad) + i0, at<double>(ws, pl.off_sig) + i0 * Np,
+                         at<int32_t>(ws, pl.off_td_bad) + i0, fail, at<double>(ws, pl.off_sig) + i0 * Np,
                          at<double>(ws, pl.off_td_wgt) + i0 * Np, at<double>(ws, pl.off_td_Cpart) + i0 * nstrip * Np,
                          at<float>(ws, pl.off_td_Tf) + i0 * npanel * 256, p->sv_rtol, vectors, C_ws ? C_ws + i0 * pl.N : nullptr,
                          ics ? ics + i0 * pl.N : nullptr, sigma ? sigma + i0 * pl.N : nullptr, info ? info + i0 : nullptr, st);
 }
 
 // Attention (when Q is given), Gram matrix, eigen-decomposition and Eq. 3-6 / 3-8.
-// Tridiagonal route: the batch is cut into groups of images (two by default from 16 images on, up to four on
-// request) whose chains run on the library's helper streams, each group starting when the one before it has
-// formed its Gram matrices.  The reduction to tridiagonal form keeps one compute unit per image busy for most
-// of the call and is bound by latency, so the kernels of the other groups fill the rest of the chip meanwhile.
-// The gain is small (about 2 % at 64 images): every kernel after the reduction is latency-bound as well and
-// takes as long for half the batch as for all of it.
+// Tridiagonal route: the batch can be cut into groups of images whose chains run on the library's helper streams, each
+// group starting when the one before it has formed its Gram matrices.  The reduction holds the registers of four
+// compute units per image for as long as it runs (64 images of 576 tokens: the whole chip), so there is nothing to
+// fill with another group's kernels until the images need more than one round over the chip: one group up to 64
+// images (6.63 ms against 7.22 ms with two for 64 images of 576 tokens), two above (12.83 against 13.03 ms for 128).
 static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const void* K, const void* V, void* O,
                        float* S, float* score, float* ics, float* sigma, int32_t* info, void* ws, hipStream_t st) {
   if (pl.method != TC_EIG_TRIDIAGONAL) {
@@ -134,7 +135,7 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
     return launch_scores(pl, p->eig_dtype, G, U, state, S, p->lambda, p->norm_mode, p->sv_rtol, at<char>(ws, pl.off_sig),
                          at<float>(ws, pl.off_C), score, ics, sigma, info, st);
   }
-  int groups = pl.groups > 0 ? pl.groups : (pl.B >= 16 ? 2 : 1);
+  int groups = pl.groups > 0 ? pl.groups : (pl.B > 64 ? 2 : 1);
   if (groups > pl.B) groups = pl.B;
   if (profiling_active()) groups = 1;  // per-kernel timing wants kernels that run alone
   hipStream_t streams[4];

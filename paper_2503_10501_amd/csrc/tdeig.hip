@@ -39,8 +39,8 @@ typedef double tb_pair __attribute__((ext_vector_type(2)));
 // is cleared.
 __global__ __launch_bounds__(256) void td_prepare_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
                                                          double* __restrict__ prep, size_t prep_stride,
-                                                         double* __restrict__ tnorm, int32_t* __restrict__ bad, int N,
-                                                         int Np) {
+                                                         double* __restrict__ tnorm, int32_t* __restrict__ bad,
+                                                         const int32_t* __restrict__ fail, int N, int Np) {
   __shared__ double wmax[4];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* db = dvec + (size_t)b * Np;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void td_prepare_kernel(const double* __restric
     pr[i] = i < N ? tb_pair{db[i] * down, e > split ? (e * down) * (e * down) : 0.0} : tb_pair{0.0, 0.0};
     if (i < N) esc[i] = e * down;
   }
-  if (tid == 0) { tnorm[b] = tn; bad[b] = 0; }
+  if (tid == 0) { tnorm[b] = tn; bad[b] = fail[b] ? 4 : 0; }
 }
 
 // G = 1 << gs lanes per eigenvalue; blockIdx.y = image.  A step evaluates the number of eigenvalues below G
@@ -740,13 +740,13 @@ __global__ __launch_bounds__(256) void td_ics_finish_kernel(const double* __rest
 }
 
 int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, const float* tauv, const float* Vc,
-                    double* lam, int2* blk, double* tnorm, double* DP, double* DM, float* W, double* rn, int32_t* bad,
+                    double* lam, int2* blk, double* tnorm, double* DP, double* DM, float* W, double* rn, int32_t* bad, const int32_t* fail,
                     double* sig, double* wgt, double* Cpart, float* Tf, float sv_rtol, bool vectors, float* C, float* C_out,
                     float* sigma_out, int32_t* info_out, hipStream_t st) {
   const int N = pl.N, Np = pl.Np, B = pl.B;
   // (the scaled copy of T lives at the start of each image's region of DP until the factorisations overwrite it)
   const size_t prep_stride = (size_t)Np * Np;
-  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, DP, prep_stride, tnorm, bad, N, Np)));
+  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, DP, prep_stride, tnorm, bad, fail, N, Np)));
   // lanes per eigenvalue: as many as keep the launch near one wavefront per SIMD (by the size of the whole call, so
   // that an image's result does not depend on how the call is cut into stream groups)
   const int gs = pl.batch_call <= 16 ? 3 : pl.batch_call <= 32 ? 2 : pl.batch_call <= 128 ? 1 : 0;

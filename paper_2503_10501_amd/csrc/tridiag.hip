@@ -3,473 +3,611 @@
 // so that the singular vectors of Section 3.3.1 (Z = U Sigma V^T, Z Z^T = U Sigma^2 U^T) become
 // U = Q W with T W = W Sigma^2 (stages 2 and 3: tdeig.hip).
 //
-// The columns of an image are reduced by one workgroup of 16 wavefronts.  The reduction is bound by
-// memory: column j needs the product of the trailing (N-j-1)^2 matrix with v_j.  Measured on MI355X a
-// single workgroup streams 110 to 150 GB/s out of its L2 and 64 of them together 5 to 6 TB/s, which is what
-// the fabric delivers to any number of compute units for a working set of this size, so one compute unit
-// per image is enough for the products at batch 64.
+// Column j needs p = A v_j over the whole trailing matrix, then A <- A - v w^T - w v^T.  From memory that is one
+// pass over the matrix per column (or a pass for the product and one for the update per panel), and one compute unit
+// per image is bound by what its memory path delivers: 3.5 us of steps plus up to 16 us of product per column at 576
+// tokens.  Here the trailing matrix never leaves the registers: a group of P workgroups, one per compute unit, holds
+// the lower triangle of one image in its vector registers (90 doubles per thread of 512, 368 KB per compute unit:
+// four compute units for 576 tokens, so 64 images fill the 256 of the chip), updates it in place and forms the
+// product in the same sweep.  What is left per column is latency: one exchange of the partial products between the
+// workgroups of the group (about 1.1 us inside an XCD), a handful of barriers, and the arithmetic (4 fused
+// multiply-adds per element of the triangle).
 //
-// The trailing matrix is only rewritten once per panel of nb columns (the scheme of LAPACK's
-// dlatrd/dsytrd): inside a panel the reflectors v and the vectors w of the rank-2 updates
-// A <- A - v w^T - w v^T are kept in LDS (panels Vp, Wp) and applied on the fly to the column being
-// reduced and to the matrix-vector product (tridiag_panel_kernel, one launch per panel).  The panels then
-// go to global memory and the trailing matrix gets the rank-2nb update on the matrix cores from a launch
-// of its own that spreads over the whole chip (tridiag_update_kernel: computed for the lower triangle,
-// stored to both): inside the panel kernel the update ran on one compute unit per image, 2 of its 10.7 ms
-// per batch of 64 and of its 9.3 ms for one image.
+// Frame.  The matrix is placed at the end of a frame of F x F (row f of the frame is row f + base of the matrix).
+// Wavefront w of workgroup (a, b) owns the rows f = i R + 8 a + w (i < LI) and lane l the columns k C + 64 b + l (k < LK), R = 8 PR
+// rows and C = 64 PC columns per step, cyclic in both directions so that every thread keeps its share as the trailing
+// matrix shrinks; element (i, k) is kept when i >= RT k, RT = C / R: the blocks below the diagonal, and in full
+// (both triangles) the C x C blocks on the diagonal.  An element below the diagonal blocks counts twice (row sum and
+// column sum), one inside them only for the column sum; no element needs a mask.
+//   MODE 0  one workgroup, F = 256: no exchange at all
+//   MODE 1  PC = 1, four workgroups, F = 576: every workgroup publishes its partial of p and its rows of the next
+//           column, everybody reads the four partials and adds them in the same order
+//   MODE 2  PC >= 2, P = 4 PC^2, F = 576 PC: the partials of an element (PR column sums, PC row sums) are added by one
+//           workgroup, which publishes the total (two exchanges, but every workgroup reads F values, not 5 PC F)
+// The O(F) part of a column (w, the next column, its reflector) is done by every workgroup for itself, bit for bit
+// the same.
 //
-// G is symmetric and stored in full.  The product p = A v reads 128-column groups of rows (a lane owns two
-// neighbouring columns, loads are 16 bytes wide and contiguous across the wavefront).  Inside the diagonal
-// block of a column group both triangles are read and a row only adds to the column sums
-// p_c += A[r][c] v_r, which need no exchange between lanes; a row below the block is fetched once and used
-// twice, for the column sums and for its own row sum sum_c A[r][c] v_c over the group's columns (the mirror
-// image above the diagonal is never read), added up over the lanes eight rows at a time.  That is 0.58 of
-// the elements of the full trailing matrices at 576 tokens.  The 16 wavefronts are dealt to the column
-// groups in proportion to their rows (tridiag_table_kernel); every partial sum has one writer and the sums
-// are added in a fixed order (results are bit-reproducible).
+// Exchange.  Values are published with relaxed agent-scope stores and polled with relaxed agent-scope loads; the lowest
+// mantissa bit of a value carries the parity of its use of the slot (two slots, used in turn), so a value announces
+// itself and no fence or flag is needed.  A slot is written again two columns later, when every workgroup has
+// published the column in between and therefore read this one.  Every wait is bounded (TD_SPIN polls); a workgroup
+// that gives up raises the image's failure flag, its group follows, and the caller reports the image as failed.
+// A group's workgroups have neighbouring ids, so the groups of a launch become resident in order and the first
+// incomplete one is the only one that waits for a compute unit; launches whose groups could block each other when
+// several streams run them at once are kept apart by the host (see launch_tridiag).
+#include <mutex>
+#include <utility>
+
 #include "tc_internal.h"
 
 namespace tc {
 
-typedef __attribute__((ext_vector_type(2))) double d2;
-typedef __attribute__((ext_vector_type(4))) double d4;
+typedef unsigned long long u64;
 
-constexpr int TD_THREADS = 1024;
-constexpr int TD_WAVES = TD_THREADS / 64;
-constexpr int TD_LDS_BYTES = 160 * 1024;  // LDS of one compute unit, all of it for the one workgroup
+constexpr int TR_THREADS = 512;
+constexpr int TR_WAVES = TR_THREADS / 64;
+constexpr int TD_SPIN = 1 << 22;  // polls before a wait is given up (seconds; a wait in good order is a microsecond)
 
-constexpr int TD_RED = 2048;              // partial column sums of the matrix-vector product
-constexpr int TD_TAB = 24;                // ints per column in the table of wavefront assignments
-
-// Row sums of the matrix-vector product (the part of a row left of its diagonal block): one double per row and
-// column group, at most sum_k max(0, Nr - 128 k), k >= 1.
-__host__ __device__ inline int tridiag_rowsum_len(int Nr) {
-  int n = 0;
-  for (int k = 128; k < Nr; k += 128) n += Nr - k;
-  return n;
+// d += (value of `row` in lane n of each row of 16 lanes) * c.  `row` holds one matrix row per lane of a row of 16:
+// the multiply-add reads the broadcast lane itself, so a row's value costs no instruction of its own.
+template <int N>
+__device__ __forceinline__ void fmac_bcast(double& d, double row, double c) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(row), "v"(c), "n"(N));
 }
 
-// Panel width that fits the LDS next to the current reflector and column (2 vectors of Nr doubles), the
-// partial sums of the matrix-vector product (columns and rows), the two panels (2 nb Nr doubles) and 1 KB of small scratch.
-int tridiag_panel_width(int N) {
-  const int Nr = round_up(N, 16);
-  long nb = ((long)TD_LDS_BYTES - 1024 - TD_RED * 8 - 2L * Nr * 8 - 8L * tridiag_rowsum_len(Nr)) / (16L * Nr);
-  nb &= ~3L;
-  return nb > 32 ? 32 : (int)nb;
+__device__ __forceinline__ void publish(u64* p, double v, unsigned tag) {
+  __hip_atomic_store(p, ((u64)__double_as_longlong(v) & ~1ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-size_t tridiag_lds_bytes(int N, int nb) {
-  const int Nr = round_up(N, 16);
-  return (size_t)(2 * nb + 2) * Nr * 8 + TD_RED * 8 + (size_t)tridiag_rowsum_len(Nr) * 8 + 1024;
+__device__ __forceinline__ u64 peek(const u64* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sum over the workgroup in a fixed order: lanes as above, wavefronts left to right.  One barrier: the caller
-// must not use the same scratch array for its next sum unless another barrier lies in between (the two sums of
-// a column step use two arrays).
-__device__ inline double td_block_sum(double x, double* scratch, int wave, int lane) {
-  x = wave_sum_dpp(x);
-  if (lane == 0) scratch[wave] = x;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int k = 0; k < TD_WAVES; k++) s += scratch[k];
-  return s;
+// True when a wait has to end: it has lasted for TD_SPIN polls, or another workgroup of the image has given up.
+__device__ __forceinline__ bool tr_give_up(int spin, const int32_t* fail) {
+  return spin >= TD_SPIN ||
+         ((spin & 1023) == 1023 && __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
 }
 
-// Totals over the 64 lanes of eight values at once (recursive halving, fixed order): lane L returns the total of
-// part[L / 8].  The halves of the wavefront and the rows of 16 lanes trade registers with the swap instructions,
-// lanes L and L^8 through a rotation of the row, the last eight lanes through quad and half-row permutations.
-__device__ inline double td_sum8(const double* part, int lane) {
+// Sums of n <= 16 values over the 64 lanes by recursive halving (fixed order).  On return lane L holds the total of value
+// `*which` (-1: of none): the halves and the rows of 16 lanes trade with the swap instructions, then L and L^8, L and
+// 7-L through lane permutations; the quads are added.  The same exchange for an odd count leaves the unpaired value's
+// partner empty.
+template <int n>
+__device__ __forceinline__ double reduce_many(double* x, int lane, int* which) {
   typedef __attribute__((ext_vector_type(2))) unsigned int u2;
-  double q[4], s[2];
+  constexpr int h1 = (n + 1) / 2, h2 = (h1 + 1) / 2, h3 = (h2 + 1) / 2, h4 = (h3 + 1) / 2;
+  static_assert(h4 == 1, "at most 16 values");
 #pragma unroll
-  for (int u = 0; u < 4; u++) {  // lanes < 32: part[u] of L and L+32; lanes >= 32: part[u + 4]
-    const u2 lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(part[u]), (unsigned)__double2loint(part[u + 4]), false, false);
-    const u2 hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(part[u]), (unsigned)__double2hiint(part[u + 4]), false, false);
-    q[u] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  for (int u = 0; u < h1; u++) {
+    const double o = u + h1 < n ? x[u + h1] : 0.0;
+    const u2 lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x[u]), (unsigned)__double2loint(o), false, false);
+    const u2 hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x[u]), (unsigned)__double2hiint(o), false, false);
+    x[u] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
   }
 #pragma unroll
-  for (int u = 0; u < 2; u++) {  // even rows of 16 lanes: q[u] of L and L+16; odd rows: q[u + 2]
-    const u2 lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(q[u]), (unsigned)__double2loint(q[u + 2]), false, false);
-    const u2 hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(q[u]), (unsigned)__double2hiint(q[u + 2]), false, false);
-    s[u] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  for (int u = 0; u < h2; u++) {
+    const double o = u + h2 < h1 ? x[u + h2] : 0.0;
+    const u2 lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x[u]), (unsigned)__double2loint(o), false, false);
+    const u2 hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x[u]), (unsigned)__double2hiint(o), false, false);
+    x[u] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
   }
-  const bool up = (lane & 8) != 0;
-  double t = (up ? s[1] : s[0]) + dpp_f64<0x128>(up ? s[0] : s[1]);  // row_ror:8, L <-> L^8
-  t += dpp_f64<0xB1>(t);   // quad_perm [1,0,3,2]
-  t += dpp_f64<0x4E>(t);   // quad_perm [2,3,0,1]
-  t += dpp_f64<0x141>(t);  // row_half_mirror
+  const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0;
+#pragma unroll
+  for (int u = 0; u < h3; u++) {
+    const double o = u + h3 < h2 ? x[u + h3] : 0.0;
+    x[u] = (b3 ? o : x[u]) + dpp_f64<0x128>(b3 ? x[u] : o);  // row_ror:8, L <-> L^8
+  }
+  const double o = h4 < h3 ? x[h4] : 0.0;
+  double t = (b2 ? o : x[0]) + dpp_f64<0x141>(b2 ? x[0] : o);  // row_half_mirror, L <-> 7-L
+  t += dpp_f64<0xB1>(t);  // quad_perm [1,0,3,2]
+  t += dpp_f64<0x4E>(t);  // quad_perm [2,3,0,1]
+  const int i3 = (b2 ? h4 : 0), i2 = i3 + (b3 ? h3 : 0), i1 = i2 + ((lane & 16) ? h2 : 0), i0 = i1 + ((lane & 32) ? h1 : 0);
+  *which = (i3 < h3 && i2 < h2 && i1 < h1 && i0 < n) ? i0 : -1;
   return t;
 }
 
-// Which wavefront works on which part of the matrix-vector product of column j: column group g (128 columns from
-// cbase + 128 g) takes the rows from its diagonal block down, R_g of them, and the 16 wavefronts are dealt so that
-// the largest R_g / n_g is as small as it can be.  tab[j][w] = g | rg << 4 | n_g << 12 for wavefront w (row group
-// rg of n_g), tab[j][16 + g] = first wavefront of g | n_g << 8.
-__global__ __launch_bounds__(256) void tridiag_table_kernel(int N, int* __restrict__ tab) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= N - 1) return;
-  const int r0 = j + 1, cbase = r0 & ~1;
-  const int ncg = (N - cbase + 127) >> 7;
-  int R[8], n[8];
-  for (int g = 0; g < 8; g++) {
-    R[g] = g < ncg ? N - max(cbase + 128 * g, r0) : 0;
-    n[g] = g < ncg ? 1 : 0;
-  }
-  for (int k = ncg; k < TD_WAVES; k++) {
-    int best = 0;
-    for (int g = 1; g < ncg; g++)
-      if (R[g] * n[best] > R[best] * n[g]) best = g;
-    n[best]++;
-  }
-  int* row = tab + (size_t)j * TD_TAB;
-  int w = 0;
-  for (int g = 0; g < 8; g++) {
-    row[16 + g] = w | (n[g] << 8);
-    for (int rg = 0; rg < n[g]; rg++) row[w++] = g | (rg << 4) | (n[g] << 12);
-  }
+// Geometry of a frame.
+template <int PC>
+struct TrShape {
+  static constexpr int MODE = PC == 0 ? 0 : PC == 1 ? 1 : 2;
+  static constexpr int PCC = PC < 2 ? 1 : PC;            // column classes of 64
+  static constexpr int PR = PC == 0 ? 1 : 4 * PCC;       // row classes of 8
+  static constexpr int LI = PC == 0 ? 32 : 18;           // rows and columns of a thread
+  static constexpr int LK = PC == 0 ? 4 : 9;
+  static constexpr int NS = 2;                           // rows are worked on in two sets of 16 or 9
+  static constexpr int R = 8 * PR, C = 64 * PCC, RT = C / R;
+  static constexpr int F = C * LK, P = PR * PCC;
+  static constexpr int E = (F + TR_THREADS - 1) / TR_THREADS;  // vector elements of a thread
+  static constexpr int OWN = 64 * LK;                    // columns of a workgroup; it has 8 LI rows
+  // exchange words of one image: two slots of (partials, one set per column sum and row sum; next column; totals)
+  static constexpr size_t WORDS = MODE == 0 ? 0 : MODE == 1 ? (size_t)2 * 5 * F : (size_t)2 * (5 * PCC + 2) * F;
+  static constexpr size_t LDS = (size_t)(3 * F + 8 * OWN + 16 * LI + 18) * 8 + (size_t)LI * 8 * 16 * 4 + 16;
+  static_assert(LI * R == F, "rows and columns must cover the same frame");
+};
+
+// Exchange memory of the launch that follows: cleared, so that no value carries the tag of its first use (1).
+__global__ __launch_bounds__(256) void tridiag_clear_kernel(u64* __restrict__ sync, size_t stride, size_t words,
+                                                            int32_t* __restrict__ fail) {
+  u64* p = sync + (size_t)blockIdx.y * stride;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) p[i] = 0;
+  if (fail && blockIdx.x == 0 && threadIdx.x == 0) fail[blockIdx.y] = 0;
 }
 
-// One task of the rank-2nb update: trailing matrix (rows and columns jend .. N-1) <- itself - Vp Wp^T - Wp Vp^T on
-// the matrix cores, for the strip of 16 rows x 64 columns (a, bch) counted from base = jend rounded down to 16;
-// product ks contracts over k = 4 ks + lane / 16 of the 2 kcols columns of [Vp | Wp] (rows) against [Wp | Vp]
-// (columns).  Only strips that reach the diagonal or lie below it are computed (64 bch <= 16 a + 15); a strip
-// strictly below the diagonal also writes its mirror image (in a strip that is skipped) where somebody reads it:
-// within 128 columns of the diagonal (the diagonal blocks of the matrix-vector product) and in the rows of the next
-// panel (a column is formed from its row).  Vp, Wp: [Nr][nb] in LDS or in global memory.
-__device__ inline void td_update_strip(double* __restrict__ A, int N, int Np, int Nr, int nb, int jend, int kcols,
-                                       const double* Vp, const double* Wp, int a, int bch, int lane) {
-  const int l15 = lane & 15, q4 = lane >> 4;
-  const int base = jend & ~15;
-  const int rt = base + 16 * a, ct = base + 64 * bch;
-  const bool below = 64 * bch + 63 < 16 * a;
-  d4 acc[4];
-#pragma unroll
-  for (int t = 0; t < 4; t++) {
-    const int cc = ct + 16 * t + l15;
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const int rr = rt + 4 * e + q4;
-      acc[t][e] = (rr < N && cc < N) ? A[(size_t)rr * Np + cc] : 0.0;
-    }
-  }
-  const int arow = min(rt + l15, Nr - 1);
-  const int ksteps = kcols >> 2;
-  for (int half = 0; half < 2; half++) {
-    const double* L = half == 0 ? Vp : Wp;   // row factor
-    const double* R = half == 0 ? Wp : Vp;   // column factor
-    for (int ks = 0; ks < ksteps; ks++) {
-      const int k = 4 * ks + q4;
-      const double av = -L[arow * nb + k];
-#pragma unroll
-      for (int t = 0; t < 4; t++) {
-        const int crow = min(ct + 16 * t + l15, Nr - 1);
-        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, R[crow * nb + k], acc[t], 0, 0, 0);
-      }
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 4; t++) {
-    const int cc = ct + 16 * t + l15;
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const int rr = rt + 4 * e + q4;
-      if (rr >= jend && cc >= jend && rr < N && cc < N) {
-        A[(size_t)rr * Np + cc] = acc[t][e];
-        if (below && (rr - cc < 128 || cc < jend + nb)) A[(size_t)cc * Np + rr] = acc[t][e];
-      }
-    }
-  }
-}
-
-// G      [B][Np][Np]  in: the Gram matrix, symmetric, stored in full; destroyed
+// G      [B][Np][Np]  in: the Gram matrix (full != 0: stored in full, else the lower triangle of the trailing matrix that the
+//                     phase before left); out: the trailing matrix from column last on, lower triangle
 // dvec   [B][Np]      out: diagonal of T
 // evec   [B][Np]      out: evec[j] = T[j+1][j], j < N-1
 // tauv   [B][Np]      out: tau_j (0 for a reflector that is the identity)
 // Vc     [B][Np/16][Np][16] out, float: the reflectors in blocks of sixteen, Vc[j / 16][i][j % 16] = v_j[i] (zeros up to
 //                     i = j, 1 at j + 1) -- the layout stage 3 copies into LDS; reflectors j >= N-1 are not written
-// panels [B][2][Nr][nb] out: the panel's Vp and Wp (zero beyond the panel's columns, up to kcols) for the update
-// One launch reduces the panels that start at j0, j0 + nb, ... below j0_stop.  fused != 0: the update after each
-// panel runs inside the kernel, on this image's compute unit (the whole reduction in one launch: better from about
-// a hundred images on, where the chip is full anyway); fused == 0: one panel per launch, the panels go to global
-// memory and tridiag_update_kernel follows.
-__global__ __launch_bounds__(TD_THREADS) void tridiag_panel_kernel(double* __restrict__ G, int N, int Np, int nb, int j0_first,
-                                                                   int j0_stop, int fused,
-                                                                   double* __restrict__ dvec, double* __restrict__ evec,
-                                                                   float* __restrict__ tauv, float* __restrict__ Vc,
-                                                                   double* __restrict__ panels, size_t panels_stride,
-                                                                   const int* __restrict__ tab) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char td_smem[];
-  const int Nr = round_up(N, 16);
-  double* Vp = reinterpret_cast<double*>(td_smem);  // [Nr][nb] reflectors of the panel
-  double* Wp = Vp + (size_t)Nr * nb;                 // [Nr][nb] their update vectors
-  double* vs = Wp + (size_t)Nr * nb;                 // [Nr] current reflector
-  double* as = vs + Nr;                              // [Nr] current column
-  double* red = as + Nr;                             // [16][128] partial column sums, one set per wavefront
-  double* yrow = red + TD_RED;                       // row sums left of the diagonal blocks, per column group
-  double* dots = yrow + tridiag_rowsum_len(Nr);      // [64] W^T v and V^T v
-  double* wsum = dots + 64;                          // [2][16] wavefront partials of td_block_sum
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  double* A = G + (size_t)b * Np * Np;
-  double* dout = dvec + (size_t)b * Np;
-  double* eout = evec + (size_t)b * Np;
-  float* tout = tauv + (size_t)b * Np;
-  float* Vout = Vc + (size_t)b * Np * Np;
-  const int l15 = lane & 15, q4 = lane >> 4;
+// sync                exchange memory, cleared
+// Columns first .. last-1 of the matrix are reduced.
+template <int PC>  // 0: the single-workgroup frame
+__global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void tridiag_kernel(
+    double* __restrict__ G, int N, int Np, int B, int first, int last, int full, double* __restrict__ dvec,
+    double* __restrict__ evec, float* __restrict__ tauv, float* __restrict__ Vc, u64* __restrict__ sync, size_t sync_stride,
+    int32_t* __restrict__ fail) {
+  typedef TrShape<PC> S;
+  constexpr int LI = S::LI, LK = S::LK, RT = S::RT, NS = S::NS, SR = S::LI / S::NS, E = S::E, MODE = S::MODE;
+  constexpr int PR = S::PR, pc = S::PCC, R = S::R, C = S::C, F = S::F, P = S::P, OWN = S::OWN;
+  static_assert(SR <= 16 && SR * NS == LI, "the rows of a set must fit the 16 lanes of a row");
+  extern __shared__ __attribute__((aligned(16))) unsigned char tr_smem[];
+  double* Va = reinterpret_cast<double*>(tr_smem);  // [F] reflector of the even columns
+  double* Vb = Va + F;                               // [F] of the odd ones
+  double* Wv = Vb + F;                               // [F] w of the column before
+  double* csb = Wv + F;                              // [8][OWN] column sums per wavefront
+  double* rsb = csb + 8 * OWN;                       // [LI * 8] row sums
+  double* colb = rsb + 8 * LI;                       // [LI * 8] this workgroup's rows of the next column
+  double* red = colb + 8 * LI;                       // [2][8] partial sums of the block reductions
+  double* one = red + 16;                            // [2] p at the reflector's first row; head of the next column
+  float* vblk = reinterpret_cast<float*>(one + 2);   // [LI * 8][16] the last sixteen reflectors, this workgroup's rows
+  int* quit = reinterpret_cast<int*>(vblk + LI * 8 * 16);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // workgroup -> (image, member): in the four-workgroup frame the members of a group have ids that differ by multiples
+  // of 8 (one XCD, one L2); larger groups are spread over all XCDs anyway
+  int img, mem;
+  if (MODE == 1) {
+    img = (int)(blockIdx.x >> 3) / P * 8 + (blockIdx.x & 7);
+    mem = (int)(blockIdx.x >> 3) % P;
+  } else {
+    img = blockIdx.x / P;
+    mem = blockIdx.x % P;
+  }
+  if (img >= B) return;
+  const int a = mem % PR, b = mem / PR;
+  double* A0 = G + (size_t)img * Np * Np;
+  double* dout = dvec + (size_t)img * Np;
+  double* eout = evec + (size_t)img * Np;
+  float* tout = tauv + (size_t)img * Np;
+  float* Vout = Vc + (size_t)img * Np * Np;
+  u64* sy = sync + (size_t)img * sync_stride;
+  const int base = N - F;                 // row of the matrix = row of the frame + base
+  const int js = first - base, je = last - base;  // columns of the frame
 
-  for (int j0 = j0_first; j0 < j0_stop; j0 += nb) {
-    const int jend = min(j0 + nb, N - 1);  // this panel reduces columns j0 .. jend-1
-    for (int j = j0; j < jend; j++) {
-      const int jj = j - j0;
-      // this column's table entries, asked for early: the wavefront's task and, for the thread's own element of p,
-      // the wavefronts of its column group
-      const int* trow = tab + (size_t)j * TD_TAB;
-      const int ent = trow[wave];
-      const int cbase = (j + 1) & ~1;            // column pairs start at an even column
-      const int ent_c = (j + 1 + tid < N) ? trow[16 + ((j + 1 + tid - cbase) >> 7)] : 0;
-      // ---- column j of the matrix as it would be with the panel's updates applied (row j, by symmetry) ----
-      const int i1 = j + tid;
-      double x = 0.0;
-      if (i1 < N) {
-        x = A[(size_t)j * Np + i1];
-        for (int c = 0; c < jj; c++) x -= Vp[i1 * nb + c] * Wp[j * nb + c] + Wp[i1 * nb + c] * Vp[j * nb + c];
-        as[i1] = x;
-      }
-      if (tid == 0) dout[j] = x;
-      // ---- Householder reflector that maps x[j+1:] onto beta e_1 ------------------------------------------
-      const double xn2 = td_block_sum((tid >= 2 && i1 < N) ? x * x : 0.0, wsum, wave, lane);  // (its barriers also publish as[])
-      const double alpha = as[j + 1];
-      double beta = alpha, tau = 0.0, scal = 0.0;
-      if (xn2 > 0.0) {
-        beta = -copysign(sqrt(alpha * alpha + xn2), alpha);
-        tau = (beta - alpha) / beta;
-        scal = 1.0 / (alpha - beta);
-      }
-      if (tid >= 1 && i1 < N) {
-        const double v = tid == 1 ? 1.0 : x * scal;
-        vs[i1] = v;
-        Vp[i1 * nb + jj] = v;
-      }
-      if (tid == 0) {
-        eout[j] = beta;
-        tout[j] = (float)tau;
-      }
-      __syncthreads();
-      // ---- p = A v over the trailing matrix (rows and columns j+1 .. N-1) -----------------------------------
-      // The matrix is symmetric and stored in full; an element below the diagonal blocks is fetched once and used
-      // twice.  Column group g = 128 columns from cbase + 128 g (a lane owns two neighbours, one 16-byte load per
-      // row).  Its rows run from the top of its diagonal block down: inside the block (128 rows, both triangles)
-      // a row only adds to the column sums p_c += A[r][c] v_r; a row r below the block also gives the part of p_r
-      // that lies in these columns, sum_c A[r][c] v_c, summed over the lanes eight rows at a time.  The rows of a
-      // group are dealt to its wavefronts in turn (table: more wavefronts for the groups with more rows).
-      const int r0 = j + 1;
-      {
-        const int cg = ent & 15, rg = (ent >> 4) & 255, nrg = ent >> 12;
-        const int C0 = cbase + (cg << 7);
-        const int c = C0 + 2 * lane;
-        const bool ok = c < N;                   // (an odd N reads the zero padding column N as the pair's second half)
-        const double* col = A + (ok ? c : cbase);
-        const double vc0 = (ok && c >= r0) ? vs[c] : 0.0, vc1 = (c + 1 < N) ? vs[c + 1] : 0.0;
-        const int dend = min(C0 + 128, N);       // rows below dend lie under the diagonal block
-        int yoff = 0;                            // where this group's row sums start
-        for (int g = 0; g < cg; g++) yoff += N - (cbase + 128 * g + 128);
-        d2 acc = d2{0.0, 0.0};
-        // Chunks of eight rows with all their loads in flight together, then a last chunk of fewer rows fetched four
-        // at a time: no row is fetched that does not count.  A chunk that reaches below the diagonal block also
-        // forms the row sums of its rows there.
-        double* yg = yrow + yoff - (C0 + 128);
-        int ib = max(C0, r0) + rg;
-        for (; ib + 7 * nrg < N; ib += 8 * nrg) {
-          d2 x[8];
+  // ---- the workgroup's share of the matrix ---------------------------------------------------------------
+  double A[LI][LK];
 #pragma unroll
-          for (int u = 0; u < 8; u++) x[u] = *reinterpret_cast<const d2*>(col + (size_t)(ib + u * nrg) * Np);
+  for (int k = 0; k < LK; k++)
 #pragma unroll
-          for (int u = 0; u < 8; u++) acc += x[u] * vs[ib + u * nrg];
-          if (ib >= dend) {  // all eight rows below the block (uniform over the wavefront)
-            double part[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) part[u] = x[u].x * vc0 + x[u].y * vc1;
-            const double tot = td_sum8(part, lane);
-            if ((lane & 7) == 0) yg[ib + (lane >> 3) * nrg] = tot;
-          } else if (ib + 7 * nrg >= dend) {  // some of them
-            double part[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) part[u] = ib + u * nrg >= dend ? x[u].x * vc0 + x[u].y * vc1 : 0.0;
-            const double tot = td_sum8(part, lane);
-            const int r = ib + (lane >> 3) * nrg;
-            if ((lane & 7) == 0 && r >= dend) yg[r] = tot;
-          }
-        }
-        if (ib < N) {
-          double part[8];
-#pragma unroll
-          for (int h = 0; h < 2; h++) {
-            d2 x[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++)
-              if (ib + (4 * h + u) * nrg < N) x[u] = *reinterpret_cast<const d2*>(col + (size_t)(ib + (4 * h + u) * nrg) * Np);  // uniform over the wavefront
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-              const int r = ib + (4 * h + u) * nrg;
-              part[4 * h + u] = 0.0;
-              if (r < N) {
-                acc += x[u] * vs[r];
-                if (r >= dend) part[4 * h + u] = x[u].x * vc0 + x[u].y * vc1;
-              }
-            }
-          }
-          const double tot = td_sum8(part, lane);
-          const int r = ib + (lane >> 3) * nrg;
-          if ((lane & 7) == 0 && r >= dend && r < N) yg[r] = tot;
-        }
-        red[(wave << 7) + 2 * lane] = acc.x;
-        red[(wave << 7) + 2 * lane + 1] = acc.y;
+    for (int i = 0; i < LI; i++)
+      if (i >= RT * k) {
+        const int r = i * R + 8 * a + w + base, c = k * C + 64 * b + lane + base;
+        double x = 0.0;
+        if (r >= first && c >= first) x = full ? A0[(size_t)r * Np + c] : A0[(size_t)max(r, c) * Np + min(r, c)];
+        A[i][k] = x;
       }
-      // ---- W^T v and V^T v for the panel's earlier columns: one wavefront per dot product ------------------
-      for (int id = wave; id < 2 * jj; id += TD_WAVES) {
-        const double* P = id < jj ? Wp + id : Vp + (id - jj);
-        double s = 0.0;
-        for (int i = r0 + lane; i < N; i += 64) s += P[i * nb] * vs[i];
-        s = wave_sum_dpp(s);
-        if (lane == 0) dots[id] = s;
-      }
-      __syncthreads();
-      // ---- p <- tau (A v - V (W^T v) - W (V^T v)),  w = p - (tau/2) (p^T v) v -------------------------------
-      const int c = r0 + tid;
-      double pc = 0.0, vc = 0.0;
-      if (c < N) {
-        const int cgc = (c - cbase) >> 7;
-        const int w0 = ent_c & 255, w1 = w0 + (ent_c >> 8), cl = c - cbase - (cgc << 7);
-        for (int w = w0; w < w1; w++) pc += red[(w << 7) + cl];  // fixed order: the wavefronts of the column's group,
-        int yoff = 0;                                            // then the row sums of the groups to its left
-        for (int g = 0; g < cgc; g++) {
-          const int top = cbase + 128 * g + 128;
-          pc += yrow[yoff + (c - top)];
-          yoff += N - top;
-        }
-        for (int k = 0; k < jj; k++) pc -= Vp[c * nb + k] * dots[k] + Wp[c * nb + k] * dots[jj + k];
-        pc *= tau;
-        vc = vs[c];
-      }
-      const double pv = td_block_sum(pc * vc, wsum + TD_WAVES, wave, lane);
-      if (c < N) Wp[c * nb + jj] = pc - 0.5 * tau * pv * vc;
-      __syncthreads();
+  for (int f = tid; f < 3 * F; f += TR_THREADS) Va[f] = 0.0;  // both reflectors and w
+  for (int e = tid; e < LI * 8 * 16; e += TR_THREADS) vblk[e] = 0.f;
+  if (tid == 0) *quit = 0;
+
+  // this thread's elements of the vectors: frame rows F - 1 - tid - 512 u, so that the live ones stay in the low threads
+  double x[E];
+#pragma unroll
+  for (int u = 0; u < E; u++) {
+    const int f = F - 1 - tid - TR_THREADS * u;
+    x[u] = f >= js ? A0[(size_t)(f + base) * Np + first] : 0.0;
+  }
+  double part = 0.0;
+#pragma unroll
+  for (int u = 0; u < E; u++) {
+    const int f = F - 1 - tid - TR_THREADS * u;
+    if (f >= js + 2) part += x[u] * x[u];
+    if (f == js + 1) one[1] = x[u];
+    if (f == js && mem == 0) dout[first] = x[u];
+  }
+  part = wave_sum_dpp(part);
+  if (lane == 0) red[8 + w] = part;
+  __syncthreads();
+
+  bool bad = false;
+  for (int j = js; j < min(je, F - 1); j++) {
+    double* Vn = (j & 1) ? Vb : Va;        // this column's reflector
+    const double* Vo = (j & 1) ? Va : Vb;  // the one before
+    // ---- Householder reflector that maps x[j+1:] onto beta e_1 ------------------------------------------
+    double xn2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < TR_WAVES; k++) xn2 += red[8 + k];
+    const double alpha = one[1];
+    double beta = alpha, tau = 0.0, scal = 0.0;
+    if (xn2 > 0.0) {
+      beta = -copysign(sqrt(alpha * alpha + xn2), alpha);
+      tau = (beta - alpha) / beta;
+      scal = 1.0 / (alpha - beta);
     }
-    // ---- end of the panel ----------------------------------------------------------------------------------
-    const int cnt = jend - j0;          // columns reduced in this panel
-    const int kcols = round_up(cnt, 4); // contraction length per factor, padded with zero columns
-    // the reflectors leave as float rows (stage 3 applies them in float32), four columns per 16-byte store: j0 is a
-    // multiple of 4, so the four lie in one block of sixteen; slots of a last group past column jend - 1 get zeros
-    // (stage 3 does not use them)
-    for (int g4 = 0; g4 < kcols; g4 += 4) {
-      const int j = j0 + g4;
-      for (int i = tid; i < N; i += TD_THREADS) {
-        float4 v;
-        v.x = (g4 < cnt && i > j) ? (float)Vp[i * nb + g4] : 0.f;
-        v.y = (g4 + 1 < cnt && i > j + 1) ? (float)Vp[i * nb + g4 + 1] : 0.f;
-        v.z = (g4 + 2 < cnt && i > j + 2) ? (float)Vp[i * nb + g4 + 2] : 0.f;
-        v.w = (g4 + 3 < cnt && i > j + 3) ? (float)Vp[i * nb + g4 + 3] : 0.f;
-        *reinterpret_cast<float4*>(&Vout[((size_t)(j >> 4) * Np + i) * 16 + (j & 15)]) = v;
+    const int jr = j + base;  // column of the matrix
+#pragma unroll
+    for (int u = 0; u < E; u++) {
+      const int f = F - 1 - tid - TR_THREADS * u;
+      if (f >= j + 1) {
+        x[u] = f == j + 1 ? 1.0 : x[u] * scal;
+        Vn[f] = x[u];
+        if (b == 0 && (MODE == 0 || ((f >> 3) % PR) == a)) vblk[(f / R * 8 + (f & 7)) * 16 + (jr & 15)] = (float)x[u];
       }
     }
-    if (kcols > cnt) {  // a last, shorter panel: columns cnt .. kcols-1 still hold the previous panel
-      for (int e = tid; e < Nr * (kcols - cnt); e += TD_THREADS) {
-        const int i = e / (kcols - cnt), k = cnt + e % (kcols - cnt);
-        Vp[i * nb + k] = 0.0;
-        Wp[i * nb + k] = 0.0;
+    if (tid == 0) {
+      Vn[j] = 0.0;
+      if (j > 0) Vn[j - 1] = 0.0;
+      if (mem == 0) {
+        eout[jr] = beta;
+        tout[jr] = (float)tau;
       }
     }
     __syncthreads();
-    if (fused) {  // strips are dealt to the wavefronts round-robin
-      const int base = jend & ~15;
-      const int nrt = (N - base + 15) >> 4, ncc = (N - base + 63) >> 6;
-      int idx = 0;
-      for (int a = 0; a < nrt; a++) {
-        const int n_a = min(ncc, (a >> 2) + 1);
-        for (int bch = 0; bch < n_a; bch++, idx++)
-          if ((idx & (TD_WAVES - 1)) == wave) td_update_strip(A, N, Np, Nr, nb, jend, kcols, Vp, Wp, a, bch, lane);
+
+    // ---- A <- A - v w^T - w v^T with the column before, and p = A v ---------------------------------------
+    const int kmin = (j + 1) / C;
+    const bool owner = MODE != 2 || (((j + 1) >> 6) % pc) == b;
+    const int l0 = (j + 1) & 63;
+    double cs[LK];
+#pragma unroll
+    for (int k = 0; k < LK; k++) cs[k] = 0.0;
+#pragma unroll
+    for (int s = 0; s < NS; s++) {
+      if (s + 1 < NS && RT * kmin > s * SR + SR - 1) continue;  // every row of the set is done with
+      const int fr = (s * SR + min(lane & 15, SR - 1)) * R + 8 * a + w;
+      const double vo = Vo[fr], wo = Wv[fr], vn = Vn[fr];
+      double rs[SR];
+#pragma unroll
+      for (int q = 0; q < SR; q++) rs[q] = 0.0;
+#pragma unroll
+      for (int k = 0; k < LK; k++) {
+        if (RT * k > s * SR + SR - 1) continue;
+        if (k < kmin) continue;
+        const int fc = k * C + 64 * b + lane;
+        const double vc = Vn[fc], nv = -Vo[fc], nw = -Wv[fc];
+        asm volatile("s_nop 1");
+        auto row = [&](auto qc) {
+          constexpr int q = decltype(qc)::value;
+          const int i = s * SR + q;
+          if (i >= RT * k) {
+            fmac_bcast<q>(A[i][k], vo, nw);
+            fmac_bcast<q>(A[i][k], wo, nv);
+            if (i >= RT * (k + 1)) rs[q] = fma(A[i][k], vc, rs[q]);
+            fmac_bcast<q>(cs[k], vn, A[i][k]);
+          }
+        };
+        [&]<int... q>(std::integer_sequence<int, q...>) { (row(std::integral_constant<int, q>{}), ...); }(std::make_integer_sequence<int, SR>{});
+        if (k == kmin && owner && lane == l0) {
+#pragma unroll
+          for (int q = 0; q < SR; q++)
+            if (s * SR + q >= RT * k) colb[(s * SR + q) * 8 + w] = A[s * SR + q][k];
+        }
       }
-      __syncthreads();  // the rewritten matrix is visible to the whole workgroup
-    } else {
-      // the panels for the update of the trailing matrix (rows that the update does not store are written as zero)
-      double* Vg = panels + (size_t)b * panels_stride;
-      double* Wg = Vg + (size_t)Nr * nb;
-      // (the update reads rows from jend rounded down to 16 on; sixteen lanes per row, no index divisions)
-      for (int k = tid & 15; k < kcols; k += 16)
-        for (int i = (jend & ~15) + (tid >> 4); i < Nr; i += TD_THREADS / 16) {
-          Vg[i * nb + k] = (i >= jend && i < N) ? Vp[i * nb + k] : 0.0;
-          Wg[i * nb + k] = (i >= jend && i < N) ? Wp[i * nb + k] : 0.0;
+      int which;
+      const double t = reduce_many<SR>(rs, lane, &which);
+      if (which >= 0 && (lane & 3) == 0) rsb[(s * SR + which) * 8 + w] = t;
+    }
+#pragma unroll
+    for (int k = 0; k < LK; k++)
+      if (k >= kmin) csb[w * OWN + 64 * k + lane] = cs[k];
+    __syncthreads();
+
+    // ---- p in every workgroup -------------------------------------------------------------------------------
+    const unsigned tag = (((j - js) >> 1) & 1) ^ 1;
+    const int slot = (j - js) & 1;
+    double p[E], col[E];
+    if (MODE == 0) {
+#pragma unroll
+      for (int u = 0; u < E; u++) {
+        const int f = F - 1 - tid - TR_THREADS * u;
+        p[u] = col[u] = 0.0;
+        if (f > j) {
+          double s = rsb[f];
+#pragma unroll
+          for (int k = 0; k < TR_WAVES; k++) s += csb[k * OWN + f];
+          p[u] = s;
+          col[u] = colb[f];
+        }
+      }
+    } else if (MODE == 1) {
+      u64* Y = sy + (size_t)slot * 5 * F;  // [4][F] partials, then [F] the next column
+#pragma unroll
+      for (int u = 0; u < E; u++) {
+        const int f = F - 1 - tid - TR_THREADS * u;
+        if (f > j) {
+          const bool mine = ((f >> 3) & 3) == a;  // a row of this workgroup
+          const int o = (f >> 5) * 8 + (f & 7);
+          double s = mine ? rsb[o] : 0.0;
+#pragma unroll
+          for (int k = 0; k < TR_WAVES; k++) s += csb[k * OWN + f];
+          publish(Y + (size_t)a * F + f, s, tag);
+          if (mine) publish(Y + (size_t)4 * F + f, colb[o], tag);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < E; u++) {
+        const int f = F - 1 - tid - TR_THREADS * u;
+        p[u] = col[u] = 0.0;
+        if (f > j) {
+          u64 y[5];
+          for (int spin = 0;; spin++) {
+            bool ok = true;
+#pragma unroll
+            for (int q = 0; q < 5; q++) y[q] = peek(Y + (size_t)q * F + f);
+#pragma unroll
+            for (int q = 0; q < 5; q++) ok &= (y[q] & 1) == tag;
+            if (ok) break;
+            if (tr_give_up(spin, fail + img)) { bad = true; break; }
+          }
+          p[u] = (__longlong_as_double((long long)y[0]) + __longlong_as_double((long long)y[1])) +
+                 (__longlong_as_double((long long)y[2]) + __longlong_as_double((long long)y[3]));
+          col[u] = __longlong_as_double((long long)y[4]);
+        }
+      }
+    }
+    if (MODE == 2) {
+      u64* YC = sy + (size_t)slot * (5 * pc + 2) * F;  // [PR][F] column sums by row class
+      u64* YR = YC + (size_t)PR * F;                   // [PC][F] row sums by column class
+      u64* YN = YR + (size_t)pc * F;                   // [F] the next column
+      u64* YT = YN + F;                                // [F] totals
+      for (int o = tid; o < OWN; o += TR_THREADS) {
+        const int f = (o >> 6) * C + 64 * b + (o & 63);
+        if (f > j) {
+          double s = 0.0;
+#pragma unroll
+          for (int k = 0; k < TR_WAVES; k++) s += csb[k * OWN + o];
+          publish(YC + (size_t)a * F + f, s, tag);
+        }
+      }
+      if (tid < 8 * LI) {
+        const int f = (tid >> 3) * R + 8 * a + (tid & 7);
+        if (f > j) {
+          publish(YR + (size_t)b * F + f, rsb[tid], tag);
+          if (owner) publish(YN + f, colb[tid], tag);
+        }
+      }
+      // totals of this workgroup's share of its rows: four lanes per element
+      constexpr int NQ = 5 * pc, PER = (NQ + 3) / 4;
+      const int o = (tid >> 2) * pc + b;
+      const int ft = (o >> 3) * R + 8 * a + (o & 7);
+      if (o < 8 * LI && ft > j) {
+        u64 y[PER];
+        for (int spin = 0;; spin++) {
+          bool ok = true;
+#pragma unroll
+          for (int q = 0; q < PER; q++) y[q] = peek(YC + (size_t)min(4 * q + (tid & 3), NQ - 1) * F + ft);  // (YR follows YC)
+#pragma unroll
+          for (int q = 0; q < PER; q++) ok &= (y[q] & 1) == tag;
+          if (ok) break;
+          if (tr_give_up(spin, fail + img)) { bad = true; break; }
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < PER; q++) s += 4 * q + (tid & 3) < NQ ? __longlong_as_double((long long)y[q]) : 0.0;
+        s += dpp_f64<0xB1>(s);  // the quad
+        s += dpp_f64<0x4E>(s);
+        if ((tid & 3) == 0) publish(YT + ft, s, tag);
+      }
+#pragma unroll
+      for (int u = 0; u < E; u++) p[u] = col[u] = 0.0;
+      {
+        u64 yt[E], yn[E];
+        for (int spin = 0;; spin++) {
+          bool ok = true;
+#pragma unroll
+          for (int u = 0; u < E; u++) {
+            const int f = F - 1 - tid - TR_THREADS * u;
+            if (f > j) {
+              yt[u] = peek(YT + f);
+              yn[u] = peek(YN + f);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < E; u++) {
+            const int f = F - 1 - tid - TR_THREADS * u;
+            if (f > j) ok &= (yt[u] & 1) == tag && (yn[u] & 1) == tag;
+          }
+          if (ok) break;
+          if (tr_give_up(spin, fail + img)) { bad = true; break; }
+        }
+#pragma unroll
+        for (int u = 0; u < E; u++) {
+          const int f = F - 1 - tid - TR_THREADS * u;
+          if (f > j) {
+            p[u] = __longlong_as_double((long long)yt[u]);
+            col[u] = __longlong_as_double((long long)yn[u]);
+          }
+        }
+      }
+    }
+    if (MODE != 0 && bad) *quit = 1;
+
+    // ---- w = p - (tau/2) (p^T v) v with p <- tau p; the next column -------------------------------------------
+    part = 0.0;
+#pragma unroll
+    for (int u = 0; u < E; u++) {
+      const int f = F - 1 - tid - TR_THREADS * u;
+      p[u] *= tau;
+      if (f > j) part += p[u] * x[u];
+      if (f == j + 1) one[0] = p[u];
+    }
+    part = wave_sum_dpp(part);
+    if (lane == 0) red[w] = part;
+    __syncthreads();
+    if (MODE != 0 && *quit) break;  // uniform
+    double pv = 0.0;
+#pragma unroll
+    for (int k = 0; k < TR_WAVES; k++) pv += red[k];
+    const double half = 0.5 * tau * pv, w1 = one[0] - half;
+    part = 0.0;
+#pragma unroll
+    for (int u = 0; u < E; u++) {
+      const int f = F - 1 - tid - TR_THREADS * u;
+      if (f > j) {
+        const double wf = p[u] - half * x[u];
+        Wv[f] = wf;
+        x[u] = col[u] - x[u] * w1 - wf;  // (the reflector's first entry is 1)
+        if (f >= j + 3) part += x[u] * x[u];
+        if (f == j + 2) one[1] = x[u];
+        if (f == j + 1 && mem == 0) dout[jr + 1] = x[u];
+      }
+    }
+    if (tid == 0) Wv[j] = 0.0;
+    part = wave_sum_dpp(part);
+    if (lane == 0) red[8 + w] = part;
+    // ---- sixteen reflectors complete: this workgroup's rows of them leave in 16-byte pieces ---------------------
+    if ((jr & 15) == 15 || j == min(je, F - 1) - 1) {
+      if (b == 0)
+        for (int e = tid; e < LI * 8 * 4; e += TR_THREADS) {
+          const int o = e >> 2, r = (o >> 3) * R + 8 * a + (o & 7) + base;
+          if (r >= (jr & ~15) && r >= 0) {
+            float4* src = reinterpret_cast<float4*>(vblk + o * 16 + 4 * (e & 3));
+            *reinterpret_cast<float4*>(Vout + ((size_t)(jr >> 4) * Np + r) * 16 + 4 * (e & 3)) = *src;
+            *src = float4{0.f, 0.f, 0.f, 0.f};
+          }
         }
     }
+    __syncthreads();
   }
-  if (fused && tid == 0) {
-    dout[N - 1] = A[(size_t)(N - 1) * Np + (N - 1)];
-    eout[N - 1] = 0.0;
-    tout[N - 1] = 0.f;
+  if (MODE != 0 && *quit) {
+    if (tid == 0) __hip_atomic_store(fail + img, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  if (last == N) {
+    if (tid == 0 && mem == 0) {
+      eout[N - 1] = 0.0;
+      tout[N - 1] = 0.f;
+    }
+    return;
+  }
+  // ---- the trailing matrix with the last column's update, for the next phase --------------------------------------
+  const double* Vo = (je & 1) ? Va : Vb;
+#pragma unroll
+  for (int k = 0; k < LK; k++)
+#pragma unroll
+    for (int i = 0; i < LI; i++)
+      if (i >= RT * k) {
+        const int fr = i * R + 8 * a + w, fc = k * C + 64 * b + lane;
+        if (fr >= je && fc >= je && fr >= fc) {
+          const double y = A[i][k] - Vo[fr] * Wv[fc] - Wv[fr] * Vo[fc];
+          A0[(size_t)(fr + base) * Np + fc + base] = y;
+        }
+      }
+}
+
+// ---- host ---------------------------------------------------------------------------------------------------
+struct TrFrame { int mode, F, P; size_t words; };
+constexpr int TR_SIZES = 7;  // frames: 0 the single workgroup, n: PC = 1, 2, 3, 4, 5, 7
+static const TrFrame TR_FRAMES[TR_SIZES] = {
+#define TR_ENTRY(PC_) {TrShape<PC_>::MODE, TrShape<PC_>::F, TrShape<PC_>::P, TrShape<PC_>::WORDS}
+    TR_ENTRY(0), TR_ENTRY(1), TR_ENTRY(2), TR_ENTRY(3), TR_ENTRY(4), TR_ENTRY(5), TR_ENTRY(7)
+#undef TR_ENTRY
+};
+
+// The phases of a reduction: a frame works on the columns it is worth having, then hands the trailing matrix (through G)
+// to a smaller one.  The next frame is the largest that needs fewer exchanges per column or lets more images run
+// at once, so that the launch takes fewer rounds over the 256 compute units.  (Hand-overs lie at multiples of 16
+// columns: the blocks of sixteen reflectors.)
+struct TrPhase { int size, first, last; size_t off; };  // off: where its exchange words start
+static int tr_phases(int N, int B, TrPhase* out, size_t* words) {
+  auto rounds = [&](int s) { const int at_once = 256 / TR_FRAMES[s].P; return (B + at_once - 1) / at_once; };
+  int size = 0, n = 0, first = 0;
+  while (size < TR_SIZES && TR_FRAMES[size].F < N) size++;
+  *words = 0;
+  if (size == TR_SIZES) return 0;
+  while (true) {
+    int next = size - 1;
+    while (next >= 0 && TR_FRAMES[next].mode == TR_FRAMES[size].mode && rounds(next) >= rounds(size)) next--;
+    const int last = next >= 0 ? round_up(N - TR_FRAMES[next].F, 16) : N;
+    out[n++] = TrPhase{size, first, last, *words};
+    *words += TR_FRAMES[size].words;
+    if (next < 0) return n;
+    size = next;
+    first = last;
   }
 }
 
-// The update of the trailing matrix after a panel as a launch of its own: one wavefront per strip (td_update_strip),
-// panels read from global memory.
-__global__ __launch_bounds__(256) void tridiag_update_kernel(double* __restrict__ G, int N, int Np, int nb, int jend,
-                                                             int kcols, const double* __restrict__ panels,
-                                                             size_t panels_stride, int ntasks) {
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
-  const int task = blockIdx.x * 4 + (tid >> 6);
-  if (task >= ntasks) return;  // uniform over the wavefront; no barrier in this kernel
-  const int Nr = round_up(N, 16);
-  const int base = jend & ~15;
-  const int ncc = (N - base + 63) >> 6;
-  int a = 0, rest = task;  // row tile a has min(ncc, a / 4 + 1) strips
-  for (;;) {
-    const int n_a = min(ncc, (a >> 2) + 1);
-    if (rest < n_a) break;
-    rest -= n_a;
-    a++;
-  }
-  const double* Vg = panels + (size_t)b * panels_stride;
-  td_update_strip(G + (size_t)b * Np * Np, N, Np, Nr, nb, jend, kcols, Vg, Vg + (size_t)Nr * nb, a, rest, lane);
+bool tridiag_fits(int N) { return N <= TR_FRAMES[TR_SIZES - 1].F; }
+
+size_t tridiag_sync_bytes(int N, int B) {  // exchange memory of one image
+  TrPhase ph[TR_SIZES];
+  size_t words;
+  tr_phases(N, B, ph, &words);
+  return align256(words * 8 + 8);
 }
 
-// The last diagonal entry, after the last update.
-__global__ __launch_bounds__(64) void tridiag_last_kernel(const double* __restrict__ G, int N, int Np,
-                                                          double* __restrict__ dvec, double* __restrict__ evec,
-                                                          float* __restrict__ tauv) {
-  const int b = blockIdx.x;
-  if (threadIdx.x == 0) {
-    dvec[(size_t)b * Np + N - 1] = G[(size_t)b * Np * Np + (size_t)(N - 1) * Np + (N - 1)];
-    evec[(size_t)b * Np + N - 1] = 0.0;
-    tauv[(size_t)b * Np + N - 1] = 0.f;
+// Launches of large groups are kept apart: two of them from different streams could each hold compute units that the
+// other's incomplete group waits for.  One launch leaves at most P - 1 workgroups waiting, and a process has four
+// hardware queues, so groups of up to 64 can never fill the 256 compute units with waiting workgroups and need no
+// order.  (Not while a graph is captured: its launches have the order of the graph.)
+static int tr_in_order(int P, hipStream_t st, bool before) {
+  static std::mutex mx;
+  static hipEvent_t ev[64];
+  static bool used[64];
+  if (P <= 64) return TC_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return TC_OK;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return TC_ERR_HIP;
+  if (before) {
+    mx.lock();
+    if (!used[dev] && hipEventCreateWithFlags(&ev[dev], hipEventDisableTiming) != hipSuccess) { mx.unlock(); return TC_ERR_HIP; }
+    if (used[dev] && hipStreamWaitEvent(st, ev[dev], 0) != hipSuccess) { mx.unlock(); return TC_ERR_HIP; }
+    used[dev] = true;
+    return TC_OK;  // the lock is held until the event is recorded behind the launch
   }
+  const hipError_t e = hipEventRecord(ev[dev], st);
+  mx.unlock();
+  return e == hipSuccess ? TC_OK : TC_ERR_HIP;
 }
 
-int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float* tauv, float* Vc, double* panels,
-                   size_t panels_stride, int* tab, hipStream_t st) {
-  const int N = pl.N, nb = tridiag_panel_width(N);
-  if (nb < 4) return TC_ERR_SHAPE;
-  if ((size_t)2 * round_up(N, 16) * nb > panels_stride) return TC_ERR_WORKSPACE;
-  const size_t lds = tridiag_lds_bytes(N, nb);
-  // more than 64 KB of dynamic LDS has to be allowed per function (a cheap host call, repeated so that it
-  // holds on whichever device is current)
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_panel_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          TD_LDS_BYTES) != hipSuccess)
+template <int PC>
+static int tr_launch(const Plan& pl, const TrPhase& ph, double* G, double* dvec, double* evec, float* tauv, float* Vc, u64* sync,
+                     size_t stride, int32_t* fail, hipStream_t st) {
+  typedef TrShape<PC> S;
+  if (S::LDS > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_kernel<PC>),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS) != hipSuccess)
     return TC_ERR_HIP;
-  TC_TIMED(PK_TRIDIAG_UPDATE, 2, st, (tridiag_table_kernel<<<(N + 255) / 256, 256, 0, st>>>(N, tab)));
-  if (pl.batch_call >= 96) {  // the chip is full of images: the whole reduction in one launch, updates on the image's own compute unit
-    TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_panel_kernel<<<pl.B, TD_THREADS, lds, st>>>(G, N, pl.Np, nb, 0, N - 1, 1, dvec, evec, tauv, Vc, panels, panels_stride, tab)));
-    return check_launch();
+  const int grid = (S::MODE == 1 ? (pl.B + 7) / 8 * 8 : pl.B) * S::P;
+  int rc = tr_in_order(S::P, st, true);
+  if (rc != TC_OK) return rc;
+  TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_kernel<PC><<<grid, TR_THREADS, S::LDS, st>>>(G, pl.N, pl.Np, pl.B, ph.first, ph.last, ph.first == 0, dvec, evec, tauv, Vc, sync + ph.off, stride, fail)));
+  rc = check_launch();
+  const int rc2 = tr_in_order(S::P, st, false);
+  return rc != TC_OK ? rc : rc2;
+}
+
+int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float* tauv, float* Vc, void* sync, size_t sync_bytes,
+                   int32_t* fail, hipStream_t st) {
+  TrPhase ph[TR_SIZES];
+  size_t words;
+  const int n = tr_phases(pl.N, pl.batch_call, ph, &words);
+  if (n == 0) return TC_ERR_SHAPE;
+  const size_t stride = sync_bytes / 8;
+  if (words > stride) return TC_ERR_WORKSPACE;
+  u64* sy = static_cast<u64*>(sync);
+  const unsigned per = (unsigned)((words + 1023) / 1024);
+  TC_TIMED(PK_TRIDIAG_UPDATE, 0, st, (tridiag_clear_kernel<<<dim3(per < 1 ? 1 : per > 64 ? 64 : per, pl.B), 256, 0, st>>>(sy, stride, words, fail)));
+  for (int i = 0; i < n; i++) {
+    int rc = TC_ERR_SHAPE;
+#define TR_CASE(SIZE_, PC_) case SIZE_: rc = tr_launch<PC_>(pl, ph[i], G, dvec, evec, tauv, Vc, sy, stride, fail, st); break;
+    switch (ph[i].size) {
+      TR_CASE(0, 0) TR_CASE(1, 1) TR_CASE(2, 2) TR_CASE(3, 3) TR_CASE(4, 4) TR_CASE(5, 5) TR_CASE(6, 7)
+    }
+#undef TR_CASE
+    if (rc != TC_OK) return rc;
   }
-  for (int j0 = 0; j0 < N - 1; j0 += nb) {
-    const int jend = j0 + nb < N - 1 ? j0 + nb : N - 1;
-    const int kcols = round_up(jend - j0, 4);
-    TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_panel_kernel<<<pl.B, TD_THREADS, lds, st>>>(G, N, pl.Np, nb, j0, j0 + 1, 0, dvec, evec, tauv, Vc, panels, panels_stride, tab)));
-    const int base = jend & ~15;
-    const int nrt = (N - base + 15) >> 4, ncc = (N - base + 63) >> 6;
-    int ntasks = 0;
-    for (int a = 0; a < nrt; a++) ntasks += ncc < (a >> 2) + 1 ? ncc : (a >> 2) + 1;
-    TC_TIMED(PK_TRIDIAG_UPDATE, 0, st, (tridiag_update_kernel<<<dim3((ntasks + 3) / 4, pl.B), 256, 0, st>>>(G, N, pl.Np, nb, jend, kcols, panels, panels_stride, ntasks)));
-  }
-  TC_TIMED(PK_TRIDIAG_UPDATE, 1, st, (tridiag_last_kernel<<<pl.B, 64, 0, st>>>(G, N, pl.Np, dvec, evec, tauv)));
   return check_launch();
 }
 
