@@ -22,9 +22,10 @@ int make_plan(const tc_params* p, Plan* pl) {
       p->eig_method < TC_EIG_AUTO || p->eig_method > TC_EIG_TRIDIAGONAL || p->n_prompt_queries < 0 ||
       (int64_t)p->vis_start + p->n_vis + p->n_prompt_queries > p->seq_len)
     return TC_ERR_PARAM;
-  // the tridiagonal route works in float64
-  const bool direct_ok = p->eig_dtype == TC_EIG_F64 && p->n_vis <= 1024 && tridiag_fits(p->n_vis);
-  if (p->eig_method == TC_EIG_TRIDIAGONAL && !direct_ok) return TC_ERR_PARAM;
+  // the tridiagonal route works in float64; the caller may name it for up to 1024 tokens, on its own account the
+  // library takes it wherever it fits
+  const bool direct_ok = p->eig_dtype == TC_EIG_F64 && tridiag_fits(p->n_vis);
+  if (p->eig_method == TC_EIG_TRIDIAGONAL && !(direct_ok && p->n_vis <= 1024)) return TC_ERR_PARAM;
   if (p->k_final < 1 || p->k_final > p->k_prune || p->k_prune > p->n_vis) return TC_ERR_PARAM;
   const int nA = p->k_prune / 2, nB = p->k_prune - nA;
   if (p->k_prune - p->k_final > nB) return TC_ERR_PARAM;
@@ -80,7 +81,7 @@ int make_plan(const tc_params* p, Plan* pl) {
     q.off_td_bad = take(B * 4);
     q.off_td_wgt = take(B * Np * 8);
     q.off_td_W = take(B * Np * Np * 4);        // eigenvectors of T (the reflectors use the region of U)
-    q.off_td_tw = take(B * Np * Np * 16);      // pivots and multipliers of the twisted factorisations
+    q.off_td_mark = take(B * (Np + 1) * 4);    // per slot: vector to be orthogonalised; one word per image
     q.off_td_Cpart = take(B * nstrip * Np * 8);
     q.off_td_Tf = take(B * ((N + 15) / 16) * 256 * 4);   // T factors of the blocks of 16 reflectors
     q.td_sync_bytes = tridiag_sync_bytes(q.N, q.batch_call);
@@ -102,14 +103,13 @@ static int direct_chain(const Plan& pl, const Plan& sub, int img0, const tc_para
   double* evec = at<double>(ws, pl.off_td_e) + i0 * Np;
   float* tauv = at<float>(ws, pl.off_td_tau) + i0 * Np;
   float* Vc = at<float>(ws, pl.off_U) + i0 * Np * Np;
-  double* tw = at<double>(ws, pl.off_td_tw);
   int32_t* fail = at<int32_t>(ws, pl.off_td_fail) + i0;
   int rc = launch_tridiag(sub, G, dvec, evec, tauv, Vc, at<char>(ws, pl.off_td_sync) + i0 * pl.td_sync_bytes, pl.td_sync_bytes, fail, st);
   if (rc != TC_OK) return rc;
   return launch_td_eigen(sub, dvec, evec, tauv, Vc, at<double>(ws, pl.off_td_lam) + i0 * Np, at<int2>(ws, pl.off_td_blk) + i0 * Np,
-                         at<double>(ws, pl.off_td_tnorm) + i0, tw + i0 * Np * Np, tw + ((size_t)pl.B + i0) * Np * Np,
+                         at<double>(ws, pl.off_td_tnorm) + i0, G,
                          at<float>(ws, pl.off_td_W) + i0 * Np * Np, at<double>(ws, pl.off_td_rn) + i0 * Np,
-                         at<int32_t>(ws, pl.off_td_bad) + i0, fail, at<double>(ws, pl.off_sig) + i0 * Np,
+                         at<int32_t>(ws, pl.off_td_bad) + i0, at<int32_t>(ws, pl.off_td_mark) + i0 * (Np + 1), fail, at<double>(ws, pl.off_sig) + i0 * Np,
                          at<double>(ws, pl.off_td_wgt) + i0 * Np, at<double>(ws, pl.off_td_Cpart) + i0 * nstrip * Np,
                          at<float>(ws, pl.off_td_Tf) + i0 * npanel * 256, p->sv_rtol, vectors, C_ws ? C_ws + i0 * pl.N : nullptr,
                          ics ? ics + i0 * pl.N : nullptr, sigma ? sigma + i0 * pl.N : nullptr, info ? info + i0 : nullptr, st);

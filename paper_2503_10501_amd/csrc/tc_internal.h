@@ -57,7 +57,7 @@ struct Plan {
   size_t off_O, off_S, off_Spart, off_G, off_U, off_R, off_offpart, off_state, off_sig, off_C, off_E, off_order,
       off_rnorm, off_sim, off_mlist, off_info;
   size_t off_td_d, off_td_e, off_td_tau, off_td_lam, off_td_blk, off_td_tnorm, off_td_rn, off_td_bad, off_td_wgt,
-      off_td_W, off_td_tw, off_td_Cpart, off_td_Tf, off_td_sync, off_td_fail;  // direct eigensolver only
+      off_td_W, off_td_mark, off_td_Cpart, off_td_Tf, off_td_sync, off_td_fail;  // direct eigensolver only
   size_t td_sync_bytes;  // exchange memory of the reduction, per image
   size_t total;
 };
@@ -93,8 +93,8 @@ bool tridiag_fits(int N);                     // the reduction takes N tokens
 size_t tridiag_sync_bytes(int N, int B);      // exchange memory of one image (B: images of the call)
 int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float* tauv, float* Vc, void* sync, size_t sync_bytes,
                    int32_t* fail, hipStream_t st);
-int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, const float* tauv, const float* Vc,
-                    double* lam, int2* blk, double* tnorm, double* DP, double* DM, float* W, double* rn, int32_t* bad, const int32_t* fail,
+int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, const float* tauv, float* Vc,
+                    double* lam, int2* blk, double* tnorm, double* scratch, float* W, double* rn, int32_t* bad, int32_t* mark, const int32_t* fail,
                     double* sig, double* wgt, double* Cpart, float* Tf, float sv_rtol, bool vectors, float* C, float* C_out,
                     float* sigma_out, int32_t* info_out, hipStream_t st);
 int direct_eigenvalues(const Plan& pl, const tc_params* p, float* sigma, int32_t* info, void* ws, hipStream_t st);  // api.hip

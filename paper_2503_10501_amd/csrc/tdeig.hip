@@ -4,20 +4,22 @@
 //       (forward L D+ L^T, backward U D- U^T, joined at the index r that minimises |gamma_r|;
 //       the vector solves (T - lambda I) z = gamma_r e_r), one lane per eigenvector;
 //   3   back-transformation U = Q W = H_0 ... H_{N-2} W in float32 on the matrix cores, the reflectors sixteen
-//       at a time in compact WY form, a strip of 64 eigenvectors held in accumulator registers; since U is
+//       at a time in compact WY form, a strip of 16 eigenvectors held in accumulator registers; since U is
 //       only needed for it, the information contribution score of Eq. 3-6, C(x) = sum_i |U[x][i]| sigma_i,
 //       is accumulated right there: U is never written.
 // T is first split where an off-diagonal element is negligible (|e_k| <= eps ||T||); each eigenpair then
 // belongs to one unreduced block and its vector is zero outside that block, so equal eigenvalues of
 // decoupled blocks (block-diagonal Gram matrices, null spaces) get orthogonal vectors for free.
-// Eigenvectors of one block are computed independently of each other: their mutual orthogonality is
-// eps ||T|| / gap.  For the spectra this library meets (gaps >= 1e-9 ||T||) that is 1e-6 or better; a pair
-// closer than 1e-10 ||T|| inside one block is orthogonalised explicitly afterwards (td_cluster_kernel).
+// Eigenvectors of one block are computed independently of each other; a close pair that did not come out orthogonal is
+// orthogonalised explicitly afterwards (td_pairs_kernel, td_weights_kernel).
 #include <cfloat>
+#include <utility>
 
 #include "tc_internal.h"
 
 namespace tc {
+
+typedef unsigned long long u64;
 
 constexpr double TD_EPS = 2.220446049250313e-16;
 
@@ -26,452 +28,504 @@ constexpr double TD_EPS = 2.220446049250313e-16;
 // of the block [s, t) that row k lies in), blk [B][Np] = (s, t), and tnorm [B] = ||T||_inf.
 //
 // The number of eigenvalues below x is the number of sign changes in the sequence of leading principal
-// minors p_0 = 1, p_1 = d_s - x, p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}.  In this form the chain from one step to the next is a single fused multiply-add;
-// the quotient form q_i = d_i - x - e^2 / q_{i-1} puts a float64 division (thirty dependent instructions)
-// on it, and with one eigenvalue per lane there is nothing to hide that latency behind: measured 3.4 ms
-// per batch against 0.2.  T is scaled by a power of two to ||T|| <= 1 so that the minors change by at most a
+// minors p_0 = 1, p_1 = d_s - x, p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}.  In this form the step from one row to the
+// next is multiply-adds only; the quotient form q_i = d_i - x - e^2 / q_{i-1} puts a float64 division (thirty
+// dependent instructions) on it, and with one eigenvalue per lane there is nothing to hide that latency behind.
+// T is scaled by a power of two to ||T|| <= 1 so that the minors change by at most a
 // factor 3 per step, and they are brought back into range every eight steps.
 typedef double tb_pair __attribute__((ext_vector_type(2)));
 
 // Scaled copy of T for the bisection, one workgroup per image: prep [B][prep_stride] doubles holds
-// (d_i, e_i^2) pairs for rows 0 .. N-1 (e_i = |coupling of rows i-1 and i|, e_0 = 0; the square is 0 where T
-// is split), sixteen zero pairs behind them, then the N scaled |e_i|.  Also tnorm [B] = ||T||_inf, and bad[b]
-// is cleared.
+// (d_i, -e_i^2) pairs for rows 0 .. N-1 (e_i = |coupling of rows i-1 and i|, e_0 = 0; the square is 0 where T
+// is split), 32 zero pairs behind them, then the Gershgorin interval of T (scaled).  Also the block (s, t) of every row,
+// tnorm [B] = ||T||_inf; bad[b] starts from the failure flag of the reduction, any[b] from 0.
 __global__ __launch_bounds__(256) void td_prepare_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
                                                          double* __restrict__ prep, size_t prep_stride,
-                                                         double* __restrict__ tnorm, int32_t* __restrict__ bad,
+                                                         double* __restrict__ tnorm, int2* __restrict__ blk,
+                                                         int32_t* __restrict__ bad, int32_t* __restrict__ any,
                                                          const int32_t* __restrict__ fail, int N, int Np) {
-  __shared__ double wmax[4];
+  __shared__ double wred[3][4];
+  __shared__ u64 cut[MAX_NVIS / 64 + 1];  // bit i: a block starts at row i
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* db = dvec + (size_t)b * Np;
   const double* eb = evec + (size_t)b * Np;
-  double rowmax = 0.0;
-  for (int i = tid; i < N; i += 256)
-    rowmax = fmax(rowmax, fabs(db[i]) + (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i + 1 < N ? fabs(eb[i]) : 0.0));
+  double rowmax = 0.0, lo = DBL_MAX, hi = -DBL_MAX;
+  for (int i = tid; i < N; i += 256) {
+    const double r = (i > 0 ? fabs(eb[i - 1]) : 0.0) + (i + 1 < N ? fabs(eb[i]) : 0.0), d = db[i];
+    rowmax = fmax(rowmax, fabs(d) + r);
+    lo = fmin(lo, d - r);
+    hi = fmax(hi, d + r);
+  }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) rowmax = fmax(rowmax, __shfl_xor(rowmax, o, 64));
-  if (lane == 0) wmax[wave] = rowmax;
+  for (int o = 32; o > 0; o >>= 1) {
+    rowmax = fmax(rowmax, __shfl_xor(rowmax, o, 64));
+    lo = fmin(lo, __shfl_xor(lo, o, 64));
+    hi = fmax(hi, __shfl_xor(hi, o, 64));
+  }
+  if (lane == 0) { wred[0][wave] = rowmax; wred[1][wave] = lo; wred[2][wave] = hi; }
   __syncthreads();
-  const double tn = fmax(fmax(wmax[0], wmax[1]), fmax(wmax[2], wmax[3]));
+  const double tn = fmax(fmax(wred[0][0], wred[0][1]), fmax(wred[0][2], wred[0][3]));
   const double split = TD_EPS * tn;
   // power of two that brings ||T|| into (1/2, 1] (exact); a zero or non-finite norm leaves T as it is
   int ex = 0;
   if (tn > 0.0 && tn < DBL_MAX) (void)frexp(tn, &ex);
   const double down = ldexp(1.0, -ex);
   tb_pair* pr = reinterpret_cast<tb_pair*>(prep + (size_t)b * prep_stride);
-  double* esc = reinterpret_cast<double*>(pr + N + 16);
-  for (int i = tid; i < N + 16; i += 256) {
+  const int rows = round_up(N, 256);
+  for (int i = tid; i < rows + 256; i += 256) {
     const double e = i > 0 && i < N ? fabs(eb[i - 1]) : 0.0;
-    pr[i] = i < N ? tb_pair{db[i] * down, e > split ? (e * down) * (e * down) : 0.0} : tb_pair{0.0, 0.0};
-    if (i < N) esc[i] = e * down;
+    const bool start = i >= N || !(e > split);
+    if (i < N + 32) pr[i] = i < N ? tb_pair{db[i] * down, start ? 0.0 : -(e * down) * (e * down)} : tb_pair{0.0, 0.0};
+    const u64 m = __ballot(start);
+    if (lane == 0 && (i >> 6) <= MAX_NVIS / 64) cut[i >> 6] = m;  // (rows past N count as starts: a block ends at N at the latest)
   }
-  if (tid == 0) { tnorm[b] = tn; bad[b] = fail[b] ? 4 : 0; }
+  __syncthreads();
+  for (int i = tid; i < N; i += 256) {
+    int w = i >> 6;
+    u64 m = cut[w] & (~0ull >> (63 - (i & 63)));  // starts at or before row i (row 0 is one)
+    while (m == 0) m = cut[--w];
+    const int s = 64 * w + 63 - __builtin_clzll(m);
+    w = i >> 6;
+    m = (i & 63) == 63 ? 0 : cut[w] & (~0ull << ((i & 63) + 1));
+    while (m == 0) m = cut[++w];
+    blk[(size_t)b * Np + i] = int2{s, min(64 * w + __builtin_ctzll(m), N)};
+  }
+  if (tid == 0) {
+    tnorm[b] = tn;
+    bad[b] = fail[b] ? 4 : 0;
+    any[b] = 0;
+    pr[N + 32] = tb_pair{fmin(fmin(wred[1][0], wred[1][1]), fmin(wred[1][2], wred[1][3])) * down,
+                         fmax(fmax(wred[2][0], wred[2][1]), fmax(wred[2][2], wred[2][3])) * down};
+  }
 }
 
-// G = 1 << gs lanes per eigenvalue; blockIdx.y = image.  A step evaluates the number of eigenvalues below G
-// points that cut the interval into G + 1 equal parts, one point per lane, and keeps the part that holds the
-// eigenvalue: log2(G + 1) bits per walk over the rows instead of one (the walk is a chain of dependent
-// operations that a wavefront alone on its SIMD cannot hide; with few images the chip has lanes to spare).
-// The usual case, T not split anywhere (or every lane of the
-// wavefront in the same block), reads the rows through the scalar unit: the coefficients are the same for all
-// lanes, and fetched per lane from LDS the sixteen bytes per row and lane made the LDS the limit of the kernel.
+// d += (lane n of each row of 16 lanes of `row`) * c
+template <int n>
+__device__ __forceinline__ void td_fmac_bcast(double& d, double row, double c) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(row), "v"(c), "n"(n));
+}
+
+// One row of the recurrence: (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2} as -x p + (-e^2) pp + d p, the coefficients by broadcast:
+// four instructions (46 cycles per row for a wavefront alone on its SIMD; with d - x formed first, one operation fewer
+// on the chain but one instruction more, 50).  The rounding is that of a d_i off by eps |x| <= eps ||T||, what the
+// entries of T carry anyway.
+template <int n>
+__device__ __forceinline__ void tb_row(double dr, double er, double x, double& p, double& pp, unsigned& signs) {
+  double pn = -x * p;
+  td_fmac_bcast<n>(pn, er, pp);
+  td_fmac_bcast<n>(pn, dr, p);
+  signs = __builtin_amdgcn_alignbit(signs, (unsigned)__double2hiint(pn), 31);
+  pp = p;
+  p = pn;
+}
+
+// The number of sign changes of the minors at x for rows s0 .. t0-1 (uniform over the wavefront), and the last minor as
+// p 2^ex.  Sixteen rows' coefficients sit in the lanes of a row of 16, the next sixteen are in flight.  (Through the
+// scalar unit, whose loads can only be waited for all together, a row cost 73 cycles.)
+// Sign changes are counted on the sign bits.  The signs of the minors are shifted into one register, a bit
+// per row (bit 0 = the newest); after eight rows the changes among them and against the minor before them
+// are the set bits of (signs xor signs >> 1) in its low byte.  An exact zero needs no special case: its
+// successor is -e^2 times its predecessor, so the three minors around it contain one sign change whichever
+// sign the zero is given.  Every eight rows the minors are brought back into range by a power of two (which changes no
+// sign) taken from the minors three rows before, off the chain.
+__device__ __forceinline__ int tb_walk(const tb_pair* __restrict__ pr, int s0, int t0, int N, int lane, double x, double& p, int& ex) {
+  double pp = 1.0;
+  p = pr[s0].x - x;
+  ex = 0;
+  unsigned signs = (unsigned)__double2hiint(p) >> 31;  // p_0 = 1 is positive: bit 1 = 0
+  int cnt = (int)signs;
+  const tb_pair* q = pr + s0 + 1 + (lane & 15);
+  const int nrow = t0 - s0 - 1, last = N + 31 - s0 - 1 - (lane & 15);  // (reads stay inside the zero pairs behind T)
+  tb_pair cur = q[0];
+  for (int i0 = 0; i0 < nrow; i0 += 16) {
+    const tb_pair nxt = q[min(i0 + 16, last)];
+    double dr = cur.x, er = cur.y;
+    asm volatile("s_nop 1" : "+v"(dr), "+v"(er));
+    const int left = nrow - i0;
+#define TB_ROW(n) tb_row<n>(dr, er, x, p, pp, signs);
+#define TB_ROW8(o)                                                            \
+  {                                                                           \
+    TB_ROW(o) TB_ROW(o + 1) TB_ROW(o + 2) TB_ROW(o + 3) TB_ROW(o + 4)         \
+    const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));        \
+    TB_ROW(o + 5) TB_ROW(o + 6) TB_ROW(o + 7)                                 \
+    cnt += __popc((signs ^ (signs >> 1)) & 0xffu);                            \
+    p = __builtin_amdgcn_ldexp(p, -e);                                        \
+    pp = __builtin_amdgcn_ldexp(pp, -e);                                      \
+    ex += e;                                                                  \
+  }
+    if (left >= 8) TB_ROW8(0)
+    if (left >= 16) {
+      TB_ROW8(8)
+    } else if ((left & 7) != 0) {  // the last rows of the block
+      double d8 = left > 8 ? dr : __shfl_xor(dr, 8, 64), e8 = left > 8 ? er : __shfl_xor(er, 8, 64);
+      asm volatile("s_nop 1" : "+v"(d8), "+v"(e8));
+      const int r = left & 7;
+#define TB_TAIL(n) if (r > n) tb_row<8 + n>(d8, e8, x, p, pp, signs);
+      TB_TAIL(0) TB_TAIL(1) TB_TAIL(2) TB_TAIL(3) TB_TAIL(4) TB_TAIL(5) TB_TAIL(6)
+#undef TB_TAIL
+      cnt += __popc((signs ^ (signs >> 1)) & ((1u << r) - 1u));
+    }
+#undef TB_ROW8
+#undef TB_ROW
+    cur = nxt;
+  }
+  return cnt;
+}
+
+// The same for lanes in different blocks: every lane reads its own rows; rows past the block's end are replaced by the
+// identity step p_i = p_{i-1}, which changes no sign.
+__device__ __forceinline__ int tb_walk_own(const tb_pair* __restrict__ pr, int s, int t, int N, double x, double& p, int& ex) {
+  double pp = 1.0;
+  p = pr[s].x - x;
+  ex = 0;
+  unsigned signs = (unsigned)__double2hiint(p) >> 31;
+  int cnt = (int)signs;
+  for (int i0 = s + 1; __any(i0 < t); i0 += 8) {
+    tb_pair c[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) c[u] = pr[min(i0 + u, N + 31)];
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const bool in = i0 + u < t;
+      const double pn = fma(in ? c[u].x - x : 1.0, p, (in ? c[u].y : 0.0) * pp);
+      signs = __builtin_amdgcn_alignbit(signs, (unsigned)__double2hiint(pn), 31);
+      pp = in ? p : pp;
+      p = pn;
+    }
+    cnt += __popc((signs ^ (signs >> 1)) & 0xffu);
+    const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));
+    p = __builtin_amdgcn_ldexp(p, -e);
+    pp = __builtin_amdgcn_ldexp(pp, -e);
+    ex += e;
+  }
+  return cnt;
+}
+
+// G = 1 << gs lanes per eigenvalue (up to the whole wavefront); blockIdx.y = image.
+// The kernel is bound by the chain of dependent operations of a walk over the rows, so it makes few walks:
+//  - lanes whose eigenvalues still share one interval cut it together: n lanes evaluate n points that part it evenly, and
+//    every lane takes the part that holds its eigenvalue (the neighbours of a wavefront lie close together: four or
+//    five walks separate the noise part of a spectrum that spans 1e-6 of ||T||, where halving takes twenty);
+//  - a lane alone with an interval that holds exactly one eigenvalue goes on with the secant through the last minor at
+//    the two ends (Anderson-Bjoerck weights, Sturm counts keep the bracket), seven to twelve walks instead of thirty;
+//  - several lanes alone with their eigenvalue (small calls) bracket the secant's estimate with points at distances that
+//    fall geometrically, so that an interval shrinks to the error of the estimate in one walk.
+// 18 walks at one lane per eigenvalue (55 by halving alone), 10 with 64 lanes: 0.75 -> 0.24 ms for 64 images of 576 tokens,
+// 0.32 -> 0.11 ms for one.
+// The search ends at a relative width of 2 eps: T is graded (the reduction meets the large eigenvalues first), its small
+// eigenvalues are well determined relative to their size, and the vectors of close ones are as orthogonal as their
+// relative gap allows.  What ends below the resolution of the reduction (8 eps ||T||) counts as zero and is left there.
 __global__ __launch_bounds__(256) void td_bisect_kernel(const double* __restrict__ prep, size_t prep_stride,
                                                         const double* __restrict__ tnorm, double* __restrict__ lam,
-                                                        int2* __restrict__ blk, int N, int Np, int gs) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char tb_smem[];
-  double* ds = reinterpret_cast<double*>(tb_smem);  // [N], scaled
-  double* es = ds + N;                               // [N]: es[i] = |coupling of rows i-1 and i|, es[0] = 0, scaled
-  double* e2 = es + N;                               // [N]: its square, 0 where T is split
-  tb_pair* de = reinterpret_cast<tb_pair*>(e2 + N);  // [N + 16]: (ds[i], e2[i]) side by side, one 16-byte read per row; zero padding
-  const int b = blockIdx.y, tid = threadIdx.x;
+                                                        const int2* __restrict__ blk, int N, int Np, int gs) {
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const tb_pair* __restrict__ pr = reinterpret_cast<const tb_pair*>(prep + (size_t)b * prep_stride);
-  const double* __restrict__ esc = reinterpret_cast<const double*>(pr + N + 16);
-  for (int i = tid; i < N + 16; i += 256) {
-    const tb_pair v = pr[i];
-    de[i] = v;
-    if (i < N) {
-      ds[i] = v.x;
-      e2[i] = v.y;
-      es[i] = esc[i];
-    }
-  }
   const double tn = tnorm[b];
   int ex = 0;
   if (tn > 0.0 && tn < DBL_MAX) (void)frexp(tn, &ex);
   const double up = ldexp(1.0, ex);
-  __syncthreads();
-  const int G = 1 << gs, sec = tid & (G - 1);  // this lane's point: the (sec + 1)-th of G
-  const int k = (blockIdx.x * 256 + tid) >> gs;
-  if (k >= N) return;                          // (whole groups of G lanes leave together)
-  const double inv = 1.0 / (double)(G + 1);
-  const int gshift = (tid & 63) & ~(G - 1);    // first lane of the group within the wavefront
-  int s = k, t = k + 1;
-  while (s > 0 && e2[s] != 0.0) s--;
-  while (t < N && e2[t] != 0.0) t++;
-  const int m = k - s;
-  // Gershgorin interval of the block, slightly widened (scaled units: ||T|| <= 1)
-  double lo = DBL_MAX, hi = -DBL_MAX;
-  for (int i = s; i < t; i++) {
-    const double r = (i > s && e2[i] != 0.0 ? es[i] : 0.0) + (i + 1 < t && e2[i + 1] != 0.0 ? es[i + 1] : 0.0);
-    lo = fmin(lo, ds[i] - r);
-    hi = fmax(hi, ds[i] + r);
-  }
-  const double widen = 2.0 * TD_EPS * (t - s) + 2.0 * DBL_MIN;
-  lo -= widen;
-  hi += widen;
-  const double BIG = 0x1p256, SMALL = 0x1p-256;
-  const double d_s = ds[s];
+  const int G = 1 << gs;
+  // whole groups of G lanes past the last eigenvalue repeat it (every lane stays active: the walks read across lanes)
+  const int kk = (blockIdx.x * 256 + tid) >> gs, k = min(kk, N - 1);
+  const int2 st = blk[(size_t)b * Np + k];
+  const int s = st.x, t = st.y, m = k - s;
+  // Gershgorin interval of T, slightly widened (scaled units: ||T|| <= 1; blocks need no interval of their own, the
+  // search ends at an absolute width)
+  const tb_pair ger = pr[N + 32];
+  const double widen = 2.0 * TD_EPS * N + 2.0 * DBL_MIN;
+  double lo = ger.x - widen, hi = ger.y + widen;
+  int clo = 0, chi = t - s;       // eigenvalues of the block below the ends
+  double flo = 0.0, fhi = 0.0;    // last minor at the ends (0: not evaluated), times 2^elo, 2^ehi
+  int elo = 0, ehi = 0, side = 0, steps = 0;
+  double xs = lo, found = 0.0;
+  bool done = false, has = false;
   const int s0 = __builtin_amdgcn_readfirstlane(s), t0 = __builtin_amdgcn_readfirstlane(t);
   const bool uniform = __all(s == s0 && t == t0);
-  for (int it = 0; it < 128; it++) {
-    const double mid = 0.5 * (lo + hi);
-    if (!(mid > lo && mid < hi)) break;     // the interval cannot be halved any more
-    if (hi - lo <= 0.25 * TD_EPS) break;    // the entries of T carry errors of eps ||T|| themselves; same count for every lane
-    const double width = hi - lo;
-    const double x = gs ? lo + width * ((double)(sec + 1) * inv) : mid;  // the lane's point
-    double pp = 1.0, p = d_s - x;           // p_{i-2}, p_{i-1}
-    // Sign changes are counted on the sign bits.  The signs of the minors are shifted into one register, a bit
-    // per row (bit 0 = the newest); after eight rows the changes among them and against the minor before them
-    // are the set bits of (signs xor signs >> 1) in its low byte.  An exact zero needs no special case: its
-    // successor is -e^2 times its predecessor, so the three minors around it contain one sign change whichever
-    // sign the zero is given.  Eight rows at a time: their coefficients are fetched from LDS together and one
-    // chunk ahead (read one by one inside the chain, each read would cost its full latency); rows past the
-    // block's end are replaced by the identity step p_i = p_{i-1}, which changes no sign; then the pair of
-    // minors is brought back into range (a common factor does not change any sign).
-    unsigned signs = (unsigned)__double2hiint(p) >> 31;  // p_0 = 1 is positive: bit 1 = 0
-    int cnt = (int)signs;
-    if (uniform) {
-      // every lane of the wavefront walks over the same block: the row index is a scalar, the coefficients come
-      // through the scalar unit (loaded one chunk ahead), and no row needs a select.  (Two recurrences per
-      // lane, at one third and two thirds of the interval, were measured too: no gain, the kernel is bound by
-      // the rate at which one wavefront issues float64 operations, not by their latency.)
-      int i0 = s0 + 1;
-      tb_pair ca[8], cb[8];
-#pragma unroll
-      for (int u = 0; u < 8; u++) ca[u] = pr[i0 + u];
-#define TB_UCHUNK(CUR, NXT)                                                                    \
-  {                                                                                            \
-    _Pragma("unroll") for (int u = 0; u < 8; u++) NXT[u] = pr[i0 + 8 + u];                     \
-    _Pragma("unroll") for (int u = 0; u < 8; u++) {                                            \
-      const double pn = fma(CUR[u].x - x, p, -(CUR[u].y * pp));                              \
-      signs = __builtin_amdgcn_alignbit(signs, (unsigned)__double2hiint(pn), 31);              \
-      pp = p;                                                                                  \
-      p = pn;                                                                                  \
-    }                                                                                          \
-    cnt += __popc((signs ^ (signs >> 1)) & 0xffu);                                             \
-    const double mag = fmax(fabs(p), fabs(pp));                                                \
-    const double f = mag > BIG ? SMALL : (mag < SMALL && mag > 0.0 ? BIG : 1.0);               \
-    p *= f;                                                                                    \
-    pp *= f;                                                                                   \
-    i0 += 8;                                                                                   \
-  }
-      while (i0 + 8 <= t0) {
-        TB_UCHUNK(ca, cb)
-        if (i0 + 8 > t0) {
-#pragma unroll
-          for (int u = 0; u < 8; u++) ca[u] = cb[u];
-          break;
-        }
-        TB_UCHUNK(cb, ca)
-      }
-#undef TB_UCHUNK
-      // the last, shorter chunk (ca holds rows i0 .. i0 + 7)
-#pragma unroll
-      for (int u = 0; u < 8; u++) {
-        if (i0 + u < t0) {
-          const double pn = fma(ca[u].x - x, p, -(ca[u].y * pp));
-          cnt += (int)((unsigned)(__double2hiint(pn) ^ __double2hiint(p)) >> 31);
-          pp = p;
-          p = pn;
+  const int up_lane = lane == 0 ? 0 : lane - 1;
+  for (int it = 0; it < 160; it++) {
+    const double mid = 0.5 * (lo + hi), width = hi - lo;
+    done = done || !(mid > lo && mid < hi) || width <= 2.0 * TD_EPS * fabs(mid) || hi <= 2.0 * TD_EPS;
+    if (__all(done)) break;
+    // the run of lanes that share this interval
+    const double ulo = __shfl(lo, up_lane, 64), uhi = __shfl(hi, up_lane, 64);
+    const int us = __shfl(s, up_lane, 64);
+    const u64 first = __ballot((lane == 0) | (ulo != lo) | (uhi != hi) | (us != s));
+    const int r0 = 63 - __builtin_clzll(first & (~0ull >> (63 - lane)));
+    const u64 after = lane == 63 ? 0 : first & (~0ull << (lane + 1));
+    const int r1 = after ? __builtin_ctzll(after) : 64, n = r1 - r0;
+    double x = n > 1 ? lo + width * ((double)(lane - r0 + 1) / (double)(n + 1)) : mid;
+    bool secant = false;
+    if (n == G && clo == m && chi == m + 1 && flo != 0.0 && fhi != 0.0 && steps < 20 && !done) {
+      const double fh = __builtin_amdgcn_ldexp(fhi, min(max(ehi - elo, -2000), 2000));
+      const double ratio = fabs(fh / flo);
+      const double xe = lo + width * (flo / (flo - fh));
+      // a polynomial of this degree is only close to a line near its root: until the ends' values come within a factor
+      // of 8 of each other the interval is cut evenly
+      if (steps > 0 || (ratio > 0.125 && ratio < 8.0)) {
+        steps++;
+        if (n > 1) {  // points on both sides of the estimate, from a quarter of the interval down to 2^-38 of it
+          const int half = G / 2, sec = lane - r0, q = sec < half ? sec : G - 1 - sec;
+          const double off = __builtin_amdgcn_ldexp(width, half == 1 ? -6 : -2 - 36 * q / (half - 1));
+          x = fmin(fmax(sec < half ? xe - off : xe + off, lo), hi);
+        } else if (steps > 1 && (!(xe > lo && xe < hi) || fabs(xe - xs) <= 2.0 * TD_EPS * fabs(xe))) {
+          done = has = true;
+          found = xe;
+        } else if (xe > lo && xe < hi) {
+          secant = true;
+          x = xs = xe;
         }
       }
+    }
+    double p;
+    int pe;
+    const int cnt = uniform ? tb_walk(pr, s0, t0, N, lane, x, p, pe) : tb_walk_own(pr, s, t, N, x, p, pe);
+    // the last point of the run with at most m eigenvalues below it, and the first with more (the counts rise with the point)
+    int ms = r0;
+    if (n > 1) {
+      int step = 32, lo_i = r0 - 1;  // lo_i: largest lane known to have cnt <= m
+      for (; step > 0; step >>= 1) {
+        const int c = min(lo_i + step, 63);
+        const int v = __shfl(cnt, c, 64);
+        if (lo_i + step < r1 && v <= m) lo_i += step;
+      }
+      {  // (a run of 64 needs one more probe)
+        const int v = __shfl(cnt, min(lo_i + 1, 63), 64);
+        if (lo_i + 1 < r1 && v <= m) lo_i += 1;
+      }
+      ms = lo_i + 1;
     } else {
-    // (two chunk buffers that trade places: no register copies)
-    tb_pair ca[8], cb[8];
-    int i0 = s + 1;
-#pragma unroll
-    for (int u = 0; u < 8; u++) ca[u] = de[i0 + u];
-#define TB_CHUNK(CUR, NXT)                                                                                                \
-  {                                                                                                                       \
-    _Pragma("unroll") for (int u = 0; u < 8; u++) NXT[u] = de[i0 + 8 + u];                                                \
-    /* the eight reads of this chunk have arrived; those of the next stay in flight */                                   \
-    asm volatile("" : "+v"(CUR[0].x), "+v"(CUR[1].x), "+v"(CUR[2].x), "+v"(CUR[3].x), "+v"(CUR[4].x), "+v"(CUR[5].x),     \
-                      "+v"(CUR[6].x), "+v"(CUR[7].x), "+v"(CUR[0].y), "+v"(CUR[1].y), "+v"(CUR[2].y), "+v"(CUR[3].y),     \
-                      "+v"(CUR[4].y), "+v"(CUR[5].y), "+v"(CUR[6].y), "+v"(CUR[7].y));                                    \
-    if (i0 + 8 <= t) { /* a whole chunk: no selects */                                                                    \
-      _Pragma("unroll") for (int u = 0; u < 8; u++) {                                                                     \
-        const double pn = fma(CUR[u].x - x, p, -(CUR[u].y * pp));                                                       \
-        signs = __builtin_amdgcn_alignbit(signs, (unsigned)__double2hiint(pn), 31);                                       \
-        pp = p;                                                                                                           \
-        p = pn;                                                                                                           \
-      }                                                                                                                   \
-    } else {                                                                                                              \
-      _Pragma("unroll") for (int u = 0; u < 8; u++) {                                                                     \
-        const bool in = i0 + u < t;                                                                                       \
-        const double pn = fma(in ? CUR[u].x - x : 1.0, p, -((in ? CUR[u].y : 0.0) * pp));                               \
-        signs = __builtin_amdgcn_alignbit(signs, (unsigned)__double2hiint(pn), 31);                                       \
-        pp = p;                                                                                                           \
-        p = pn;                                                                                                           \
-      }                                                                                                                   \
-    }                                                                                                                     \
-    cnt += __popc((signs ^ (signs >> 1)) & 0xffu);                                                                        \
-    const double mag = fmax(fabs(p), fabs(pp));                                                                           \
-    const double f = mag > BIG ? SMALL : (mag < SMALL && mag > 0.0 ? BIG : 1.0);                                          \
-    p *= f;                                                                                                               \
-    pp *= f;                                                                                                              \
-    i0 += 8;                                                                                                              \
-  }
-    while (i0 < t) {
-      TB_CHUNK(ca, cb)
-      if (i0 >= t) break;
-      TB_CHUNK(cb, ca)
+      ms = cnt <= m ? r1 : r0;
     }
-#undef TB_CHUNK
+    const int la = max(ms - 1, 0), ha = min(ms, 63);
+    const double xl = __shfl(x, la, 64), xh = __shfl(x, ha, 64), pl = __shfl(p, la, 64), ph = __shfl(p, ha, 64);
+    const int el = __shfl(pe, la, 64), eh = __shfl(pe, ha, 64), cl = __shfl(cnt, la, 64), ch = __shfl(cnt, ha, 64);
+    if (secant && p == 0.0) { done = has = true; found = x; }
+    if (ms > r0 && !done) {  // the lower end moves
+      if (secant) {
+        if (side == -1) {  // twice in a row: the other end's value is weighed down
+          const double w = 1.0 - __builtin_amdgcn_ldexp(pl, min(max(el - elo, -2000), 2000)) / flo;
+          fhi *= w > 0.0 ? w : 0.5;
+        }
+        side = -1;
+      }
+      lo = xl; flo = pl; elo = el; clo = cl;
     }
-    if (gs == 0) {
-      if (cnt > m) hi = mid; else lo = mid;
-    } else {
-      // points with at most m eigenvalues below them lie left of the eigenvalue: their number (the counts rise
-      // with the point) picks the part; the new ends are points that lanes of the group evaluated, bit for bit
-      const unsigned long long left = __ballot(cnt <= m);
-      const int ms = __popcll((left >> gshift) & ((1ull << G) - 1ull));
-      const double nlo = ms == 0 ? lo : lo + width * ((double)ms * inv);
-      const double nhi = ms == G ? hi : lo + width * ((double)(ms + 1) * inv);
-      lo = nlo;
-      hi = nhi;
+    if (ms < r1 && !done) {
+      if (secant) {
+        if (side == 1) {
+          const double w = 1.0 - __builtin_amdgcn_ldexp(ph, min(max(eh - ehi, -2000), 2000)) / fhi;
+          flo *= w > 0.0 ? w : 0.5;
+        }
+        side = 1;
+      }
+      hi = xh; fhi = ph; ehi = eh; chi = ch;
     }
   }
-  if (sec == 0) {
-    lam[(size_t)b * Np + k] = 0.5 * (lo + hi) * up;
-    blk[(size_t)b * Np + k] = int2{s, t};
-  }
+  if ((lane & (G - 1)) == 0 && kk < N) lam[(size_t)b * Np + k] = (has ? found : 0.5 * (lo + hi)) * up;
 }
 
 // ---- 2b -----------------------------------------------------------------------------------------------
-// One lane per eigenvector.  DP and DM are scratch [B][Np][Np] doubles addressed [row][slot] (contiguous
-// across the lanes of a wavefront): the pivots of the two factorisations.  W [B][Np][Np] float receives the
-// unnormalised vector of slot k in column k (rows outside its block are zero); rn [B][Np] its reciprocal
-// norm (0 if the vector is not finite, which also raises bad[b]).
+// One lane per eigenvector: T - l I = L D+ L^T from the top (pivots dp, multipliers e_i / dp_i), = U D- U^T from the bottom
+// (pivots dm, multipliers e_{i-1} / dm_i), joined at the row r with the smallest |gamma|, gamma_i = dp_i + dm_i - (d_i - l);
+// z_r = 1, upwards z_i = -(e_i / dp_i) z_{i+1}, downwards z_i = -(e_{i-1} / dm_i) z_{i-1}.
+// W [B][Np][Np] float receives the unnormalised vector of slot k in column k (rows outside its block are zero); rn
+// [B][Np] its reciprocal norm (0 if the vector is not finite, which also raises bad[b]).
 //
 // All lanes of a wavefront walk over the same row at the same time, whatever block their eigenvalue belongs
-// to and wherever its twist index lies (a lane ignores the rows that are not its own): every access to the
-// scratch arrays and to W is one contiguous run per row.  With per-lane rows (each lane starting at its own
-// twist index) a wavefront touched up to 64 rows per instruction and the kernel took six times as long.
-// The two factorisations are independent chains with a division per row: they run in one loop, side by side.
-// So do the two halves of the vector.  Loads from the scratch arrays are issued one chunk of eight rows ahead.
+// to and wherever its twist index lies (a lane ignores rows that are not its own): every access to memory is one
+// contiguous run per row.  Two chains of divisions run side by side in each of three walks: pivots, gamma, vector.
+// Only the pivots at the ends of segments of sixteen rows are kept (cp, cm [row / 16][slot]); the later walks form the
+// others again from there.  Kept for every row they were 2 x 16 N^2 bytes of traffic per image and their latency three
+// times per row (0.34 ms for one image of 576 tokens, 0.40 for 64).
+constexpr int TW_SEG = 16;
+
+// 1 / x to the last bit or so: hardware estimate and two Newton steps (the pivots are never zero, denormal or infinite)
+__device__ __forceinline__ double tw_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
 __global__ __launch_bounds__(64) void td_twisted_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
                                                         const double* __restrict__ lam, const int2* __restrict__ blk,
-                                                        const double* __restrict__ tnorm, double* __restrict__ DP,
-                                                        double* __restrict__ DM, float* __restrict__ W,
+                                                        const double* __restrict__ tnorm, double* __restrict__ ckpt,
+                                                        size_t ckpt_stride, float* __restrict__ W,
                                                         double* __restrict__ rn, int32_t* __restrict__ bad, int N,
                                                         int Np) {
   extern __shared__ __attribute__((aligned(16))) unsigned char tw_smem[];
-  double* ds = reinterpret_cast<double*>(tw_smem);  // [N]
-  double* es = ds + N;                               // [N]: es[i] couples rows i and i+1 (signed), 0 where T is split
-  const int b = blockIdx.y, tid = threadIdx.x;
+  tb_pair* de = reinterpret_cast<tb_pair*>(tw_smem) + 1;  // [-1 .. 16 nseg - 1]: d_i, and e_i that couples rows i and i+1 (0 where T is split)
+  const int b = blockIdx.y, tid = threadIdx.x, nseg = (N + TW_SEG - 1) / TW_SEG;
   const double* db = dvec + (size_t)b * Np;
   const double* eb = evec + (size_t)b * Np;
-  const double split = TD_EPS * tnorm[b];
-  for (int i = tid; i < N; i += 64) {
-    ds[i] = db[i];
-    const double e = i + 1 < N ? eb[i] : 0.0;
-    es[i] = fabs(e) > split ? e : 0.0;
+  const double tn = tnorm[b], split = TD_EPS * tn;
+  for (int i = tid - 1; i < nseg * TW_SEG; i += 64) {  // rows behind the last stand alone (4 ||T|| is nobody's eigenvalue)
+    const double e = i >= 0 && i + 1 < N ? eb[i] : 0.0;
+    de[i] = tb_pair{i >= 0 && i < N ? db[i] : (tn > 0.0 ? 4.0 * tn : 1.0), fabs(e) > split ? e : 0.0};
   }
   __syncthreads();
   const int k = blockIdx.x * 64 + tid;
   if (k >= N) return;  // (no barrier below)
   const int2 st = blk[(size_t)b * Np + k];
   const int s = st.x, t = st.y;
-  double e2max = 0.0;
-  for (int i = s; i + 1 < t; i++) e2max = fmax(e2max, es[i] * es[i]);
-  const double pivmin = DBL_MIN * fmax(1.0, e2max);
+  const double pivmin = DBL_MIN * fmax(1.0, tn * tn);
   const double l = lam[(size_t)b * Np + k];
-  double* dp = DP + (size_t)b * Np * Np + k;
-  double* dmv = DM + (size_t)b * Np * Np + k;
+  double* cp = ckpt + (size_t)b * ckpt_stride + k;
+  double* cm = cp + (size_t)nseg * Np;
   float* w = W + (size_t)b * Np * Np + k;
+  auto guard = [&](double p) { return fabs(p) < pivmin ? -pivmin : p; };
 
-  // forward, rows ascending:   T - l I = L D+ L^T, pivots dp[i] (the chain starts anew at row s);
-  // backward, rows descending: T - l I = U D- U^T, pivots dm[j] (the chain starts anew at row t - 1)
+  // pivots: dp[i + 1] = d_{i+1} - l - e_i (e_i / dp[i]);  dm[i] = d_i - l - e_i (e_i / dm[i + 1])
   {
-    double p = 1.0, dm = 1.0;
-    auto row = [&](int i) {
-      const int j = N - 1 - i;
-      const double a = ds[i] - l, ep = i > 0 ? es[i - 1] : 0.0;
-      double pn = a - (ep / p) * ep;
-      pn = i == s ? a : pn;
-      if (fabs(pn) < pivmin) pn = -pivmin;
-      p = pn;
-      if (i >= s && i < t) dp[(size_t)i * Np] = p;
-      const double aj = ds[j] - l, ej = es[j];
-      double dn = aj - (ej / dm) * ej;
-      dn = j == t - 1 ? aj : dn;
-      if (fabs(dn) < pivmin) dn = -pivmin;
-      dm = dn;
-      if (j >= s && j < t) dmv[(size_t)j * Np] = dm;
-    };
-    int i0 = 0;
-    for (; i0 + 8 <= N; i0 += 8) {
+    double p = guard(de[0].x - l), q = guard(de[nseg * TW_SEG - 1].x - l);
+    for (int c = 0; c < nseg; c++) {
+      const int u0 = c * TW_SEG, v0 = (nseg - 1 - c) * TW_SEG;
+      cp[(size_t)c * Np] = p;
+      cm[(size_t)(nseg - 1 - c) * Np] = q;
+      if (c == nseg - 1) break;
+      double e = de[u0].y;
 #pragma unroll
-      for (int u = 0; u < 8; u++) row(i0 + u);
+      for (int u = 0; u < TW_SEG; u++) {
+        const tb_pair a = de[u0 + u + 1], z = de[v0 + TW_SEG - 2 - u];
+        p = guard(fma(-e, e * tw_rcp(p), a.x - l));
+        e = a.y;
+        q = guard(fma(-z.y, z.y * tw_rcp(q), z.x - l));
+      }
     }
-    for (; i0 < N; i0++) row(i0);
   }
-
-#define TD_ARRIVED8(f) \
-  asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]));
-  // twist index: gamma_i = dp[i] + dm[i] - (d_i - l), the row with the smallest |gamma| (rows descending, the
-  // first of equal ones wins).  Rows outside the block hold whatever the scratch memory held: not looked at.
+  // the two pivots of the rows of a segment
+  auto segment_p = [&](int c, double p, double* f) {
+    double e = de[c * TW_SEG].y;
+#pragma unroll
+    for (int u = 0; u < TW_SEG; u++) {
+      f[u] = p;
+      if (u + 1 < TW_SEG) {
+        const tb_pair a = de[c * TW_SEG + u + 1];
+        p = guard(fma(-e, e * tw_rcp(p), a.x - l));
+        e = a.y;
+      }
+    }
+  };
+  auto segment_m = [&](int c, double q, double* h) {
+#pragma unroll
+    for (int u = TW_SEG - 1; u >= 0; u--) {
+      h[u] = q;
+      if (u > 0) {
+        const tb_pair z = de[c * TW_SEG + u - 1];
+        q = guard(fma(-z.y, z.y * tw_rcp(q), z.x - l));
+      }
+    }
+  };
+  // twist index: the row with the smallest |gamma| (the last of equal ones wins)
   double gbest = DBL_MAX;
   int r = t - 1;
   {
-    double f[8], h[8], fn[8], hn[8];
+    double p = cp[0], q = cm[0];
+    for (int c = 0; c < nseg; c++) {
+      const int cn = min(c + 1, nseg - 1);
+      const double pn = cp[(size_t)cn * Np], qn = cm[(size_t)cn * Np];
+      double f[TW_SEG], h[TW_SEG];
+      segment_p(c, p, f);
+      segment_m(c, q, h);
 #pragma unroll
-    for (int u = 0; u < 8; u++) {
-      const size_t row = (size_t)max(N - 1 - u, 0) * Np;
-      f[u] = dp[row];
-      h[u] = dmv[row];
-    }
-    for (int hi = N - 1; hi >= 0; hi -= 8) {
-#pragma unroll
-      for (int u = 0; u < 8; u++) {
-        const size_t row = (size_t)max(hi - 8 - u, 0) * Np;
-        fn[u] = dp[row];
-        hn[u] = dmv[row];
-      }
-      TD_ARRIVED8(f)
-      TD_ARRIVED8(h)
-#pragma unroll
-      for (int u = 0; u < 8; u++) {
-        const int i = hi - u;
-        const double g = fabs(f[u] + h[u] - (ds[max(i, 0)] - l));
-        const bool take = i >= s && i < t && (g < gbest || !(gbest == gbest));
+      for (int u = 0; u < TW_SEG; u++) {
+        const int i = c * TW_SEG + u;
+        const double g = fabs(f[u] + h[u] - (de[i].x - l));
+        const bool take = i >= s && i < t && g <= gbest;
         gbest = take ? g : gbest;
         r = take ? i : r;
       }
-#pragma unroll
-      for (int u = 0; u < 8; u++) { f[u] = fn[u]; h[u] = hn[u]; }
+      p = pn;
+      q = qn;
     }
   }
-
-  // the vector: z_r = 1; upwards from r with the multipliers e_i / dp[i] of L (rows descending), downwards with
-  // the multipliers e_{i-1} / dm[i] of U (rows ascending); zero outside the block
+  // the vector: upwards from r over the segments from the last to the first, downwards from the first to the last
   double zu = 1.0, zd = 1.0, nrm = 1.0;
   {
-    double f[8], h[8], fn[8], hn[8];
+    double p = cp[(size_t)(nseg - 1) * Np], q = cm[0];
+    for (int c = 0; c < nseg; c++) {
+      const int cu = nseg - 1 - c, cn = min(c + 1, nseg - 1);
+      const double pn = cp[(size_t)(nseg - 1 - cn) * Np], qn = cm[(size_t)cn * Np];
+      double f[TW_SEG], h[TW_SEG];
+      segment_p(cu, p, f);
+      segment_m(c, q, h);
 #pragma unroll
-    for (int u = 0; u < 8; u++) {
-      f[u] = dp[(size_t)max(N - 1 - u, 0) * Np];
-      h[u] = dmv[(size_t)min(u, N - 1) * Np];
-    }
-    for (int c0 = 0; c0 < N; c0 += 8) {
-#pragma unroll
-      for (int u = 0; u < 8; u++) {
-        fn[u] = dp[(size_t)max(N - 1 - c0 - 8 - u, 0) * Np];
-        hn[u] = dmv[(size_t)min(c0 + 8 + u, N - 1) * Np];
-      }
-      TD_ARRIVED8(f)
-      TD_ARRIVED8(h)
-#pragma unroll
-      for (int u = 0; u < 8; u++) {
-        const int c = c0 + u;
-        const bool in = c < N;
-        const int iu = max(N - 1 - c, 0), id = min(c, N - 1);
-        {  // rows iu <= r
-          const double q = es[iu] / f[u];
-          const bool act = in && iu >= s && iu < r;
-          const double zn = -q * zu;
+      for (int u = 0; u < TW_SEG; u++) {
+        {  // rows up to r
+          const int i = cu * TW_SEG + TW_SEG - 1 - u;
+          const double zn = -(de[i].y * tw_rcp(f[TW_SEG - 1 - u])) * zu;
+          const bool act = i >= s && i < r;
           zu = act ? zn : zu;
           nrm += act ? zn * zn : 0.0;
-          if (in && iu <= r) w[(size_t)iu * Np] = iu < s ? 0.f : (iu == r ? 1.f : (float)zu);
+          if (i <= r) w[(size_t)i * Np] = i < s ? 0.f : (i == r ? 1.f : (float)zu);
         }
-        {  // rows id > r
-          const double q = es[max(id - 1, 0)] / h[u];
-          const bool act = in && id > r && id < t;
-          const double zn = -q * zd;
+        {  // rows behind r
+          const int i = c * TW_SEG + u;
+          const double zn = -(de[i - 1].y * tw_rcp(h[u])) * zd;
+          const bool act = i > r && i < t;
           zd = act ? zn : zd;
           nrm += act ? zn * zn : 0.0;
-          if (in && id > r) w[(size_t)id * Np] = id >= t ? 0.f : (float)zd;
+          if (i > r && i < N) w[(size_t)i * Np] = i >= t ? 0.f : (float)zd;
         }
       }
-#pragma unroll
-      for (int u = 0; u < 8; u++) { f[u] = fn[u]; h[u] = hn[u]; }
+      p = pn;
+      q = qn;
     }
   }
-#undef TD_ARRIVED8
   const bool fin = nrm == nrm && nrm < DBL_MAX && nrm < 1e60;  // float storage of z holds |z| < 3e38 relative to z_r = 1
   rn[(size_t)b * Np + k] = fin ? 1.0 / sqrt(nrm) : 0.0;
   if (!fin) atomicOr(&bad[b], 1);
 }
 
 // ---- close eigenvalues inside one block -----------------------------------------------------------------
-// One workgroup per image walks over the slots of every block in ascending order of eigenvalue.  A slot
-// whose eigenvalue lies within 1e-10 ||T|| of its predecessor's joins the predecessor's cluster and its
-// vector is orthogonalised (modified Gram-Schmidt, float64 accumulation) against the cluster's earlier
-// vectors.  If nothing independent is left of it (the two vectors were the same to 1e-3) the pair cannot
-// be separated this way: bad[b] gets bit 2 and the caller's info turns negative.
-__global__ __launch_bounds__(256) void td_cluster_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
-                                                         const double* __restrict__ tnorm, float* __restrict__ W,
-                                                         double* __restrict__ rn, int32_t* __restrict__ bad, int N,
-                                                         int Np) {
-  __shared__ double red[4];
-  __shared__ int any;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// The vectors of one block are computed independently of each other.  Two neighbours closer than 1e-10 ||T|| are compared:
+// if they are not orthogonal to 1e-6 (T is not graded there, or the eigenvalues agree to 1e-10 of their size), the later one
+// is marked to be orthogonalised.  Eigenvalues that count as zero (below the resolution of the reduction) get weight 0 in
+// Eq. 3-6: their vectors are left as they are, however many of them there are (the null space of a rank-deficient
+// matrix).  One workgroup per 64 slots; mark [B][Np] is written for every slot, any [B] collects.
+__device__ inline double td_zero_floor(double tn) { return tn > 0.0 ? 8.0 * TD_EPS * tn : DBL_MAX; }  // (every eigenvalue of an all-zero matrix is zero)
+
+__global__ __launch_bounds__(256) void td_pairs_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
+                                                       const double* __restrict__ tnorm, const float* __restrict__ W,
+                                                       const double* __restrict__ rn, int32_t* __restrict__ mark,
+                                                       int32_t* __restrict__ any, int N, int Np) {
+  __shared__ double part[4][64];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k = blockIdx.x * 64 + lane;
   const double* lb = lam + (size_t)b * Np;
   const int2* bb = blk + (size_t)b * Np;
-  double* rb = rn + (size_t)b * Np;
-  float* Wb = W + (size_t)b * Np * Np;
-  const double ctol = 1e-10 * tnorm[b];
-  // vectors of eigenvalues that count as zero (below the resolution of the reduction) get weight 0 in Eq. 3-6: they
-  // are left as they are, however many of them there are (the null space of a rank-deficient matrix)
-  const double floor0 = tnorm[b] > 0.0 ? 8.0 * TD_EPS * tnorm[b] : DBL_MAX;
-  // quick exit: no close pair anywhere (the usual case)
-  if (tid == 0) any = 0;
-  __syncthreads();
-  int mine = 0;
-  for (int k = 1 + tid; k < N; k += 256) mine |= (bb[k].x == bb[k - 1].x && lb[k] - lb[k - 1] <= ctol && lb[k] > floor0) ? 1 : 0;
-  if (mine) any = 1;  // every writer stores the same value
-  __syncthreads();
-  if (!any) return;
-  auto block_sum = [&](double x) {
-    x = wave_sum(x);
-    __syncthreads();
-    if (lane == 0) red[wave] = x;
-    __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
-  };
-  int first = 0;  // first slot of the current cluster
-  for (int k = 1; k < N; k++) {
-    const bool close = bb[k].x == bb[k - 1].x && lb[k] - lb[k - 1] <= ctol && lb[k] > floor0;  // uniform over the workgroup
-    if (!close) { first = k; continue; }
+  const double tn = tnorm[b];
+  const bool close = k > 0 && k < N && bb[k].x == bb[k - 1].x && lb[k] - lb[k - 1] <= 1e-10 * tn && lb[k] > td_zero_floor(tn);
+  if (!__any(close)) {  // the same in all four wavefronts
+    if (wave == 0 && k < N) mark[(size_t)b * Np + k] = 0;
+    return;
+  }
+  const float* Wb = W + (size_t)b * Np * Np;
+  double dot = 0.0;
+  if (close) {
     const int s = bb[k].x, t = bb[k].y;
-    for (int j = first; j < k; j++) {
-      double dot = 0.0;
-      for (int i = s + tid; i < t; i += 256) dot += (double)Wb[(size_t)i * Np + j] * (double)Wb[(size_t)i * Np + k];
-      dot = block_sum(dot) * rb[j] * rb[j];  // column j has norm 1 / rb[j]
-      for (int i = s + tid; i < t; i += 256)
-        Wb[(size_t)i * Np + k] = (float)((double)Wb[(size_t)i * Np + k] - dot * (double)Wb[(size_t)i * Np + j]);
-      __syncthreads();
-    }
-    double n2 = 0.0;
-    for (int i = s + tid; i < t; i += 256) { const double v = Wb[(size_t)i * Np + k]; n2 += v * v; }
-    n2 = block_sum(n2);
-    const double before = rb[k] > 0.0 ? 1.0 / (rb[k] * rb[k]) : 0.0;
-    __syncthreads();
-    if (tid == 0) {
-      if (!(n2 > 1e-6 * before)) atomicOr(&bad[b], 2);
-      rb[k] = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
-    }
-    __syncthreads();
+    for (int i = s + wave; i < t; i += 4) dot += (double)Wb[(size_t)i * Np + k] * (double)Wb[(size_t)i * Np + k - 1];
+  }
+  part[wave][lane] = dot;
+  __syncthreads();
+  if (wave == 0 && k < N) {
+    dot = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+    const bool m = close && !(fabs(dot) * rn[(size_t)b * Np + k] * rn[(size_t)b * Np + k - 1] <= 1e-6);
+    mark[(size_t)b * Np + k] = m;
+    if (m) atomicOr(&any[b], 1);
   }
 }
 
-// ---- weights of Eq. 3-6 -----------------------------------------------------------------------------------
+// ---- marked vectors, weights of Eq. 3-6 ---------------------------------------------------------------------
+// Marked slots first: a run of them and the slot before it are a cluster, every vector of which is orthogonalised (modified
+// Gram-Schmidt, float64 accumulation) against the earlier ones.  If nothing independent is left of it (two vectors were the
+// same to 1e-3) the pair cannot be separated this way: bad[b] gets bit 2 and the caller's info turns negative.
 // sigma_k = sqrt(max(lambda_k, 0)); wgt[k] = sigma_k * rn[k] (0 for terms dropped by sv_rtol): the factor that
 // turns the unnormalised vector of slot k into its term of C.  Also the optional outputs of tc_ipgs_score that
 // do not need the vectors: sigma sorted in descending order, and info.
-__global__ __launch_bounds__(256) void td_weights_kernel(const double* __restrict__ lam, const double* __restrict__ rn,
-                                                         const double* __restrict__ tnorm,
-                                                         const int32_t* __restrict__ bad, float sv_rtol,
+__global__ __launch_bounds__(256) void td_weights_kernel(const double* __restrict__ lam, double* __restrict__ rn,
+                                                         const double* __restrict__ tnorm, const int2* __restrict__ blk,
+                                                         const int32_t* __restrict__ mark, const int32_t* __restrict__ any,
+                                                         float* __restrict__ W, int32_t* __restrict__ bad, float sv_rtol,
                                                          double* __restrict__ sig, double* __restrict__ wgt,
                                                          float* __restrict__ sigma_out, int32_t* __restrict__ info_out,
                                                          int N, int Np) {
@@ -480,9 +534,45 @@ __global__ __launch_bounds__(256) void td_weights_kernel(const double* __restric
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* lb = lam + (size_t)b * Np;
   double* sb = sig + (size_t)b * Np;
+  if (wgt && any[b]) {  // uniform
+    const int32_t* mb = mark + (size_t)b * Np;
+    const int2* bb = blk + (size_t)b * Np;
+    double* rb = rn + (size_t)b * Np;
+    float* Wb = W + (size_t)b * Np * Np;
+    auto block_sum = [&](double x) {
+      x = wave_sum(x);
+      __syncthreads();
+      if (lane == 0) wmax[wave] = x;
+      __syncthreads();
+      return (wmax[0] + wmax[1]) + (wmax[2] + wmax[3]);
+    };
+    int first = 0;  // first slot of the current cluster
+    for (int k = 1; k < N; k++) {
+      if (!mb[k]) { first = k; continue; }
+      const int s = bb[k].x, t = bb[k].y;
+      for (int j = first; j < k; j++) {
+        double dot = 0.0;
+        for (int i = s + tid; i < t; i += 256) dot += (double)Wb[(size_t)i * Np + j] * (double)Wb[(size_t)i * Np + k];
+        dot = block_sum(dot) * rb[j] * rb[j];  // column j has norm 1 / rb[j]
+        for (int i = s + tid; i < t; i += 256)
+          Wb[(size_t)i * Np + k] = (float)((double)Wb[(size_t)i * Np + k] - dot * (double)Wb[(size_t)i * Np + j]);
+        __syncthreads();
+      }
+      double n2 = 0.0;
+      for (int i = s + tid; i < t; i += 256) { const double v = Wb[(size_t)i * Np + k]; n2 += v * v; }
+      n2 = block_sum(n2);
+      const double before = rb[k] > 0.0 ? 1.0 / (rb[k] * rb[k]) : 0.0;
+      __syncthreads();
+      if (tid == 0) {
+        if (!(n2 > 1e-6 * before)) atomicOr(&bad[b], 2);
+        rb[k] = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+      }
+      __syncthreads();
+    }
+  }
   // Eigenvalues come out of the reduction and the bisection with an absolute error of a few eps ||T||: what lies
   // below that is zero (an all-zero matrix, the null space of a rank-deficient one).
-  const double floor0 = tnorm[b] > 0.0 ? 8.0 * TD_EPS * tnorm[b] : DBL_MAX;  // (every eigenvalue of an all-zero matrix is zero)
+  const double floor0 = td_zero_floor(tnorm[b]);
   double mx = 0.0;
   int nanflag = 0;
   for (int i = tid; i < Np; i += 256) {
@@ -538,192 +628,168 @@ __global__ __launch_bounds__(256) void td_weights_kernel(const double* __restric
 typedef __attribute__((ext_vector_type(4))) float f4;
 constexpr int BT_K = 16;  // reflectors per block
 
-// T of every block of 16 reflectors: one workgroup per (block, image).  The block goes through LDS once
-// (16-byte accesses); thread (a, c) then forms v_a^T v_c from there.
-__global__ __launch_bounds__(256) void td_tfactor_kernel(const float* __restrict__ Vc, const float* __restrict__ tauv,
+// T of every block of 16 reflectors, one workgroup per (block, image).  S = V^T V on the matrix cores: a lane's element
+// V[4 s + lane / 16][lane % 16] is operand A and operand B of step s alike, the wavefronts take the steps in turn and
+// their parts are added in a fixed order.  Then lane a forms row a of T in registers.  Also clears the rows of the block
+// behind the last token (up to a multiple of 16), which the back-transformation reads.
+__global__ __launch_bounds__(256) void td_tfactor_kernel(float* __restrict__ Vc, const float* __restrict__ tauv,
                                                          float* __restrict__ Tf, int N, int Np, int npanel) {
-  constexpr int VP = BT_K + 1;
-  extern __shared__ __attribute__((aligned(16))) float tf_smem[];  // [N - j0][VP]
-  __shared__ float S[BT_K][BT_K];   // S[a][c] = v_a^T v_c, a < c
-  __shared__ float T[BT_K][BT_K];
+  __shared__ float part[4][BT_K][BT_K];
+  __shared__ float S[BT_K][BT_K];
   const int p = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, q4 = lane >> 4;
   const int j0 = BT_K * p, rows = N - j0;
-  const f4* src = reinterpret_cast<const f4*>(Vc + (size_t)b * Np * Np + (size_t)p * Np * BT_K + (size_t)j0 * BT_K);
-  for (int e = tid; e < rows * 4; e += 256) {
-    const int i = e >> 2, m = 4 * (e & 3);
-    const f4 v = src[e];
-    float* d = &tf_smem[i * VP + m];
+  float* Vb = Vc + (size_t)b * Np * Np + (size_t)p * Np * BT_K + (size_t)j0 * BT_K;
+  f4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int r = 4 * wave + q4; r - q4 < rows; r += 16) {
+    const float v = r < rows ? Vb[(size_t)r * BT_K + l15] : 0.f;
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v, v, acc, 0, 0, 0);
+  }
 #pragma unroll
-    for (int u = 0; u < 4; u++) d[u] = j0 + m + u <= N - 2 ? v[u] : 0.f;  // reflectors past N-2 do not exist: their slots were never written
+  for (int j = 0; j < 4; j++) part[wave][4 * q4 + j][l15] = acc[j];
+  {  // rows N .. round_up(N, 16) - 1
+    const int r = rows + (tid >> 4);
+    if (r < round_up(N, 16) - j0) Vb[(size_t)r * BT_K + l15] = 0.f;
   }
   __syncthreads();
   {
-    const int a = tid / BT_K, c = tid % BT_K;
-    float dot = 0.f;
-    if (a < c)  // v_c is zero up to row j0 + c
-      for (int i = c + 1; i < rows; i++) dot += tf_smem[i * VP + a] * tf_smem[i * VP + c];
-    S[a][c] = dot;
-    T[a][c] = 0.f;
+    const int x = tid / BT_K, c = tid % BT_K;
+    S[x][c] = (part[0][x][c] + part[1][x][c]) + (part[2][x][c] + part[3][x][c]);
   }
   __syncthreads();
-  if (wave == 0) {  // column by column; lane a owns row a
+  if (tid < BT_K) {
+    float t[BT_K];
+    float* out = Tf + ((size_t)b * npanel + p) * (BT_K * BT_K) + tid * BT_K;
+#pragma unroll
     for (int c = 0; c < BT_K; c++) {
       const float tau = j0 + c <= N - 2 ? tauv[(size_t)b * Np + j0 + c] : 0.f;
-      float acc = 0.f;
-      if (lane < c)
-        for (int r = lane; r < c; r++) acc += T[lane][r] * S[r][c];
-      if (lane < c) T[lane][c] = -tau * acc;
-      if (lane == c) T[c][c] = tau;
-      // (a wavefront runs in lockstep and the LDS serves its accesses in order: column c is complete before c + 1 reads it)
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-      __builtin_amdgcn_wave_barrier();
+      float sum = 0.f;
+#pragma unroll
+      for (int r = 0; r < c; r++) sum += t[r] * S[r][c];  // (t[r] is zero for r < this row)
+      t[c] = tid < c ? -tau * sum : (tid == c ? tau : 0.f);
+      out[c] = t[c];
     }
   }
-  __syncthreads();
-  Tf[((size_t)b * npanel + p) * (BT_K * BT_K) + tid] = T[tid / BT_K][tid % BT_K];
 }
 
-// A strip of 16 CT eigenvectors (columns k0 .. k0 + 16 CT - 1 of W) lives in the accumulator registers of the four
-// wavefronts of a workgroup for the whole kernel: wavefront w owns the row tiles rt = 4 t + w (16 rows each),
-// as CT 16x16 column tiles; element j of a lane is (row 4 (lane / 16) + j, column lane % 16) of its tile.
-// Per block of reflectors, last block first:
+// A strip of 16 eigenvectors (columns k0 .. k0 + 15 of W) lives in the accumulator registers of NW wavefronts for the
+// whole kernel: wavefront w of the strip owns the row tiles rt = NW t + w (16 rows each), t < TPW; element j of a lane is
+// (row 4 (lane / 16) + j, column lane % 16) of its tile.  Per block of reflectors, last block first:
 //   Z  = V^T U     contraction over rows; the B operand of matrix-core step j is accumulator element j itself
 //                  (rows j, 4 + j, 8 + j, 12 + j of the tile), the A operand the matching rows of V;
-//                  the four wavefronts' parts are added in a fixed order through LDS
-//   Z2 = T Z       one 16x16x16 product per column tile, same trick on the accumulator of Z
+//                  with NW > 1 the wavefronts' parts are added in a fixed order through LDS
+//   Z2 = T Z       one 16x16x16 product, same trick on the accumulator of Z
 //   U -= V Z2      likewise on the accumulator of Z2.
-// V of the block goes through LDS, transposed to [row][reflector].  Only row tiles that the block reaches
-// (rows > j0) take part.  At the end the strip's share of Eq. 3-6, Cpart[strip][x] = sum_k |U[x][k]| wgt[k],
-// is reduced across the 16 lanes of a row and written; U itself is not.  CT is chosen by the launcher so that
-// the workgroups fill the chip in whole rounds and the accumulators fit the register file.
-template <int TPW, int CT>
-__global__ __launch_bounds__(256) void td_backtransform_kernel(const float* __restrict__ W, const float* __restrict__ Vc,
-                                                               const float* __restrict__ Tf,
-                                                               const double* __restrict__ wgt,
-                                                               double* __restrict__ Cpart, int N, int Np, int nstrip,
-                                                               int npanel) {
-  constexpr int VP = BT_K + 1;       // LDS pitch of a row of V
-  constexpr int ROWS = 64 * TPW;     // rows covered by the workgroup (>= Np)
-  extern __shared__ __attribute__((aligned(16))) float bt_smem[];
-  float* vt = bt_smem;                         // [ROWS][VP]
-  constexpr int SW = 16 * CT;                  // width of the strip
-  float* zbuf = vt + ROWS * VP;                // [4][16][SW] the wavefronts' parts of Z
-  float* tl = zbuf + 4 * BT_K * SW;            // [16][16]
-  const int b = blockIdx.y, strip = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l15 = lane & 15, q4 = lane >> 4;
-  const int k0 = strip * SW;
+// A wavefront reads the rows of V that it owns straight from the L2, BT_AHEAD tiles ahead of the matrix cores (no other
+// wavefront of the workgroup uses them in the same strip; staging them in LDS for four strips together cost two barriers
+// and a transposing copy per block and kept one wavefront per SIMD: 0.52 ms for 64 images of 576 tokens against the 0.16 ms
+// that the matrix cores need).  The tiles are walked from the last one up and the walk ends at the block's own rows, so
+// that it is straight code whose loads in flight the compiler can count.
+// At the end the strip's share of Eq. 3-6, Cpart[strip][x] = sum_k |U[x][k]| wgt[k],
+// is reduced across the 16 lanes of a row and written; U itself is not.
+constexpr int BT_AHEAD = 6;
+// f(n - 1), f(n - 2), ... f(0) with the index as a constant, until one of them returns false.
+template <int n, typename F>
+__device__ __forceinline__ void walk_down(F f) {
+  [&]<int... i>(std::integer_sequence<int, i...>) { (void)(f(std::integral_constant<int, n - 1 - i>{}) && ...); }(std::make_integer_sequence<int, n>{});
+}
+template <int TPW, int NW, int SPW>  // SPW strips per workgroup
+__global__ __launch_bounds__(64 * NW * SPW) __attribute__((amdgpu_waves_per_eu(2))) void td_backtransform_kernel(const float* __restrict__ W, const float* __restrict__ Vc,
+                                                                         const float* __restrict__ Tf,
+                                                                         const double* __restrict__ wgt,
+                                                                         double* __restrict__ Cpart, int B, int N, int Np, int nstrip,
+                                                                         int npanel) {
+  __shared__ __attribute__((aligned(16))) float zbuf[NW > 1 ? 2 : 1][SPW][NW > 1 ? NW : 1][NW > 1 ? 256 : 4];
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, q4 = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), w = wv % NW, sl = wv / NW;
+  int b, group;
+  if (!group_on_xcd(blockIdx.x, (nstrip + SPW - 1) / SPW, B, &b, &group)) return;  // an image's strips share its reflectors: one XCD
+  const int strip = min(group * SPW + sl, nstrip - 1);  // a strip too many repeats the last one (its wavefronts must meet the barriers)
+  const int k0 = strip * 16, ntile = (N + 15) >> 4;
   const float* Wb = W + (size_t)b * Np * Np;
   const float* Vb = Vc + (size_t)b * Np * Np;
-  f4 acc[TPW][CT];
+  const int tl = (ntile - 1 - w) / NW;  // this wavefront's last tile (ntile > w, or it has none)
+  const bool any = ntile > w;
+  f4 acc[TPW];
 #pragma unroll
   for (int t = 0; t < TPW; t++)
 #pragma unroll
-    for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const int row = 16 * (4 * t + wave) + 4 * q4 + j, col = k0 + 16 * ct + l15;
-        acc[t][ct][j] = (row < N && col < N) ? Wb[(size_t)row * Np + col] : 0.f;
-      }
-  // The block's reflectors [row][16] are a straight copy, 16 bytes per access; the copy of the next block is
-  // in flight (in registers) while the matrix cores work on this one.
-  constexpr int PER = ROWS * 4 / 256;  // 16-byte pieces per thread when the block covers every row
-  f4 piece[PER];
-  float t_next;
-  auto fetch = [&](int p) {
-    const f4* src = reinterpret_cast<const f4*>(Vb + (size_t)p * Np * BT_K);
-#pragma unroll
-    for (int u = 0; u < PER; u++) {
-      const int e = tid + 256 * u, i = e >> 2;      // row i, quarter e & 3
-      piece[u] = (i >= BT_K * p && i < N) ? src[e] : f4{0.f, 0.f, 0.f, 0.f};
-    }
-    t_next = Tf[((size_t)b * npanel + p) * (BT_K * BT_K) + tid];
-  };
-  fetch(npanel - 1);
-  for (int p = npanel - 1; p >= 0; p--) {
-    const int j0 = BT_K * p;
-    __syncthreads();  // the previous block no longer reads vt, tl, zbuf
-#pragma unroll
-    for (int u = 0; u < PER; u++) {
-      const int e = tid + 256 * u, i = e >> 2, m = 4 * (e & 3);
-      if (i >= j0) {
-        const bool last = j0 + m + 3 > N - 2;  // reflectors past N-2 do not exist: their slots were never written
-        float* d = &vt[i * VP + m];
-        d[0] = (!last || j0 + m <= N - 2) ? piece[u][0] : 0.f;
-        d[1] = (!last || j0 + m + 1 <= N - 2) ? piece[u][1] : 0.f;
-        d[2] = (!last || j0 + m + 2 <= N - 2) ? piece[u][2] : 0.f;
-        d[3] = (!last || j0 + m + 3 <= N - 2) ? piece[u][3] : 0.f;
-      }
-    }
-    tl[tid] = t_next;
-    if (p > 0) fetch(p - 1);
-    __syncthreads();
-    f4 z[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++) z[ct] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < TPW; t++) {
-      const int rt = 4 * t + wave;
-      if (rt >= p) {  // uniform: rows 16 rt .. 16 rt + 15 reach beyond j0 = 16 p
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-          const float a = vt[(16 * rt + 4 * q4 + j) * VP + l15];
-#pragma unroll
-          for (int ct = 0; ct < CT; ct++) z[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, acc[t][ct][j], z[ct], 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-      for (int j = 0; j < 4; j++) zbuf[(wave * BT_K + 4 * q4 + j) * SW + 16 * ct + l15] = z[ct][j];
-    __syncthreads();
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++)
-#pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const int o = (4 * q4 + j) * SW + 16 * ct + l15;
-        z[ct][j] = (zbuf[o] + zbuf[BT_K * SW + o]) + (zbuf[2 * BT_K * SW + o] + zbuf[3 * BT_K * SW + o]);
-      }
-    f4 z2[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++) z2[ct] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
     for (int j = 0; j < 4; j++) {
-      const float a = tl[l15 * BT_K + 4 * q4 + j];
-#pragma unroll
-      for (int ct = 0; ct < CT; ct++) z2[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, z[ct][j], z2[ct], 0, 0, 0);
+      const int row = 16 * (NW * t + w) + 4 * q4 + j, col = k0 + l15;
+      acc[t][j] = (row < N && col < N) ? Wb[(size_t)row * Np + col] : 0.f;
     }
+  for (int p = npanel - 1; p >= 0; p--) {
+    const float* Vp = Vb + (size_t)p * Np * BT_K;
+    const int tf = p > w ? (p - w + NW - 1) / NW : 0;  // first tile that reaches the block's rows
+    const f4 tt = *reinterpret_cast<const f4*>(Tf + ((size_t)b * npanel + p) * (BT_K * BT_K) + l15 * BT_K + 4 * q4);
+    constexpr int TS = 16 * NW * BT_K;                              // from one of the wavefront's tiles to the next
+    const float* Vt = Vp + 16 * w * BT_K;                           // its tile 0 (uniform)
+    const int oz = 4 * q4 * BT_K + l15;                             // rows 4 q4 + j, reflector l15
+    const int ou = l15 * BT_K + 4 * q4;                             // row l15, reflectors 4 q4 + j
+    auto load_z = [&](int t) {
+      const float* s = Vt + t * TS;
+      return f4{s[oz], s[oz + BT_K], s[oz + 2 * BT_K], s[oz + 3 * BT_K]};
+    };
+    auto load_u = [&](int t) { return *reinterpret_cast<const f4*>(Vt + t * TS + ou); };
+    f4 ring[BT_AHEAD];
+    f4 z = {0.f, 0.f, 0.f, 0.f}, za = z;
+    if (any && tl >= tf) {
+      // static walk over t = TPW-1 .. 0; tiles past tl are skipped, the walk ends below tf
 #pragma unroll
-    for (int t = 0; t < TPW; t++) {
-      const int rt = 4 * t + wave;
-      if (rt >= p) {
+      for (int u = 0; u < BT_AHEAD; u++) ring[(TPW - 1 - u + 16 * BT_AHEAD) % BT_AHEAD] = load_z(min(max(TPW - 1 - u, tf), tl));
+      walk_down<TPW>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        if (t < tf) return false;
+        const f4 v = ring[t % BT_AHEAD];
+        ring[t % BT_AHEAD] = load_z(min(max(t - BT_AHEAD, tf), tl));
+        if (t <= tl) {
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
-          const float a = -vt[(16 * rt + l15) * VP + 4 * q4 + j];
-#pragma unroll
-          for (int ct = 0; ct < CT; ct++) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, z2[ct][j], acc[t][ct], 0, 0, 0);
+          for (int j = 0; j < 4; j++) {
+            if (t & 1) za = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j], acc[t][j], za, 0, 0, 0);
+            else z = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j], acc[t][j], z, 0, 0, 0);
+          }
         }
-      }
+        return true;
+      });
+#pragma unroll
+      for (int u = 0; u < BT_AHEAD; u++) ring[(TPW - 1 - u + 16 * BT_AHEAD) % BT_AHEAD] = load_u(min(max(TPW - 1 - u, tf), tl));
+    }
+    z += za;
+    if constexpr (NW > 1) {  // (two buffers in turn: one barrier per block)
+      f4* zb = reinterpret_cast<f4*>(&zbuf[p & 1][sl][0][0]);
+      zb[w * 64 + lane] = z;
+      __syncthreads();
+      z = zb[lane];
+#pragma unroll
+      for (int q = 1; q < NW; q++) z += zb[q * 64 + lane];
+    }
+    f4 z2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; j++) z2 = __builtin_amdgcn_mfma_f32_16x16x4f32(-tt[j], z[j], z2, 0, 0, 0);
+    if (any && tl >= tf) {
+      walk_down<TPW>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        if (t < tf) return false;
+        const f4 v = ring[t % BT_AHEAD];
+        ring[t % BT_AHEAD] = load_u(min(max(t - BT_AHEAD, tf), tl));
+        if (t <= tl) {
+#pragma unroll
+          for (int j = 0; j < 4; j++) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j], z2[j], acc[t], 0, 0, 0);
+        }
+        return true;
+      });
     }
   }
   // Eq. 3-6, this strip's share
-  double wk[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ct++) {
-    const int col = k0 + 16 * ct + l15;
-    wk[ct] = col < N ? wgt[(size_t)b * Np + col] : 0.0;
-  }
+  const int col = k0 + l15;
+  const double wk = col < N ? wgt[(size_t)b * Np + col] : 0.0;
   double* Cp = Cpart + ((size_t)b * nstrip + strip) * Np;
 #pragma unroll
   for (int t = 0; t < TPW; t++)
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-      double term = 0.0;
-#pragma unroll
-      for (int ct = 0; ct < CT; ct++) term += fabs((double)acc[t][ct][j]) * wk[ct];
-      term = row16_sum_dpp(term);
-      const int row = 16 * (4 * t + wave) + 4 * q4 + j;
+      const double term = row16_sum_dpp(fabs((double)acc[t][j]) * wk);
+      const int row = 16 * (NW * t + w) + 4 * q4 + j;
       if (l15 == 0 && row < N) Cp[row] = term;
     }
 }
@@ -739,75 +805,53 @@ __global__ __launch_bounds__(256) void td_ics_finish_kernel(const double* __rest
   if (C_out) C_out[(size_t)b * N + x] = (float)s;
 }
 
-int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, const float* tauv, const float* Vc,
-                    double* lam, int2* blk, double* tnorm, double* DP, double* DM, float* W, double* rn, int32_t* bad, const int32_t* fail,
+int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, const float* tauv, float* Vc,
+                    double* lam, int2* blk, double* tnorm, double* scratch, float* W, double* rn, int32_t* bad, int32_t* mark, const int32_t* fail,
                     double* sig, double* wgt, double* Cpart, float* Tf, float sv_rtol, bool vectors, float* C, float* C_out,
                     float* sigma_out, int32_t* info_out, hipStream_t st) {
   const int N = pl.N, Np = pl.Np, B = pl.B;
-  // (the scaled copy of T lives at the start of each image's region of DP until the factorisations overwrite it)
-  const size_t prep_stride = (size_t)Np * Np;
-  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, DP, prep_stride, tnorm, bad, fail, N, Np)));
+  // The image's part of `scratch` (Np^2 doubles) holds the scaled copy of T first, the pivots of the factorisations later.
+  const size_t stride = (size_t)Np * Np;
+  int32_t* any = mark + (size_t)B * Np;  // (one word per image behind the marks of the group's images)
+  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, scratch, stride, tnorm, blk, bad, any, fail, N, Np)));
   // lanes per eigenvalue: as many as keep the launch near one wavefront per SIMD (by the size of the whole call, so
   // that an image's result does not depend on how the call is cut into stream groups)
-  const int gs = pl.batch_call <= 16 ? 3 : pl.batch_call <= 32 ? 2 : pl.batch_call <= 128 ? 1 : 0;
-  TC_TIMED(PK_BISECT, 0, st, (td_bisect_kernel<<<dim3(((N << gs) + 255) / 256, B), 256, (size_t)5 * N * 8 + 256, st>>>(DP, prep_stride, tnorm, lam, blk, N, Np, gs)));
+  int gs = 0;
+  while (gs < 6 && ((long long)N * pl.batch_call << (gs + 1)) <= 64 * 1024) gs++;
+  TC_TIMED(PK_BISECT, 0, st, (td_bisect_kernel<<<dim3(((N << gs) + 255) / 256, B), 256, 0, st>>>(scratch, stride, tnorm, lam, blk, N, Np, gs)));
   int n2 = 1;
   while (n2 < N) n2 <<= 1;
   const size_t shm_sig = sigma_out ? (size_t)n2 * sizeof(float) : 0;
   if (!vectors) {  // eigenvalues only (the information-quantity tool)
-    TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, nullptr, tnorm, bad, 0.f, sig, nullptr, sigma_out, info_out, N, Np)));
+    TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, nullptr, tnorm, blk, nullptr, nullptr, nullptr, bad, 0.f, sig, nullptr, sigma_out, info_out, N, Np)));
     return check_launch();
   }
-  TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 64, (size_t)2 * N * 8, st>>>(dvec, evec, lam, blk, tnorm, DP, DM, W, rn, bad, N, Np)));
-  TC_TIMED(PK_TWISTED, 1, st, (td_cluster_kernel<<<B, 256, 0, st>>>(lam, blk, tnorm, W, rn, bad, N, Np)));
-  TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, rn, tnorm, bad, sv_rtol, sig, wgt, sigma_out, info_out, N, Np)));
-  const int npanel = (N + BT_K - 1) / BT_K;
   {
-    const size_t shm = (size_t)N * (BT_K + 1) * sizeof(float);
-    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_tfactor_kernel),
+    const size_t shm = (size_t)((N + TW_SEG - 1) / TW_SEG * TW_SEG + 1) * 16;
+    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_twisted_kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
       return TC_ERR_HIP;
-    TC_TIMED(PK_BACKTF, 0, st, (td_tfactor_kernel<<<dim3(npanel, B), 256, shm, st>>>(Vc, tauv, Tf, N, Np, npanel)));
+    TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 64, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, bad, N, Np)));
   }
-  // Width of the strips (16 CT eigenvectors per workgroup, one workgroup per compute unit at a time): the one
-  // with the least (rounds over the chip) x (work of a workgroup: CT column tiles plus a fixed part of about
-  // one); above 576 rows at most two column tiles fit the registers next to the row tiles.
-  int ct_best = 1;
-  {
-    long best = -1;
-    for (int ct = Np > 576 ? 2 : 4; ct >= 1; ct--) {
-      const long wgs = (long)((N + 16 * ct - 1) / (16 * ct)) * B, rounds = (wgs + 255) / 256;
-      const long cost = rounds * (ct + 1);
-      if (best < 0 || cost < best) { best = cost; ct_best = ct; }
-    }
-  }
-  const int nstrip = (N + 16 * ct_best - 1) / (16 * ct_best);
-  const dim3 gb(nstrip, B);
-#define TC_BACKTF2(TPW_, CT_)                                                                                               \
-  {                                                                                                                         \
-    const size_t shm = ((size_t)64 * TPW_ * (BT_K + 1) + 4 * BT_K * 16 * CT_ + BT_K * BT_K) * sizeof(float);                \
-    if (shm > 64 * 1024 &&                                                                                                  \
-        hipFuncSetAttribute(reinterpret_cast<const void*>(td_backtransform_kernel<TPW_, CT_>),                              \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)                            \
-      return TC_ERR_HIP;                                                                                                    \
-    TC_TIMED(PK_BACKTF, 1, st, (td_backtransform_kernel<TPW_, CT_><<<gb, 256, shm, st>>>(W, Vc, Tf, wgt, Cpart, N, Np, nstrip, npanel))); \
-  }
-#define TC_BACKTF(TPW_)                                    \
-  {                                                        \
-    if (ct_best == 4) TC_BACKTF2(TPW_, 4)                  \
-    else if (ct_best == 3) TC_BACKTF2(TPW_, 3)             \
-    else if (ct_best == 2) TC_BACKTF2(TPW_, 2)             \
-    else TC_BACKTF2(TPW_, 1)                               \
-  }
-  if (Np <= 64) TC_BACKTF(1)
-  else if (Np <= 128) TC_BACKTF(2)
-  else if (Np <= 256) TC_BACKTF(4)
-  else if (Np <= 576) TC_BACKTF(9)
-  else if (Np <= 1024) {
-    if (ct_best == 2) TC_BACKTF2(16, 2) else TC_BACKTF2(16, 1)
-  } else return TC_ERR_SHAPE;
+  TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3((N + 63) / 64, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, N, Np)));
+  TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, rn, tnorm, blk, mark, any, W, bad, sv_rtol, sig, wgt, sigma_out, info_out, N, Np)));
+  const int npanel = (N - 1 + BT_K - 1) / BT_K, nstrip = (N + 15) / 16;  // blocks of reflectors, strips of eigenvectors
+  if (npanel > 0) TC_TIMED(PK_BACKTF, 0, st, (td_tfactor_kernel<<<dim3(npanel, B), 256, 0, st>>>(Vc, tauv, Tf, N, Np, npanel)));
+#define TC_BACKTF(TPW_, NW_, SPW_)                                                                                                   \
+  TC_TIMED(PK_BACKTF, 1, st, (td_backtransform_kernel<TPW_, NW_, SPW_><<<grid_for_groups((nstrip + SPW_ - 1) / SPW_, B), 64 * NW_ * SPW_, 0, st>>>(W, Vc, Tf, wgt, Cpart, B, N, Np, nstrip, npanel)))
+  // Wavefronts per strip: as few as hold it (up to 36 row tiles in a wavefront's registers) once the strips alone fill the
+  // chip, four (by the size of the whole call: the order of a sum must not depend on stream groups) before that.
+  const bool few = (long long)nstrip * pl.batch_call <= 512;
+  if (N <= 64) TC_BACKTF(4, 1, 4);
+  else if (N <= 256 && few) TC_BACKTF(4, 4, 1);
+  else if (N <= 256) TC_BACKTF(16, 1, 4);
+  else if (N <= 576 && few) TC_BACKTF(9, 4, 1);
+  else if (N <= 576) TC_BACKTF(36, 1, 4);
+  else if (N <= 1152) TC_BACKTF(18, 4, 1);
+  else if (N <= 2304) TC_BACKTF(18, 8, 1);
+  else if (N <= 4096) TC_BACKTF(32, 8, 1);
+  else return TC_ERR_SHAPE;
 #undef TC_BACKTF
-#undef TC_BACKTF2
   TC_TIMED(PK_ICS, 0, st, (td_ics_finish_kernel<<<dim3((N + 255) / 256, B), 256, 0, st>>>(Cpart, C, C_out, N, Np, nstrip)));
   return check_launch();
 }
