@@ -8,10 +8,11 @@
 // per image is bound by what its memory path delivers: 3.5 us of steps plus up to 16 us of product per column at 576
 // tokens.  Here the trailing matrix never leaves the registers: a group of P workgroups, one per compute unit, holds
 // the lower triangle of one image in its vector registers (90 doubles per thread of 512, 368 KB per compute unit:
-// four compute units for 576 tokens, so 64 images fill the 256 of the chip), updates it in place and forms the
-// product in the same sweep.  What is left per column is latency: one exchange of the partial products between the
-// workgroups of the group (about 1.1 us inside an XCD), a handful of barriers, and the arithmetic (4 fused
-// multiply-adds per element of the triangle).
+// four compute units for 576 tokens, so 64 images fill the 256 of the chip) and updates it in place.  What is left per
+// column is latency: one exchange of the partial products between the workgroups of the group (about 1.1 us inside an
+// XCD), three barriers with their scalars, and the arithmetic (4 fused multiply-adds per element of the triangle, one
+// every 4.3 clocks of a SIMD).  The update runs while the partial products are on their way.  Measured at 576 tokens:
+// 2.3 ms for one image and for 64 (5.6 and 8.8 ms with the matrix in memory), 18 ms at 2880 tokens (470 ms).
 //
 // Frame.  The matrix is placed at the end of a frame of F x F (row f of the frame is row f + base of the matrix).
 // Wavefront w of workgroup (a, b) owns the rows f = i R + 8 a + w (i < LI) and lane l the columns k C + 64 b + l (k < LK), R = 8 PR
@@ -55,6 +56,11 @@ __device__ __forceinline__ void fmac_bcast(double& d, double row, double c) {
   asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(row), "v"(c), "n"(N));
 }
 
+template <int N>
+__device__ __forceinline__ void fmac_bcast_neg(double& d, double row, double c) {
+  asm("v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(row), "v"(c), "n"(N));
+}
+
 __device__ __forceinline__ void publish(u64* p, double v, unsigned tag) {
   __hip_atomic_store(p, ((u64)__double_as_longlong(v) & ~1ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -68,42 +74,59 @@ __device__ __forceinline__ bool tr_give_up(int spin, const int32_t* fail) {
          ((spin & 1023) == 1023 && __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
 }
 
-// Sums of n <= 16 values over the 64 lanes by recursive halving (fixed order).  On return lane L holds the total of value
-// `*which` (-1: of none): the halves and the rows of 16 lanes trade with the swap instructions, then L and L^8, L and
-// 7-L through lane permutations; the quads are added.  The same exchange for an odd count leaves the unpaired value's
-// partner empty.
+// Sums of 8 or 16 values over the 64 lanes by recursive halving (fixed order).  On return lane L holds the total of value
+// *which: the halves and the rows of 16 lanes trade with the swap instructions, then L and L^8, (16 values) L and 7-L
+// through lane permutations; what is left of a row of lanes is added.
 template <int n>
 __device__ __forceinline__ double reduce_many(double* x, int lane, int* which) {
   typedef __attribute__((ext_vector_type(2))) unsigned int u2;
-  constexpr int h1 = (n + 1) / 2, h2 = (h1 + 1) / 2, h3 = (h2 + 1) / 2, h4 = (h3 + 1) / 2;
-  static_assert(h4 == 1, "at most 16 values");
+  static_assert(n == 8 || n == 16, "");
 #pragma unroll
-  for (int u = 0; u < h1; u++) {
-    const double o = u + h1 < n ? x[u + h1] : 0.0;
-    const u2 lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x[u]), (unsigned)__double2loint(o), false, false);
-    const u2 hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x[u]), (unsigned)__double2hiint(o), false, false);
+  for (int u = 0; u < n / 2; u++) {
+    const u2 lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x[u]), (unsigned)__double2loint(x[u + n / 2]), false, false);
+    const u2 hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x[u]), (unsigned)__double2hiint(x[u + n / 2]), false, false);
     x[u] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
   }
 #pragma unroll
-  for (int u = 0; u < h2; u++) {
-    const double o = u + h2 < h1 ? x[u + h2] : 0.0;
-    const u2 lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x[u]), (unsigned)__double2loint(o), false, false);
-    const u2 hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x[u]), (unsigned)__double2hiint(o), false, false);
+  for (int u = 0; u < n / 4; u++) {
+    const u2 lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x[u]), (unsigned)__double2loint(x[u + n / 4]), false, false);
+    const u2 hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x[u]), (unsigned)__double2hiint(x[u + n / 4]), false, false);
     x[u] = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
   }
   const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0;
 #pragma unroll
-  for (int u = 0; u < h3; u++) {
-    const double o = u + h3 < h2 ? x[u + h3] : 0.0;
-    x[u] = (b3 ? o : x[u]) + dpp_f64<0x128>(b3 ? x[u] : o);  // row_ror:8, L <-> L^8
-  }
-  const double o = h4 < h3 ? x[h4] : 0.0;
-  double t = (b2 ? o : x[0]) + dpp_f64<0x141>(b2 ? x[0] : o);  // row_half_mirror, L <-> 7-L
+  for (int u = 0; u < n / 8; u++)
+    x[u] = (b3 ? x[u + n / 8] : x[u]) + dpp_f64<0x128>(b3 ? x[u] : x[u + n / 8]);  // row_ror:8, L <-> L^8
+  double t;
+  if (n == 16) t = (b2 ? x[1] : x[0]) + dpp_f64<0x141>(b2 ? x[0] : x[1]);  // row_half_mirror, L <-> 7-L
+  else t = x[0] + dpp_f64<0x141>(x[0]);
   t += dpp_f64<0xB1>(t);  // quad_perm [1,0,3,2]
   t += dpp_f64<0x4E>(t);  // quad_perm [2,3,0,1]
-  const int i3 = (b2 ? h4 : 0), i2 = i3 + (b3 ? h3 : 0), i1 = i2 + ((lane & 16) ? h2 : 0), i0 = i1 + ((lane & 32) ? h1 : 0);
-  *which = (i3 < h3 && i2 < h2 && i1 < h1 && i0 < n) ? i0 : -1;
+  *which = ((lane & 32) ? n / 2 : 0) + ((lane & 16) ? n / 4 : 0) + (b3 ? n / 8 : 0) + (n == 16 && b2 ? 1 : 0);
   return t;
+}
+
+// f(a), f(a + 1), ... f(n - 1) with the index as a constant.
+template <int a, int n, typename F>
+__device__ __forceinline__ void walk_up(F f) {
+  [&]<int... i>(std::integer_sequence<int, i...>) { (f(std::integral_constant<int, a + i>{}), ...); }(std::make_integer_sequence<int, n - a>{});
+}
+
+__device__ __forceinline__ double sum8(const double* r) {
+  return ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
+}
+
+// 1 / x and 1 / sqrt(x) to the last bit or so: hardware estimate and Newton steps (a library division is 73 cycles of
+// dependent instructions, a square root 105, and a column waits for two of them)
+__device__ __forceinline__ double fast_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ double fast_rsq(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
 }
 
 // Geometry of a frame.
@@ -121,7 +144,8 @@ struct TrShape {
   static constexpr int OWN = 64 * LK;                    // columns of a workgroup; it has 8 LI rows
   // exchange words of one image: two slots of (partials, one set per column sum and row sum; next column; totals)
   static constexpr size_t WORDS = MODE == 0 ? 0 : MODE == 1 ? (size_t)2 * 5 * F : (size_t)2 * (5 * PCC + 2) * F;
-  static constexpr size_t LDS = (size_t)(3 * F + 8 * OWN + 16 * LI + 18) * 8 + (size_t)LI * 8 * 16 * 4 + 16;
+  static constexpr size_t LDS = (size_t)(4 * (F + F / 32) + 8 * OWN + 16 * LI + 36) * 8 + (size_t)LI * 8 * 16 * 4 + 16;
+  static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
   static_assert(LI * R == F, "rows and columns must cover the same frame");
 };
 
@@ -141,7 +165,12 @@ __global__ __launch_bounds__(256) void tridiag_clear_kernel(u64* __restrict__ sy
 // Vc     [B][Np/16][Np][16] out, float: the reflectors in blocks of sixteen, Vc[j / 16][i][j % 16] = v_j[i] (zeros up to
 //                     i = j, 1 at j + 1) -- the layout stage 3 copies into LDS; reflectors j >= N-1 are not written
 // sync                exchange memory, cleared
-// Columns first .. last-1 of the matrix are reduced.
+__device__ __forceinline__ int tr_at(int f) { return f + (f >> 5); }
+
+// The index as a value that the compiler knows nothing about.
+template <bool on>
+__device__ __forceinline__ void fresh(int& x) { if (on) asm volatile("" : "+v"(x)); }
+
 template <int PC>  // 0: the single-workgroup frame
 __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void tridiag_kernel(
     double* __restrict__ G, int N, int Np, int B, int first, int last, int full, double* __restrict__ dvec,
@@ -150,17 +179,22 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   typedef TrShape<PC> S;
   constexpr int LI = S::LI, LK = S::LK, RT = S::RT, NS = S::NS, SR = S::LI / S::NS, E = S::E, MODE = S::MODE;
   constexpr int PR = S::PR, pc = S::PCC, R = S::R, C = S::C, F = S::F, P = S::P, OWN = S::OWN;
+  static_assert(SR * R % 32 == 0, "a set of rows must be whole units of the padded vectors");
   static_assert(SR <= 16 && SR * NS == LI, "the rows of a set must fit the 16 lanes of a row");
   extern __shared__ __attribute__((aligned(16))) unsigned char tr_smem[];
-  double* Va = reinterpret_cast<double*>(tr_smem);  // [F] reflector of the even columns
-  double* Vb = Va + F;                               // [F] of the odd ones
-  double* Wv = Vb + F;                               // [F] w of the column before
-  double* csb = Wv + F;                              // [8][OWN] column sums per wavefront
+  // The three vectors are read by rows (a wavefront's rows, R apart) and by columns (64 in a row): with a double skipped
+  // after every 32 both are free of bank conflicts.
+  constexpr int FX = F + F / 32;
+  double* Va = reinterpret_cast<double*>(tr_smem);  // [FX] reflector of the even columns
+  double* Vb = Va + FX;                              // [FX] of the odd ones
+  double* Wv = Vb + FX;                              // [FX] w of the column before
+  double* X = Wv + FX;                               // [FX] the column being reduced (zero up to and with its diagonal)
+  double* csb = X + FX;                              // [8][OWN] column sums per wavefront
   double* rsb = csb + 8 * OWN;                       // [LI * 8] row sums
   double* colb = rsb + 8 * LI;                       // [LI * 8] this workgroup's rows of the next column
-  double* red = colb + 8 * LI;                       // [2][8] partial sums of the block reductions
-  double* one = red + 16;                            // [2] p at the reflector's first row; head of the next column
-  float* vblk = reinterpret_cast<float*>(one + 2);   // [LI * 8][16] the last sixteen reflectors, this workgroup's rows
+  double* red = colb + 8 * LI;                       // [4][8] partial sums of the block reductions
+  double* one = red + 32;                            // [4] p at the reflector's first row, head of the next column; v and w of the column before at that row
+  float* vblk = reinterpret_cast<float*>(one + 4);   // [LI * 8][16] the last sixteen reflectors, this workgroup's rows
   int* quit = reinterpret_cast<int*>(vblk + LI * 8 * 16);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -197,147 +231,242 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         if (r >= first && c >= first) x = full ? A0[(size_t)r * Np + c] : A0[(size_t)max(r, c) * Np + min(r, c)];
         A[i][k] = x;
       }
-  for (int f = tid; f < 3 * F; f += TR_THREADS) Va[f] = 0.0;  // both reflectors and w
+  for (int e = tid; e < 4 * FX; e += TR_THREADS) Va[e] = 0.0;  // the four vectors
   for (int e = tid; e < LI * 8 * 16; e += TR_THREADS) vblk[e] = 0.f;
   if (tid == 0) *quit = 0;
 
   // this thread's elements of the vectors: frame rows F - 1 - tid - 512 u, so that the live ones stay in the low threads
-  double x[E];
-#pragma unroll
-  for (int u = 0; u < E; u++) {
-    const int f = F - 1 - tid - TR_THREADS * u;
-    x[u] = f >= js ? A0[(size_t)(f + base) * Np + first] : 0.0;
-  }
-  double part = 0.0;
-#pragma unroll
-  for (int u = 0; u < E; u++) {
-    const int f = F - 1 - tid - TR_THREADS * u;
-    if (f >= js + 2) part += x[u] * x[u];
-    if (f == js + 1) one[1] = x[u];
-    if (f == js && mem == 0) dout[first] = x[u];
-  }
-  part = wave_sum_dpp(part);
-  if (lane == 0) red[8 + w] = part;
-  __syncthreads();
-
-  bool bad = false;
-  for (int j = js; j < min(je, F - 1); j++) {
-    double* Vn = (j & 1) ? Vb : Va;        // this column's reflector
-    const double* Vo = (j & 1) ? Va : Vb;  // the one before
-    // ---- Householder reflector that maps x[j+1:] onto beta e_1 ------------------------------------------
-    double xn2 = 0.0;
-#pragma unroll
-    for (int k = 0; k < TR_WAVES; k++) xn2 += red[8 + k];
-    const double alpha = one[1];
-    double beta = alpha, tau = 0.0, scal = 0.0;
-    if (xn2 > 0.0) {
-      beta = -copysign(sqrt(alpha * alpha + xn2), alpha);
-      tau = (beta - alpha) / beta;
-      scal = 1.0 / (alpha - beta);
-    }
-    const int jr = j + base;  // column of the matrix
+  {
+    double part = 0.0;
+    __syncthreads();  // (X has been cleared)
 #pragma unroll
     for (int u = 0; u < E; u++) {
       const int f = F - 1 - tid - TR_THREADS * u;
+      if (f < js) continue;
+      const double x = A0[(size_t)(f + base) * Np + first];
+      if (f > js) X[tr_at(f)] = x;
+      if (f >= js + 2) part += x * x;
+      if (f == js + 1) one[1] = x;
+      if (f == js && mem == 0) dout[first] = x;
+    }
+    part = wave_sum_dpp(part);
+    if (lane == 0) red[8 + w] = part;
+  }
+  __syncthreads();
+
+  // place of a thread's element u in the vectors (tr_at of F - 1 - t - 512 u, as one address and a constant)
+  auto own_at = [](int t, int u) { return tr_at(F - 1 - t - TR_THREADS * (E - 1)) + (TR_THREADS + TR_THREADS / 32) * (E - 1 - u); };
+  bool bad = false;
+  for (int j = js; j < min(je, F - 1); j++) {
+    // (what hangs on the thread index is formed anew in every stage: kept across the sweeps, it would push the matrix out
+    // of the registers)
+    int tj = tid;
+    fresh<MODE != 0>(tj);
+    int lj = tj & 63;
+    double* Vn = (j & 1) ? Vb : Va;        // this column's reflector
+    const double* Vo = (j & 1) ? Va : Vb;  // the one before
+    const int jr = j + base;               // column of the matrix
+    // ---- Householder reflector that maps x[j+1:] onto beta e_1 ------------------------------------------
+    // (every workgroup and every wavefront for itself; X holds the column, the reflector is X scal with a 1 on top)
+    const double xn2 = sum8(red + 8);
+    const double alpha = one[1];
+    double beta = alpha, tau = 0.0, scal = 0.0;
+    if (xn2 > 0.0) {
+      const double n2 = fma(alpha, alpha, xn2), rb = fast_rsq(n2);
+      double nb = n2 * rb;
+      nb = fma(0.5 * rb, fma(-nb, nb, n2), nb);          // |beta| = sqrt(n2)
+      beta = -copysign(nb, alpha);
+      tau = fma(fabs(alpha), rb, 1.0);                   // (beta - alpha) / beta
+      scal = copysign(fast_rcp(fabs(alpha) + nb), alpha);  // 1 / (alpha - beta)
+    }
+#pragma unroll
+    for (int u = 0; u < E; u++) {
+      const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
       if (f >= j + 1) {
-        x[u] = f == j + 1 ? 1.0 : x[u] * scal;
-        Vn[f] = x[u];
-        if (b == 0 && (MODE == 0 || ((f >> 3) % PR) == a)) vblk[(f / R * 8 + (f & 7)) * 16 + (jr & 15)] = (float)x[u];
+        const double v = f == j + 1 ? 1.0 : X[g] * scal;
+        Vn[g] = v;
+        if (b == 0 && (MODE == 0 || ((f >> 3) % PR) == a)) vblk[(f / R * 8 + (f & 7)) * 16 + (jr & 15)] = (float)v;
       }
     }
-    if (tid == 0) {
-      Vn[j] = 0.0;
-      if (j > 0) Vn[j - 1] = 0.0;
+    if (tj == 0) {
+      Vn[tr_at(j)] = 0.0;
+      if (j > 0) Vn[tr_at(j - 1)] = 0.0;
       if (mem == 0) {
         eout[jr] = beta;
         tout[jr] = (float)tau;
       }
     }
-    __syncthreads();
 
-    // ---- A <- A - v w^T - w v^T with the column before, and p = A v ---------------------------------------
+    fresh<MODE != 0>(tj);
+    lj = tj & 63;
+    // ---- p = A v, this workgroup's part ------------------------------------------------------------------
+    // MODE 0: the update with the column before is applied in the same sweep.  Otherwise the product is formed with the
+    // matrix as it is and published, and the update follows while the other workgroups' parts are on their way
+    // (below): p and the next column then still lack it, which costs two scalar products.
     const int kmin = (j + 1) / C;
     const bool owner = MODE != 2 || (((j + 1) >> 6) % pc) == b;
     const int l0 = (j + 1) & 63;
-    double cs[LK];
+    {
+      const int fc0 = tr_at(64 * b + lj);
+      // MODE 0 goes through its 32 rows in two sweeps (fewer sums in flight), the other modes through 18 in one
+      constexpr int SW = MODE == 0 ? 2 : 1, RW = LI / SW;
+      double cs[SW > 1 ? LK : 1];
+      if (SW > 1)
 #pragma unroll
-    for (int k = 0; k < LK; k++) cs[k] = 0.0;
+        for (int k = 0; k < LK; k++) cs[SW > 1 ? k : 0] = 0.0;
+      walk_up<0, SW>([&](auto sc) {
+        constexpr int sw = decltype(sc)::value, i0 = sw * RW, i1 = i0 + RW;  // rows of the sweep
+        if (sw + 1 < SW && RT * kmin >= i1) return;                         // every row of the sweep is done with
+        constexpr int s0 = i0 / SR, s1 = (i1 - 1) / SR;                     // sets of rows it takes in
+        // column values of the first live class; the next class's are on their way while one is worked on
+        double xc = X[fc0 + kmin * (C + C / 32)], oc = 0.0, wc = 0.0;
+        if (MODE == 0) { oc = Vo[fc0 + kmin * (C + C / 32)]; wc = Wv[fc0 + kmin * (C + C / 32)]; }
+        const int fr0 = min(lj & 15, SR - 1) * R + 8 * a + w, gr0 = tr_at(fr0);
+        double vn[s1 - s0 + 1], vo[s1 - s0 + 1], wo[s1 - s0 + 1];
 #pragma unroll
-    for (int s = 0; s < NS; s++) {
-      if (s + 1 < NS && RT * kmin > s * SR + SR - 1) continue;  // every row of the set is done with
-      const int fr = (s * SR + min(lane & 15, SR - 1)) * R + 8 * a + w;
-      const double vo = Vo[fr], wo = Wv[fr], vn = Vn[fr];
-      double rs[SR];
-#pragma unroll
-      for (int q = 0; q < SR; q++) rs[q] = 0.0;
-#pragma unroll
-      for (int k = 0; k < LK; k++) {
-        if (RT * k > s * SR + SR - 1) continue;
-        if (k < kmin) continue;
-        const int fc = k * C + 64 * b + lane;
-        const double vc = Vn[fc], nv = -Vo[fc], nw = -Wv[fc];
-        asm volatile("s_nop 1");
-        auto row = [&](auto qc) {
-          constexpr int q = decltype(qc)::value;
-          const int i = s * SR + q;
-          if (i >= RT * k) {
-            fmac_bcast<q>(A[i][k], vo, nw);
-            fmac_bcast<q>(A[i][k], wo, nv);
-            if (i >= RT * (k + 1)) rs[q] = fma(A[i][k], vc, rs[q]);
-            fmac_bcast<q>(cs[k], vn, A[i][k]);
-          }
-        };
-        [&]<int... q>(std::integer_sequence<int, q...>) { (row(std::integral_constant<int, q>{}), ...); }(std::make_integer_sequence<int, SR>{});
-        if (k == kmin && owner && lane == l0) {
-#pragma unroll
-          for (int q = 0; q < SR; q++)
-            if (s * SR + q >= RT * k) colb[(s * SR + q) * 8 + w] = A[s * SR + q][k];
+        for (int s = s0; s <= s1; s++) {
+          const int fr = fr0 + s * SR * R, g = gr0 + s * (SR * R + SR * R / 32);
+          vn[s - s0] = fr == j + 1 ? 1.0 : X[g] * scal;
+          if (MODE == 0) { vo[s - s0] = Vo[g]; wo[s - s0] = Wv[g]; }
         }
-      }
-      int which;
-      const double t = reduce_many<SR>(rs, lane, &which);
-      if (which >= 0 && (lane & 3) == 0) rsb[(s * SR + which) * 8 + w] = t;
-    }
+        double vc = (owner && lj == l0) ? 1.0 : xc * scal;
+        constexpr int j0 = i0 > RT ? i0 : RT, NR = i1 - j0;  // rows with a row sum (those of the first diagonal block have none)
+        double rs[NR];
 #pragma unroll
-    for (int k = 0; k < LK; k++)
-      if (k >= kmin) csb[w * OWN + 64 * k + lane] = cs[k];
+        for (int q = 0; q < NR; q++) rs[q] = 0.0;
+        walk_up<0, LK>([&](auto kc) {
+          constexpr int k = decltype(kc)::value, r0 = RT * k > i0 ? RT * k : i0;
+          if constexpr (r0 < i1) {
+            if (k < kmin) return;
+            constexpr int fn = (k + 1 < LK ? k + 1 : k) * (C + C / 32);
+            const double xn = X[fc0 + fn], on = MODE == 0 ? Vo[fc0 + fn] : 0.0, wn = MODE == 0 ? Wv[fc0 + fn] : 0.0;
+            double c0 = SW > 1 ? cs[SW > 1 ? k : 0] : 0.0, c1 = 0.0;
+            asm volatile("s_nop 1");
+            walk_up<r0, i1>([&](auto ic) {
+              constexpr int i = decltype(ic)::value, s = i / SR - s0, q = i % SR;
+              if constexpr (MODE == 0) {
+                fmac_bcast_neg<q>(A[i][k], vo[s], wc);
+                fmac_bcast_neg<q>(A[i][k], wo[s], oc);
+              }
+              if constexpr (i >= RT * (k + 1)) rs[i - j0] = fma(A[i][k], vc, rs[i - j0]);
+              fmac_bcast<q>(i & 1 ? c1 : c0, vn[s], A[i][k]);
+            });
+            if constexpr (sw + 1 < SW) cs[SW > 1 ? k : 0] = c0 + c1;
+            else csb[w * OWN + 64 * k + lj] = c0 + c1;
+            if (k == kmin && owner && lj == l0) {
+#pragma unroll
+              for (int i = r0; i < i1; i++) colb[i * 8 + w] = A[i][k];
+            }
+            vc = xn * scal;
+            oc = on;
+            wc = wn;
+          }
+        });
+        // row sums (rows up to the end of the live diagonal block have none), the last eight alone where they are all
+        int which;
+        const int live = RT * (kmin + 1);
+        if (NR == 16 && live < i1 - 8) {
+          const double t = reduce_many<16>(rs, lj, &which);
+          if ((lj & 3) == 0) rsb[(j0 + which) * 8 + w] = t;
+        } else if (live < i1) {
+          const double t = reduce_many<8>(rs + NR - 8, lj, &which);
+          if ((lj & 7) == 0) rsb[(i1 - 8 + which) * 8 + w] = t;
+        }
+      });
+    }
     __syncthreads();
 
     // ---- p in every workgroup -------------------------------------------------------------------------------
     const unsigned tag = (((j - js) >> 1) & 1) ^ 1;
     const int slot = (j - js) & 1;
-    double p[E], col[E];
+    fresh<MODE != 0>(tj);
+    lj = tj & 63;
+    // (with more than three elements a thread, the vectors are read again where they are wanted: no registers hold them)
+    constexpr int K = E > 3 ? 1 : E;
+    double p[E], col[E], v[K], vo[K], wo[K], dot[3] = {0.0, 0.0, 0.0};  // p^T v, w_o^T v, v_o^T v
+    auto column_sum = [&](int o) {  // over the wavefronts
+      const double* c = csb + o;
+      return ((c[0] + c[OWN]) + (c[2 * OWN] + c[3 * OWN])) + ((c[4 * OWN] + c[5 * OWN]) + (c[6 * OWN] + c[7 * OWN]));
+    };
+    auto own_values = [&]() {  // this thread's elements of the vectors
+#pragma unroll
+      for (int u = 0; u < E; u++) {
+        const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
+        const int q = min(u, K - 1);
+        v[q] = vo[q] = wo[q] = 0.0;
+        if (f > j) {
+          v[q] = Vn[g];
+          if (MODE != 0) {
+            vo[q] = Vo[g];
+            wo[q] = Wv[g];
+            dot[1] = fma(wo[q], v[q], dot[1]);
+            dot[2] = fma(vo[q], v[q], dot[2]);
+          }
+        }
+      }
+      if (MODE != 0) {
+        dot[1] = wave_sum_dpp(dot[1]);
+        dot[2] = wave_sum_dpp(dot[2]);
+      }
+    };
+    auto update = [&]() {  // A <- A - v w^T - w v^T with the column before
+      fresh<true>(tj);
+      lj = tj & 63;
+      const int fc0 = tr_at(64 * b + lj);
+      const int gr0 = tr_at(min(lj & 15, SR - 1) * R + 8 * a + w);
+      double ro[NS], rw[NS];
+      double oc = Vo[fc0 + kmin * (C + C / 32)], wc = Wv[fc0 + kmin * (C + C / 32)];
+#pragma unroll
+      for (int s = 0; s < NS; s++) {
+        const int fr = gr0 + s * (SR * R + SR * R / 32);
+        ro[s] = Vo[fr];
+        rw[s] = Wv[fr];
+      }
+      walk_up<0, LK>([&](auto kc) {
+        constexpr int k = decltype(kc)::value, fn = (k + 1 < LK ? k + 1 : k) * (C + C / 32);
+        if (k < kmin) return;
+        const double on = Vo[fc0 + fn], wn = Wv[fc0 + fn];
+        asm volatile("s_nop 1");
+        walk_up<RT * k, LI>([&](auto ic) {
+          constexpr int i = decltype(ic)::value, s = i / SR, q = i % SR;
+          fmac_bcast_neg<q>(A[i][k], ro[s], wc);
+          fmac_bcast_neg<q>(A[i][k], rw[s], oc);
+        });
+        oc = on;
+        wc = wn;
+      });
+      fresh<true>(tj);
+      lj = tj & 63;
+    };
     if (MODE == 0) {
 #pragma unroll
       for (int u = 0; u < E; u++) {
-        const int f = F - 1 - tid - TR_THREADS * u;
+        const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
         p[u] = col[u] = 0.0;
         if (f > j) {
-          double s = rsb[f];
-#pragma unroll
-          for (int k = 0; k < TR_WAVES; k++) s += csb[k * OWN + f];
-          p[u] = s;
+          p[u] = column_sum(f) + ((f >> 3) >= RT * (kmin + 1) ? rsb[f] : 0.0);
           col[u] = colb[f];
         }
       }
+      own_values();
     } else if (MODE == 1) {
       u64* Y = sy + (size_t)slot * 5 * F;  // [4][F] partials, then [F] the next column
 #pragma unroll
       for (int u = 0; u < E; u++) {
-        const int f = F - 1 - tid - TR_THREADS * u;
+        const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
         if (f > j) {
           const bool mine = ((f >> 3) & 3) == a;  // a row of this workgroup
           const int o = (f >> 5) * 8 + (f & 7);
-          double s = mine ? rsb[o] : 0.0;
-#pragma unroll
-          for (int k = 0; k < TR_WAVES; k++) s += csb[k * OWN + f];
+          const double s = column_sum(f) + (mine && (o >> 3) >= RT * (kmin + 1) ? rsb[o] : 0.0);
           publish(Y + (size_t)a * F + f, s, tag);
           if (mine) publish(Y + (size_t)4 * F + f, colb[o], tag);
         }
       }
+      update();
+      own_values();
 #pragma unroll
       for (int u = 0; u < E; u++) {
-        const int f = F - 1 - tid - TR_THREADS * u;
+        const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
         p[u] = col[u] = 0.0;
         if (f > j) {
           u64 y[5];
@@ -355,38 +484,33 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
           col[u] = __longlong_as_double((long long)y[4]);
         }
       }
-    }
-    if (MODE == 2) {
+    } else {
       u64* YC = sy + (size_t)slot * (5 * pc + 2) * F;  // [PR][F] column sums by row class
       u64* YR = YC + (size_t)PR * F;                   // [PC][F] row sums by column class
       u64* YN = YR + (size_t)pc * F;                   // [F] the next column
       u64* YT = YN + F;                                // [F] totals
-      for (int o = tid; o < OWN; o += TR_THREADS) {
+      for (int o = tj; o < OWN; o += TR_THREADS) {
         const int f = (o >> 6) * C + 64 * b + (o & 63);
+        if (f > j) publish(YC + (size_t)a * F + f, column_sum(o), tag);
+      }
+      if (tj < 8 * LI) {
+        const int f = (tj >> 3) * R + 8 * a + (tj & 7);
         if (f > j) {
-          double s = 0.0;
-#pragma unroll
-          for (int k = 0; k < TR_WAVES; k++) s += csb[k * OWN + o];
-          publish(YC + (size_t)a * F + f, s, tag);
+          publish(YR + (size_t)b * F + f, (tj >> 3) >= RT * (kmin + 1) ? rsb[tj] : 0.0, tag);
+          if (owner) publish(YN + f, colb[tj], tag);
         }
       }
-      if (tid < 8 * LI) {
-        const int f = (tid >> 3) * R + 8 * a + (tid & 7);
-        if (f > j) {
-          publish(YR + (size_t)b * F + f, rsb[tid], tag);
-          if (owner) publish(YN + f, colb[tid], tag);
-        }
-      }
+      update();
       // totals of this workgroup's share of its rows: four lanes per element
       constexpr int NQ = 5 * pc, PER = (NQ + 3) / 4;
-      const int o = (tid >> 2) * pc + b;
+      const int o = (tj >> 2) * pc + b;
       const int ft = (o >> 3) * R + 8 * a + (o & 7);
       if (o < 8 * LI && ft > j) {
         u64 y[PER];
         for (int spin = 0;; spin++) {
           bool ok = true;
 #pragma unroll
-          for (int q = 0; q < PER; q++) y[q] = peek(YC + (size_t)min(4 * q + (tid & 3), NQ - 1) * F + ft);  // (YR follows YC)
+          for (int q = 0; q < PER; q++) y[q] = peek(YC + (size_t)min(4 * q + (tj & 3), NQ - 1) * F + ft);  // (YR follows YC)
 #pragma unroll
           for (int q = 0; q < PER; q++) ok &= (y[q] & 1) == tag;
           if (ok) break;
@@ -394,82 +518,99 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         }
         double s = 0.0;
 #pragma unroll
-        for (int q = 0; q < PER; q++) s += 4 * q + (tid & 3) < NQ ? __longlong_as_double((long long)y[q]) : 0.0;
+        for (int q = 0; q < PER; q++) s += 4 * q + (tj & 3) < NQ ? __longlong_as_double((long long)y[q]) : 0.0;
         s += dpp_f64<0xB1>(s);  // the quad
         s += dpp_f64<0x4E>(s);
-        if ((tid & 3) == 0) publish(YT + ft, s, tag);
+        if ((tj & 3) == 0) publish(YT + ft, s, tag);
       }
-#pragma unroll
-      for (int u = 0; u < E; u++) p[u] = col[u] = 0.0;
-      {
-        u64 yt[E], yn[E];
+      auto collect = [&](const u64* src, double* dst) {
         for (int spin = 0;; spin++) {
+          u64 y[E];
           bool ok = true;
 #pragma unroll
           for (int u = 0; u < E; u++) {
-            const int f = F - 1 - tid - TR_THREADS * u;
-            if (f > j) {
-              yt[u] = peek(YT + f);
-              yn[u] = peek(YN + f);
-            }
+            const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
+            y[u] = f > j ? peek(src + f) : tag;
           }
 #pragma unroll
           for (int u = 0; u < E; u++) {
-            const int f = F - 1 - tid - TR_THREADS * u;
-            if (f > j) ok &= (yt[u] & 1) == tag && (yn[u] & 1) == tag;
+            ok &= (y[u] & 1) == tag;
+            dst[u] = __longlong_as_double((long long)y[u]);
           }
           if (ok) break;
           if (tr_give_up(spin, fail + img)) { bad = true; break; }
         }
-#pragma unroll
-        for (int u = 0; u < E; u++) {
-          const int f = F - 1 - tid - TR_THREADS * u;
-          if (f > j) {
-            p[u] = __longlong_as_double((long long)yt[u]);
-            col[u] = __longlong_as_double((long long)yn[u]);
-          }
-        }
-      }
+      };
+      collect(YN, col);  // (published together with the partials: it has arrived by the time the totals are)
+      own_values();
+      collect(YT, p);
     }
     if (MODE != 0 && bad) *quit = 1;
 
     // ---- w = p - (tau/2) (p^T v) v with p <- tau p; the next column -------------------------------------------
-    part = 0.0;
 #pragma unroll
     for (int u = 0; u < E; u++) {
-      const int f = F - 1 - tid - TR_THREADS * u;
-      p[u] *= tau;
-      if (f > j) part += p[u] * x[u];
-      if (f == j + 1) one[0] = p[u];
-    }
-    part = wave_sum_dpp(part);
-    if (lane == 0) red[w] = part;
-    __syncthreads();
-    if (MODE != 0 && *quit) break;  // uniform
-    double pv = 0.0;
-#pragma unroll
-    for (int k = 0; k < TR_WAVES; k++) pv += red[k];
-    const double half = 0.5 * tau * pv, w1 = one[0] - half;
-    part = 0.0;
-#pragma unroll
-    for (int u = 0; u < E; u++) {
-      const int f = F - 1 - tid - TR_THREADS * u;
-      if (f > j) {
-        const double wf = p[u] - half * x[u];
-        Wv[f] = wf;
-        x[u] = col[u] - x[u] * w1 - wf;  // (the reflector's first entry is 1)
-        if (f >= j + 3) part += x[u] * x[u];
-        if (f == j + 2) one[1] = x[u];
-        if (f == j + 1 && mem == 0) dout[jr + 1] = x[u];
+      const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
+      if (K == E) dot[0] = fma(p[u], v[min(u, K - 1)], dot[0]);  // (v is zero where f <= j)
+      else if (f > j) dot[0] = fma(p[u], Vn[g], dot[0]);
+      if (f == j + 1) {
+        one[0] = p[u];
+        if (MODE != 0) {
+          one[2] = K == E ? vo[min(u, K - 1)] : Vo[g];
+          one[3] = K == E ? wo[min(u, K - 1)] : Wv[g];
+        }
       }
     }
-    if (tid == 0) Wv[j] = 0.0;
+    dot[0] = wave_sum_dpp(dot[0]);
+    if (lj == 0) {
+      red[w] = dot[0];
+      if (MODE != 0) {
+        red[16 + w] = dot[1];
+        red[24 + w] = dot[2];
+      }
+    }
+    __syncthreads();
+    if (MODE != 0 && *quit) break;  // uniform
+    double pv = sum8(red), p1 = one[0], sw = 0.0, sv = 0.0, vo1 = 0.0, wo1 = 0.0;
+    if (MODE != 0) {  // the update with the column before that p lacks: p - v_o (w_o^T v) - w_o (v_o^T v)
+      sw = sum8(red + 16);
+      sv = sum8(red + 24);
+      vo1 = one[2];
+      wo1 = one[3];
+      p1 -= vo1 * sw + wo1 * sv;
+      pv -= 2.0 * sw * sv;
+    }
+    fresh<(E > 3)>(tj);
+    lj = tj & 63;
+    const double half = 0.5 * tau * tau * pv, w1 = tau * p1 - half;
+    double part = 0.0;
+#pragma unroll
+    for (int u = 0; u < E; u++) {
+      const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
+      if (f > j) {
+        double pf = p[u], xf = col[u];
+        const double vf = K == E ? v[min(u, K - 1)] : Vn[g];
+        if (MODE != 0) {
+          const double vof = K == E ? vo[min(u, K - 1)] : Vo[g], wof = K == E ? wo[min(u, K - 1)] : Wv[g];
+          pf -= vof * sw + wof * sv;
+          xf -= vof * wo1 + wof * vo1;
+        }
+        const double wf = tau * pf - half * vf;
+        Wv[g] = wf;
+        const double x = xf - vf * w1 - wf;  // (the reflector's first entry is 1)
+        X[g] = f == j + 1 ? 0.0 : x;
+        if (f >= j + 3) part = fma(x, x, part);
+        if (f == j + 2) one[1] = x;
+        if (f == j + 1 && mem == 0) dout[jr + 1] = x;
+      }
+    }
+    if (tj == 0) Wv[tr_at(j)] = 0.0;
     part = wave_sum_dpp(part);
-    if (lane == 0) red[8 + w] = part;
+    if (lj == 0) red[8 + w] = part;
     // ---- sixteen reflectors complete: this workgroup's rows of them leave in 16-byte pieces ---------------------
     if ((jr & 15) == 15 || j == min(je, F - 1) - 1) {
       if (b == 0)
-        for (int e = tid; e < LI * 8 * 4; e += TR_THREADS) {
+        for (int e = tj; e < LI * 8 * 4; e += TR_THREADS) {
           const int o = e >> 2, r = (o >> 3) * R + 8 * a + (o & 7) + base;
           if (r >= (jr & ~15) && r >= 0) {
             float4* src = reinterpret_cast<float4*>(vblk + o * 16 + 4 * (e & 3));
@@ -500,7 +641,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       if (i >= RT * k) {
         const int fr = i * R + 8 * a + w, fc = k * C + 64 * b + lane;
         if (fr >= je && fc >= je && fr >= fc) {
-          const double y = A[i][k] - Vo[fr] * Wv[fc] - Wv[fr] * Vo[fc];
+          const double y = A[i][k] - Vo[tr_at(fr)] * Wv[tr_at(fc)] - Wv[tr_at(fr)] * Vo[tr_at(fc)];
           A0[(size_t)(fr + base) * Np + fc + base] = y;
         }
       }
@@ -508,10 +649,10 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 
 // ---- host ---------------------------------------------------------------------------------------------------
 struct TrFrame { int mode, F, P; size_t words; };
-constexpr int TR_SIZES = 7;  // frames: 0 the single workgroup, n: PC = 1, 2, 3, 4, 5, 7
+constexpr int TR_SIZES = 7;  // frames: 0 the single workgroup, n: PC = n
 static const TrFrame TR_FRAMES[TR_SIZES] = {
 #define TR_ENTRY(PC_) {TrShape<PC_>::MODE, TrShape<PC_>::F, TrShape<PC_>::P, TrShape<PC_>::WORDS}
-    TR_ENTRY(0), TR_ENTRY(1), TR_ENTRY(2), TR_ENTRY(3), TR_ENTRY(4), TR_ENTRY(5), TR_ENTRY(7)
+    TR_ENTRY(0), TR_ENTRY(1), TR_ENTRY(2), TR_ENTRY(3), TR_ENTRY(4), TR_ENTRY(5), TR_ENTRY(6)
 #undef TR_ENTRY
 };
 
@@ -603,7 +744,7 @@ int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float*
     int rc = TC_ERR_SHAPE;
 #define TR_CASE(SIZE_, PC_) case SIZE_: rc = tr_launch<PC_>(pl, ph[i], G, dvec, evec, tauv, Vc, sy, stride, fail, st); break;
     switch (ph[i].size) {
-      TR_CASE(0, 0) TR_CASE(1, 1) TR_CASE(2, 2) TR_CASE(3, 3) TR_CASE(4, 4) TR_CASE(5, 5) TR_CASE(6, 7)
+      TR_CASE(0, 0) TR_CASE(1, 1) TR_CASE(2, 2) TR_CASE(3, 3) TR_CASE(4, 4) TR_CASE(5, 5) TR_CASE(6, 6)
     }
 #undef TR_CASE
     if (rc != TC_OK) return rc;
