@@ -69,7 +69,8 @@ typedef enum { TC_EIG_F64 = 0, TC_EIG_F32 = 1 } tc_eig_dtype;
    TC_EIG_TRIDIAGONAL  Householder reduction to tridiagonal form, eigenvalues by bisection, eigenvectors from
                        twisted factorisations, back-transformation; float64 only, n_vis <= 1024;
    TC_EIG_JACOBI       two-sided block Jacobi iteration (any n_vis, float64 or float32);
-   TC_EIG_AUTO         the tridiagonal route for float64 and n_vis <= 4032, else Jacobi */
+   TC_EIG_AUTO         the tridiagonal route for float64 and n_vis <= 3456 (1728 while the stream is
+                       being captured into a graph), else Jacobi */
 typedef enum { TC_EIG_AUTO = 0, TC_EIG_JACOBI = 1, TC_EIG_TRIDIAGONAL = 2 } tc_eig_method;
 
 typedef struct {

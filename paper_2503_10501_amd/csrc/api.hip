@@ -123,7 +123,7 @@ static int direct_chain(const Plan& pl, const Plan& sub, int img0, const tc_para
 // images (6.63 ms against 7.22 ms with two for 64 images of 576 tokens), two above (12.83 against 13.03 ms for 128).
 static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const void* K, const void* V, void* O,
                        float* S, float* score, float* ics, float* sigma, int32_t* info, void* ws, hipStream_t st) {
-  if (pl.method != TC_EIG_TRIDIAGONAL) {
+  if (pl.method != TC_EIG_TRIDIAGONAL || !tridiag_allowed(pl.N, st)) {
     int rc = TC_OK;
     if (Q && (rc = launch_attention(pl, p->dtype, p->causal, Q, K, V, O, S, at<float>(ws, pl.off_Spart), st)) != TC_OK) return rc;
     void* G = at<char>(ws, pl.off_G);

@@ -90,6 +90,7 @@ int launch_sigma(const Plan& pl, int eig_dtype, const void* G, const EigState* s
 int launch_combine(const Plan& pl, const float* C_ws, const float* S, float lambda, int norm_mode, float* E, hipStream_t st);
 // direct eigensolver (tridiag.hip, tdeig.hip)
 bool tridiag_fits(int N);                     // the reduction takes N tokens
+bool tridiag_allowed(int N, hipStream_t st);  // ... in a call on this stream (not while it is captured, for large N)
 size_t tridiag_sync_bytes(int N, int B);      // exchange memory of one image (B: images of the call)
 int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float* tauv, float* Vc, void* sync, size_t sync_bytes,
                    int32_t* fail, hipStream_t st);

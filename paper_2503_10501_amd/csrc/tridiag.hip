@@ -35,7 +35,7 @@
 // that gives up raises the image's failure flag, its group follows, and the caller reports the image as failed.
 // A group's workgroups have neighbouring ids, so the groups of a launch become resident in order and the first
 // incomplete one is the only one that waits for a compute unit; launches whose groups could block each other when
-// several streams run them at once are kept apart by the host (see launch_tridiag).
+// several streams run them at once are kept apart by the host (see tr_in_order).
 #include <mutex>
 #include <utility>
 
@@ -688,17 +688,29 @@ size_t tridiag_sync_bytes(int N, int B) {  // exchange memory of one image
   return align256(words * 8 + 8);
 }
 
-// Launches of large groups are kept apart: two of them from different streams could each hold compute units that the
-// other's incomplete group waits for.  One launch leaves at most P - 1 workgroups waiting, and a process has four
-// hardware queues, so groups of up to 64 can never fill the 256 compute units with waiting workgroups and need no
-// order.  (Not while a graph is captured: its launches have the order of the graph.)
+// A group of workgroups waits for its own members, so launches that run side by side must never hold all 256 compute units
+// with incomplete groups.  A launch leaves at most P - 1 workgroups waiting and a process has four hardware queues:
+// groups of up to TR_FREE = 36 need no order, and one launch of a larger group fits beside three of those
+// (143 + 3 * 35 < 256).  Two launches of larger groups are kept apart by an event.  A launch inside a captured graph cannot
+// be (the graph may be replayed on several streams at once): tridiag_allowed sends such calls to the Jacobi iteration.
+constexpr int TR_FREE = 36;
+
+static bool tr_capturing(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
+bool tridiag_allowed(int N, hipStream_t st) {
+  int size = 0;
+  while (size < TR_SIZES && TR_FRAMES[size].F < N) size++;
+  return size < TR_SIZES && (TR_FRAMES[size].P <= TR_FREE || !tr_capturing(st));
+}
+
 static int tr_in_order(int P, hipStream_t st, bool before) {
   static std::mutex mx;
   static hipEvent_t ev[64];
   static bool used[64];
-  if (P <= 64) return TC_OK;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return TC_OK;
+  if (P <= TR_FREE) return TC_OK;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return TC_ERR_HIP;
   if (before) {

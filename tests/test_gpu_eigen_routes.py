@@ -1,0 +1,116 @@
+"""GPU tests of the contribution score on attention outputs in hand: the frames of the reduction to tridiagonal form
+(256, 576 and multiples of 576 tokens), the split contraction of the Gram matrix, captured graphs and concurrent calls."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _tc():
+    from paper_2503_10501_amd import binding as tc
+    tc.load_library()
+    assert torch.cuda.is_available()
+    return tc
+
+
+def _params(tc, batch, n, heads, head_dim=128, **kw):
+    return tc.make_params(batch=batch, seq_len=n, vis_start=0, n_vis=n, n_heads=heads, head_dim=head_dim,
+                          hidden_dim=heads * head_dim, dtype=tc.TC_BF16, k_prune=max(1, n // 2), k_final=max(1, n // 2), lam=1.0,
+                          norm_mode=0, **kw)
+
+
+def _rows(batch, n, d, seed):
+    """bf16 rows whose singular values fall from 1 to about 1e-2."""
+    g = torch.Generator().manual_seed(seed)
+    o = torch.randn(batch, n, d, generator=g) * torch.logspace(0, -2, d)
+    return o.to(torch.bfloat16)
+
+
+class Call:
+    """Outputs and workspace of a tc_ipgs_score call."""
+
+    def __init__(self, tc, p, O):
+        B, N = p.batch, p.n_vis
+        self.tc, self.p, self.O, self.ws = tc, p, O, tc.new_workspace(p)
+        self.S = torch.zeros(B, N, device="cuda")
+        self.E, self.C, self.sigma = (torch.empty(B, N, device="cuda") for _ in range(3))
+        self.info = torch.empty(B, dtype=torch.int32, device="cuda")
+
+    def __call__(self, **kw):
+        self.tc.tc_ipgs_score(self.p, self.O, self.S, self.E, self.C, self.sigma, self.info, self.ws, **kw)
+
+    def outputs(self):
+        return [x.clone() for x in (self.E, self.C, self.sigma, self.info)]
+
+
+def _reference(O):
+    """sigma (descending) and C of one image in float64."""
+    u, s, _ = torch.linalg.svd(O.double(), full_matrices=False)
+    return torch.nn.functional.pad(s, (0, O.shape[0] - s.numel())), u.abs() @ s
+
+
+# (tokens, batch, heads of 128).  Edges of the frames (256, 576, 1152, 1728, 2304, 2880; above 3456 the Jacobi iteration), a group
+# of eight images and a ragged one of four-workgroup groups; the Gram matrix of few tiles is contracted by 8 (257 x 1), 4
+# (577 x 3 with eight chunks each, 100 x 9), 2 (256 x 33) and 1 (576 x 18) workgroups per tile.
+@pytest.mark.parametrize("n,batch,heads", [(1, 1, 2), (2, 3, 2), (17, 1, 4), (100, 9, 16), (255, 2, 8), (256, 33, 4), (257, 1, 32),
+                                           (575, 8, 8), (576, 18, 8), (577, 3, 16), (1152, 1, 16), (1153, 2, 16), (1728, 1, 16),
+                                           (1729, 1, 16), (2305, 1, 8), (2881, 1, 8), (3457, 1, 4)])
+def test_singular_values_and_scores_at_the_edges_of_the_frames(n, batch, heads):
+    # sigma: the float32 output and a few eps ||G|| on its square; C: reflectors and vectors are held in float32, a row of U is off
+    # by about sqrt(N) 2^-24, and so is its weighted sum (4e-6 at 3456 tokens; 1e-4 where the method iterates)
+    tc = _tc()
+    O = _rows(batch, n, heads * 128, 7 * n + batch)
+    call = Call(tc, _params(tc, batch, n, heads), O.cuda())
+    call()
+    torch.cuda.synchronize()
+    assert int(call.info.min()) > 0
+    for b in {0, batch // 2, batch - 1}:
+        s, c = _reference(O[b])
+        assert float((call.sigma[b].double().cpu() - s).abs().max() / s.max()) < 1e-6
+        assert float((call.C[b].double().cpu() - c).abs().max() / c.abs().max()) < (2e-5 if n <= 3456 else 1e-4), b
+
+
+@pytest.mark.parametrize("n,batch", [(300, 2), (576, 1), (1800, 1)])
+def test_a_captured_call_replays_to_the_eager_result(n, batch):
+    # 1800 tokens: groups of 64 workgroups, which two replays at once could not be kept apart: a captured call iterates instead
+    tc = _tc()
+    O = _rows(batch, n, 512, n).cuda()
+    eager = Call(tc, _params(tc, batch, n, 4, **({"eig_method": 1} if n > 1728 else {})), O)
+    eager()
+    torch.cuda.synchronize()
+    want = eager.outputs()
+    call = Call(tc, _params(tc, batch, n, 4), O.clone())
+    st = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        call(stream=torch.cuda.current_stream().cuda_stream)
+    for rep in range(3):
+        call.O.copy_(O * (1 if rep != 1 else 2))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = call.outputs()
+        if rep == 1:   # other inputs in the same buffers: twice the rows, twice the scores
+            assert float((got[1] / 2 - want[1]).abs().max() / want[1].abs().max()) < 1e-5
+        else:
+            for x, y in zip(want, got):
+                assert torch.equal(x, y)
+
+
+def test_calls_with_large_groups_on_three_streams_at_once():
+    # 1729 tokens: 64 workgroups wait for each other in each call
+    tc = _tc()
+    calls = [Call(tc, _params(tc, 1, 1729, 4), _rows(1, 1729, 512, i).cuda()) for i in range(3)]
+    alone = []
+    for c in calls:
+        c()
+        torch.cuda.synchronize()
+        alone.append(c.outputs())
+    streams = [torch.cuda.Stream() for _ in calls]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for c, s in zip(calls, streams):
+            c(stream=s.cuda_stream)
+    torch.cuda.synchronize()
+    for c, want in zip(calls, alone):
+        for x, y in zip(want, c.outputs()):
+            assert torch.equal(x, y)
