@@ -40,14 +40,14 @@ def work_model(w):
         # reduction to tridiagonal form: per column two multiply-adds per element of the trailing lower triangle for the
         # rank-2 update and two for the symmetric product (the matrix stays on the chip: read once)
         "tridiag_flops": B * 8 * sum((N - j - 1) * (N - j) // 2 for j in range(N - 1)),
-        # twisted factorisations: pivots and multipliers written and read once (2 * 8 N^2 each way), vectors written (4 N^2)
-        "twisted_bytes": B * N * N * (16 + 16 + 4),
+        # twisted factorisations: vectors written (4 N^2), the pivots of every sixteenth row written and read twice
+        "twisted_bytes": B * N * N * (4 + 2 * 8 * 3 // 16),
         # back-transformation: 4 N^3 / 2 ... each reflector touches (N-j-1) rows of N columns, 4 flops each
         "backtf_flops": B * 4 * N * sum(N - j - 1 for j in range(N - 1)),
         "backtf_bytes": B * N * N * (4 + 4),                      # vectors of T and reflectors read once
         # Eq. 3-10 similarity and the merge
         "sim_flops": B * 2 * nA * nB * D,
-        "sim_bytes": B * (kp * D * es + 4 * nA * nB),
+        "sim_bytes": B * kp * D * es,
         "rownorm_bytes": B * kp * D * es,
         "average_bytes": B * (kp + kf) * w.hidden * es,
         # Jacobi method (when it runs): Eq. 3-6 reads U once
@@ -185,9 +185,9 @@ def main():
     if kinds["tridiag"][1] > 0:   # the tridiagonal route ran
         per_row["a4_tridiagonal_reduction"] = entry("tridiag", "alu", rate(wm["tridiag_flops"], "tridiag", "T"), PEAK["vec_f64"],
                                                     "TFLOP/s", ms=ms("tridiag"))
-        per_row["a4_bisection"] = {"kernel": "bisect", "bound": "alu (float64 divisions, one lane per eigenvalue)", "ms": ms("bisect")}
-        per_row["a4_twisted_factorisation"] = entry("twisted", "hbm", rate(wm["twisted_bytes"], "twisted", "G"), PEAK["hbm_gbps"],
-                                                    "GB/s", ms=ms("twisted"))
+        per_row["a4_bisection"] = {"kernel": "bisect", "bound": "alu (chain of dependent float64 multiply-adds)", "ms": ms("bisect")}
+        per_row["a4_twisted_factorisation"] = {"kernel": "twisted", "bound": "alu (chain of dependent float64 divisions)",
+                                               "ms": ms("twisted"), "hbm_gbps": rate(wm["twisted_bytes"], "twisted", "G")}
         per_row["a4_a5_backtransform_ics"] = entry("backtransform", "alu", rate(wm["backtf_flops"], "backtransform", "T"),
                                                    PEAK["vec_f32"], "TFLOP/s", ms=ms("backtransform"))
     else:

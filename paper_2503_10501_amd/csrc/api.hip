@@ -66,7 +66,7 @@ int make_plan(const tc_params* p, Plan* pl) {
   q.off_E = take(B * N * 4);
   q.off_order = take(B * q.kp * 4);
   q.off_rnorm = take(B * q.kp * 4);
-  q.off_sim = take(B * (size_t)q.nB * (q.nA > 0 ? q.nA : 1) * 4);
+  q.off_sim = take(B * sim_elems(q) * 4);
   q.off_mlist = take(B * (size_t)(q.m > 0 ? q.m : 1) * 8);
   q.off_info = take(B * 4);
   if (q.method == TC_EIG_TRIDIAGONAL) {

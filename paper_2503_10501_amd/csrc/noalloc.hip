@@ -50,7 +50,7 @@ extern "C" int tc_merge_noalloc(const tc_params* p, const void* X, const void* m
       misaligned(merge_dst))
     return TC_ERR_ALIGN;
   // the three regions tc_merge takes from its workspace, laid out back to back
-  const size_t n_rnorm = (size_t)pl.B * pl.kp, n_sim = (size_t)pl.B * pl.nB * (pl.nA > 0 ? pl.nA : 1),
+  const size_t n_rnorm = (size_t)pl.B * pl.kp, n_sim = (size_t)pl.B * sim_elems(pl),
                n_mlist = (size_t)pl.B * (pl.m > 0 ? pl.m : 1) * 2;
   const size_t off_rnorm = 0, off_sim = align256(n_rnorm * 4), off_mlist = off_sim + align256(n_sim * 4),
                total = off_mlist + align256(n_mlist * 4);

@@ -107,7 +107,9 @@ int launch_topk(const Plan& pl, const float* E, int32_t* order, hipStream_t st);
 int launch_similarity(const Plan& pl, int dtype, const void* metric, const int32_t* order, float* rnorm, float* sim,
                       hipStream_t st);
 int launch_merge(const Plan& pl, int dtype, const void* X, const void* metric, const int32_t* order, void* X_out,
-                 int32_t* kept_idx, int32_t* merge_dst, float* rnorm, float* sim, int32_t* mlist, hipStream_t st);
+                 int32_t* kept_idx, int32_t* merge_dst, float* rnorm, void* part, int32_t* mlist, hipStream_t st);
+// elements (4 bytes) of an image's similarity matrix, or of the best keys per tile that the merge keeps in its place
+inline size_t sim_elems(const Plan& pl) { return (size_t)pl.nB * (pl.nA > 2 ? pl.nA : 2); }
 
 // ---- optional per-kernel timing (only active inside tc_profile_compress) ----------------------
 enum ProfKind {
@@ -195,6 +197,12 @@ __device__ inline bool group_on_xcd(int id, int items, int groups, int* group, i
   *item = k % items;
   *group = (k / items) * 8 + (id & 7);
   return true;
+}
+
+// A key that orders values descending, equal ones (+0 and -0 too) by ascending index: the larger key comes first.
+__device__ inline unsigned long long order_key(float v, int index) {
+  const uint32_t u = __float_as_uint(v + 0.0f);
+  return ((unsigned long long)(u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u)) << 32) | (0x7fffffffu - (uint32_t)index);
 }
 
 template <typename T>
