@@ -88,6 +88,7 @@ int make_plan(const tc_params* p, Plan* pl) {
     q.off_td_sync = take(B * q.td_sync_bytes);           // exchange memory of the reduction
     q.off_td_fail = take(B * 4);
   }
+  q.off_gpart = take(B * gram_part_bytes(q));
   q.total = off > 0 ? off : 256;
   return TC_OK;
 }
@@ -129,7 +130,7 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
     void* G = at<char>(ws, pl.off_G);
     void* U = at<char>(ws, pl.off_U);
     EigState* state = at<EigState>(ws, pl.off_state);
-    if ((rc = launch_gram(pl, p->dtype, p->eig_dtype, O, G, st)) != TC_OK) return rc;
+    if ((rc = launch_gram(pl, p->dtype, p->eig_dtype, O, G, at<double>(ws, pl.off_gpart), st)) != TC_OK) return rc;
     if ((rc = launch_jacobi(pl, p->eig_dtype, G, U, at<char>(ws, pl.off_R), at<double>(ws, pl.off_offpart), state, st)) != TC_OK)
       return rc;
     return launch_scores(pl, p->eig_dtype, G, U, state, S, p->lambda, p->norm_mode, p->sv_rtol, at<char>(ws, pl.off_sig),
@@ -158,7 +159,8 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
                             at<float>(ws, pl.off_Spart) + i0 * pl.spart_stride, streams[g]);
       if (rc != TC_OK) break;
     }
-    rc = launch_gram(sub, p->dtype, p->eig_dtype, Og, at<double>(ws, pl.off_G) + i0 * pl.Np * pl.Np, streams[g]);
+    rc = launch_gram(sub, p->dtype, p->eig_dtype, Og, at<double>(ws, pl.off_G) + i0 * pl.Np * pl.Np,
+                     at<double>(ws, pl.off_gpart) + i0 * (gram_part_bytes(pl) / 8), streams[g]);
     if (rc != TC_OK) break;
     // the next group's attention and Gram kernels (which fill the chip) start when this group's are done, so
     // that the groups' reductions start one after the other and their tails do not all come at the end

@@ -62,22 +62,47 @@ __device__ inline void widen8(const Raw8<TIn>& r, double* dst) {
 // sixteen products per four contraction indices take five 16-byte LDS reads, and a lane ends with
 // rows 8 k + r, columns 2 (4 q + p) + s: 16-byte pairs along the row for the tile, runs of eight
 // along the column for its mirror.  The next 32 columns of O are fetched into registers meanwhile.
+// A tile takes one workgroup, and its contraction is a chain of D / 32 chunks (one image of 576 x 4096: 0.17 ms on 45 of the
+// 256 compute units, 0.044 + 0.008 with eight workgroups per tile and the sum).
+// Where the tiles of a call are few, `splits` workgroups share a tile: each contracts its part of D and leaves the sums in
+// `part` [image][tile][split][8][256] (pairs, a lane's rows r), gram_sum_kernel adds them in order.
+template <typename TOut>
+__device__ inline void store_tile(const double (*acc)[2], TOut* __restrict__ Gb, int Np, int ti, int tj, int tid) {
+  typedef __attribute__((ext_vector_type(2))) TOut o2;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int p4 = lane & 3, blk = (lane >> 2) & 3, kq = lane >> 4;
+  // the lane holds rows 8 kq + r, columns 2 (4 blk + p4) + s of its quadrant
+  const int r0 = ti * 64 + (wave >> 1) * 32 + 8 * kq, c0 = tj * 64 + (wave & 1) * 32 + 2 * (4 * blk + p4);
+#pragma unroll
+  for (int r = 0; r < 8; r++)
+    *reinterpret_cast<o2*>(&Gb[(size_t)(r0 + r) * Np + c0]) = o2{(TOut)acc[r][0], (TOut)acc[r][1]};
+  if (ti != tj) {
+#pragma unroll
+    for (int sc = 0; sc < 2; sc++)
+#pragma unroll
+      for (int r = 0; r < 8; r += 2)
+        *reinterpret_cast<o2*>(&Gb[(size_t)(c0 + sc) * Np + r0 + r]) = o2{(TOut)acc[r][sc], (TOut)acc[r + 1][sc]};
+  }
+}
+
 template <typename TIn, typename TOut>
 __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TOut* __restrict__ G, int N, int D,
-                                                   int Np, int B) {
+                                                   int Np, int B, int splits, double* __restrict__ part) {
   typedef __attribute__((ext_vector_type(2))) double d2;
-  typedef __attribute__((ext_vector_type(2))) TOut o2;
   __shared__ __attribute__((aligned(16))) double As[GK][GLD];
   __shared__ __attribute__((aligned(16))) double Bs[GK][GLD];
   const int ntile = Np / 64;
   int b, t;
-  if (!group_on_xcd(blockIdx.x, ntile * (ntile + 1) / 2, B, &b, &t)) return;
+  if (!group_on_xcd(blockIdx.x, ntile * (ntile + 1) / 2 * splits, B, &b, &t)) return;
+  double* mine = part + ((size_t)b * (ntile * (ntile + 1) / 2) * splits + t) * 4096;  // (splits > 1)
+  const int split = t % splits;
+  t /= splits;
   int ti = 0;  // decode the lower-triangular tile index
   while (t >= ti + 1) { t -= ti + 1; ti++; }
   const int tj = t;
   const TIn* Ob = O + (size_t)b * N * D;
   TOut* Gb = G + (size_t)b * Np * Np;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, q4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
   const int lrow = tid & 63, kc = tid >> 6;  // loader: row within the panel, which 8-wide k chunk
   const int p4 = lane & 3, blk = (lane >> 2) & 3, kq = lane >> 4;
@@ -86,11 +111,13 @@ __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TO
   for (int r = 0; r < 8; r++) acc[r][0] = acc[r][1] = 0.0;
   const int rowA = ti * 64 + lrow, rowB = tj * 64 + lrow;
   const bool diag = ti == tj;
-  const TIn* srcA = Ob + (size_t)rowA * D + kc * 8;
-  const TIn* srcB = Ob + (size_t)rowB * D + kc * 8;
+  const int nchunk = D / GK;  // (D is a multiple of 64)
+  const int kbeg = (int)((long long)nchunk * split / splits) * GK, kend = (int)((long long)nchunk * (split + 1) / splits) * GK;
+  const TIn* srcA = Ob + (size_t)rowA * D + kbeg + kc * 8;
+  const TIn* srcB = Ob + (size_t)rowB * D + kbeg + kc * 8;
   Raw8<TIn> ra = rowA < N ? fetch8<TIn>(srcA) : zero8<TIn>();
   Raw8<TIn> rb = (!diag && rowB < N) ? fetch8<TIn>(srcB) : zero8<TIn>();
-  for (int k0 = 0; k0 < D; k0 += GK) {
+  for (int k0 = 0; k0 < kend - kbeg; k0 += GK) {
     double va[8], vb[8];
     widen8<TIn>(ra, va);
     if (!diag) widen8<TIn>(rb, vb);
@@ -101,7 +128,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TO
       if (!diag) Bs[kc * 8 + i][lrow] = vb[i];
     }
     __syncthreads();
-    if (k0 + GK < D) {  // in flight during the products
+    if (k0 + GK < kend - kbeg) {  // in flight during the products
       if (rowA < N) ra = fetch8<TIn>(srcA + k0 + GK);
       if (!diag && rowB < N) rb = fetch8<TIn>(srcB + k0 + GK);
     }
@@ -120,39 +147,61 @@ __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TO
       }
     }
   }
-  // the lane holds rows 8 kq + r, columns 2 (4 blk + p4) + s of its quadrant
-  const int r0 = ti * 64 + wr * 32 + 8 * kq, c0 = tj * 64 + wc * 32 + 2 * (4 * blk + p4);
+  if (splits > 1) {
 #pragma unroll
-  for (int r = 0; r < 8; r++)
-    *reinterpret_cast<o2*>(&Gb[(size_t)(r0 + r) * Np + c0]) = o2{(TOut)acc[r][0], (TOut)acc[r][1]};
-  if (!diag) {
-#pragma unroll
-    for (int sc = 0; sc < 2; sc++)
-#pragma unroll
-      for (int r = 0; r < 8; r += 2)
-        *reinterpret_cast<o2*>(&Gb[(size_t)(c0 + sc) * Np + r0 + r]) = o2{(TOut)acc[r][sc], (TOut)acc[r + 1][sc]};
+    for (int r = 0; r < 8; r++) *reinterpret_cast<d2*>(mine + ((size_t)r * 256 + tid) * 2) = d2{acc[r][0], acc[r][1]};
+    return;
   }
+  store_tile<TOut>(acc, Gb, Np, ti, tj, tid);
 }
 
-int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, hipStream_t st) {
-  const int nt = pl.Np / 64;
-  dim3 grid(grid_for_groups(nt * (nt + 1) / 2, pl.B)), block(256);
-  if (dtype == TC_BF16) {
-    if (eig_dtype == TC_EIG_F64)
-      TC_TIMED(PK_GRAM, 0, st, (gram_kernel<uint16_t, double><<<grid, block, 0, st>>>((const uint16_t*)O, (double*)G, pl.N, pl.D, pl.Np, pl.B)));
-    else
-      TC_TIMED(PK_GRAM, 0, st, (gram_kernel<uint16_t, float><<<grid, block, 0, st>>>((const uint16_t*)O, (float*)G, pl.N, pl.D, pl.Np, pl.B)));
-  } else if (dtype == TC_F16) {
-    if (eig_dtype == TC_EIG_F64)
-      TC_TIMED(PK_GRAM, 0, st, (gram_kernel<f16_t, double><<<grid, block, 0, st>>>((const f16_t*)O, (double*)G, pl.N, pl.D, pl.Np, pl.B)));
-    else
-      TC_TIMED(PK_GRAM, 0, st, (gram_kernel<f16_t, float><<<grid, block, 0, st>>>((const f16_t*)O, (float*)G, pl.N, pl.D, pl.Np, pl.B)));
-  } else {
-    if (eig_dtype == TC_EIG_F64)
-      TC_TIMED(PK_GRAM, 0, st, (gram_kernel<float, double><<<grid, block, 0, st>>>((const float*)O, (double*)G, pl.N, pl.D, pl.Np, pl.B)));
-    else
-      TC_TIMED(PK_GRAM, 0, st, (gram_kernel<float, float><<<grid, block, 0, st>>>((const float*)O, (float*)G, pl.N, pl.D, pl.Np, pl.B)));
+template <typename TOut>
+__global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict__ part, TOut* __restrict__ G, int Np, int splits) {
+  typedef __attribute__((ext_vector_type(2))) double d2;
+  const int tid = threadIdx.x, b = blockIdx.y;
+  int t = blockIdx.x, ti = 0;
+  const double* p = part + ((size_t)b * gridDim.x + t) * splits * 4096 + 2 * tid;
+  while (t >= ti + 1) { t -= ti + 1; ti++; }
+  double acc[8][2];
+#pragma unroll
+  for (int r = 0; r < 8; r++) acc[r][0] = acc[r][1] = 0.0;
+  for (int s = 0; s < splits; s++) {
+#pragma unroll
+    for (int r = 0; r < 8; r++) {
+      const d2 v = *reinterpret_cast<const d2*>(p + (size_t)s * 4096 + r * 512);
+      acc[r][0] += v.x;
+      acc[r][1] += v.y;
+    }
   }
+  store_tile<TOut>(acc, G + (size_t)b * Np * Np, Np, ti, t, tid);
+}
+
+// Workgroups per tile: as many as keep the launch within three per compute unit, with at least eight chunks each (by the size
+// of the whole call: the order of a sum must not depend on stream groups).
+int gram_splits(const Plan& pl) {
+  const int nt = pl.Np / 64;
+  const long long tiles = (long long)nt * (nt + 1) / 2 * pl.batch_call;
+  int s = 1;
+  while (s < 8 && tiles * s * 2 <= 768 && pl.D / GK >= 16 * s) s *= 2;
+  return s;
+}
+size_t gram_part_bytes(const Plan& pl) {  // of one image
+  const size_t nt = pl.Np / 64, s = gram_splits(pl);
+  return s > 1 ? nt * (nt + 1) / 2 * s * 4096 * 8 : 0;
+}
+
+template <typename TIn, typename TOut>
+static void run_gram(const Plan& pl, const void* O, void* G, double* part, hipStream_t st) {
+  const int nt = pl.Np / 64, tiles = nt * (nt + 1) / 2, splits = gram_splits(pl);
+  TC_TIMED(PK_GRAM, 0, st, (gram_kernel<TIn, TOut><<<grid_for_groups(tiles * splits, pl.B), 256, 0, st>>>((const TIn*)O, (TOut*)G, pl.N, pl.D, pl.Np, pl.B, splits, part)));
+  if (splits > 1) TC_TIMED(PK_GRAM, 1, st, (gram_sum_kernel<TOut><<<dim3(tiles, pl.B), 256, 0, st>>>(part, (TOut*)G, pl.Np, splits)));
+}
+
+int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, double* part, hipStream_t st) {
+  const bool f64 = eig_dtype == TC_EIG_F64;
+  if (dtype == TC_BF16) f64 ? run_gram<uint16_t, double>(pl, O, G, part, st) : run_gram<uint16_t, float>(pl, O, G, part, st);
+  else if (dtype == TC_F16) f64 ? run_gram<f16_t, double>(pl, O, G, part, st) : run_gram<f16_t, float>(pl, O, G, part, st);
+  else f64 ? run_gram<float, double>(pl, O, G, part, st) : run_gram<float, float>(pl, O, G, part, st);
   return check_launch();
 }
 
