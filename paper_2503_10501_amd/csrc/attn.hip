@@ -454,6 +454,7 @@ __global__ __launch_bounds__(256) void attn_score_reduce(const float* __restrict
   if (x < N) {
     const float* sp = Spart + (size_t)b * stride + x;
     const int i1 = min(rows, (q + 1) * per);
+#pragma unroll 10
     for (int i = q * per; i < i1; i++) acc += (double)sp[(size_t)i * N];
   }
   part[q][xl] = acc;

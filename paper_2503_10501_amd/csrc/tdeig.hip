@@ -333,7 +333,9 @@ __global__ __launch_bounds__(256) void td_bisect_kernel(const double* __restrict
 //
 // All lanes of a wavefront walk over the same row at the same time, whatever block their eigenvalue belongs
 // to and wherever its twist index lies (a lane ignores rows that are not its own): every access to memory is one
-// contiguous run per row.  Two chains of divisions run side by side in each of three walks: pivots, gamma, vector.
+// contiguous run per row.  Two chains of divisions, one per wavefront, in each of three walks: pivots, gamma (four
+// wavefronts, a quarter of the segments each), vector.  With both chains in one wavefront a row took 306 clocks:
+// 0.22 -> 0.11 ms for one image of 576 tokens, 0.24 -> 0.18 for 64, 1.18 -> 0.75 for 8 of 2880.
 // Only the pivots at the ends of segments of sixteen rows are kept (cp, cm [row / 16][slot]); the later walks form the
 // others again from there.  Kept for every row they were 2 x 16 N^2 bytes of traffic per image and their latency three
 // times per row (0.34 ms for one image of 576 tokens, 0.40 for 64).
@@ -346,7 +348,7 @@ __device__ __forceinline__ double tw_rcp(double x) {
   return fma(fma(-x, r, 1.0), r, r);
 }
 
-__global__ __launch_bounds__(64) void td_twisted_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
+__global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
                                                         const double* __restrict__ lam, const int2* __restrict__ blk,
                                                         const double* __restrict__ tnorm, double* __restrict__ ckpt,
                                                         size_t ckpt_stride, float* __restrict__ W,
@@ -354,44 +356,56 @@ __global__ __launch_bounds__(64) void td_twisted_kernel(const double* __restrict
                                                         int Np) {
   extern __shared__ __attribute__((aligned(16))) unsigned char tw_smem[];
   tb_pair* de = reinterpret_cast<tb_pair*>(tw_smem) + 1;  // [-1 .. 16 nseg - 1]: d_i, and e_i that couples rows i and i+1 (0 where T is split)
-  const int b = blockIdx.y, tid = threadIdx.x, nseg = (N + TW_SEG - 1) / TW_SEG;
+  __shared__ double gs[4][64];
+  __shared__ int rs[4][64];
+  __shared__ double ns[64];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, nseg = (N + TW_SEG - 1) / TW_SEG;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double* db = dvec + (size_t)b * Np;
   const double* eb = evec + (size_t)b * Np;
   const double tn = tnorm[b], split = TD_EPS * tn;
-  for (int i = tid - 1; i < nseg * TW_SEG; i += 64) {  // rows behind the last stand alone (4 ||T|| is nobody's eigenvalue)
+  for (int i = tid - 1; i < nseg * TW_SEG; i += 256) {  // rows behind the last stand alone (4 ||T|| is nobody's eigenvalue)
     const double e = i >= 0 && i + 1 < N ? eb[i] : 0.0;
     de[i] = tb_pair{i >= 0 && i < N ? db[i] : (tn > 0.0 ? 4.0 * tn : 1.0), fabs(e) > split ? e : 0.0};
   }
   __syncthreads();
-  const int k = blockIdx.x * 64 + tid;
-  if (k >= N) return;  // (no barrier below)
-  const int2 st = blk[(size_t)b * Np + k];
+  const int k = blockIdx.x * 64 + lane, kr = min(k, N - 1);  // (lanes past the last vector repeat it and store nothing but pivots)
+  const int2 st = blk[(size_t)b * Np + kr];
   const int s = st.x, t = st.y;
   const double pivmin = DBL_MIN * fmax(1.0, tn * tn);
-  const double l = lam[(size_t)b * Np + k];
+  const double l = lam[(size_t)b * Np + kr];
   double* cp = ckpt + (size_t)b * ckpt_stride + k;
   double* cm = cp + (size_t)nseg * Np;
   float* w = W + (size_t)b * Np * Np + k;
   auto guard = [&](double p) { return fabs(p) < pivmin ? -pivmin : p; };
 
   // pivots: dp[i + 1] = d_{i+1} - l - e_i (e_i / dp[i]);  dm[i] = d_i - l - e_i (e_i / dm[i + 1])
-  {
-    double p = guard(de[0].x - l), q = guard(de[nseg * TW_SEG - 1].x - l);
+  if (wv == 0) {
+    double p = guard(de[0].x - l);
     for (int c = 0; c < nseg; c++) {
-      const int u0 = c * TW_SEG, v0 = (nseg - 1 - c) * TW_SEG;
       cp[(size_t)c * Np] = p;
-      cm[(size_t)(nseg - 1 - c) * Np] = q;
       if (c == nseg - 1) break;
-      double e = de[u0].y;
+      double e = de[c * TW_SEG].y;
 #pragma unroll
       for (int u = 0; u < TW_SEG; u++) {
-        const tb_pair a = de[u0 + u + 1], z = de[v0 + TW_SEG - 2 - u];
+        const tb_pair a = de[c * TW_SEG + u + 1];
         p = guard(fma(-e, e * tw_rcp(p), a.x - l));
         e = a.y;
+      }
+    }
+  } else if (wv == 1) {
+    double q = guard(de[nseg * TW_SEG - 1].x - l);
+    for (int c = nseg - 1; c >= 0; c--) {
+      cm[(size_t)c * Np] = q;
+      if (c == 0) break;
+#pragma unroll
+      for (int u = 0; u < TW_SEG; u++) {
+        const tb_pair z = de[c * TW_SEG + TW_SEG - 2 - u];
         q = guard(fma(-z.y, z.y * tw_rcp(q), z.x - l));
       }
     }
   }
+  __syncthreads();
   // the two pivots of the rows of a segment
   auto segment_p = [&](int c, double p, double* f) {
     double e = de[c * TW_SEG].y;
@@ -415,13 +429,14 @@ __global__ __launch_bounds__(64) void td_twisted_kernel(const double* __restrict
       }
     }
   };
-  // twist index: the row with the smallest |gamma| (the last of equal ones wins)
+  // twist index: the row with the smallest |gamma| (the last of equal ones wins); a quarter of the segments each
   double gbest = DBL_MAX;
-  int r = t - 1;
-  {
-    double p = cp[0], q = cm[0];
-    for (int c = 0; c < nseg; c++) {
-      const int cn = min(c + 1, nseg - 1);
+  int r = -1;
+  const int c0 = nseg * wv / 4, c1 = nseg * (wv + 1) / 4;
+  if (c0 < c1) {
+    double p = cp[(size_t)c0 * Np], q = cm[(size_t)c0 * Np];
+    for (int c = c0; c < c1; c++) {
+      const int cn = min(c + 1, c1 - 1);
       const double pn = cp[(size_t)cn * Np], qn = cm[(size_t)cn * Np];
       double f[TW_SEG], h[TW_SEG];
       segment_p(c, p, f);
@@ -438,39 +453,61 @@ __global__ __launch_bounds__(64) void td_twisted_kernel(const double* __restrict
       q = qn;
     }
   }
+  gs[wv][lane] = gbest;
+  rs[wv][lane] = r;
+  __syncthreads();
+  r = t - 1;
+  gbest = DBL_MAX;
+#pragma unroll
+  for (int u = 0; u < 4; u++) {
+    const double g = gs[u][lane];
+    const int ru = rs[u][lane];
+    const bool take = ru >= 0 && g <= gbest;
+    gbest = take ? g : gbest;
+    r = take ? ru : r;
+  }
   // the vector: upwards from r over the segments from the last to the first, downwards from the first to the last
-  double zu = 1.0, zd = 1.0, nrm = 1.0;
-  {
-    double p = cp[(size_t)(nseg - 1) * Np], q = cm[0];
+  const bool on = k < N;
+  double z = 1.0, nrm = 0.0;
+  if (wv == 0) {
+    double p = cp[(size_t)(nseg - 1) * Np];
+    for (int c = nseg - 1; c >= 0; c--) {
+      const double pn = cp[(size_t)max(c - 1, 0) * Np];
+      double f[TW_SEG];
+      segment_p(c, p, f);
+#pragma unroll
+      for (int u = TW_SEG - 1; u >= 0; u--) {
+        const int i = c * TW_SEG + u;
+        const double zn = -(de[i].y * tw_rcp(f[u])) * z;
+        const bool act = i >= s && i < r;
+        z = act ? zn : z;
+        nrm += act ? zn * zn : 0.0;
+        if (on && i <= r) w[(size_t)i * Np] = i < s ? 0.f : (i == r ? 1.f : (float)z);
+      }
+      p = pn;
+    }
+  } else if (wv == 1) {
+    double q = cm[0];
     for (int c = 0; c < nseg; c++) {
-      const int cu = nseg - 1 - c, cn = min(c + 1, nseg - 1);
-      const double pn = cp[(size_t)(nseg - 1 - cn) * Np], qn = cm[(size_t)cn * Np];
-      double f[TW_SEG], h[TW_SEG];
-      segment_p(cu, p, f);
+      const double qn = cm[(size_t)min(c + 1, nseg - 1) * Np];
+      double h[TW_SEG];
       segment_m(c, q, h);
 #pragma unroll
       for (int u = 0; u < TW_SEG; u++) {
-        {  // rows up to r
-          const int i = cu * TW_SEG + TW_SEG - 1 - u;
-          const double zn = -(de[i].y * tw_rcp(f[TW_SEG - 1 - u])) * zu;
-          const bool act = i >= s && i < r;
-          zu = act ? zn : zu;
-          nrm += act ? zn * zn : 0.0;
-          if (i <= r) w[(size_t)i * Np] = i < s ? 0.f : (i == r ? 1.f : (float)zu);
-        }
-        {  // rows behind r
-          const int i = c * TW_SEG + u;
-          const double zn = -(de[i - 1].y * tw_rcp(h[u])) * zd;
-          const bool act = i > r && i < t;
-          zd = act ? zn : zd;
-          nrm += act ? zn * zn : 0.0;
-          if (i > r && i < N) w[(size_t)i * Np] = i >= t ? 0.f : (float)zd;
-        }
+        const int i = c * TW_SEG + u;
+        const double zn = -(de[i - 1].y * tw_rcp(h[u])) * z;
+        const bool act = i > r && i < t;
+        z = act ? zn : z;
+        nrm += act ? zn * zn : 0.0;
+        if (on && i > r && i < N) w[(size_t)i * Np] = i >= t ? 0.f : (float)z;
       }
-      p = pn;
       q = qn;
     }
+    ns[lane] = nrm;
   }
+  __syncthreads();
+  if (wv != 0 || !on) return;
+  nrm += ns[lane] + 1.0;
   const bool fin = nrm == nrm && nrm < DBL_MAX && nrm < 1e60;  // float storage of z holds |z| < 3e38 relative to z_r = 1
   rn[(size_t)b * Np + k] = fin ? 1.0 / sqrt(nrm) : 0.0;
   if (!fin) atomicOr(&bad[b], 1);
@@ -800,6 +837,7 @@ __global__ __launch_bounds__(256) void td_ics_finish_kernel(const double* __rest
   const int b = blockIdx.y, x = blockIdx.x * 256 + threadIdx.x;
   if (x >= N) return;
   double s = 0.0;
+#pragma unroll 12
   for (int t = 0; t < nstrip; t++) s += Cpart[((size_t)b * nstrip + t) * Np + x];
   C[(size_t)b * N + x] = (float)s;
   if (C_out) C_out[(size_t)b * N + x] = (float)s;
@@ -831,7 +869,7 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_twisted_kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
       return TC_ERR_HIP;
-    TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 64, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, bad, N, Np)));
+    TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, bad, N, Np)));
   }
   TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3((N + 63) / 64, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, N, Np)));
   TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, rn, tnorm, blk, mark, any, W, bad, sv_rtol, sig, wgt, sigma_out, info_out, N, Np)));
