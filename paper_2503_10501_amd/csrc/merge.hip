@@ -163,6 +163,8 @@ __global__ __launch_bounds__(256) void sim_tile_kernel(const uint16_t* __restric
 // 64 x 64 form is a chain of D / 64 chunks on a handful of compute units (one image of 256 survivors: 5 + 43 -> 21 us; 64 images of
 // 128: 15 + 51 -> 34 us).
 constexpr int SW = 8;
+// Where the forms meet: 64 images of 256 survivors (256 tiles of 64 x 64) 59 us in tiles, 102 split; 64 of 128 (64 tiles) 66 in tiles
+// with norms of their own, 34 split.
 constexpr long long SIM_FEW = 192;
 template <bool F16>
 __global__ __launch_bounds__(64 * SW) void sim_split_kernel(const uint16_t* __restrict__ metric, const int32_t* __restrict__ order,
