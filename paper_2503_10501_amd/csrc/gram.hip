@@ -62,10 +62,20 @@ __device__ inline void widen8(const Raw8<TIn>& r, double* dst) {
 // sixteen products per four contraction indices take five 16-byte LDS reads, and a lane ends with
 // rows 8 k + r, columns 2 (4 q + p) + s: 16-byte pairs along the row for the tile, runs of eight
 // along the column for its mirror.  The next 32 columns of O are fetched into registers meanwhile.
-// A tile takes one workgroup, and its contraction is a chain of D / 32 chunks (one image of 576 x 4096: 0.17 ms on 45 of the
-// 256 compute units, 0.044 + 0.008 with eight workgroups per tile and the sum).
-// Where the tiles of a call are few, `splits` workgroups share a tile: each contracts its part of D and leaves the sums in
-// `part` [image][tile][split][8][256] (pairs, a lane's rows r), gram_sum_kernel adds them in order.
+// A tile takes one workgroup, and its contraction is a chain of D / 32 chunks (one image of 576 x 4096: 0.169 ms on 45 of the 256
+// compute units, 0.069 with three workgroups per tile and the sum).
+// Where the tiles of a call are few, `splits` workgroups share a tile: each contracts its part of D and leaves its sums,
+// gram_sum_kernel adds them in order.  A float64 G keeps the first part in the place of the tile, rows of 64 as they come;
+// the others (all of them for a float32 G) go to `part` [image][tile][split][8][256] (pairs, a lane's rows r).
+template <typename TOut>
+__host__ __device__ constexpr int parts_in_g() { return sizeof(TOut) == sizeof(double) ? 1 : 0; }
+
+// the place of element 2 (256 r + tid) of the first part: four wavefronts, eight rows of the tile at a time
+template <typename TOut>
+__device__ inline TOut* place_in_g(TOut* Gb, int Np, int ti, int tj, int r, int tid) {
+  return Gb + (size_t)(ti * 64 + 8 * r + (tid >> 5)) * Np + tj * 64 + ((2 * tid) & 63);
+}
+
 template <typename TOut>
 __device__ inline void store_tile(const double (*acc)[2], TOut* __restrict__ Gb, int Np, int ti, int tj, int tid) {
   typedef __attribute__((ext_vector_type(2))) TOut o2;
@@ -94,9 +104,9 @@ __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TO
   const int ntile = Np / 64;
   int b, t;
   if (!group_on_xcd(blockIdx.x, ntile * (ntile + 1) / 2 * splits, B, &b, &t)) return;
-  double* mine = part + ((size_t)b * (ntile * (ntile + 1) / 2) * splits + t) * 4096;  // (splits > 1)
   const int split = t % splits;
   t /= splits;
+  double* mine = part + (((size_t)b * (ntile * (ntile + 1) / 2) + t) * (splits - parts_in_g<TOut>()) + split - parts_in_g<TOut>()) * 4096;
   int ti = 0;  // decode the lower-triangular tile index
   while (t >= ti + 1) { t -= ti + 1; ti++; }
   const int tj = t;
@@ -148,6 +158,11 @@ __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TO
     }
   }
   if (splits > 1) {
+    if (split < parts_in_g<TOut>()) {
+#pragma unroll
+      for (int r = 0; r < 8; r++) *reinterpret_cast<d2*>(place_in_g(Gb, Np, ti, tj, r, tid)) = d2{acc[r][0], acc[r][1]};
+      return;
+    }
 #pragma unroll
     for (int r = 0; r < 8; r++) *reinterpret_cast<d2*>(mine + ((size_t)r * 256 + tid) * 2) = d2{acc[r][0], acc[r][1]};
     return;
@@ -160,12 +175,21 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict_
   typedef __attribute__((ext_vector_type(2))) double d2;
   const int tid = threadIdx.x, b = blockIdx.y;
   int t = blockIdx.x, ti = 0;
-  const double* p = part + ((size_t)b * gridDim.x + t) * splits * 4096 + 2 * tid;
+  const double* p = part + ((size_t)b * gridDim.x + t) * (splits - parts_in_g<TOut>()) * 4096 + 2 * tid;
+  TOut* Gb = G + (size_t)b * Np * Np;
   while (t >= ti + 1) { t -= ti + 1; ti++; }
   double acc[8][2];
 #pragma unroll
   for (int r = 0; r < 8; r++) acc[r][0] = acc[r][1] = 0.0;
-  for (int s = 0; s < splits; s++) {
+  if (parts_in_g<TOut>()) {
+#pragma unroll
+    for (int r = 0; r < 8; r++) {
+      const d2 v = *reinterpret_cast<const d2*>(place_in_g(Gb, Np, ti, t, r, tid));
+      acc[r][0] = v.x;
+      acc[r][1] = v.y;
+    }
+  }
+  for (int s = 0; s < splits - parts_in_g<TOut>(); s++) {
 #pragma unroll
     for (int r = 0; r < 8; r++) {
       const d2 v = *reinterpret_cast<const d2*>(p + (size_t)s * 4096 + r * 512);
@@ -173,22 +197,26 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict_
       acc[r][1] += v.y;
     }
   }
-  store_tile<TOut>(acc, G + (size_t)b * Np * Np, Np, ti, t, tid);
+  __syncthreads();  // the first part has been read by everyone
+  store_tile<TOut>(acc, Gb, Np, ti, t, tid);
 }
 
-// Workgroups per tile: as many as keep the launch within three per compute unit, with at least eight chunks each (by the size
-// of the whole call: the order of a sum must not depend on stream groups).
+// Workgroups per tile: as many as keep the launch within three per compute unit, with at least eight chunks each and no more
+// than 3 MiB of parts per image: a workspace stays in proportion to the batch (one image of 576 x 4096 needs 11 MB; eight
+// workgroups per tile would double that to save another 0.012 ms of 2.5).  By the size of the whole call: the order of a sum
+// must not depend on stream groups.
+static size_t part_bytes(const Plan& pl, int splits) {  // of one image
+  const size_t nt = pl.Np / 64, parts = splits - (pl.tsize == 8 ? parts_in_g<double>() : parts_in_g<float>());
+  return splits > 1 ? nt * (nt + 1) / 2 * parts * 4096 * 8 : 0;
+}
 int gram_splits(const Plan& pl) {
   const int nt = pl.Np / 64;
   const long long tiles = (long long)nt * (nt + 1) / 2 * pl.batch_call;
   int s = 1;
-  while (s < 8 && tiles * s * 2 <= 768 && pl.D / GK >= 16 * s) s *= 2;
+  while (s < 8 && tiles * (s + 1) <= 768 && pl.D / GK >= 8 * (s + 1) && part_bytes(pl, s + 1) <= (3u << 20)) s++;
   return s;
 }
-size_t gram_part_bytes(const Plan& pl) {  // of one image
-  const size_t nt = pl.Np / 64, s = gram_splits(pl);
-  return s > 1 ? nt * (nt + 1) / 2 * s * 4096 * 8 : 0;
-}
+size_t gram_part_bytes(const Plan& pl) { return part_bytes(pl, gram_splits(pl)); }
 
 template <typename TIn, typename TOut>
 static void run_gram(const Plan& pl, const void* O, void* G, double* part, hipStream_t st) {
