@@ -62,6 +62,8 @@ __device__ inline void widen8(const Raw8<TIn>& r, double* dst) {
 // sixteen products per four contraction indices take five 16-byte LDS reads, and a lane ends with
 // rows 8 k + r, columns 2 (4 q + p) + s: 16-byte pairs along the row for the tile, runs of eight
 // along the column for its mirror.  The next 32 columns of O are fetched into registers meanwhile.
+// In a tile on the diagonal the upper right quadrant is the mirror of the lower left one, bit for bit: its wavefront only
+// loads and leaves the matrix cores of its SIMD to the other workgroups (64 images of 576 x 4096: 1.83 -> 1.76 ms).
 // A tile takes one workgroup, and its contraction is a chain of D / 32 chunks (one image of 576 x 4096: 0.169 ms on 45 of the 256
 // compute units, 0.069 with three workgroups per tile and the sum).
 // Where the tiles of a call are few, `splits` workgroups share a tile: each contracts its part of D and leaves its sums,
@@ -82,11 +84,12 @@ __device__ inline void store_tile(const double (*acc)[2], TOut* __restrict__ Gb,
   const int lane = tid & 63, wave = tid >> 6;
   const int p4 = lane & 3, blk = (lane >> 2) & 3, kq = lane >> 4;
   // the lane holds rows 8 kq + r, columns 2 (4 blk + p4) + s of its quadrant
+  if (ti == tj && wave == 1) return;
   const int r0 = ti * 64 + (wave >> 1) * 32 + 8 * kq, c0 = tj * 64 + (wave & 1) * 32 + 2 * (4 * blk + p4);
 #pragma unroll
   for (int r = 0; r < 8; r++)
     *reinterpret_cast<o2*>(&Gb[(size_t)(r0 + r) * Np + c0]) = o2{(TOut)acc[r][0], (TOut)acc[r][1]};
-  if (ti != tj) {
+  if (ti != tj || wave == 2) {
 #pragma unroll
     for (int sc = 0; sc < 2; sc++)
 #pragma unroll
@@ -142,6 +145,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TO
       if (rowA < N) ra = fetch8<TIn>(srcA + k0 + GK);
       if (!diag && rowB < N) rb = fetch8<TIn>(srcB + k0 + GK);
     }
+    if (diag && wave == 1) continue;  // the mirror of wavefront 2's quadrant
     const double(*Bp)[GLD] = diag ? As : Bs;
 #pragma unroll
     for (int kk = 0; kk < GK; kk += 4) {
