@@ -251,8 +251,8 @@ def main():
         out["metric_string_counts"] = {"k_prune": 256, "k_final": 192, "ms_per_step": round(ms2, 3),
                                        "value": round(B / (ms2 * 1e-3), 2), "unit": "images/s"}
         # Not the headline: the same K steps issued round-robin on several streams, each with its own workspace and
-        # outputs.  Behind the Gram matrix a step keeps 64 to 768 wavefronts busy, so independent batches overlap;
-        # a serving loop with more than one batch queued would see this rate.
+        # outputs.  The reduction of one batch is bound by the latency of its columns, attention and Gram by the matrix
+        # cores, so independent batches overlap; a serving loop with more than one batch queued would see this rate.
         def in_flight(n_streams, steps):
             pf = tc.params_for(w, eig_method=method, stream_groups=1)
             streams = [torch.cuda.Stream() for _ in range(n_streams)]

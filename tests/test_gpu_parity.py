@@ -42,7 +42,7 @@ def _small(name):
     return Workload(name, *SMALL[name])
 
 
-METHODS = {"tridiagonal": 2, "jacobi": 1}   # tc_eig_method; 0 (automatic) picks the tridiagonal route up to 1024 tokens
+METHODS = {"tridiagonal": 2, "jacobi": 1}   # tc_eig_method; 0 (automatic) picks the tridiagonal route up to 3456 tokens
 
 
 @pytest.mark.parametrize("method", list(METHODS))
