@@ -11,7 +11,7 @@
 // belongs to one unreduced block and its vector is zero outside that block, so equal eigenvalues of
 // decoupled blocks (block-diagonal Gram matrices, null spaces) get orthogonal vectors for free.
 // Eigenvectors of one block are computed independently of each other; a close pair that did not come out orthogonal is
-// orthogonalised explicitly afterwards (td_pairs_kernel, td_weights_kernel).
+// orthogonalised explicitly afterwards (td_pairs_kernel, td_orthogonalise_kernel).
 #include <cfloat>
 #include <utility>
 
@@ -589,55 +589,204 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
 }
 
 // ---- close eigenvalues inside one block -----------------------------------------------------------------
-// The vectors of one block are computed independently of each other.  Two neighbours closer than 1e-10 ||T|| are compared:
-// if they are not orthogonal to 1e-6 (T is not graded there, or the eigenvalues agree to 1e-10 of their size), the later one
-// is marked to be orthogonalised.  Eigenvalues that count as zero (below the resolution of the reduction) get weight 0 in
-// Eq. 3-6: their vectors are left as they are, however many of them there are (the null space of a rank-deficient
-// matrix).  One workgroup per 64 slots; mark [B][Np] is written for every slot, any [B] collects.
+// The vectors of one block are computed independently of each other.  A run is a set of neighbouring slots of one block,
+// each closer than 1e-10 ||T|| to the next; vectors of different runs are orthogonal to about eps / 1e-10 and are left as they
+// are.  td_pairs_kernel compares every two vectors of a run; where two are not orthogonal to what float32 vectors can be
+// (T is not graded there, or the eigenvalues agree to their last bits), td_orthogonalise_kernel orthogonalises the whole run:
+// comparing neighbours only, or mending single slots, leaves pairs further apart as they were (up to 7e-5 in groups of
+// four).  Eigenvalues that count as zero (below the resolution of the reduction) get weight 0 in Eq. 3-6: their vectors are
+// left as they are, however many of them there are (the null space of a rank-deficient matrix).
+constexpr double TD_CLOSE = 1e-10;             // of ||T||
+constexpr double TD_ORTHOGONAL = 4.0 / (1 << 24);  // largest scalar product of two unit vectors that passes
 __device__ inline double td_zero_floor(double tn) { return tn > 0.0 ? 8.0 * TD_EPS * tn : DBL_MAX; }  // (every eigenvalue of an all-zero matrix is zero)
+// slot k belongs to the run of slot k - 1
+__device__ inline bool td_close(const double* lb, const int2* bb, double tn, int k, int N) {
+  const double zero = td_zero_floor(tn);
+  return k > 0 && k < N && bb[k].x == bb[k - 1].x && lb[k] - lb[k - 1] <= TD_CLOSE * tn && lb[k] > zero && lb[k - 1] > zero;
+}
 
+// One workgroup per 64 slots, against these and (a run may be long) the tiles of 64 before them.  mark [B][Np] is written for
+// every slot: 1 if an earlier vector of its run is not orthogonal to it; any [B] collects.
 __global__ __launch_bounds__(256) void td_pairs_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
                                                        const double* __restrict__ tnorm, const float* __restrict__ W,
                                                        const double* __restrict__ rn, int32_t* __restrict__ mark,
                                                        int32_t* __restrict__ any, int N, int Np) {
-  __shared__ double part[4][64];
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int k = blockIdx.x * 64 + lane;
+  constexpr int CH = 32;  // rows at a time
+  __shared__ float wk[CH][68], wj[CH][68];
+  __shared__ int start[64];  // first slot of the run of slot 64 blockIdx.x + i
+  __shared__ int hit[64];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k0 = blockIdx.x * 64;
   const double* lb = lam + (size_t)b * Np;
   const int2* bb = blk + (size_t)b * Np;
+  const double* rb = rn + (size_t)b * Np;
   const double tn = tnorm[b];
-  const bool close = k > 0 && k < N && bb[k].x == bb[k - 1].x && lb[k] - lb[k - 1] <= 1e-10 * tn && lb[k] > td_zero_floor(tn);
-  if (!__any(close)) {  // the same in all four wavefronts
-    if (wave == 0 && k < N) mark[(size_t)b * Np + k] = 0;
+  const u64 cl = __ballot(td_close(lb, bb, tn, k0 + lane, N));  // the same in all four wavefronts
+  if (cl == 0) {
+    if (wave == 0 && k0 + lane < N) mark[(size_t)b * Np + k0 + lane] = 0;
     return;
   }
-  const float* Wb = W + (size_t)b * Np * Np;
-  double dot = 0.0;
-  if (close) {
-    const int s = bb[k].x, t = bb[k].y;
-    for (int i = s + wave; i < t; i += 4) dot += (double)Wb[(size_t)i * Np + k] * (double)Wb[(size_t)i * Np + k - 1];
+  int before = k0;  // where the run of slot k0 begins (slot 0 is close to nothing)
+  if (cl & 1)
+    for (int t = k0 - 64;; t -= 64) {
+      const u64 open = ~__ballot(td_close(lb, bb, tn, t + lane, N));
+      before = t;
+      if (open) { before = t + 63 - __builtin_clzll(open); break; }
+      if (t == 0) break;
+    }
+  if (wave == 0) {
+    const u64 open = ~cl & (~0ull >> (63 - lane));
+    start[lane] = open ? k0 + 63 - __builtin_clzll(open) : before;
+    hit[lane] = 0;
   }
-  part[wave][lane] = dot;
+  const float* Wb = W + (size_t)b * Np * Np;
+  const int tx = tid & 15, ty = tid >> 4;  // slots 4 ty + a against 4 tx + c
+  for (int j0 = k0; j0 + 63 >= before && j0 >= 0; j0 -= 64) {
+    double dot[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; a++)
+#pragma unroll
+      for (int c = 0; c < 4; c++) dot[a][c] = 0.0;
+    for (int i0 = 0; i0 < N; i0 += CH) {  // (a vector is zero outside its block)
+      __syncthreads();
+      for (int r = wave; r < CH; r += 4) {
+        const bool in = i0 + r < N;
+        wk[r][lane] = in ? Wb[(size_t)(i0 + r) * Np + k0 + lane] : 0.f;
+        wj[r][lane] = in ? Wb[(size_t)(i0 + r) * Np + j0 + lane] : 0.f;
+      }
+      __syncthreads();
+#pragma unroll 4
+      for (int r = 0; r < CH; r++) {
+        double x[4], y[4];
+#pragma unroll
+        for (int a = 0; a < 4; a++) {
+          x[a] = (double)wk[r][4 * ty + a];
+          y[a] = (double)wj[r][4 * tx + a];
+        }
+#pragma unroll
+        for (int a = 0; a < 4; a++)
+#pragma unroll
+          for (int c = 0; c < 4; c++) dot[a][c] = fma(x[a], y[c], dot[a][c]);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 4; a++)
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        const int k = k0 + 4 * ty + a, j = j0 + 4 * tx + c;
+        if (k < N && j < k && j >= start[4 * ty + a] && !(fabs(dot[a][c]) * rb[k] * rb[j] <= TD_ORTHOGONAL)) hit[4 * ty + a] = 1;
+      }
+  }
   __syncthreads();
-  if (wave == 0 && k < N) {
-    dot = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
-    const bool m = close && !(fabs(dot) * rn[(size_t)b * Np + k] * rn[(size_t)b * Np + k - 1] <= 1e-6);
-    mark[(size_t)b * Np + k] = m;
-    if (m) atomicOr(&any[b], 1);
+  if (wave == 0 && k0 + lane < N) {
+    mark[(size_t)b * Np + k0 + lane] = hit[lane];
+    if (hit[lane]) atomicOr(&any[b], 1);
   }
 }
 
-// ---- marked vectors, weights of Eq. 3-6 ---------------------------------------------------------------------
-// Marked slots first: a run of them and the slot before it are a cluster, every vector of which is orthogonalised (modified
-// Gram-Schmidt, float64 accumulation) against the earlier ones.  If nothing independent is left of it (two vectors were the
-// same to 1e-3) the pair cannot be separated this way: bad[b] gets bit 2 and the caller's info turns negative.
+// The runs that hold a marked slot (few calls have one), a workgroup for those that begin in its 64 slots: every vector of a
+// run is orthogonalised, in float64 and twice, against the earlier ones.  If nothing independent is left of it (two vectors
+// were the same to 1e-3) the pair cannot be separated this way: bad[b] gets bit 2 and the caller's info turns negative.
+constexpr int TO_THREADS = 512, TO_WAVES = TO_THREADS / 64;
+static size_t td_orthogonalise_lds(int N) { return (size_t)N * 8 + (TO_WAVES + 1) * 64 * 8; }
+
+__global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
+                                                                      const double* __restrict__ tnorm, const int32_t* __restrict__ mark,
+                                                                      const int32_t* __restrict__ any, float* __restrict__ W,
+                                                                      double* __restrict__ rn, int32_t* __restrict__ bad, int N, int Np) {
+  const int b = blockIdx.y;
+  if (!any[b]) return;
+  extern __shared__ __attribute__((aligned(16))) unsigned char to_smem[];
+  double* x = reinterpret_cast<double*>(to_smem);  // [N] the vector in hand
+  double* part = x + N;                           // [TO_WAVES][64]
+  double* coef = part + TO_WAVES * 64;             // [64]
+  __shared__ double wsum[TO_WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double* lb = lam + (size_t)b * Np;
+  const int2* bb = blk + (size_t)b * Np;
+  const int32_t* mb = mark + (size_t)b * Np;
+  double* rb = rn + (size_t)b * Np;
+  float* Wb = W + (size_t)b * Np * Np;
+  const double tn = tnorm[b];
+
+  auto norm2 = [&](int n) {  // of x, the same in every thread
+    double v = 0.0;
+    __syncthreads();
+    for (int i = tid; i < n; i += TO_THREADS) v = fma(x[i], x[i], v);
+    v = wave_sum(v);
+    if (lane == 0) wsum[wave] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int q = 0; q < TO_WAVES; q++) t += wsum[q];
+    return t;
+  };
+  // x less its parts along the vectors of slots j0 .. j1 - 1 (rows s .. s + n - 1), 64 at a time
+  auto project = [&](int j0, int j1, int s, int n) {
+    for (int j = j0; j < j1; j += 64) {
+      const int cnt = min(64, j1 - j), jl = j + min(lane, cnt - 1);
+      double v = 0.0;
+      __syncthreads();
+      for (int i = wave; i < n; i += TO_WAVES) v = fma((double)Wb[(size_t)(s + i) * Np + jl], x[i], v);
+      part[wave * 64 + lane] = v;
+      __syncthreads();
+      if (wave == 0) {
+        double t = 0.0;
+        for (int q = 0; q < TO_WAVES; q++) t += part[q * 64 + lane];
+        coef[lane] = lane < cnt ? t * rb[jl] * rb[jl] : 0.0;  // column j has norm 1 / rb[j]
+      }
+      __syncthreads();
+      for (int i = tid; i < n; i += TO_THREADS) {
+        const float* row = Wb + (size_t)(s + i) * Np + j;
+        double v2 = x[i];
+        for (int c = 0; c < cnt; c++) v2 = fma(-coef[c], (double)row[c], v2);
+        x[i] = v2;
+      }
+    }
+    __syncthreads();
+  };
+  for (int first = blockIdx.x * 64; first < min(N, (int)blockIdx.x * 64 + 64); first++) {
+    if (td_close(lb, bb, tn, first, N)) continue;  // (uniform, as all that follows)
+    int end = first + 1;
+    bool marked = false;
+    for (; td_close(lb, bb, tn, end, N); end++) marked = marked || mb[end];
+    if (!marked) continue;
+    const int s = bb[first].x, n = bb[first].y - s;
+    for (int k = first + 1; k < end; k++) {
+      const double r = rb[k];
+      __syncthreads();
+      for (int i = tid; i < n; i += TO_THREADS) x[i] = (double)Wb[(size_t)(s + i) * Np + k] * r;
+      __syncthreads();
+      project(first, k, s, n);
+      project(first, k, s, n);
+      const double left = norm2(n);
+      if (!(left > 1e-6)) {
+        if (tid == 0) {
+          atomicOr(&bad[b], 2);
+          rb[k] = 0.0;
+        }
+        __syncthreads();
+        continue;
+      }
+      const double f = 1.0 / sqrt(left);
+      __syncthreads();
+      for (int i = tid; i < n; i += TO_THREADS) {
+        const float y = (float)(x[i] * f);
+        Wb[(size_t)(s + i) * Np + k] = y;
+        x[i] = (double)y;
+      }
+      const double v = norm2(n);
+      if (tid == 0) rb[k] = 1.0 / sqrt(v);
+      __syncthreads();
+    }
+  }
+}
+
+// ---- weights of Eq. 3-6 -----------------------------------------------------------------------------------
 // sigma_k = sqrt(max(lambda_k, 0)); wgt[k] = sigma_k * rn[k] (0 for terms dropped by sv_rtol): the factor that
 // turns the unnormalised vector of slot k into its term of C.  Also the optional outputs of tc_ipgs_score that
 // do not need the vectors: sigma sorted in descending order, and info.
-__global__ __launch_bounds__(256) void td_weights_kernel(const double* __restrict__ lam, double* __restrict__ rn,
-                                                         const double* __restrict__ tnorm, const int2* __restrict__ blk,
-                                                         const int32_t* __restrict__ mark, const int32_t* __restrict__ any,
-                                                         float* __restrict__ W, int32_t* __restrict__ bad, float sv_rtol,
+__global__ __launch_bounds__(256) void td_weights_kernel(const double* __restrict__ lam, const double* __restrict__ rn,
+                                                         const double* __restrict__ tnorm,
+                                                         const int32_t* __restrict__ bad, float sv_rtol,
                                                          double* __restrict__ sig, double* __restrict__ wgt,
                                                          float* __restrict__ sigma_out, int32_t* __restrict__ info_out,
                                                          int N, int Np) {
@@ -646,42 +795,6 @@ __global__ __launch_bounds__(256) void td_weights_kernel(const double* __restric
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* lb = lam + (size_t)b * Np;
   double* sb = sig + (size_t)b * Np;
-  if (wgt && any[b]) {  // uniform
-    const int32_t* mb = mark + (size_t)b * Np;
-    const int2* bb = blk + (size_t)b * Np;
-    double* rb = rn + (size_t)b * Np;
-    float* Wb = W + (size_t)b * Np * Np;
-    auto block_sum = [&](double x) {
-      x = wave_sum(x);
-      __syncthreads();
-      if (lane == 0) wmax[wave] = x;
-      __syncthreads();
-      return (wmax[0] + wmax[1]) + (wmax[2] + wmax[3]);
-    };
-    int first = 0;  // first slot of the current cluster
-    for (int k = 1; k < N; k++) {
-      if (!mb[k]) { first = k; continue; }
-      const int s = bb[k].x, t = bb[k].y;
-      for (int j = first; j < k; j++) {
-        double dot = 0.0;
-        for (int i = s + tid; i < t; i += 256) dot += (double)Wb[(size_t)i * Np + j] * (double)Wb[(size_t)i * Np + k];
-        dot = block_sum(dot) * rb[j] * rb[j];  // column j has norm 1 / rb[j]
-        for (int i = s + tid; i < t; i += 256)
-          Wb[(size_t)i * Np + k] = (float)((double)Wb[(size_t)i * Np + k] - dot * (double)Wb[(size_t)i * Np + j]);
-        __syncthreads();
-      }
-      double n2 = 0.0;
-      for (int i = s + tid; i < t; i += 256) { const double v = Wb[(size_t)i * Np + k]; n2 += v * v; }
-      n2 = block_sum(n2);
-      const double before = rb[k] > 0.0 ? 1.0 / (rb[k] * rb[k]) : 0.0;
-      __syncthreads();
-      if (tid == 0) {
-        if (!(n2 > 1e-6 * before)) atomicOr(&bad[b], 2);
-        rb[k] = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
-      }
-      __syncthreads();
-    }
-  }
   // Eigenvalues come out of the reduction and the bisection with an absolute error of a few eps ||T||: what lies
   // below that is zero (an all-zero matrix, the null space of a rank-deficient one).
   const double floor0 = td_zero_floor(tnorm[b]);
@@ -711,7 +824,7 @@ __global__ __launch_bounds__(256) void td_weights_kernel(const double* __restric
       const double s = sb[i];
       wgt[(size_t)b * Np + i] = (i < N && s > thr) ? s * rn[(size_t)b * Np + i] : 0.0;
     }
-  if (tid == 0 && info_out)  // 1: done (the method does not iterate); negative: an eigenvector is not finite or a cluster stayed unresolved
+  if (tid == 0 && info_out)  // 1: done (the method does not iterate); negative: an eigenvector could not be found or the reduction gave up
     info_out[b] = (bad[b] | wnan[0] | wnan[1] | wnan[2] | wnan[3]) ? -1 : 1;
   if (!sigma_out) return;
   int n2 = 1;
@@ -936,7 +1049,7 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
   while (n2 < N) n2 <<= 1;
   const size_t shm_sig = sigma_out ? (size_t)n2 * sizeof(float) : 0;
   if (!vectors) {  // eigenvalues only (the information-quantity tool)
-    TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, nullptr, tnorm, blk, nullptr, nullptr, nullptr, bad, 0.f, sig, nullptr, sigma_out, info_out, N, Np)));
+    TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, nullptr, tnorm, bad, 0.f, sig, nullptr, sigma_out, info_out, N, Np)));
     return check_launch();
   }
   {
@@ -947,7 +1060,8 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
     TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, bad, N, Np)));
   }
   TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3((N + 63) / 64, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, N, Np)));
-  TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, rn, tnorm, blk, mark, any, W, bad, sv_rtol, sig, wgt, sigma_out, info_out, N, Np)));
+  TC_TIMED(PK_TWISTED, 2, st, (td_orthogonalise_kernel<<<dim3((N + 63) / 64, B), TO_THREADS, td_orthogonalise_lds(N), st>>>(lam, blk, tnorm, mark, any, W, rn, bad, N, Np)));
+  TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, rn, tnorm, bad, sv_rtol, sig, wgt, sigma_out, info_out, N, Np)));
   const int npanel = (N - 1 + BT_K - 1) / BT_K, nstrip = (N + 15) / 16;  // blocks of reflectors, strips of eigenvectors
   if (npanel > 0) TC_TIMED(PK_BACKTF, 0, st, (td_tfactor_kernel<<<dim3(npanel, B), 256, 0, st>>>(Vc, tauv, Tf, N, Np, npanel)));
 #define TC_BACKTF(TPW_, NW_, SPW_)                                                                                                   \
