@@ -404,7 +404,8 @@ __global__ __launch_bounds__(256) void td_bisect_kernel(const double* __restrict
 // (pivots dm, multipliers e_{i-1} / dm_i), joined at the row r with the smallest |gamma|, gamma_i = dp_i + dm_i - (d_i - l);
 // z_r = 1, upwards z_i = -(e_i / dp_i) z_{i+1}, downwards z_i = -(e_{i-1} / dm_i) z_{i-1}.
 // W [B][Np][Np] float receives the unnormalised vector of slot k in column k (rows outside its block are zero); rn
-// [B][Np] its reciprocal norm (0 if the vector is not finite, which also raises bad[b]).
+// [B][Np] its reciprocal norm (0 if the vector is not finite: weakly coupled parts of T that share an eigenvalue to the last bit;
+// that raises any[b], and td_orthogonalise_kernel makes the vector anew).
 //
 // All lanes of a wavefront walk over the same row at the same time, whatever block their eigenvalue belongs
 // to and wherever its twist index lies (a lane ignores rows that are not its own): every access to memory is one
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
                                                         const double* __restrict__ lam, const int2* __restrict__ blk,
                                                         const double* __restrict__ tnorm, double* __restrict__ ckpt,
                                                         size_t ckpt_stride, float* __restrict__ W,
-                                                        double* __restrict__ rn, int32_t* __restrict__ bad, int N,
+                                                        double* __restrict__ rn, int32_t* __restrict__ any, int N,
                                                         int Np) {
   extern __shared__ __attribute__((aligned(16))) unsigned char tw_smem[];
   tb_pair* de = reinterpret_cast<tb_pair*>(tw_smem) + 1;  // [-1 .. 16 nseg - 1]: d_i, and e_i that couples rows i and i+1 (0 where T is split)
@@ -585,7 +586,7 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
   nrm += ns[lane] + 1.0;
   const bool fin = nrm == nrm && nrm < DBL_MAX && nrm < 1e60;  // float storage of z holds |z| < 3e38 relative to z_r = 1
   rn[(size_t)b * Np + k] = fin ? 1.0 / sqrt(nrm) : 0.0;
-  if (!fin) atomicOr(&bad[b], 1);
+  if (!fin) atomicOr(&any[b], 1);
 }
 
 // ---- close eigenvalues inside one block -----------------------------------------------------------------
@@ -683,13 +684,20 @@ __global__ __launch_bounds__(256) void td_pairs_kernel(const double* __restrict_
   }
 }
 
-// The runs that hold a marked slot (few calls have one), a workgroup for those that begin in its 64 slots: every vector of a
-// run is orthogonalised, in float64 and twice, against the earlier ones.  If nothing independent is left of it (two vectors
-// were the same to 1e-3) the pair cannot be separated this way: bad[b] gets bit 2 and the caller's info turns negative.
+// The runs that hold a marked slot (few calls have one), a workgroup for those that begin in its TO_SLOTS slots: every vector of a
+// run is orthogonalised, in float64 and twice, against the earlier ones.  Where less than a tenth of a vector is left (two
+// eigenvalues that agree to their last bits may come out with one vector), or td_twisted_kernel found none, it is made anew by
+// inverse iteration: a vector of no particular direction, orthogonal to the earlier ones of the run, is multiplied by
+// (T - lambda)^-1 and made orthogonal again, three times.  lambda is taken 64 eps ||T|| off the eigenvalue, which multiplies all
+// that agree with it alike (at the eigenvalue itself, one of them comes out again and again, however much of it the
+// earlier vectors hold) and what lies outside the run by 1.4e-4 of that.  An image for which this fails (T is not finite) gets
+// bad[b], and the caller's info turns negative.
 constexpr int TO_THREADS = 512, TO_WAVES = TO_THREADS / 64;
-static size_t td_orthogonalise_lds(int N) { return (size_t)N * 8 + (TO_WAVES + 1) * 64 * 8; }
+constexpr int TO_SLOTS = 16;  // of a workgroup (288 pairs in one image of 577 tokens: a chain of 0.4 ms each)
+static size_t td_orthogonalise_lds(int N) { return (size_t)N * 5 * 8 + (TO_WAVES + 1) * 64 * 8 + round_up(N, 16); }
 
-__global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
+__global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
+                                                                      const double* __restrict__ lam, const int2* __restrict__ blk,
                                                                       const double* __restrict__ tnorm, const int32_t* __restrict__ mark,
                                                                       const int32_t* __restrict__ any, float* __restrict__ W,
                                                                       double* __restrict__ rn, int32_t* __restrict__ bad, int N, int Np) {
@@ -697,16 +705,23 @@ __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const doub
   if (!any[b]) return;
   extern __shared__ __attribute__((aligned(16))) unsigned char to_smem[];
   double* x = reinterpret_cast<double*>(to_smem);  // [N] the vector in hand
-  double* part = x + N;                           // [TO_WAVES][64]
+  double* pd = x + N;                              // [N] factors of T - lambda: pivots,
+  double* pu = pd + N;                             // [N] first
+  double* pv = pu + N;                             // [N] and second superdiagonal,
+  double* pl = pv + N;                             // [N] multipliers,
+  double* part = pl + N;                           // [TO_WAVES][64]
   double* coef = part + TO_WAVES * 64;             // [64]
+  uint8_t* sw = reinterpret_cast<uint8_t*>(coef + 64);  // [N] 1: rows i and i + 1 have changed places
   __shared__ double wsum[TO_WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double* db = dvec + (size_t)b * Np;
+  const double* eb = evec + (size_t)b * Np;
   const double* lb = lam + (size_t)b * Np;
   const int2* bb = blk + (size_t)b * Np;
   const int32_t* mb = mark + (size_t)b * Np;
   double* rb = rn + (size_t)b * Np;
   float* Wb = W + (size_t)b * Np * Np;
-  const double tn = tnorm[b];
+  const double tn = tnorm[b], tiny = TD_EPS * tn;
 
   auto norm2 = [&](int n) {  // of x, the same in every thread
     double v = 0.0;
@@ -718,6 +733,10 @@ __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const doub
     double t = 0.0;
     for (int q = 0; q < TO_WAVES; q++) t += wsum[q];
     return t;
+  };
+  auto scale = [&](int n, double f) {
+    for (int i = tid; i < n; i += TO_THREADS) x[i] *= f;
+    __syncthreads();
   };
   // x less its parts along the vectors of slots j0 .. j1 - 1 (rows s .. s + n - 1), 64 at a time
   auto project = [&](int j0, int j1, int s, int n) {
@@ -743,28 +762,91 @@ __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const doub
     }
     __syncthreads();
   };
-  for (int first = blockIdx.x * 64; first < min(N, (int)blockIdx.x * 64 + 64); first++) {
+  // T - lambda of rows s .. s + n - 1 as triangular factors, rows exchanged for the larger pivot (one thread: a chain)
+  auto factor = [&](int s, int n, double l) {
+    double d = db[s] - l, u = n > 1 ? eb[s] : 0.0;
+    for (int i = 0; i + 1 < n; i++) {
+      const double e = eb[s + i], dn = db[s + i + 1] - l, un = i + 2 < n ? eb[s + i + 1] : 0.0;
+      if (fabs(d) >= fabs(e)) {
+        const double m = e / d;
+        pd[i] = d; pu[i] = u; pv[i] = 0.0; pl[i] = m; sw[i] = 0;
+        d = dn - m * u;
+        u = un;
+      } else {
+        const double m = d / e;
+        pd[i] = e; pu[i] = dn; pv[i] = un; pl[i] = m; sw[i] = 1;
+        d = u - m * dn;
+        u = -m * un;
+      }
+    }
+    pd[n - 1] = fabs(d) < tiny ? tiny : d;
+    pu[n - 1] = pv[n - 1] = 0.0;
+  };
+  auto solve = [&](int n) {
+    double p = x[0];
+    for (int i = 0; i + 1 < n; i++) {
+      const double q = x[i + 1], m = pl[i];
+      if (sw[i]) { x[i] = q; p = p - m * q; }
+      else { x[i] = p; p = q - m * p; }
+    }
+    double y1 = p / pd[n - 1], y2 = 0.0;
+    x[n - 1] = y1;
+    for (int i = n - 2; i >= 0; i--) {
+      const double y = (x[i] - pu[i] * y1 - pv[i] * y2) / pd[i];
+      x[i] = y;
+      y2 = y1;
+      y1 = y;
+    }
+  };
+
+  for (int first = blockIdx.x * TO_SLOTS; first < min(N, (int)(blockIdx.x + 1) * TO_SLOTS); first++) {
     if (td_close(lb, bb, tn, first, N)) continue;  // (uniform, as all that follows)
     int end = first + 1;
     bool marked = false;
-    for (; td_close(lb, bb, tn, end, N); end++) marked = marked || mb[end];
-    if (!marked) continue;
+    const bool lost = rb[first] == 0.0;
+    for (; td_close(lb, bb, tn, end, N); end++) marked = marked || mb[end];  // (a slot without a vector is marked)
     const int s = bb[first].x, n = bb[first].y - s;
-    for (int k = first + 1; k < end; k++) {
+    if (lost && !(lb[first] > td_zero_floor(tn))) {  // its weight is zero
+      for (int i = tid; i < n; i += TO_THREADS) Wb[(size_t)(s + i) * Np + first] = 0.f;
+      continue;
+    }
+    for (int k = lost ? first : first + 1; k < (marked ? end : lost ? first + 1 : first); k++) {
       const double r = rb[k];
       __syncthreads();
       for (int i = tid; i < n; i += TO_THREADS) x[i] = (double)Wb[(size_t)(s + i) * Np + k] * r;
       __syncthreads();
       project(first, k, s, n);
       project(first, k, s, n);
-      const double left = norm2(n);
-      if (!(left > 1e-6)) {
-        if (tid == 0) {
-          atomicOr(&bad[b], 2);
-          rb[k] = 0.0;
+      double left = norm2(n);
+      if (!(left >= 0.01)) {
+        if (tid == 0) factor(s, n, lb[k] + 64.0 * tiny);
+        for (int i = tid; i < n; i += TO_THREADS) {
+          uint32_t h = (uint32_t)(i + 1) * 0x9e3779b1u ^ (uint32_t)(k + 1) * 0x85ebca6bu;
+          h = (h ^ (h >> 15)) * 0x2c1b3c6du;
+          x[i] = (double)(int32_t)(h ^ (h >> 13)) * 0x1p-31;
         }
         __syncthreads();
-        continue;
+        project(first, k, s, n);
+        bool ok = false;
+        for (int it = 0; it < 6 && !ok; it++) {
+          scale(n, 1.0 / sqrt(norm2(n)));
+          if (tid == 0) solve(n);
+          const double y2 = norm2(n);
+          if (!(y2 > 0.0 && y2 < DBL_MAX)) break;
+          scale(n, 1.0 / sqrt(y2));
+          project(first, k, s, n);
+          project(first, k, s, n);
+          left = norm2(n);
+          ok = it > 1 && left >= 0.25;
+        }
+        if (!ok) {
+          if (tid == 0) {
+            bad[b] = 1;
+            rb[k] = 0.0;
+          }
+          __syncthreads();
+          continue;
+        }
       }
       const double f = 1.0 / sqrt(left);
       __syncthreads();
@@ -1057,10 +1139,16 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_twisted_kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
       return TC_ERR_HIP;
-    TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, bad, N, Np)));
+    TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, any, N, Np)));
   }
   TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3((N + 63) / 64, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, N, Np)));
-  TC_TIMED(PK_TWISTED, 2, st, (td_orthogonalise_kernel<<<dim3((N + 63) / 64, B), TO_THREADS, td_orthogonalise_lds(N), st>>>(lam, blk, tnorm, mark, any, W, rn, bad, N, Np)));
+  {
+    const size_t shm = td_orthogonalise_lds(N);
+    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_orthogonalise_kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+      return TC_ERR_HIP;
+    TC_TIMED(PK_TWISTED, 2, st, (td_orthogonalise_kernel<<<dim3((N + TO_SLOTS - 1) / TO_SLOTS, B), TO_THREADS, shm, st>>>(dvec, evec, lam, blk, tnorm, mark, any, W, rn, bad, N, Np)));
+  }
   TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, rn, tnorm, bad, sv_rtol, sig, wgt, sigma_out, info_out, N, Np)));
   const int npanel = (N - 1 + BT_K - 1) / BT_K, nstrip = (N + 15) / 16;  // blocks of reflectors, strips of eigenvectors
   if (npanel > 0) TC_TIMED(PK_BACKTF, 0, st, (td_tfactor_kernel<<<dim3(npanel, B), 256, 0, st>>>(Vc, tauv, Tf, N, Np, npanel)));

@@ -49,11 +49,13 @@ def _basis_behind(c, P, rng):
     return best
 
 
-# Values that come four times but for some entries of the matrix that are off by one, which parts them by 1e-10 ... 1e-12 of
-# their square (and moves their subspace by less than 1e-8).  sv_rtol keeps the largest value only.
+# Values that come 2, 4 or 6 times, equal to the last bit (bumps = 0) or, with some entries of the matrix off by one, parted by
+# 1e-10 ... 1e-12 of their square (which moves their subspace by less than 1e-8).  sv_rtol keeps the largest value only.
 # Vectors and reflectors are held in float32: a row of U is off by about sqrt(N) 2^-24.  Vectors whose eigenvalues lie just over 1e-10
 # of the norm apart are orthogonal to eps / 1e-10 = 2.2e-6 without help.
-@pytest.mark.parametrize("p,m,bumps,seed", [(577, 4, 4, 232), (1153, 4, 4, 122), (1153, 4, 4, 344), (1753, 4, 8, 55), (3169, 4, 8, 206)])
+@pytest.mark.parametrize("p,m,bumps,seed", [(61, 4, 0, 1), (577, 2, 0, 1), (577, 4, 0, 1), (577, 4, 1, 1), (577, 4, 4, 232),
+                                            (577, 6, 1, 1), (1153, 4, 0, 1), (1153, 4, 4, 122), (1153, 4, 4, 344), (1753, 4, 0, 1),
+                                            (1753, 4, 8, 55), (3169, 4, 1, 1), (3169, 4, 8, 206)])
 def test_vectors_of_close_singular_values_are_orthonormal(p, m, bumps, seed):
     from paper_2503_10501_amd import binding as tc
     D, batch = (p + 63) // 64 * 64, 2
