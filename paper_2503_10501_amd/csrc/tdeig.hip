@@ -38,12 +38,13 @@ typedef double tb_pair __attribute__((ext_vector_type(2)));
 // Scaled copy of T for the bisection, one workgroup per image: prep [B][prep_stride] doubles holds
 // (d_i, -e_i^2) pairs for rows 0 .. N-1 (e_i = |coupling of rows i-1 and i|, e_0 = 0; the square is 0 where T
 // is split), 32 zero pairs behind them, then the Gershgorin interval of T (scaled).  Also the block (s, t) of every row,
-// tnorm [B] = ||T||_inf; bad[b] starts from the failure flag of the reduction, any[b] from 0.
+// tnorm [B] = ||T||_inf; bad[b] starts from the failure flag of the reduction, mark [B][Np] from N, any[b] from 0.
 __global__ __launch_bounds__(256) void td_prepare_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
                                                          double* __restrict__ prep, size_t prep_stride,
                                                          double* __restrict__ tnorm, int2* __restrict__ blk,
-                                                         int32_t* __restrict__ bad, int32_t* __restrict__ any,
-                                                         const int32_t* __restrict__ fail, int N, int Np) {
+                                                         int32_t* __restrict__ bad, int32_t* __restrict__ mark,
+                                                         int32_t* __restrict__ any, const int32_t* __restrict__ fail, int N,
+                                                         int Np) {
   __shared__ double wred[3][4];
   __shared__ u64 cut[MAX_NVIS / 64 + 1];  // bit i: a block starts at row i
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -89,6 +90,7 @@ __global__ __launch_bounds__(256) void td_prepare_kernel(const double* __restric
     m = (i & 63) == 63 ? 0 : cut[w] & (~0ull << ((i & 63) + 1));
     while (m == 0) m = cut[++w];
     blk[(size_t)b * Np + i] = int2{s, min(64 * w + __builtin_ctzll(m), N)};
+    mark[(size_t)b * Np + i] = N;
   }
   if (tid == 0) {
     tnorm[b] = tn;
@@ -592,13 +594,14 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
 // ---- close eigenvalues inside one block -----------------------------------------------------------------
 // The vectors of one block are computed independently of each other.  A run is a set of neighbouring slots of one block,
 // each closer than 1e-10 ||T|| to the next; vectors of different runs are orthogonal to about eps / 1e-10 and are left as they
-// are.  td_pairs_kernel compares every two vectors of a run; where two are not orthogonal to what float32 vectors can be
-// (T is not graded there, or the eigenvalues agree to their last bits), td_orthogonalise_kernel orthogonalises the whole run:
-// comparing neighbours only, or mending single slots, leaves pairs further apart as they were (up to 7e-5 in groups of
-// four).  Eigenvalues that count as zero (below the resolution of the reduction) get weight 0 in Eq. 3-6: their vectors are
-// left as they are, however many of them there are (the null space of a rank-deficient matrix).
+// are.  td_pairs_kernel compares every two vectors of a run; where two are not orthogonal to 1e-6 (T is not graded there, or
+// the eigenvalues agree to their last bits), td_orthogonalise_kernel orthogonalises all from the one to the other: comparing
+// neighbours only, or mending single slots, leaves pairs further apart as they were (up to 7e-5 in groups of four).  The rest of
+// the run, hundreds of vectors where rows have been averaged by attention, came out orthogonal and stays.  Eigenvalues that
+// count as zero (below the resolution of the reduction) get weight 0 in Eq. 3-6: their vectors are left as they are, however
+// many of them there are (the null space of a rank-deficient matrix).
 constexpr double TD_CLOSE = 1e-10;             // of ||T||
-constexpr double TD_ORTHOGONAL = 4.0 / (1 << 24);  // largest scalar product of two unit vectors that passes
+constexpr float TD_ORTHOGONAL = 1e-6f;         // largest scalar product of two unit vectors that passes
 __device__ inline double td_zero_floor(double tn) { return tn > 0.0 ? 8.0 * TD_EPS * tn : DBL_MAX; }  // (every eigenvalue of an all-zero matrix is zero)
 // slot k belongs to the run of slot k - 1
 __device__ inline bool td_close(const double* lb, const int2* bb, double tn, int k, int N) {
@@ -606,95 +609,110 @@ __device__ inline bool td_close(const double* lb, const int2* bb, double tn, int
   return k > 0 && k < N && bb[k].x == bb[k - 1].x && lb[k] - lb[k - 1] <= TD_CLOSE * tn && lb[k] > zero && lb[k - 1] > zero;
 }
 
-// One workgroup per 64 slots, against these and (a run may be long) the tiles of 64 before them.  mark [B][Np] is written for
-// every slot: 1 if an earlier vector of its run is not orthogonal to it; any [B] collects.
+// One workgroup per two tiles of 64 slots, the first not before the second; most find no run that reaches from one to the
+// other and end.  (Rows that attention has averaged have hundreds of eigenvalues below 1e-10 ||T||: with one workgroup per
+// tile and all tiles before it, on the vector units, 227 us for four images of 701 tokens and 473 for two of 1499.)  The
+// vectors are read as operands of the float32 matrix cores, at unit length: the products are off by a few 2^-24.
+// mark [B][Np], N before, becomes the first slot of the run whose vector is not orthogonal to that of the slot (which need not
+// be looked at where td_twisted_kernel found no vector); any [B] collects.
+typedef __attribute__((ext_vector_type(4))) float f4;
 __global__ __launch_bounds__(256) void td_pairs_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
                                                        const double* __restrict__ tnorm, const float* __restrict__ W,
                                                        const double* __restrict__ rn, int32_t* __restrict__ mark,
                                                        int32_t* __restrict__ any, int N, int Np) {
-  constexpr int CH = 32;  // rows at a time
-  __shared__ float wk[CH][68], wj[CH][68];
-  __shared__ int start[64];  // first slot of the run of slot 64 blockIdx.x + i
-  __shared__ int hit[64];
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k0 = blockIdx.x * 64;
+  constexpr int ST = 8;      // steps of four rows in flight
+  __shared__ int start[64];  // the first slot, of this run of slot k0 + i, that lies in the second tile or behind it
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tj = blockIdx.x, ti = 0;
+  while (tj >= ti + 1) { tj -= ti + 1; ti++; }
+  const int k0 = 64 * ti, j0 = 64 * tj;
   const double* lb = lam + (size_t)b * Np;
   const int2* bb = blk + (size_t)b * Np;
   const double* rb = rn + (size_t)b * Np;
   const double tn = tnorm[b];
   const u64 cl = __ballot(td_close(lb, bb, tn, k0 + lane, N));  // the same in all four wavefronts
-  if (cl == 0) {
-    if (wave == 0 && k0 + lane < N) mark[(size_t)b * Np + k0 + lane] = 0;
-    return;
+  if (cl == 0) return;
+  int before = k0;
+  if (ti != tj) {  // does the run of slot k0 begin in the second tile or before it?
+    if (!(cl & 1)) return;
+    for (int t = k0 - 64; t > j0; t -= 64)
+      if (~__ballot(td_close(lb, bb, tn, t + lane, N))) return;
+    const u64 open = ~__ballot(td_close(lb, bb, tn, j0 + lane, N));
+    before = open ? j0 + 63 - __builtin_clzll(open) : j0;
   }
-  int before = k0;  // where the run of slot k0 begins (slot 0 is close to nothing)
-  if (cl & 1)
-    for (int t = k0 - 64;; t -= 64) {
-      const u64 open = ~__ballot(td_close(lb, bb, tn, t + lane, N));
-      before = t;
-      if (open) { before = t + 63 - __builtin_clzll(open); break; }
-      if (t == 0) break;
-    }
   if (wave == 0) {
     const u64 open = ~cl & (~0ull >> (63 - lane));
     start[lane] = open ? k0 + 63 - __builtin_clzll(open) : before;
-    hit[lane] = 0;
-  }
-  const float* Wb = W + (size_t)b * Np * Np;
-  const int tx = tid & 15, ty = tid >> 4;  // slots 4 ty + a against 4 tx + c
-  for (int j0 = k0; j0 + 63 >= before && j0 >= 0; j0 -= 64) {
-    double dot[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-      for (int c = 0; c < 4; c++) dot[a][c] = 0.0;
-    for (int i0 = 0; i0 < N; i0 += CH) {  // (a vector is zero outside its block)
-      __syncthreads();
-      for (int r = wave; r < CH; r += 4) {
-        const bool in = i0 + r < N;
-        wk[r][lane] = in ? Wb[(size_t)(i0 + r) * Np + k0 + lane] : 0.f;
-        wj[r][lane] = in ? Wb[(size_t)(i0 + r) * Np + j0 + lane] : 0.f;
-      }
-      __syncthreads();
-#pragma unroll 4
-      for (int r = 0; r < CH; r++) {
-        double x[4], y[4];
-#pragma unroll
-        for (int a = 0; a < 4; a++) {
-          x[a] = (double)wk[r][4 * ty + a];
-          y[a] = (double)wj[r][4 * tx + a];
-        }
-#pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-          for (int c = 0; c < 4; c++) dot[a][c] = fma(x[a], y[c], dot[a][c]);
-      }
-    }
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-      for (int c = 0; c < 4; c++) {
-        const int k = k0 + 4 * ty + a, j = j0 + 4 * tx + c;
-        if (k < N && j < k && j >= start[4 * ty + a] && !(fabs(dot[a][c]) * rb[k] * rb[j] <= TD_ORTHOGONAL)) hit[4 * ty + a] = 1;
-      }
   }
   __syncthreads();
-  if (wave == 0 && k0 + lane < N) {
-    mark[(size_t)b * Np + k0 + lane] = hit[lane];
-    if (hit[lane]) atomicOr(&any[b], 1);
+  // a wavefront compares 32 slots of the first tile with 32 of the second
+  const int kw = 32 * (wave >> 1), ka = k0 + kw, ja = j0 + 32 * (wave & 1), l31 = lane & 31;
+  if (!__any(ka + l31 < N && ja < ka + l31 && start[kw + l31] <= ja + 31)) return;
+  const int l15 = lane & 15, q4 = lane >> 4;
+  const int r0 = bb[j0].x, r1 = bb[min(k0 + 63, N - 1)].y;  // rows of the blocks that meet here (a vector is zero outside its own)
+  const float* Wb = W + (size_t)b * Np * Np;
+  const float* src[4] = {Wb + ka + l15, Wb + ka + 16 + l15, Wb + ja + l15, Wb + ja + 16 + l15};
+  float unit[4];
+#pragma unroll
+  for (int u = 0; u < 4; u++) unit[u] = (float)rb[min((u < 2 ? ka : ja) + 16 * (u & 1) + l15, N - 1)];
+  f4 acc[2][2];
+#pragma unroll
+  for (int x = 0; x < 2; x++)
+#pragma unroll
+    for (int y = 0; y < 2; y++) acc[x][y] = f4{0.f, 0.f, 0.f, 0.f};
+  float cur[ST][4], nxt[ST][4];
+  auto load = [&](int r, float (*d)[4]) {
+#pragma unroll
+    for (int t = 0; t < ST; t++)
+#pragma unroll
+      for (int u = 0; u < 4; u++) d[t][u] = src[u][(size_t)min(r + 4 * t + q4, r1 - 1) * Np];
+  };
+  load(r0, cur);
+  for (int r = r0; r < r1; r += 4 * ST) {
+    load(r + 4 * ST, nxt);
+#pragma unroll
+    for (int t = 0; t < ST; t++) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) v[u] = r + 4 * t + q4 < r1 ? cur[t][u] * unit[u] : 0.f;
+#pragma unroll
+      for (int x = 0; x < 2; x++)
+#pragma unroll
+        for (int y = 0; y < 2; y++) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[x], v[2 + y], acc[x][y], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < ST; t++)
+#pragma unroll
+      for (int u = 0; u < 4; u++) cur[t][u] = nxt[t][u];
   }
+  bool found = false;
+#pragma unroll
+  for (int x = 0; x < 2; x++)
+#pragma unroll
+    for (int y = 0; y < 2; y++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const int i = 16 * x + 4 * q4 + e, k = ka + i, j = ja + 16 * y + l15;
+        if (k < N && j < k && j >= start[kw + i] && !(fabsf(acc[x][y][e]) <= TD_ORTHOGONAL) && rb[k] > 0.0 && rb[j] > 0.0) {
+          atomicMin(&mark[(size_t)b * Np + k], j);
+          found = true;
+        }
+      }
+  if (__any(found) && lane == 0) atomicOr(&any[b], 1);
 }
 
-// The runs that hold a marked slot (few calls have one), a workgroup for those that begin in its TO_SLOTS slots: every vector of a
-// run is orthogonalised, in float64 and twice, against the earlier ones.  Where less than a tenth of a vector is left (two
-// eigenvalues that agree to their last bits may come out with one vector), or td_twisted_kernel found none, it is made anew by
-// inverse iteration: a vector of no particular direction, orthogonal to the earlier ones of the run, is multiplied by
-// (T - lambda)^-1 and made orthogonal again, three times.  lambda is taken 64 eps ||T|| off the eigenvalue, which multiplies all
-// that agree with it alike (at the eigenvalue itself, one of them comes out again and again, however much of it the
-// earlier vectors hold) and what lies outside the run by 1.4e-4 of that.  An image for which this fails (T is not finite) gets
-// bad[b], and the caller's info turns negative.
+// What td_pairs_kernel and td_twisted_kernel have marked (few calls have any), a workgroup for the runs that begin in its
+// TO_SLOTS slots.  Slots from a marked one back to its mark, and those that overlap, form a cluster: every vector of it is
+// orthogonalised, in float64 and twice, against the earlier ones.  Where less than a tenth of a vector is left (two eigenvalues
+// that agree to their last bits may come out with one vector), or there was none, it is made anew by inverse iteration: a
+// vector of no particular direction is made orthogonal to the others of the run (but those of the cluster that are still to
+// come), multiplied by (T - lambda)^-1 and made orthogonal again, three times.  lambda is taken 64 eps ||T|| off the eigenvalue,
+// which multiplies all that agree with it alike (at the eigenvalue itself, one of them comes out again and again, however much
+// of it the earlier vectors hold) and what lies outside the run by 1.4e-4 of that.  An image for which this fails (T is not
+// finite) gets bad[b], and the caller's info turns negative.
 constexpr int TO_THREADS = 512, TO_WAVES = TO_THREADS / 64;
 constexpr int TO_SLOTS = 16;  // of a workgroup (288 pairs in one image of 577 tokens: a chain of 0.4 ms each)
-static size_t td_orthogonalise_lds(int N) { return (size_t)N * 5 * 8 + (TO_WAVES + 1) * 64 * 8 + round_up(N, 16); }
+static size_t td_orthogonalise_lds(int N) { return (size_t)N * 5 * 8 + (TO_WAVES + 1) * 64 * 8 + round_up(N, 16) + (size_t)N * 4; }
 
 __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
                                                                       const double* __restrict__ lam, const int2* __restrict__ blk,
@@ -711,7 +729,8 @@ __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const doub
   double* pl = pv + N;                             // [N] multipliers,
   double* part = pl + N;                           // [TO_WAVES][64]
   double* coef = part + TO_WAVES * 64;             // [64]
-  uint8_t* sw = reinterpret_cast<uint8_t*>(coef + 64);  // [N] 1: rows i and i + 1 have changed places
+  int* low = reinterpret_cast<int*>(coef + 64);    // [N] the smallest mark of slot i and all behind it
+  uint8_t* sw = reinterpret_cast<uint8_t*>(low + N);  // [N] 1: rows i and i + 1 have changed places
   __shared__ double wsum[TO_WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* db = dvec + (size_t)b * Np;
@@ -750,13 +769,13 @@ __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const doub
       if (wave == 0) {
         double t = 0.0;
         for (int q = 0; q < TO_WAVES; q++) t += part[q * 64 + lane];
-        coef[lane] = lane < cnt ? t * rb[jl] * rb[jl] : 0.0;  // column j has norm 1 / rb[j]
+        coef[lane] = lane < cnt && rb[jl] > 0.0 ? t * rb[jl] * rb[jl] : 0.0;  // column j has norm 1 / rb[j], or is none (0)
       }
       __syncthreads();
       for (int i = tid; i < n; i += TO_THREADS) {
         const float* row = Wb + (size_t)(s + i) * Np + j;
         double v2 = x[i];
-        for (int c = 0; c < cnt; c++) v2 = fma(-coef[c], (double)row[c], v2);
+        for (int c = 0; c < cnt; c++) v2 = coef[c] != 0.0 ? fma(-coef[c], (double)row[c], v2) : v2;
         x[i] = v2;
       }
     }
@@ -799,65 +818,90 @@ __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const doub
     }
   };
 
-  for (int first = blockIdx.x * TO_SLOTS; first < min(N, (int)(blockIdx.x + 1) * TO_SLOTS); first++) {
-    if (td_close(lb, bb, tn, first, N)) continue;  // (uniform, as all that follows)
-    int end = first + 1;
-    bool marked = false;
-    const bool lost = rb[first] == 0.0;
-    for (; td_close(lb, bb, tn, end, N); end++) marked = marked || mb[end];  // (a slot without a vector is marked)
-    const int s = bb[first].x, n = bb[first].y - s;
-    if (lost && !(lb[first] > td_zero_floor(tn))) {  // its weight is zero
-      for (int i = tid; i < n; i += TO_THREADS) Wb[(size_t)(s + i) * Np + first] = 0.f;
+  // low: each thread its own stretch from the back, then what lies behind the stretch (part as 512 ints)
+  {
+    int* tail = reinterpret_cast<int*>(part);
+    const int per = (N + TO_THREADS - 1) / TO_THREADS, i0 = min(N, tid * per), i1 = min(N, i0 + per);
+    int m = N;
+    for (int i = i1 - 1; i >= i0; i--) low[i] = m = min(m, mb[i]);
+    tail[tid] = m;
+    __syncthreads();
+    m = N;
+    for (int t = tid + 1; t < TO_THREADS; t++) m = min(m, tail[t]);
+    for (int i = i0; i < i1; i++) low[i] = min(low[i], m);
+    __syncthreads();
+  }
+
+  for (int begin = blockIdx.x * TO_SLOTS; begin < min(N, (int)(blockIdx.x + 1) * TO_SLOTS); begin++) {
+    if (td_close(lb, bb, tn, begin, N)) continue;  // (uniform, as all that follows)
+    const int s = bb[begin].x, n = bb[begin].y - s;
+    if (rb[begin] == 0.0 && !(lb[begin] > td_zero_floor(tn))) {  // (a run of its own) its weight is zero
+      for (int i = tid; i < n; i += TO_THREADS) Wb[(size_t)(s + i) * Np + begin] = 0.f;
       continue;
     }
-    for (int k = lost ? first : first + 1; k < (marked ? end : lost ? first + 1 : first); k++) {
-      const double r = rb[k];
-      __syncthreads();
-      for (int i = tid; i < n; i += TO_THREADS) x[i] = (double)Wb[(size_t)(s + i) * Np + k] * r;
-      __syncthreads();
-      project(first, k, s, n);
-      project(first, k, s, n);
-      double left = norm2(n);
-      if (!(left >= 0.01)) {
-        if (tid == 0) factor(s, n, lb[k] + 64.0 * tiny);
-        for (int i = tid; i < n; i += TO_THREADS) {
-          uint32_t h = (uint32_t)(i + 1) * 0x9e3779b1u ^ (uint32_t)(k + 1) * 0x85ebca6bu;
-          h = (h ^ (h >> 15)) * 0x2c1b3c6du;
-          x[i] = (double)(int32_t)(h ^ (h >> 13)) * 0x1p-31;
-        }
-        __syncthreads();
-        project(first, k, s, n);
-        bool ok = false;
-        for (int it = 0; it < 6 && !ok; it++) {
-          scale(n, 1.0 / sqrt(norm2(n)));
-          if (tid == 0) solve(n);
-          const double y2 = norm2(n);
-          if (!(y2 > 0.0 && y2 < DBL_MAX)) break;
-          scale(n, 1.0 / sqrt(y2));
+    int stop = begin + 1;  // end of the run
+    while (td_close(lb, bb, tn, stop, N)) stop++;
+    for (int first = begin, end; first < stop; first = end) {
+      end = first + 1;  // end of the cluster
+      while (end < stop && low[end] < end) end++;
+      for (int k = first; k < end; k++) {
+        const double r = rb[k];
+        if (k == first && r > 0.0) continue;
+        double left = 0.0;
+        if (r > 0.0) {
+          __syncthreads();
+          for (int i = tid; i < n; i += TO_THREADS) x[i] = (double)Wb[(size_t)(s + i) * Np + k] * r;
+          __syncthreads();
           project(first, k, s, n);
           project(first, k, s, n);
           left = norm2(n);
-          ok = it > 1 && left >= 0.25;
         }
-        if (!ok) {
-          if (tid == 0) {
-            bad[b] = 1;
-            rb[k] = 0.0;
+        if (!(left >= 0.01)) {
+          __syncthreads();
+          if (tid == 0) factor(s, n, lb[k] + 64.0 * tiny);
+          for (int i = tid; i < n; i += TO_THREADS) {
+            uint32_t h = (uint32_t)(i + 1) * 0x9e3779b1u ^ (uint32_t)(k + 1) * 0x85ebca6bu;
+            h = (h ^ (h >> 15)) * 0x2c1b3c6du;
+            x[i] = (double)(int32_t)(h ^ (h >> 13)) * 0x1p-31;
           }
           __syncthreads();
-          continue;
+          auto others = [&]() {
+            project(begin, k, s, n);
+            project(end, stop, s, n);
+          };
+          others();
+          bool ok = false;
+          for (int it = 0; it < 6 && !ok; it++) {
+            scale(n, 1.0 / sqrt(norm2(n)));
+            if (tid == 0) solve(n);
+            const double y2 = norm2(n);
+            if (!(y2 > 0.0 && y2 < DBL_MAX)) break;
+            scale(n, 1.0 / sqrt(y2));
+            others();
+            others();
+            left = norm2(n);
+            ok = it > 1 && left >= 0.25;
+          }
+          if (!ok) {
+            if (tid == 0) {
+              bad[b] = 1;
+              rb[k] = 0.0;
+            }
+            __syncthreads();
+            continue;
+          }
         }
+        const double f = 1.0 / sqrt(left);
+        __syncthreads();
+        for (int i = tid; i < n; i += TO_THREADS) {
+          const float y = (float)(x[i] * f);
+          Wb[(size_t)(s + i) * Np + k] = y;
+          x[i] = (double)y;
+        }
+        const double v = norm2(n);
+        if (tid == 0) rb[k] = 1.0 / sqrt(v);
+        __syncthreads();
       }
-      const double f = 1.0 / sqrt(left);
-      __syncthreads();
-      for (int i = tid; i < n; i += TO_THREADS) {
-        const float y = (float)(x[i] * f);
-        Wb[(size_t)(s + i) * Np + k] = y;
-        x[i] = (double)y;
-      }
-      const double v = norm2(n);
-      if (tid == 0) rb[k] = 1.0 / sqrt(v);
-      __syncthreads();
     }
   }
 }
@@ -932,7 +976,6 @@ __global__ __launch_bounds__(256) void td_weights_kernel(const double* __restric
 // U = H_0 H_1 ... H_{N-2} W, sixteen reflectors at a time in compact WY form (the scheme of LAPACK's
 // dlarft/dlarfb): H_j0 ... H_j0+15 = I - V T V^T with V the 16 reflectors and T upper triangular,
 //     T[c][c] = tau_c,   T[0:c, c] = -tau_c T[0:c, 0:c] (V[:, 0:c]^T v_c).
-typedef __attribute__((ext_vector_type(4))) float f4;
 constexpr int BT_K = 16;  // reflectors per block
 
 // T of every block of 16 reflectors, one workgroup per (block, image).  S = V^T V on the matrix cores: a lane's element
@@ -1121,7 +1164,7 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
   // The image's part of `scratch` (Np^2 doubles) holds the scaled copy of T first, the pivots of the factorisations later.
   const size_t stride = (size_t)Np * Np;
   int32_t* any = mark + (size_t)B * Np;  // (one word per image behind the marks of the group's images)
-  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, scratch, stride, tnorm, blk, bad, any, fail, N, Np)));
+  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, scratch, stride, tnorm, blk, bad, mark, any, fail, N, Np)));
   // lanes per eigenvalue: as many as keep the launch near one wavefront per SIMD (by the size of the whole call, so
   // that an image's result does not depend on how the call is cut into stream groups)
   int gs = 0;
@@ -1141,7 +1184,8 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
       return TC_ERR_HIP;
     TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, any, N, Np)));
   }
-  TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3((N + 63) / 64, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, N, Np)));
+  const int nt = (N + 63) / 64;
+  TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3(nt * (nt + 1) / 2, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, N, Np)));
   {
     const size_t shm = td_orthogonalise_lds(N);
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_orthogonalise_kernel),
