@@ -61,9 +61,12 @@ __device__ __forceinline__ void fmac_bcast_neg(double& d, double row, double c) 
   asm("v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(row), "v"(c), "n"(N));
 }
 
+// The lowest bit makes room for the tag by rounding to nearest even, and a reader clears the tag: zero arrives as zero.
 __device__ __forceinline__ void publish(u64* p, double v, unsigned tag) {
-  __hip_atomic_store(p, ((u64)__double_as_longlong(v) & ~1ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const u64 y = (u64)__double_as_longlong(v);
+  __hip_atomic_store(p, ((y + ((y >> 1) & 1)) & ~1ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ double received(u64 y) { return __longlong_as_double((long long)(y & ~1ull)); }
 __device__ __forceinline__ u64 peek(const u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -479,9 +482,8 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
             if (ok) break;
             if (tr_give_up(spin, fail + img)) { bad = true; break; }
           }
-          p[u] = (__longlong_as_double((long long)y[0]) + __longlong_as_double((long long)y[1])) +
-                 (__longlong_as_double((long long)y[2]) + __longlong_as_double((long long)y[3]));
-          col[u] = __longlong_as_double((long long)y[4]);
+          p[u] = (received(y[0]) + received(y[1])) + (received(y[2]) + received(y[3]));
+          col[u] = received(y[4]);
         }
       }
     } else {
@@ -518,7 +520,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         }
         double s = 0.0;
 #pragma unroll
-        for (int q = 0; q < PER; q++) s += 4 * q + (tj & 3) < NQ ? __longlong_as_double((long long)y[q]) : 0.0;
+        for (int q = 0; q < PER; q++) s += 4 * q + (tj & 3) < NQ ? received(y[q]) : 0.0;
         s += dpp_f64<0xB1>(s);  // the quad
         s += dpp_f64<0x4E>(s);
         if ((tj & 3) == 0) publish(YT + ft, s, tag);
@@ -535,7 +537,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
           for (int u = 0; u < E; u++) {
             ok &= (y[u] & 1) == tag;
-            dst[u] = __longlong_as_double((long long)y[u]);
+            dst[u] = received(y[u]);
           }
           if (ok) break;
           if (tr_give_up(spin, fail + img)) { bad = true; break; }

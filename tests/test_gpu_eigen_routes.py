@@ -114,3 +114,19 @@ def test_calls_with_large_groups_on_three_streams_at_once():
     for c, want in zip(calls, alone):
         for x, y in zip(want, c.outputs()):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n", [64, 257, 576, 577, 1153])
+def test_an_all_zero_image_scores_zero(n):
+    # the exchanged values are zeros too
+    tc = _tc()
+    O = _rows(3, n, 512, n)
+    O[1] = 0
+    call = Call(tc, _params(tc, 3, n, 4), O.cuda())
+    call()
+    torch.cuda.synchronize()
+    assert call.info.cpu().tolist() == [1, 1, 1]
+    assert not call.C[1].any() and not call.sigma[1].any() and not call.E[1].any()
+    for b in (0, 2):
+        s, c = _reference(O[b])
+        assert float((call.C[b].double().cpu() - c).abs().max() / c.abs().max()) < 2e-5, b
