@@ -84,12 +84,25 @@ int make_plan(const tc_params* p, Plan* pl) {
     q.off_td_mark = take(B * (Np + 1) * 4);    // per slot: vector to be orthogonalised; one word per image
     q.off_td_Cpart = take(B * nstrip * Np * 8);
     q.off_td_Tf = take(B * ((N + 15) / 16) * 256 * 4);   // T factors of the blocks of 16 reflectors
-    q.td_sync_bytes = tridiag_sync_bytes(q.N, q.batch_call);
+    q.td_sync_bytes = tridiag_sync_bytes(q.N);
     q.off_td_sync = take(B * q.td_sync_bytes);           // exchange memory of the reduction
     q.off_td_fail = take(B * 4);
   }
-  q.off_gpart = take(B * gram_part_bytes(q));
+  q.off_gpart = take(gram_reserve_bytes(q));
   q.total = off > 0 ? off : 256;
+  // A workspace also serves calls with fewer tokens (tc_info_rank on a subset of rows is one): just above the largest
+  // reduction the tridiagonal route needs more than the iteration.
+  if (p->eig_method == TC_EIG_AUTO && p->eig_dtype == TC_EIG_F64 && p->n_vis > tridiag_most()) {
+    tc_params r = *p;
+    r.n_vis = tridiag_most();
+    if (r.k_prune > r.n_vis) r.k_prune = r.n_vis;
+    const int most = r.k_prune - r.k_prune / 2;  // merged tokens
+    r.k_final = r.k_prune - (q.m < most ? q.m : most);
+    Plan smaller;
+    const int rc = make_plan(&r, &smaller);
+    if (rc != TC_OK) return rc;
+    if (smaller.total > q.total) q.total = smaller.total;
+  }
   return TC_OK;
 }
 

@@ -221,6 +221,15 @@ int gram_splits(const Plan& pl) {
   return s;
 }
 size_t gram_part_bytes(const Plan& pl) { return part_bytes(pl, gram_splits(pl)); }
+// What a plan sets aside for the parts of all its images.  The parts themselves get fewer where another tile or image takes
+// away a workgroup per tile; a workspace must not, since a smaller call has to fit it: an image has at most 3 MiB and at most as
+// many parts as D allows, a call at most a part for each of its 768 workgroups.
+size_t gram_reserve_bytes(const Plan& pl) {
+  const int most = pl.D / GK / 8 < 8 ? pl.D / GK / 8 : 8;
+  const size_t image = part_bytes(pl, most), lim = (size_t)3 << 20, call = (size_t)768 * 4096 * 8;
+  const size_t all = (image < lim ? image : lim) * pl.B;
+  return all < call ? all : call;
+}
 
 template <typename TIn, typename TOut>
 static void run_gram(const Plan& pl, const void* O, void* G, double* part, hipStream_t st) {

@@ -79,7 +79,8 @@ inline int check_ws(const Plan& pl, const void* ws, size_t ws_bytes) {
 // ---- stage launchers (each returns a tc_status; all work is enqueued on `st`) ----------
 int launch_attention(const Plan& pl, int dtype, int causal, const void* Q, const void* K, const void* V, void* O,
                      float* S, float* Spart, hipStream_t st);
-size_t gram_part_bytes(const Plan& pl);  // partial sums of one image
+size_t gram_part_bytes(const Plan& pl);     // partial sums of one image
+size_t gram_reserve_bytes(const Plan& pl);  // room for those of the call
 int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, double* part, hipStream_t st);
 int launch_jacobi(const Plan& pl, int eig_dtype, void* G, void* U /* nullptr: eigenvalues only */, void* R,
                   double* offpart, EigState* state, hipStream_t st);
@@ -92,7 +93,8 @@ int launch_combine(const Plan& pl, const float* C_ws, const float* S, float lamb
 // direct eigensolver (tridiag.hip, tdeig.hip)
 bool tridiag_fits(int N);                     // the reduction takes N tokens
 bool tridiag_allowed(int N, hipStream_t st);  // ... in a call on this stream (not while it is captured, for large N)
-size_t tridiag_sync_bytes(int N, int B);      // exchange memory of one image (B: images of the call)
+size_t tridiag_sync_bytes(int N);             // exchange memory of one image
+int tridiag_most();                           // the largest N that fits
 int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float* tauv, float* Vc, void* sync, size_t sync_bytes,
                    int32_t* fail, hipStream_t st);
 int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, const float* tauv, float* Vc,

@@ -683,10 +683,16 @@ static int tr_phases(int N, int B, TrPhase* out, size_t* words) {
 
 bool tridiag_fits(int N) { return N <= TR_FRAMES[TR_SIZES - 1].F; }
 
-size_t tridiag_sync_bytes(int N, int B) {  // exchange memory of one image
-  TrPhase ph[TR_SIZES];
-  size_t words;
-  tr_phases(N, B, ph, &words);
+int tridiag_most() { return TR_FRAMES[TR_SIZES - 1].F; }
+
+// Exchange memory of one image: that of every frame that may take part (which do depends on the number of images; the size of
+// a workspace must not fall when that or N grows).
+size_t tridiag_sync_bytes(int N) {
+  size_t words = 0;
+  for (int size = 0; size < TR_SIZES; size++) {
+    words += TR_FRAMES[size].words;
+    if (TR_FRAMES[size].F >= N) break;
+  }
   return align256(words * 8 + 8);
 }
 

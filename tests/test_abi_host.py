@@ -52,6 +52,28 @@ def test_workspace_size_and_status_strings():
     assert len({tc.tc_status_string(-i) for i in range(8)}) == 8
 
 
+@pytest.mark.parametrize("heads,head_dim,kw", [(32, 128, {}), (1, 64, {}), (4, 128, {}), (16, 64, {"eig_dtype": 1}),
+                                               (32, 128, {"eig_method": 1}), (8, 128, {"dtype": 0})])
+def test_a_workspace_serves_every_smaller_call(heads, head_dim, kw):
+    # fewer tokens (tc_info_rank plans for the rows it is given) or fewer images never need more bytes: over all tiles of 64 tokens
+    # with the frames of the reduction (576 k) and its end (3456) among them
+    tc = _binding()
+
+    def need(batch, n, k=1):
+        args = dict(dtype=tc.TC_BF16, lam=0.5, norm_mode=1)
+        args.update(kw)
+        return tc.tc_workspace_bytes(tc.make_params(batch=batch, seq_len=n + 64, vis_start=36, n_vis=n, n_heads=heads, head_dim=head_dim,
+                                                    hidden_dim=heads * head_dim, k_prune=k, k_final=(k + 1) // 2, **args))
+
+    tokens = sorted({n for t in range(1, 65) for n in (64 * t - 63, 64 * t - 1, 64 * t)})
+    for batch in (1, 2, 3, 5, 8, 20, 64):
+        sizes = [need(batch, n, max(1, n // 3)) for n in tokens]
+        assert all(a > 0 and a <= b for a, b in zip(sizes, sizes[1:])), batch
+    for n in (64, 100, 256, 257, 576, 577, 832, 1153, 2880, 3456, 3457, 4096):
+        sizes = [need(batch, n, n // 2) for batch in range(1, 260)]
+        assert all(a > 0 and a <= b for a, b in zip(sizes, sizes[1:])), n
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("n_vis", 0, -2), ("n_vis", 5000, -2), ("head_dim", 96, -2), ("hidden_dim", 100, -2), ("vis_start", 600, -2),
     ("dtype", 7, -3), ("eig_dtype", 3, -3), ("lambda_", 1.5, -4), ("lambda_", -0.1, -4), ("k_final", 0, -4),
