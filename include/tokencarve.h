@@ -15,8 +15,10 @@
  *     memory, frees none and keeps no pointer after the call returns.  The only
  *     state it keeps is up to three helper streams per device, created the first
  *     time a batch is split into stream groups (see tc_params.stream_groups) and
- *     kept until the process ends; their work is ordered after what is already on
- *     `stream` and `stream` waits for it before the next stage.
+ *     kept until the process ends (their work is ordered after what is already on
+ *     `stream` and `stream` waits for it before the next stage), and an event per
+ *     device, by which reductions of more than 576 tokens that are enqueued on
+ *     different streams run one after the other.
  *   - All scratch memory comes from `ws` (`ws_bytes` >= tc_workspace_bytes(p)).
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *     default stream) and the call returns without waiting for it.  Two calls may
@@ -70,7 +72,11 @@ typedef enum { TC_EIG_F64 = 0, TC_EIG_F32 = 1 } tc_eig_dtype;
                        twisted factorisations, back-transformation; float64 only, n_vis <= 1024;
    TC_EIG_JACOBI       two-sided block Jacobi iteration (any n_vis, float64 or float32);
    TC_EIG_AUTO         the tridiagonal route for float64 and n_vis <= 3456 (1728 while the stream is
-                       being captured into a graph), else Jacobi */
+                       being captured into a graph), else Jacobi; less on a partition of the GPU with fewer than 256
+                       compute units (1152 on one with 32).
+   Above 256 tokens the tridiagonal route shares an image between workgroups that must be resident together.  Where the
+   compute units are taken (by other processes, say) for a quarter of a second, the image is reduced by one workgroup
+   instead: the result is the same but for rounding, and late (18 ms for 576 tokens, 2.6 s for 2880). */
 typedef enum { TC_EIG_AUTO = 0, TC_EIG_JACOBI = 1, TC_EIG_TRIDIAGONAL = 2 } tc_eig_method;
 
 typedef struct {
@@ -134,7 +140,7 @@ TC_API int tc_attn_output(const tc_params* p, const void* Q, const void* K, cons
  *                             (1 for an all-zero matrix, which needs none), negated if the tolerance was
  *                             not reached within jacobi_max_sweeps.  Tridiagonal method: 1, or -1 if an
  *                             eigenvector could not be found (O is not finite) or the workgroups of the
- *                             reduction waited for each other in vain.  Optional
+ *                             reduction lost each other.  Optional
  */
 TC_API int tc_ipgs_score(const tc_params* p, const void* O, const float* attn_score, float* score,
                   float* ics, float* sigma, int32_t* info, void* ws, size_t ws_bytes, void* stream);

@@ -31,21 +31,24 @@
 // Exchange.  Values are published with relaxed agent-scope stores and polled with relaxed agent-scope loads; the lowest
 // mantissa bit of a value carries the parity of its use of the slot (two slots, used in turn), so a value announces
 // itself and no fence or flag is needed.  A slot is written again two columns later, when every workgroup has
-// published the column in between and therefore read this one.  Every wait is bounded (TD_SPIN polls); a workgroup
-// that gives up raises the image's failure flag, its group follows, and the caller reports the image as failed.
-// A group's workgroups have neighbouring ids, so the groups of a launch become resident in order and the first
-// incomplete one is the only one that waits for a compute unit; launches whose groups could block each other when
-// several streams run them at once are kept apart by the host (see tr_in_order).
+// published the column in between and therefore read this one.
+// A group waits for its own members, which must all be resident.  Nothing promises that: the hardware deals a launch to the
+// XCDs by id and every XCD starts its share by itself, other streams, other processes and replays of graphs compete for the
+// compute units.  So the members count themselves in first, and a group that is not complete after a while gives its
+// compute units back before it has written anything; tridiag_alone_kernel then reduces the image by one workgroup.  A
+// group that is complete stays resident and its waits end.  (They are bounded all the same, TD_SPIN polls: a workgroup that gives up
+// raises the image's failure flag, its group follows, and the caller reports the image as failed.)
+// Launches of this library that would strand each other are kept apart by the host (see tr_in_order).
 #include <mutex>
 #include <utility>
 
 #include "tc_internal.h"
+#include "tridiag_frames.h"
 
 namespace tc {
 
 typedef unsigned long long u64;
 
-constexpr int TR_THREADS = 512;
 constexpr int TR_WAVES = TR_THREADS / 64;
 constexpr int TD_SPIN = 1 << 22;  // polls before a wait is given up (seconds; a wait in good order is a microsecond)
 
@@ -75,6 +78,23 @@ __device__ __forceinline__ u64 peek(const u64* p) {
 __device__ __forceinline__ bool tr_give_up(int spin, const int32_t* fail) {
   return spin >= TD_SPIN ||
          ((spin & 1023) == 1023 && __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
+}
+
+// The members of a group count themselves in.  True when the group is not complete after `patience` polls (at once where that
+// is negative): the first member to
+// find that out sets the top bit, which nobody does once the count is whole, so all members decide alike, those
+// too that get their compute unit later.
+__device__ __forceinline__ bool tr_stranded(u64* arrived, u64 P, int patience) {
+  constexpr u64 off = 1ull << 63;
+  if (patience < 0) return true;
+  for (int spin = 0;; spin++) {
+    u64 n = peek(arrived);
+    if (n & off) return true;
+    if (n >= P) return false;
+    if (spin >= patience &&
+        __hip_atomic_compare_exchange_strong(arrived, &n, n | off, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return true;
+  }
 }
 
 // Sums of 8 or 16 values over the 64 lanes by recursive halving (fixed order).  On return lane L holds the total of value
@@ -132,26 +152,6 @@ __device__ __forceinline__ double fast_rsq(double x) {
   return fma(0.5 * r, fma(-x * r, r, 1.0), r);
 }
 
-// Geometry of a frame.
-template <int PC>
-struct TrShape {
-  static constexpr int MODE = PC == 0 ? 0 : PC == 1 ? 1 : 2;
-  static constexpr int PCC = PC < 2 ? 1 : PC;            // column classes of 64
-  static constexpr int PR = PC == 0 ? 1 : 4 * PCC;       // row classes of 8
-  static constexpr int LI = PC == 0 ? 32 : 18;           // rows and columns of a thread
-  static constexpr int LK = PC == 0 ? 4 : 9;
-  static constexpr int NS = 2;                           // rows are worked on in two sets of 16 or 9
-  static constexpr int R = 8 * PR, C = 64 * PCC, RT = C / R;
-  static constexpr int F = C * LK, P = PR * PCC;
-  static constexpr int E = (F + TR_THREADS - 1) / TR_THREADS;  // vector elements of a thread
-  static constexpr int OWN = 64 * LK;                    // columns of a workgroup; it has 8 LI rows
-  // exchange words of one image: two slots of (partials, one set per column sum and row sum; next column; totals)
-  static constexpr size_t WORDS = MODE == 0 ? 0 : MODE == 1 ? (size_t)2 * 5 * F : (size_t)2 * (5 * PCC + 2) * F;
-  static constexpr size_t LDS = (size_t)(4 * (F + F / 32) + 8 * OWN + 16 * LI + 36) * 8 + (size_t)LI * 8 * 16 * 4 + 16;
-  static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
-  static_assert(LI * R == F, "rows and columns must cover the same frame");
-};
-
 // Exchange memory of the launch that follows: cleared, so that no value carries the tag of its first use (1).
 __global__ __launch_bounds__(256) void tridiag_clear_kernel(u64* __restrict__ sync, size_t stride, size_t words,
                                                             int32_t* __restrict__ fail) {
@@ -178,7 +178,7 @@ template <int PC>  // 0: the single-workgroup frame
 __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void tridiag_kernel(
     double* __restrict__ G, int N, int Np, int B, int first, int last, int full, double* __restrict__ dvec,
     double* __restrict__ evec, float* __restrict__ tauv, float* __restrict__ Vc, u64* __restrict__ sync, size_t sync_stride,
-    int32_t* __restrict__ fail) {
+    u64* __restrict__ arrived, int patience, int xcds, int32_t* __restrict__ fail) {
   typedef TrShape<PC> S;
   constexpr int LI = S::LI, LK = S::LK, RT = S::RT, NS = S::NS, SR = S::LI / S::NS, E = S::E, MODE = S::MODE;
   constexpr int PR = S::PR, pc = S::PCC, R = S::R, C = S::C, F = S::F, P = S::P, OWN = S::OWN;
@@ -202,16 +202,19 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   // workgroup -> (image, member): in the four-workgroup frame the members of a group have ids that differ by multiples
-  // of 8 (one XCD, one L2); larger groups are spread over all XCDs anyway
+  // of the number of XCDs (one XCD, one L2); larger groups are spread over all XCDs anyway
   int img, mem;
   if (MODE == 1) {
-    img = (int)(blockIdx.x >> 3) / P * 8 + (blockIdx.x & 7);
-    mem = (int)(blockIdx.x >> 3) % P;
+    const int t = (int)blockIdx.x / xcds;
+    img = t / P * xcds + (int)blockIdx.x % xcds;
+    mem = t % P;
   } else {
     img = blockIdx.x / P;
     mem = blockIdx.x % P;
   }
   if (img >= B) return;
+  if (first > 0 && fail[img] != 0) return;  // (the phase before has not been)
+  if (MODE != 0 && tid == 0) __hip_atomic_fetch_add(arrived + (size_t)img * sync_stride, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int a = mem % PR, b = mem / PR;
   double* A0 = G + (size_t)img * Np * Np;
   double* dout = dvec + (size_t)img * Np;
@@ -236,12 +239,16 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       }
   for (int e = tid; e < 4 * FX; e += TR_THREADS) Va[e] = 0.0;  // the four vectors
   for (int e = tid; e < LI * 8 * 16; e += TR_THREADS) vblk[e] = 0.f;
-  if (tid == 0) *quit = 0;
+  if (tid == 0) *quit = MODE != 0 && tr_stranded(arrived + (size_t)img * sync_stride, P, patience) ? 1 : 0;
 
   // this thread's elements of the vectors: frame rows F - 1 - tid - 512 u, so that the live ones stay in the low threads
   {
     double part = 0.0;
     __syncthreads();  // (X has been cleared)
+    if (MODE != 0 && *quit) {  // uniform; nothing has been written
+      if (tid == 0) __hip_atomic_store(fail + img, 1 + first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
 #pragma unroll
     for (int u = 0; u < E; u++) {
       const int f = F - 1 - tid - TR_THREADS * u;
@@ -624,7 +631,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     __syncthreads();
   }
   if (MODE != 0 && *quit) {
-    if (tid == 0) __hip_atomic_store(fail + img, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_store(fail + img, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
   if (last == N) {
@@ -649,76 +656,137 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       }
 }
 
+// ---- a stranded image -----------------------------------------------------------------------------------------
+// The reduction by one workgroup with the matrix in memory: from the column the stranded phase would have begun with, one
+// pass over the trailing matrix per column (the update with the column before and the product).  It waits for nobody.  Rare,
+// so plain: 18 ms for an image of 576 tokens, 0.12 s for one of 1024, 2.6 s for one of 2880.
+constexpr int AL_THREADS = 1024, AL_WAVES = AL_THREADS / 64;
+static size_t alone_lds(int N) { return (size_t)(4 * N + 2 * AL_WAVES) * 8; }
+
+__global__ __launch_bounds__(AL_THREADS) void tridiag_alone_kernel(double* __restrict__ G, int N, int Np, double* __restrict__ dvec,
+                                                                   double* __restrict__ evec, float* __restrict__ tauv,
+                                                                   float* __restrict__ Vc, int32_t* __restrict__ fail) {
+  const int img = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (fail[img] <= 0) return;
+  const int first = fail[img] - 1;
+  extern __shared__ __attribute__((aligned(16))) unsigned char al_smem[];
+  double* v = reinterpret_cast<double*>(al_smem);  // [N] the reflector (x before it)
+  double* p = v + N;                               // [N] A v
+  double* vo = p + N;                              // [N] reflector and w of the column before
+  double* wo = vo + N;
+  double* red = wo + N;  // [2][AL_WAVES]
+  double* A = G + (size_t)img * Np * Np;
+  float* V = Vc + (size_t)img * Np * Np;
+  // (a hand-over leaves the lower triangle)
+  if (first > 0)
+    for (int r = first + wave; r < N; r += AL_WAVES)
+      for (int c = first + lane; c < r; c += 64) A[(size_t)c * Np + r] = A[(size_t)r * Np + c];
+  for (int i = tid; i < N; i += AL_THREADS) vo[i] = wo[i] = 0.0;
+  auto sum = [&](double x, int which) {
+    x = wave_sum(x);
+    if (lane == 0) red[which * AL_WAVES + wave] = x;
+    __syncthreads();
+    double t = 0.0;
+    for (int q = 0; q < AL_WAVES; q++) t += red[which * AL_WAVES + q];
+    return t;
+  };
+  __syncthreads();
+  for (int j = first; j < N - 1; j++) {
+    const double* row = A + (size_t)j * Np;
+    double n2 = 0.0;
+    for (int i = j + tid; i < N; i += AL_THREADS) {
+      const double x = row[i] - vo[j] * wo[i] - wo[j] * vo[i];
+      v[i] = x;
+      if (i >= j + 2) n2 = fma(x, x, n2);
+    }
+    n2 = sum(n2, 0);
+    const double alpha = v[j + 1];
+    double beta = alpha, tau = 0.0, scal = 0.0;
+    if (n2 > 0.0) {
+      beta = -copysign(sqrt(fma(alpha, alpha, n2)), alpha);
+      tau = (beta - alpha) / beta;
+      scal = 1.0 / (alpha - beta);
+    }
+    if (tid == 0) {
+      dvec[(size_t)img * Np + j] = v[j];
+      evec[(size_t)img * Np + j] = beta;
+      tauv[(size_t)img * Np + j] = (float)tau;
+    }
+    __syncthreads();
+    float* out = V + (size_t)(j >> 4) * Np * 16 + (j & 15);
+    const bool end = j == N - 2;  // (the places behind the last reflector are zero)
+    for (int i = (j & ~15) + tid; i < N; i += AL_THREADS) {
+      const double y = i <= j ? 0.0 : i == j + 1 ? 1.0 : v[i] * scal;
+      v[i] = y;
+      out[(size_t)i * 16] = (float)y;
+      if (end)
+        for (int c = (j & 15) + 1; c < 16; c++) out[(size_t)i * 16 + c - (j & 15)] = 0.f;
+    }
+    __syncthreads();
+    double pv = 0.0;
+    for (int i = j + 1 + wave; i < N; i += AL_WAVES) {
+      double* a = A + (size_t)i * Np;
+      const double vi = vo[i], wi = wo[i];
+      double s = 0.0;
+      for (int k = j + 1 + lane; k < N; k += 64) {
+        const double x = a[k] - vi * wo[k] - wi * vo[k];
+        a[k] = x;
+        s = fma(x, v[k], s);
+      }
+      s = wave_sum(s);
+      if (lane == 0) p[i] = s;
+      pv = fma(s, v[i], pv);
+    }
+    pv = sum(lane == 0 ? pv : 0.0, 1);
+    const double half = 0.5 * tau * tau * pv;
+    for (int i = j + 1 + tid; i < N; i += AL_THREADS) {
+      vo[i] = v[i];
+      wo[i] = tau * p[i] - half * v[i];
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    dvec[(size_t)img * Np + N - 1] = A[(size_t)(N - 1) * Np + N - 1] - 2.0 * vo[N - 1] * wo[N - 1];
+    evec[(size_t)img * Np + N - 1] = 0.0;
+    tauv[(size_t)img * Np + N - 1] = 0.f;
+    fail[img] = 0;
+  }
+}
+
 // ---- host ---------------------------------------------------------------------------------------------------
-struct TrFrame { int mode, F, P; size_t words; };
-constexpr int TR_SIZES = 7;  // frames: 0 the single workgroup, n: PC = n
-static const TrFrame TR_FRAMES[TR_SIZES] = {
-#define TR_ENTRY(PC_) {TrShape<PC_>::MODE, TrShape<PC_>::F, TrShape<PC_>::P, TrShape<PC_>::WORDS}
-    TR_ENTRY(0), TR_ENTRY(1), TR_ENTRY(2), TR_ENTRY(3), TR_ENTRY(4), TR_ENTRY(5), TR_ENTRY(6)
-#undef TR_ENTRY
-};
+}  // namespace tc
 
-// The phases of a reduction: a frame works on the columns it is worth having, then hands the trailing matrix (through G)
-// to a smaller one.  The next frame is the largest that needs fewer exchanges per column or lets more images run
-// at once, so that the launch takes fewer rounds over the 256 compute units.  (Hand-overs lie at multiples of 16
-// columns: the blocks of sixteen reflectors.)
-struct TrPhase { int size, first, last; size_t off; };  // off: where its exchange words start
-static int tr_phases(int N, int B, TrPhase* out, size_t* words) {
-  auto rounds = [&](int s) { const int at_once = 256 / TR_FRAMES[s].P; return (B + at_once - 1) / at_once; };
-  int size = 0, n = 0, first = 0;
-  while (size < TR_SIZES && TR_FRAMES[size].F < N) size++;
-  *words = 0;
-  if (size == TR_SIZES) return 0;
-  while (true) {
-    int next = size - 1;
-    while (next >= 0 && TR_FRAMES[next].mode == TR_FRAMES[size].mode && rounds(next) >= rounds(size)) next--;
-    const int last = next >= 0 ? round_up(N - TR_FRAMES[next].F, 16) : N;
-    out[n++] = TrPhase{size, first, last, *words};
-    *words += TR_FRAMES[size].words;
-    if (next < 0) return n;
-    size = next;
-    first = last;
-  }
-}
+// Polls before a group gives up waiting for its members (a quarter of a second; a round of the largest frame over the chip
+// takes 25 ms).  A variable for the tests, no part of the interface: -n strands the groups from phase n - 1 of a call on.
+constexpr int TR_PATIENCE = 1 << 18;
+extern "C" __attribute__((visibility("default"))) int tc_group_patience = TR_PATIENCE;
 
+namespace tc {
 bool tridiag_fits(int N) { return N <= TR_FRAMES[TR_SIZES - 1].F; }
-
 int tridiag_most() { return TR_FRAMES[TR_SIZES - 1].F; }
+size_t tridiag_sync_bytes(int N) { return align256(tr_sync_words(N) * 8); }
 
-// Exchange memory of one image: that of every frame that may take part (which do depends on the number of images; the size of
-// a workspace must not fall when that or N grows).
-size_t tridiag_sync_bytes(int N) {
-  size_t words = 0;
-  for (int size = 0; size < TR_SIZES; size++) {
-    words += TR_FRAMES[size].words;
-    if (TR_FRAMES[size].F >= N) break;
-  }
-  return align256(words * 8 + 8);
+static int compute_units() {  // of the current device
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  return n;
 }
-
-// A group of workgroups waits for its own members, so launches that run side by side must never hold all 256 compute units
-// with incomplete groups.  A launch leaves at most P - 1 workgroups waiting and a process has four hardware queues:
-// groups of up to TR_FREE = 36 need no order, and one launch of a larger group fits beside three of those
-// (143 + 3 * 35 < 256).  Two launches of larger groups are kept apart by an event.  A launch inside a captured graph cannot
-// be (the graph may be replayed on several streams at once): tridiag_allowed sends such calls to the Jacobi iteration.
-constexpr int TR_FREE = 36;
 
 static bool tr_capturing(hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
 }
 
-bool tridiag_allowed(int N, hipStream_t st) {
-  int size = 0;
-  while (size < TR_SIZES && TR_FRAMES[size].F < N) size++;
-  return size < TR_SIZES && (TR_FRAMES[size].P <= TR_FREE || !tr_capturing(st));
-}
+bool tridiag_allowed(int N, hipStream_t st) { return tr_runs(N, compute_units(), tr_capturing(st)); }
 
+// Two launches of frames that span XCDs, side by side on different streams, can strand each other's groups: an XCD deals out
+// its workgroups by itself, so one may fill with the first launch and another with the second.  An event keeps them apart.
+// (A group of four lies on one XCD: a launch leaves at most three workgroups waiting there.)
 static int tr_in_order(int P, hipStream_t st, bool before) {
   static std::mutex mx;
   static hipEvent_t ev[64];
   static bool used[64];
-  if (P <= TR_FREE) return TC_OK;
+  if (!tr_apart(P) || tr_capturing(st)) return TC_OK;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return TC_ERR_HIP;
   if (before) {
@@ -735,15 +803,15 @@ static int tr_in_order(int P, hipStream_t st, bool before) {
 
 template <int PC>
 static int tr_launch(const Plan& pl, const TrPhase& ph, double* G, double* dvec, double* evec, float* tauv, float* Vc, u64* sync,
-                     size_t stride, int32_t* fail, hipStream_t st) {
+                     size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st) {
   typedef TrShape<PC> S;
   if (S::LDS > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_kernel<PC>),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS) != hipSuccess)
     return TC_ERR_HIP;
-  const int grid = (S::MODE == 1 ? (pl.B + 7) / 8 * 8 : pl.B) * S::P;
+  const int grid = (S::MODE == 1 ? (pl.B + xcds - 1) / xcds * xcds : pl.B) * S::P;
   int rc = tr_in_order(S::P, st, true);
   if (rc != TC_OK) return rc;
-  TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_kernel<PC><<<grid, TR_THREADS, S::LDS, st>>>(G, pl.N, pl.Np, pl.B, ph.first, ph.last, ph.first == 0, dvec, evec, tauv, Vc, sync + ph.off, stride, fail)));
+  TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_kernel<PC><<<grid, TR_THREADS, S::LDS, st>>>(G, pl.N, pl.Np, pl.B, ph.first, ph.last, ph.first == 0, dvec, evec, tauv, Vc, sync + ph.off, stride, arrived, patience, xcds, fail)));
   rc = check_launch();
   const int rc2 = tr_in_order(S::P, st, false);
   return rc != TC_OK ? rc : rc2;
@@ -751,23 +819,32 @@ static int tr_launch(const Plan& pl, const TrPhase& ph, double* G, double* dvec,
 
 int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float* tauv, float* Vc, void* sync, size_t sync_bytes,
                    int32_t* fail, hipStream_t st) {
+  const int cus = compute_units(), xcds = cus >= 64 ? cus / 32 : 1;  // (32 compute units each)
   TrPhase ph[TR_SIZES];
   size_t words;
-  const int n = tr_phases(pl.N, pl.batch_call, ph, &words);
+  const int n = tr_phases(pl.N, pl.batch_call, cus, ph, &words);
   if (n == 0) return TC_ERR_SHAPE;
   const size_t stride = sync_bytes / 8;
-  if (words > stride) return TC_ERR_WORKSPACE;
+  if (words + TR_SIZES > stride) return TC_ERR_WORKSPACE;
   u64* sy = static_cast<u64*>(sync);
-  const unsigned per = (unsigned)((words + 1023) / 1024);
-  TC_TIMED(PK_TRIDIAG_UPDATE, 0, st, (tridiag_clear_kernel<<<dim3(per < 1 ? 1 : per > 64 ? 64 : per, pl.B), 256, 0, st>>>(sy, stride, words, fail)));
+  const unsigned per = (unsigned)((words + TR_SIZES + 1023) / 1024);
+  TC_TIMED(PK_TRIDIAG_UPDATE, 0, st, (tridiag_clear_kernel<<<dim3(per > 64 ? 64 : per, pl.B), 256, 0, st>>>(sy, stride, words + TR_SIZES, fail)));
   for (int i = 0; i < n; i++) {
+    const int set = tc_group_patience, patience = set >= 0 ? set : i + 1 >= -set ? -1 : TR_PATIENCE;
     int rc = TC_ERR_SHAPE;
-#define TR_CASE(SIZE_, PC_) case SIZE_: rc = tr_launch<PC_>(pl, ph[i], G, dvec, evec, tauv, Vc, sy, stride, fail, st); break;
+#define TR_CASE(SIZE_, PC_) case SIZE_: rc = tr_launch<PC_>(pl, ph[i], G, dvec, evec, tauv, Vc, sy, stride, sy + words + i, patience, xcds, fail, st); break;
     switch (ph[i].size) {
       TR_CASE(0, 0) TR_CASE(1, 1) TR_CASE(2, 2) TR_CASE(3, 3) TR_CASE(4, 4) TR_CASE(5, 5) TR_CASE(6, 6)
     }
 #undef TR_CASE
     if (rc != TC_OK) return rc;
+  }
+  if (TR_FRAMES[ph[0].size].P > 1) {
+    const size_t shm = alone_lds(pl.N);
+    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_alone_kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+      return TC_ERR_HIP;
+    TC_TIMED(PK_TRIDIAG, 1, st, (tridiag_alone_kernel<<<pl.B, AL_THREADS, shm, st>>>(G, pl.N, pl.Np, dvec, evec, tauv, Vc, fail)));
   }
   return check_launch();
 }

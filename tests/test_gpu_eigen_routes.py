@@ -1,5 +1,7 @@
 """GPU tests of the contribution score on attention outputs in hand: the frames of the reduction to tridiagonal form
 (256, 576 and multiples of 576 tokens), the split contraction of the Gram matrix, captured graphs and concurrent calls."""
+import ctypes
+
 import pytest
 import torch
 
@@ -96,10 +98,13 @@ def test_a_captured_call_replays_to_the_eager_result(n, batch):
                 assert torch.equal(x, y)
 
 
-def test_calls_with_large_groups_on_three_streams_at_once():
-    # 1729 tokens: 64 workgroups wait for each other in each call
+# (calls, tokens, images): workgroups that wait for each other, all calls together: 192 of 64 (which fit the chip at once), 320 of
+# 16, 384 of 36, 576 of 64, 176 of 4 beside 128 of 16
+@pytest.mark.parametrize("shapes", [[(1729, 1)] * 3, [(701, 10)] * 2, [(1400, 5), (1153, 4), (1729, 1)], [(2200, 3)] * 3,
+                                    [(576, 22), (576, 22), (900, 8)]])
+def test_calls_on_several_streams_at_once(shapes):
     tc = _tc()
-    calls = [Call(tc, _params(tc, 1, 1729, 4), _rows(1, 1729, 512, i).cuda()) for i in range(3)]
+    calls = [Call(tc, _params(tc, b, n, 4), _rows(b, n, 512, i).cuda()) for i, (n, b) in enumerate(shapes)]
     alone = []
     for c in calls:
         c()
@@ -114,6 +119,43 @@ def test_calls_with_large_groups_on_three_streams_at_once():
     for c, want in zip(calls, alone):
         for x, y in zip(want, c.outputs()):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n,batch", [(200, 300), (600, 66)])
+def test_groups_of_images_give_what_one_group_gives(n, batch):
+    tc = _tc()
+    O = _rows(batch, n, 256, n).cuda()
+    out = []
+    for groups in (1, 0, 3):
+        call = Call(tc, _params(tc, batch, n, 2, stream_groups=groups), O)
+        call()
+        torch.cuda.synchronize()
+        out.append(call.outputs())
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("n,batch,phase", [(257, 1, 0), (300, 9, 0), (576, 2, 0), (577, 2, 0), (577, 2, 1), (1000, 1, 1), (1153, 2, 0),
+                                           (1153, 2, 1), (1729, 1, 2)])
+def test_images_whose_groups_are_not_resident_at_once(n, batch, phase):
+    # the groups give up from this phase on: one workgroup per image does the rest
+    tc = _tc()
+    patience = ctypes.c_int.in_dll(tc.load_library(), "tc_group_patience")
+    O = _rows(batch, n, 512, 7 * n)
+    call = Call(tc, _params(tc, batch, n, 4), O.cuda())
+    usual = patience.value
+    patience.value = -1 - phase
+    try:
+        call()
+        torch.cuda.synchronize()
+    finally:
+        patience.value = usual
+    assert call.info.cpu().tolist() == [1] * batch
+    for b in {0, batch - 1}:
+        s, c = _reference(O[b])
+        assert float((call.sigma[b].double().cpu() - s).abs().max() / s.max()) < 1e-6
+        assert float((call.C[b].double().cpu() - c).abs().max() / c.abs().max()) < 2e-5, b
 
 
 @pytest.mark.parametrize("n", [64, 257, 576, 577, 1153])

@@ -1,0 +1,77 @@
+"""Host test (no GPU): the frames of the register-resident reduction, their phases and which of them a device can hold, for whole
+and partitioned devices.  csrc/tridiag_frames.h is host code; it is compiled here into a program that answers questions."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2503_10501_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "tridiag_frames.h"
+using namespace tc;
+int main() {
+  int N, B, cus;
+  while (std::scanf("%d %d %d", &N, &B, &cus) == 3) {
+    TrPhase ph[TR_SIZES];
+    size_t words;
+    const int n = tr_phases(N, B, cus, ph, &words);
+    std::printf("%d %d %zu %zu %d", tr_runs(N, cus, false), tr_runs(N, cus, true), words, tr_sync_words(N), n);
+    for (int i = 0; i < n; i++)
+      std::printf(" %d %d %d %d %d", TR_FRAMES[ph[i].size].F, TR_FRAMES[ph[i].size].P, ph[i].first, ph[i].last, tr_apart(TR_FRAMES[ph[i].size].P));
+    std::printf("\n");
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("frames")
+    src, exe = d / "frames.cpp", d / "frames"
+    src.write_text(PROGRAM)
+    subprocess.run([gxx, "-std=c++20", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+
+    def run(questions):
+        out = subprocess.run([str(exe)], input="\n".join("%d %d %d" % q for q in questions), capture_output=True, text=True, check=True)
+        rows = [[int(x) for x in line.split()] for line in out.stdout.splitlines()]
+        assert len(rows) == len(questions)
+        return [(r[0], r[1], r[2], r[3], [tuple(r[5 + 5 * i:10 + 5 * i]) for i in range(r[4])]) for r in rows]
+    return run
+
+
+SIZES = [1, 2, 255, 256, 257, 575, 576, 577, 701, 1024, 1152, 1153, 1728, 1729, 2304, 2305, 2880, 2881, 3456]
+
+
+@pytest.mark.parametrize("cus", [256, 128, 64, 32, 8])
+def test_phases_cover_every_column_once(ask, cus):
+    questions = [(n, b, cus) for n in SIZES for b in (1, 2, 3, 7, 17, 64, 300)]
+    for (n, b, _), (_, _, words, room, phases) in zip(questions, ask(questions)):
+        assert phases[0][2] == 0 and phases[-1][3] == n
+        for (F, P, first, last, _), nxt in zip(phases, phases[1:]):
+            assert last == nxt[2] and last % 16 == 0   # blocks of sixteen reflectors
+        for F, P, first, last, _ in phases:
+            assert n - first <= F and first <= last
+        assert words + len(phases) <= room
+
+
+@pytest.mark.parametrize("cus,most,captured", [(256, 3456, 1728), (128, 2880, 1152), (64, 2304, 576), (32, 1152, 576), (8, 576, 256)])
+def test_a_group_fits_the_device(ask, cus, most, captured):
+    questions = [(n, 1, cus) for n in SIZES + [3457, 4096]]
+    for (n, _, _), (runs, in_graph, _, _, phases) in zip(questions, ask(questions)):
+        assert runs == (n <= most) and in_graph == (n <= captured), n
+        if runs:
+            assert all(P <= cus for _, P, _, _, _ in phases)
+        # groups on one XCD leave at most three workgroups waiting there, with the four hardware queues of a process twelve of 32:
+        # all others are kept apart
+        assert all(apart == (P > 4) for _, P, _, _, apart in phases)
+
+
+def test_the_end_of_the_frames(ask):
+    assert [bool(r[4]) for r in ask([(3456, 1, 256), (3457, 1, 256)])] == [True, False]
