@@ -64,6 +64,14 @@ __device__ __forceinline__ void fmac_bcast_neg(double& d, double row, double c) 
   asm("v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(row), "v"(c), "n"(N));
 }
 
+// Two wait states must lie between a write of a register and its use as a broadcast, and the compiler keeps none for an asm
+// operand.  As inputs, the rows are written before the wait; that nothing else writes them on the way to the multiply-adds is
+// checked in the compiler's output by a test.  (Tied to the multiply-adds as well, through an operand that passes through,
+// a call of one image of 576 tokens takes 2.54 ms in place of 2.52.)
+__device__ __forceinline__ void settle(double a, double b) { asm volatile("s_nop 1" : : "v"(a), "v"(b)); }
+__device__ __forceinline__ void settle(double a, double b, double c) { asm volatile("s_nop 1" : : "v"(a), "v"(b), "v"(c)); }
+__device__ __forceinline__ void settle(double a, double b, double c, double d) { asm volatile("s_nop 1" : : "v"(a), "v"(b), "v"(c), "v"(d)); }
+
 // The lowest bit makes room for the tag by rounding to nearest even, and a reader clears the tag: zero arrives as zero.
 __device__ __forceinline__ void publish(u64* p, double v, unsigned tag) {
   const u64 y = (u64)__double_as_longlong(v);
@@ -351,7 +359,8 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
             constexpr int fn = (k + 1 < LK ? k + 1 : k) * (C + C / 32);
             const double xn = X[fc0 + fn], on = MODE == 0 ? Vo[fc0 + fn] : 0.0, wn = MODE == 0 ? Wv[fc0 + fn] : 0.0;
             double c0 = SW > 1 ? cs[SW > 1 ? k : 0] : 0.0, c1 = 0.0;
-            asm volatile("s_nop 1");
+            if constexpr (MODE == 0) settle(vn[0], vo[0], wo[0]);
+            else settle(vn[0], vn[1]);
             walk_up<r0, i1>([&](auto ic) {
               constexpr int i = decltype(ic)::value, s = i / SR - s0, q = i % SR;
               if constexpr (MODE == 0) {
@@ -436,7 +445,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         constexpr int k = decltype(kc)::value, fn = (k + 1 < LK ? k + 1 : k) * (C + C / 32);
         if (k < kmin) return;
         const double on = Vo[fc0 + fn], wn = Wv[fc0 + fn];
-        asm volatile("s_nop 1");
+        settle(ro[0], ro[1], rw[0], rw[1]);
         walk_up<RT * k, LI>([&](auto ic) {
           constexpr int i = decltype(ic)::value, s = i / SR, q = i % SR;
           fmac_bcast_neg<q>(A[i][k], ro[s], wc);
