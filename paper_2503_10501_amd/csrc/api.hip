@@ -81,7 +81,7 @@ int make_plan(const tc_params* p, Plan* pl) {
     q.off_td_bad = take(B * 4);
     q.off_td_wgt = take(B * Np * 8);
     q.off_td_W = take(B * Np * Np * 4);        // eigenvectors of T (the reflectors use the region of U)
-    q.off_td_mark = take(B * (Np + 1) * 4);    // per slot: vector to be orthogonalised; one word per image
+    q.off_td_mark = take(B * (Np + 2) * 4);    // per slot: vector to be orthogonalised; two words per image
     q.off_td_Cpart = take(B * nstrip * Np * 8);
     q.off_td_Tf = take(B * ((N + 15) / 16) * 256 * 4);   // T factors of the blocks of 16 reflectors
     q.td_sync_bytes = tridiag_sync_bytes(q.N);
@@ -123,7 +123,7 @@ static int direct_chain(const Plan& pl, const Plan& sub, int img0, const tc_para
   return launch_td_eigen(sub, dvec, evec, tauv, Vc, at<double>(ws, pl.off_td_lam) + i0 * Np, at<int2>(ws, pl.off_td_blk) + i0 * Np,
                          at<double>(ws, pl.off_td_tnorm) + i0, G,
                          at<float>(ws, pl.off_td_W) + i0 * Np * Np, at<double>(ws, pl.off_td_rn) + i0 * Np,
-                         at<int32_t>(ws, pl.off_td_bad) + i0, at<int32_t>(ws, pl.off_td_mark) + i0 * (Np + 1), fail, at<double>(ws, pl.off_sig) + i0 * Np,
+                         at<int32_t>(ws, pl.off_td_bad) + i0, at<int32_t>(ws, pl.off_td_mark) + i0 * (Np + 2), fail, at<double>(ws, pl.off_sig) + i0 * Np,
                          at<double>(ws, pl.off_td_wgt) + i0 * Np, at<double>(ws, pl.off_td_Cpart) + i0 * nstrip * Np,
                          at<float>(ws, pl.off_td_Tf) + i0 * npanel * 256, p->sv_rtol, vectors, C_ws ? C_ws + i0 * pl.N : nullptr,
                          ics ? ics + i0 * pl.N : nullptr, sigma ? sigma + i0 * pl.N : nullptr, info ? info + i0 : nullptr, st);

@@ -38,13 +38,13 @@ typedef double tb_pair __attribute__((ext_vector_type(2)));
 // Scaled copy of T for the bisection, one workgroup per image: prep [B][prep_stride] doubles holds
 // (d_i, -e_i^2) pairs for rows 0 .. N-1 (e_i = |coupling of rows i-1 and i|, e_0 = 0; the square is 0 where T
 // is split), 32 zero pairs behind them, then the Gershgorin interval of T (scaled).  Also the block (s, t) of every row,
-// tnorm [B] = ||T||_inf; bad[b] starts from the failure flag of the reduction, mark [B][Np] from N, any[b] from 0.
+// tnorm [B] = ||T||_inf; bad[b] starts from the failure flag of the reduction, mark [B][Np] from N, any[b] and need[b] from 0.
 __global__ __launch_bounds__(256) void td_prepare_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
                                                          double* __restrict__ prep, size_t prep_stride,
                                                          double* __restrict__ tnorm, int2* __restrict__ blk,
                                                          int32_t* __restrict__ bad, int32_t* __restrict__ mark,
-                                                         int32_t* __restrict__ any, const int32_t* __restrict__ fail, int N,
-                                                         int Np) {
+                                                         int32_t* __restrict__ any, int32_t* __restrict__ need,
+                                                         const int32_t* __restrict__ fail, int N, int Np) {
   __shared__ double wred[3][4];
   __shared__ u64 cut[MAX_NVIS / 64 + 1];  // bit i: a block starts at row i
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -96,6 +96,7 @@ __global__ __launch_bounds__(256) void td_prepare_kernel(const double* __restric
     tnorm[b] = tn;
     bad[b] = fail[b] ? 4 : 0;
     any[b] = 0;
+    need[b] = 0;
     pr[N + 32] = tb_pair{fmin(fmin(wred[1][0], wred[1][1]), fmin(wred[1][2], wred[1][3])) * down,
                          fmax(fmax(wred[2][0], wred[2][1]), fmax(wred[2][2], wred[2][3])) * down};
   }
@@ -609,6 +610,96 @@ __device__ inline bool td_close(const double* lb, const int2* bb, double tn, int
   return k > 0 && k < N && bb[k].x == bb[k - 1].x && lb[k] - lb[k - 1] <= TD_CLOSE * tn && lb[k] > zero && lb[k - 1] > zero;
 }
 
+// A product of all vectors in runs, U^T (U r) - r with r of no particular values, shows whether any two are not orthogonal for the
+// price of two passes over the vectors; four such r leave a pair that is off by 1e-5 a chance of 1e-4 to hide (by 1e-4, of
+// 1e-8).  Above 576 tokens the pairs of an image are compared only where this finds something: for eight images of 2880
+// tokens with runs of two thousand the comparison is 0.9 ms on the matrix cores, the product 0.11.
+constexpr int TP_R = 4;
+constexpr int TP_ABOVE = 576;
+__device__ inline double td_probe_weight(int p, int k) {  // between 0.5 and 1 in size
+  uint32_t h = (uint32_t)(TP_R * k + p + 1) * 0x9e3779b1u;
+  h = (h ^ (h >> 16)) * 0x85ebca6bu;
+  h ^= h >> 13;
+  const double v = 0.5 + (double)(h & 0x7fffffu) * 0x1p-24;
+  return (h >> 31) ? -v : v;
+}
+__device__ inline bool td_in_run(const double* lb, const int2* bb, double tn, int k, int N) {
+  return td_close(lb, bb, tn, k, N) || td_close(lb, bb, tn, k + 1, N);
+}
+
+// y = U r of 64 rows (y [Np][TP_R] of the image in `ckpt`, which td_twisted_kernel is done with).
+constexpr int TP_THREADS = 1024, TP_WAVES = TP_THREADS / 64;
+__global__ __launch_bounds__(TP_THREADS) void td_probe_rows_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
+                                                            const double* __restrict__ tnorm, const float* __restrict__ W,
+                                                            const double* __restrict__ rn, double* __restrict__ ckpt,
+                                                            size_t ckpt_stride, int N, int Np) {
+  extern __shared__ float weight[];  // [TP_R][N]: over the vector's norm, 0 outside runs
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double* lb = lam + (size_t)b * Np;
+  const int2* bb = blk + (size_t)b * Np;
+  const double tn = tnorm[b];
+  int found = 0;
+  for (int k = tid; k < N; k += TP_THREADS) {
+    const bool in = td_in_run(lb, bb, tn, k, N);
+    found |= in;
+    for (int p = 0; p < TP_R; p++) weight[p * N + k] = in ? (float)(td_probe_weight(p, k) * rn[(size_t)b * Np + k]) : 0.f;
+  }
+  if (!__syncthreads_or(found)) return;
+  double* y = ckpt + (size_t)b * ckpt_stride;
+  for (int r = wave; r < 64; r += TP_WAVES) {
+    const int i = 64 * blockIdx.x + r;
+    if (i >= N) break;
+    const float* row = W + ((size_t)b * Np + i) * Np;
+    double s[TP_R] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int k = lane; k < N; k += 64) {
+      const double v = (double)row[k];
+#pragma unroll
+      for (int p = 0; p < TP_R; p++) s[p] = fma(v, (double)weight[p * N + k], s[p]);
+    }
+#pragma unroll
+    for (int p = 0; p < TP_R; p++) {
+      const double t = wave_sum_dpp(s[p]);
+      if (lane == 0) y[(size_t)i * TP_R + p] = t;
+    }
+  }
+}
+
+// need[b] becomes 1 where U^T y is not r.  One workgroup per 64 slots.
+__global__ __launch_bounds__(TP_THREADS) void td_probe_slots_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
+                                                             const double* __restrict__ tnorm, const float* __restrict__ W,
+                                                             const double* __restrict__ rn, const double* __restrict__ ckpt,
+                                                             size_t ckpt_stride, int32_t* __restrict__ need, int N, int Np) {
+  __shared__ double part[TP_WAVES][TP_R][64];
+  const int b = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), k = 64 * blockIdx.x + lane;
+  const bool in = td_in_run(lam + (size_t)b * Np, blk + (size_t)b * Np, tnorm[b], k, N);
+  if (!__any(in)) return;  // the same in all wavefronts
+  const int r0 = blk[(size_t)b * Np + 64 * blockIdx.x].x, r1 = blk[(size_t)b * Np + min(64 * (int)blockIdx.x + 63, N - 1)].y;
+  const double* y = ckpt + (size_t)b * ckpt_stride;
+  const float* col = W + (size_t)b * Np * Np + k;
+  double s[TP_R] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int i = r0 + wave; i < r1; i += TP_WAVES) {
+    const double v = (double)col[(size_t)i * Np];
+#pragma unroll
+    for (int p = 0; p < TP_R; p++) s[p] = fma(v, y[(size_t)i * TP_R + p], s[p]);
+  }
+#pragma unroll
+  for (int p = 0; p < TP_R; p++) part[wave][p][lane] = s[p];
+  __syncthreads();
+  if (wave != 0) return;
+  bool off = false;
+  if (in)
+#pragma unroll
+    for (int p = 0; p < TP_R; p++) {
+      double z = 0.0;
+      for (int w = 0; w < TP_WAVES; w++) z += part[w][p][lane];
+      z *= rn[(size_t)b * Np + k];
+      off = off || !(fabs(z - td_probe_weight(p, k)) <= TD_ORTHOGONAL);
+    }
+  if (__any(off) && lane == 0) need[b] = 1;
+}
+
 // One workgroup per two tiles of 64 slots, the first not before the second; most find no run that reaches from one to the
 // other and end.  (Rows that attention has averaged have hundreds of eigenvalues below 1e-10 ||T||: with one workgroup per
 // tile and all tiles before it, on the vector units, 227 us for four images of 701 tokens and 473 for two of 1499.)  The
@@ -619,10 +710,12 @@ typedef __attribute__((ext_vector_type(4))) float f4;
 __global__ __launch_bounds__(256) void td_pairs_kernel(const double* __restrict__ lam, const int2* __restrict__ blk,
                                                        const double* __restrict__ tnorm, const float* __restrict__ W,
                                                        const double* __restrict__ rn, int32_t* __restrict__ mark,
-                                                       int32_t* __restrict__ any, int N, int Np) {
+                                                       int32_t* __restrict__ any, const int32_t* __restrict__ need, int N,
+                                                       int Np) {
   constexpr int ST = 8;      // steps of four rows in flight
   __shared__ int start[64];  // the first slot, of this run of slot k0 + i, that lies in the second tile or behind it
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (need && !need[b]) return;
   int tj = blockIdx.x, ti = 0;
   while (tj >= ti + 1) { tj -= ti + 1; ti++; }
   const int k0 = 64 * ti, j0 = 64 * tj;
@@ -1163,8 +1256,9 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
   const int N = pl.N, Np = pl.Np, B = pl.B;
   // The image's part of `scratch` (Np^2 doubles) holds the scaled copy of T first, the pivots of the factorisations later.
   const size_t stride = (size_t)Np * Np;
-  int32_t* any = mark + (size_t)B * Np;  // (one word per image behind the marks of the group's images)
-  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, scratch, stride, tnorm, blk, bad, mark, any, fail, N, Np)));
+  int32_t* any = mark + (size_t)B * Np;  // (two words per image behind the marks of the group's images)
+  int32_t* need = any + B;
+  TC_TIMED(PK_BISECT, 0, st, (td_prepare_kernel<<<B, 256, 0, st>>>(dvec, evec, scratch, stride, tnorm, blk, bad, mark, any, need, fail, N, Np)));
   // lanes per eigenvalue: as many as keep the launch near one wavefront per SIMD (by the size of the whole call, so
   // that an image's result does not depend on how the call is cut into stream groups)
   int gs = 0;
@@ -1185,7 +1279,13 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
     TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, any, N, Np)));
   }
   const int nt = (N + 63) / 64;
-  TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3(nt * (nt + 1) / 2, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, N, Np)));
+  const bool probe = N > TP_ABOVE;
+  if (probe) {
+    const size_t shm = (size_t)TP_R * N * 4;
+    TC_TIMED(PK_TWISTED, 1, st, (td_probe_rows_kernel<<<dim3(nt, B), TP_THREADS, shm, st>>>(lam, blk, tnorm, W, rn, scratch, stride, N, Np)));
+    TC_TIMED(PK_TWISTED, 1, st, (td_probe_slots_kernel<<<dim3(nt, B), TP_THREADS, 0, st>>>(lam, blk, tnorm, W, rn, scratch, stride, need, N, Np)));
+  }
+  TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3(nt * (nt + 1) / 2, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, probe ? need : nullptr, N, Np)));
   {
     const size_t shm = td_orthogonalise_lds(N);
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_orthogonalise_kernel),
