@@ -103,7 +103,7 @@ typedef struct {
   int32_t eig_method;   /* tc_eig_method; TC_EIG_TRIDIAGONAL with TC_EIG_F32 or n_vis > 1024 is rejected (TC_ERR_PARAM) */
   int32_t stream_groups; /* groups of images whose eigensolver work (tridiagonal route: attention and Gram matrix
                             too) runs on helper streams and overlaps: 0 = the library chooses (Jacobi: 1, 2 or 4 by
-                            the amount of work; tridiagonal: 2 above 64 images), 1 = everything on `stream`,
+                            the amount of work; tridiagonal: 2 above 64 images, up to 384 tokens above 256), 1 = everything on `stream`,
                             2..4 = that many groups.  Results do not depend on it.                      */
   int32_t n_prompt_queries; /* P, text-guided variant of Eq. 3-7: the P query rows after the visual block (positions
                             vis_start + n_vis .. + P - 1) join the visual query rows in the column mean, which

@@ -131,10 +131,13 @@ static int direct_chain(const Plan& pl, const Plan& sub, int img0, const tc_para
 
 // Attention (when Q is given), Gram matrix, eigen-decomposition and Eq. 3-6 / 3-8.
 // Tridiagonal route: the batch can be cut into groups of images whose chains run on the library's helper streams, each
-// group starting when the one before it has formed its Gram matrices.  The reduction holds the registers of four
-// compute units per image for as long as it runs (64 images of 576 tokens: the whole chip), so there is nothing to
-// fill with another group's kernels until the images need more than one round over the chip: one group up to 64
-// images (6.63 ms against 7.22 ms with two for 64 images of 576 tokens), two above (12.83 against 13.03 ms for 128).
+// group starting when the one before it has formed its Gram matrices.  The reduction holds the registers of its compute units
+// for as long as it runs, so another group's kernels only find room where the images need more than one round over the
+// chip.  At 576 tokens (four compute units an image) that is above 64 images: one group and two, 5.49 and 6.20 ms for 64
+// images, 7.52 and 6.71 for 72, 8.48 and 7.90 for 96, 9.89 and 9.98 for 128; 701 tokens, 72 images 10.1 and 9.5; 1152 to 2000
+// tokens, 66 to 72 images 1 % slower with two.  Up to 256 tokens (one compute unit an image) and not far above (the last 256
+// columns of every reduction) it is above 256 images: 256 tokens, 128 images 2.38 and 2.61, 257 images 2.43 and 2.12; 300 tokens,
+// 128 images 1.99 and 2.20; 400 tokens, 96 images 4.94 and 4.91.
 static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const void* K, const void* V, void* O,
                        float* S, float* score, float* ics, float* sigma, int32_t* info, void* ws, hipStream_t st) {
   if (pl.method != TC_EIG_TRIDIAGONAL || !tridiag_allowed(pl.N, st)) {
@@ -149,7 +152,7 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
     return launch_scores(pl, p->eig_dtype, G, U, state, S, p->lambda, p->norm_mode, p->sv_rtol, at<char>(ws, pl.off_sig),
                          at<float>(ws, pl.off_C), score, ics, sigma, info, st);
   }
-  int groups = pl.groups > 0 ? pl.groups : (pl.B > 64 ? 2 : 1);
+  int groups = pl.groups > 0 ? pl.groups : (pl.B > (pl.N <= 384 ? 256 : 64) ? 2 : 1);
   if (groups > pl.B) groups = pl.B;
   if (profiling_active()) groups = 1;  // per-kernel timing wants kernels that run alone
   hipStream_t streams[4];
