@@ -130,7 +130,7 @@ TC_API int tc_attn_output(const tc_params* p, const void* Q, const void* K, cons
 
 /*
  * Section 3.3.1.  SVD of O[b] = U Sigma V^T is realised as the eigen-decomposition of the Gram
- * matrix O O^T = U Sigma^2 U^T (batched block-Jacobi); Eq. 3-6 then Eq. 3-8.
+ * matrix O O^T = U Sigma^2 U^T (method: see tc_eig_method); Eq. 3-6 then Eq. 3-8.
  *   O           [B, N, D] dtype
  *   attn_score  [B, N] float, may be NULL only when lambda == 0
  *   score       [B, N] float  E of Eq. 3-8
@@ -160,7 +160,7 @@ TC_API int tc_select_topk(const tc_params* p, const float* score, int32_t* order
  *   metric  [B, N, D] dtype            (the attention output O)
  *   order   [B, k_prune] int32         from tc_select_topk; an entry outside [0, N) is clamped
  *   sim     [B, |B|, |A|] float        written; nothing is written when |A| = 0 (k_prune = 1)
- * tc_merge computes the same matrix into its workspace.
+ * tc_merge forms the same values and keeps the best of each row of a tile instead of the matrix.
  */
 TC_API int tc_similarity(const tc_params* p, const void* metric, const int32_t* order, float* sim, void* ws,
                          size_t ws_bytes, void* stream);
@@ -184,10 +184,10 @@ TC_API int tc_merge(const tc_params* p, const void* X, const void* metric, const
 /*
  * tc_merge for callers that cannot allocate or pass a workspace: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as tc_merge, but
- * the scratch (row norms, similarity matrix, merge list) comes from a static device array of
+ * the scratch (row norms, best similarities per tile, merge list) comes from a static device array of
  * TC_NOALLOC_SCRATCH_BYTES inside the library, which every GPU the library is used on holds from the
  * first call until the process ends.  The call allocates and frees nothing and enqueues kernels only
- * (no memset nodes).  It needs 4 B k_p + 4 B |A| |B| + 8 B max(m, 1) bytes (each term rounded up to 256) and returns
+ * (no memset nodes).  It needs 4 B k_p + 4 B |B| max(|A|, 2) + 8 B max(m, 1) bytes (each term rounded up to 256) and returns
  * TC_ERR_SCRATCH, launching nothing, when that exceeds the array.  All calls on one GPU share the array:
  * calls that overlap in time on the same GPU (different streams or host threads) race; calls ordered on
  * one stream are safe.
@@ -224,7 +224,8 @@ typedef enum {
   TC_PROF_ATTN = 0, TC_PROF_ATTN_REDUCE, TC_PROF_GRAM, TC_PROF_JACOBI_INIT, TC_PROF_JACOBI_SOLVE,
   TC_PROF_JACOBI_UPDATE, TC_PROF_JACOBI_UPDATE_U, TC_PROF_JACOBI_SWEEP_END, TC_PROF_SIGMA, TC_PROF_ICS, TC_PROF_COMBINE, TC_PROF_TOPK,
   TC_PROF_ROWNORM, TC_PROF_SIM, TC_PROF_ASSIGN, TC_PROF_AVERAGE, TC_PROF_TRIDIAG, TC_PROF_BISECT, TC_PROF_TWISTED,
-  TC_PROF_BACKTRANSFORM, TC_PROF_TRIDIAG_UPDATE, TC_PROF_KINDS
+  TC_PROF_BACKTRANSFORM, TC_PROF_TRIDIAG_UPDATE /* the reduction's exchange memory cleared; images reduced alone */,
+  TC_PROF_KINDS
 } tc_prof_kind;
 TC_API int tc_profile_compress(const tc_params* p, const void* Q, const void* K, const void* V, const void* X,
                                void* X_out, int32_t* kept_idx, int32_t* merge_dst, int32_t* info, void* ws,
@@ -249,7 +250,7 @@ TC_API int tc_profile_compress(const tc_params* p, const void* Q, const void* K,
  *          singular values that far below the largest one.
  *   rank   [B] device int32, written
  *   sigma  [B, n_rows] device float, optional: the singular values, descending
- *   info   [B] device int32, optional: sweeps used, negative if not converged
+ *   info   [B] device int32, optional: as for tc_ipgs_score
  *   ws     workspace of tc_workspace_bytes(p) bytes (its contents are destroyed)
  * n_rows = 0 gives rank 0.  Errors as for tc_ipgs_score; 0 <= n_rows <= n_vis else TC_ERR_SHAPE.
  */

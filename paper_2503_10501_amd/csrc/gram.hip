@@ -206,8 +206,8 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict_
 }
 
 // Workgroups per tile: as many as keep the launch within three per compute unit, with at least eight chunks each and no more
-// than 3 MiB of parts per image: a workspace stays in proportion to the batch (one image of 576 x 4096 needs 11 MB; eight
-// workgroups per tile would double that to save another 0.012 ms of 2.5).  By the size of the whole call: the order of a sum
+// than 3 MiB of parts per image: a workspace stays in proportion to the batch (one image of 576 x 4096 needs 14 MB; eight
+// workgroups per tile would add 7 to save another 0.012 ms of 2.5).  By the size of the whole call: the order of a sum
 // must not depend on stream groups.
 static size_t part_bytes(const Plan& pl, int splits) {  // of one image
   const size_t nt = pl.Np / 64, parts = splits - (pl.tsize == 8 ? parts_in_g<double>() : parts_in_g<float>());

@@ -1,5 +1,5 @@
 // tc_merge_noalloc: Stage II (Section 3.3.2) for callers that cannot allocate.  Same kernels as
-// tc_merge; the scratch they need (row norms, the similarity matrix, the merge list) lives in a
+// tc_merge; the scratch they need (row norms, the best similarities per tile, the merge list) lives in a
 // file-scope device array instead of a caller-supplied workspace.
 #include <mutex>
 

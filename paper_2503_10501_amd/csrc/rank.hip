@@ -1,6 +1,6 @@
 // Information quantity of a set of visual tokens (Section 3.2.2 of the TokenCarve paper): the matrix
 // rank of their attention-output rows, counted as the singular values above rtol * sigma_max.  The
-// singular values come from the same Gram matrix + Jacobi eigensolver as Eq. 3-6, without the
+// singular values come from the same Gram matrix and eigensolver as Eq. 3-6, without the
 // eigenvectors.
 #include "tc_internal.h"
 

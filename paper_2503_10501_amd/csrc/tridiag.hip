@@ -12,7 +12,7 @@
 // column is latency: one exchange of the partial products between the workgroups of the group (about 1.1 us inside an
 // XCD), three barriers with their scalars, and the arithmetic (4 fused multiply-adds per element of the triangle, one
 // every 4.3 clocks of a SIMD).  The update runs while the partial products are on their way.  Measured at 576 tokens:
-// 2.3 ms for one image and for 64 (5.6 and 8.8 ms with the matrix in memory), 18 ms at 2880 tokens (470 ms).
+// 2.1 ms for one image and 2.2 for 64 (5.6 and 8.8 ms with the matrix in memory), 43 ms for eight images of 2880 tokens (470 ms).
 //
 // Frame.  The matrix is placed at the end of a frame of F x F (row f of the frame is row f + base of the matrix).
 // Wavefront w of workgroup (a, b) owns the rows f = i R + 8 a + w (i < LI) and lane l the columns k C + 64 b + l (k < LK), R = 8 PR
@@ -853,7 +853,7 @@ int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float*
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_alone_kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
       return TC_ERR_HIP;
-    TC_TIMED(PK_TRIDIAG, 1, st, (tridiag_alone_kernel<<<pl.B, AL_THREADS, shm, st>>>(G, pl.N, pl.Np, dvec, evec, tauv, Vc, fail)));
+    TC_TIMED(PK_TRIDIAG_UPDATE, 1, st, (tridiag_alone_kernel<<<pl.B, AL_THREADS, shm, st>>>(G, pl.N, pl.Np, dvec, evec, tauv, Vc, fail)));
   }
   return check_launch();
 }
