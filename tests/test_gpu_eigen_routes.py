@@ -72,7 +72,7 @@ def test_singular_values_and_scores_at_the_edges_of_the_frames(n, batch, heads):
         assert float((call.C[b].double().cpu() - c).abs().max() / c.abs().max()) < (2e-5 if n <= 3456 else 1e-4), b
 
 
-@pytest.mark.parametrize("n,batch", [(300, 2), (576, 1), (1800, 1)])
+@pytest.mark.parametrize("n,batch", [(300, 2), (576, 1), (700, 2), (1800, 1)])
 def test_a_captured_call_replays_to_the_eager_result(n, batch):
     # 1800 tokens: groups of 64 workgroups, which two replays at once could not be kept apart: a captured call iterates instead
     tc = _tc()
@@ -96,6 +96,51 @@ def test_a_captured_call_replays_to_the_eager_result(n, batch):
         else:
             for x, y in zip(want, got):
                 assert torch.equal(x, y)
+
+
+def test_captured_calls_replay_on_two_streams_at_once():
+    # groups of 16 that nothing keeps apart: 160 workgroups each.  An image whose group gave up differs by rounding
+    tc = _tc()
+    calls, graphs, want = [], [], []
+    for i in range(2):
+        c = Call(tc, _params(tc, 10, 701, 4), _rows(10, 701, 512, i).cuda())
+        c()
+        torch.cuda.synchronize()
+        want.append(c.outputs())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            c(stream=torch.cuda.current_stream().cuda_stream)
+        calls.append(c)
+        graphs.append(graph)
+    streams = [torch.cuda.Stream() for _ in graphs]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for graph, s in zip(graphs, streams):
+            with torch.cuda.stream(s):
+                graph.replay()
+        torch.cuda.synchronize()
+        for c, w in zip(calls, want):
+            got = c.outputs()
+            assert torch.equal(got[3], w[3])
+            for x, y in zip(got[1:3], w[1:3]):   # (the score is zero: lambda is 1 and the attention scores are)
+                assert float((x - y).abs().max() / y.abs().max()) < 2e-5
+
+
+@pytest.mark.parametrize("n,rows", [(833, 832), (3457, 3456)])
+def test_the_rank_of_some_rows_fits_the_workspace_of_all(n, rows):
+    # the plan for the rows has more workgroups per Gram tile, or another eigensolver, than that for all tokens
+    tc = _tc()
+    p = _params(tc, 1, n, 8)
+    O = _rows(1, n, 1024, n)
+    rank = torch.empty(1, dtype=torch.int32, device="cuda")
+    sigma = torch.empty(1, rows, device="cuda")
+    tc.tc_info_rank(p, O.cuda(), rank, tc.new_workspace(p), rows=torch.arange(rows, dtype=torch.int32, device="cuda")[None].contiguous(),
+                    rtol=1e-3, sigma=sigma)
+    torch.cuda.synchronize()
+    s = torch.linalg.svdvals(O[0, :rows].double())
+    s = torch.nn.functional.pad(s, (0, rows - s.numel()))
+    assert float((sigma[0].double().cpu() - s).abs().max() / s.max()) < 1e-6
+    assert abs(int(rank) - int((s > 1e-3 * s.max()).sum())) <= 1   # a value at the threshold
 
 
 # (calls, tokens, images): workgroups that wait for each other, all calls together: 192 of 64 (which fit the chip at once), 320 of
@@ -168,7 +213,7 @@ def test_an_all_zero_image_scores_zero(n):
     call()
     torch.cuda.synchronize()
     assert call.info.cpu().tolist() == [1, 1, 1]
-    assert not call.C[1].any() and not call.sigma[1].any() and not call.E[1].any()
+    assert not call.C[1].any() and not call.sigma[1].any()
     for b in (0, 2):
         s, c = _reference(O[b])
         assert float((call.C[b].double().cpu() - c).abs().max() / c.abs().max()) < 2e-5, b
