@@ -139,8 +139,9 @@ TC_API int tc_attn_output(const tc_params* p, const void* Q, const void* K, cons
  *   info        [B] int32     > 0: done, < 0: failed, never 0.  Jacobi method: the number of sweeps used
  *                             (1 for an all-zero matrix, which needs none), negated if the tolerance was
  *                             not reached within jacobi_max_sweeps.  Tridiagonal method: 1, or -1 if an
- *                             eigenvector could not be found (O is not finite) or the workgroups of the
- *                             reduction lost each other.  Optional
+ *                             eigenvector could not be found (only where O is not finite, and not always
+ *                             there: the scores say so too) or the workgroups of the reduction lost each
+ *                             other.  Optional
  */
 TC_API int tc_ipgs_score(const tc_params* p, const void* O, const float* attn_score, float* score,
                   float* ics, float* sigma, int32_t* info, void* ws, size_t ws_bytes, void* stream);

@@ -618,7 +618,7 @@ constexpr int TP_R = 4;
 constexpr int TP_ABOVE = 576;
 __device__ inline double td_probe_weight(int p, int k) {  // between 0.5 and 1 in size
   uint32_t h = (uint32_t)(TP_R * k + p + 1) * 0x9e3779b1u;
-  h = (h ^ (h >> 16)) * 0x85ebca6bu;
+  h = (h ^ (h >> 16)) * 0xa3b1956bu;
   h ^= h >> 13;
   const double v = 0.5 + (double)(h & 0x7fffffu) * 0x1p-24;
   return (h >> 31) ? -v : v;
@@ -953,8 +953,8 @@ __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const doub
           __syncthreads();
           if (tid == 0) factor(s, n, lb[k] + 64.0 * tiny);
           for (int i = tid; i < n; i += TO_THREADS) {
-            uint32_t h = (uint32_t)(i + 1) * 0x9e3779b1u ^ (uint32_t)(k + 1) * 0x85ebca6bu;
-            h = (h ^ (h >> 15)) * 0x2c1b3c6du;
+            uint32_t h = (uint32_t)(i + 1) * 0x9e3779b1u ^ (uint32_t)(k + 1) * 0xa3b1956bu;
+            h = (h ^ (h >> 15)) * 0x5f8c2e17u;
             x[i] = (double)(int32_t)(h ^ (h >> 13)) * 0x1p-31;
           }
           __syncthreads();

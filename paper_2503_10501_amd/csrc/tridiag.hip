@@ -89,9 +89,8 @@ __device__ __forceinline__ bool tr_give_up(int spin, const int32_t* fail) {
 }
 
 // The members of a group count themselves in.  True when the group is not complete after `patience` polls (at once where that
-// is negative): the first member to
-// find that out sets the top bit, which nobody does once the count is whole, so all members decide alike, those
-// too that get their compute unit later.
+// is negative): the first member to find that out sets the top bit, which nobody does once the count is whole, so all
+// members decide alike, those too that get their compute unit later.
 __device__ __forceinline__ bool tr_stranded(u64* arrived, u64 P, int patience) {
   constexpr u64 off = 1ull << 63;
   if (patience < 0) return true;
