@@ -198,7 +198,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   double* Va = reinterpret_cast<double*>(tr_smem);  // [FX] reflector of the even columns
   double* Vb = Va + FX;                              // [FX] of the odd ones
   double* Wv = Vb + FX;                              // [FX] w of the column before
-  double* X = Wv + FX;                               // [FX] the column being reduced (zero up to and with its diagonal)
+  double* X = Wv + FX;                               // [FX] the column being reduced below its head (zero up to and with the head)
   double* csb = X + FX;                              // [8][OWN] column sums per wavefront
   double* rsb = csb + 8 * OWN;                       // [LI * 8] row sums
   double* colb = rsb + 8 * LI;                       // [LI * 8] this workgroup's rows of the next column
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       const int f = F - 1 - tid - TR_THREADS * u;
       if (f < js) continue;
       const double x = A0[(size_t)(f + base) * Np + first];
-      if (f > js) X[tr_at(f)] = x;
+      if (f > js + 1) X[tr_at(f)] = x;
       if (f >= js + 2) part += x * x;
       if (f == js + 1) one[1] = x;
       if (f == js && mem == 0) dout[first] = x;
@@ -283,40 +283,11 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     double* Vn = (j & 1) ? Vb : Va;        // this column's reflector
     const double* Vo = (j & 1) ? Va : Vb;  // the one before
     const int jr = j + base;               // column of the matrix
-    // ---- Householder reflector that maps x[j+1:] onto beta e_1 ------------------------------------------
-    // (every workgroup and every wavefront for itself; X holds the column, the reflector is X scal with a 1 on top)
-    const double xn2 = sum8(red + 8);
-    const double alpha = one[1];
-    double beta = alpha, tau = 0.0, scal = 0.0;
-    if (xn2 > 0.0) {
-      const double n2 = fma(alpha, alpha, xn2), rb = fast_rsq(n2);
-      double nb = n2 * rb;
-      nb = fma(0.5 * rb, fma(-nb, nb, n2), nb);          // |beta| = sqrt(n2)
-      beta = -copysign(nb, alpha);
-      tau = fma(fabs(alpha), rb, 1.0);                   // (beta - alpha) / beta
-      scal = copysign(fast_rcp(fabs(alpha) + nb), alpha);  // 1 / (alpha - beta)
-    }
-#pragma unroll
-    for (int u = 0; u < E; u++) {
-      const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
-      if (f >= j + 1) {
-        const double v = f == j + 1 ? 1.0 : X[g] * scal;
-        Vn[g] = v;
-        if (b == 0 && (MODE == 0 || ((f >> 3) % PR) == a)) vblk[(f / R * 8 + (f & 7)) * 16 + (jr & 15)] = (float)v;
-      }
-    }
-    if (tj == 0) {
-      Vn[tr_at(j)] = 0.0;
-      if (j > 0) Vn[tr_at(j - 1)] = 0.0;
-      if (mem == 0) {
-        eout[jr] = beta;
-        tout[jr] = (float)tau;
-      }
-    }
-
-    fresh<MODE != 0>(tj);
-    lj = tj & 63;
-    // ---- p = A v, this workgroup's part ------------------------------------------------------------------
+    // ---- A x, this workgroup's part -----------------------------------------------------------------------
+    // The reflector is v = e_(j+1) + scal x with x the column below its head, so p = A v is the next column plus scal A x:
+    // the sweep waits for no norm, and the chain of a square root, a reciprocal and the scaling runs while the parts are on
+    // their way.  (With v in the sweep it stood before it: eight images of 2880 tokens 59.6 ms, now 55.6; four of 701 3.45,
+    // now 3.39; one of 576 2.53 either way, where issuing the instructions is what takes the time.)
     // MODE 0: the update with the column before is applied in the same sweep.  Otherwise the product is formed with the
     // matrix as it is and published, and the update follows while the other workgroups' parts are on their way
     // (below): p and the next column then still lack it, which costs two scalar products.
@@ -336,17 +307,16 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         if (sw + 1 < SW && RT * kmin >= i1) return;                         // every row of the sweep is done with
         constexpr int s0 = i0 / SR, s1 = (i1 - 1) / SR;                     // sets of rows it takes in
         // column values of the first live class; the next class's are on their way while one is worked on
-        double xc = X[fc0 + kmin * (C + C / 32)], oc = 0.0, wc = 0.0;
+        double vc = X[fc0 + kmin * (C + C / 32)], oc = 0.0, wc = 0.0;
         if (MODE == 0) { oc = Vo[fc0 + kmin * (C + C / 32)]; wc = Wv[fc0 + kmin * (C + C / 32)]; }
-        const int fr0 = min(lj & 15, SR - 1) * R + 8 * a + w, gr0 = tr_at(fr0);
+        const int gr0 = tr_at(min(lj & 15, SR - 1) * R + 8 * a + w);
         double vn[s1 - s0 + 1], vo[s1 - s0 + 1], wo[s1 - s0 + 1];
 #pragma unroll
         for (int s = s0; s <= s1; s++) {
-          const int fr = fr0 + s * SR * R, g = gr0 + s * (SR * R + SR * R / 32);
-          vn[s - s0] = fr == j + 1 ? 1.0 : X[g] * scal;
+          const int g = gr0 + s * (SR * R + SR * R / 32);
+          vn[s - s0] = X[g];
           if (MODE == 0) { vo[s - s0] = Vo[g]; wo[s - s0] = Wv[g]; }
         }
-        double vc = (owner && lj == l0) ? 1.0 : xc * scal;
         constexpr int j0 = i0 > RT ? i0 : RT, NR = i1 - j0;  // rows with a row sum (those of the first diagonal block have none)
         double rs[NR];
 #pragma unroll
@@ -375,7 +345,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
               for (int i = r0; i < i1; i++) colb[i * 8 + w] = A[i][k];
             }
-            vc = xn * scal;
+            vc = xn;
             oc = on;
             wc = wn;
           }
@@ -406,14 +376,31 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       const double* c = csb + o;
       return ((c[0] + c[OWN]) + (c[2 * OWN] + c[3 * OWN])) + ((c[4 * OWN] + c[5 * OWN]) + (c[6 * OWN] + c[7 * OWN]));
     };
-    auto own_values = [&]() {  // this thread's elements of the vectors
+    double beta, tau, scal;
+    // Householder reflector that maps x[j+1:] onto beta e_1 (every workgroup and every wavefront for itself), and this
+    // thread's elements of the vectors
+    auto own_values = [&]() {
+      const double xn2 = sum8(red + 8);
+      const double alpha = one[1];
+      beta = alpha;
+      tau = scal = 0.0;
+      if (xn2 > 0.0) {
+        const double n2 = fma(alpha, alpha, xn2), rb = fast_rsq(n2);
+        double nb = n2 * rb;
+        nb = fma(0.5 * rb, fma(-nb, nb, n2), nb);          // |beta| = sqrt(n2)
+        beta = -copysign(nb, alpha);
+        tau = fma(fabs(alpha), rb, 1.0);                   // (beta - alpha) / beta
+        scal = copysign(fast_rcp(fabs(alpha) + nb), alpha);  // 1 / (alpha - beta)
+      }
 #pragma unroll
       for (int u = 0; u < E; u++) {
         const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
         const int q = min(u, K - 1);
         v[q] = vo[q] = wo[q] = 0.0;
         if (f > j) {
-          v[q] = Vn[g];
+          v[q] = f == j + 1 ? 1.0 : X[g] * scal;
+          Vn[g] = v[q];
+          if (b == 0 && (MODE == 0 || ((f >> 3) % PR) == a)) vblk[(f / R * 8 + (f & 7)) * 16 + (jr & 15)] = (float)v[q];
           if (MODE != 0) {
             vo[q] = Vo[g];
             wo[q] = Wv[g];
@@ -425,6 +412,14 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       if (MODE != 0) {
         dot[1] = wave_sum_dpp(dot[1]);
         dot[2] = wave_sum_dpp(dot[2]);
+      }
+      if (tj == 0) {
+        Vn[tr_at(j)] = 0.0;
+        if (j > 0) Vn[tr_at(j - 1)] = 0.0;
+        if (mem == 0) {
+          eout[jr] = beta;
+          tout[jr] = (float)tau;
+        }
       }
     };
     auto update = [&]() {  // A <- A - v w^T - w v^T with the column before
@@ -457,16 +452,16 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       lj = tj & 63;
     };
     if (MODE == 0) {
+      own_values();
 #pragma unroll
       for (int u = 0; u < E; u++) {
-        const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
+        const int f = F - 1 - tj - TR_THREADS * u;
         p[u] = col[u] = 0.0;
         if (f > j) {
-          p[u] = column_sum(f) + ((f >> 3) >= RT * (kmin + 1) ? rsb[f] : 0.0);
           col[u] = colb[f];
+          p[u] = fma(scal, column_sum(f) + ((f >> 3) >= RT * (kmin + 1) ? rsb[f] : 0.0), col[u]);
         }
       }
-      own_values();
     } else if (MODE == 1) {
       u64* Y = sy + (size_t)slot * 5 * F;  // [4][F] partials, then [F] the next column
 #pragma unroll
@@ -497,8 +492,8 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
             if (ok) break;
             if (tr_give_up(spin, fail + img)) { bad = true; break; }
           }
-          p[u] = (received(y[0]) + received(y[1])) + (received(y[2]) + received(y[3]));
           col[u] = received(y[4]);
+          p[u] = fma(scal, (received(y[0]) + received(y[1])) + (received(y[2]) + received(y[3])), col[u]);
         }
       }
     } else {
@@ -561,6 +556,8 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       collect(YN, col);  // (published together with the partials: it has arrived by the time the totals are)
       own_values();
       collect(YT, p);
+#pragma unroll
+      for (int u = 0; u < E; u++) p[u] = fma(scal, p[u], col[u]);
     }
     if (MODE != 0 && bad) *quit = 1;
 
@@ -615,7 +612,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         const double wf = tau * pf - half * vf;
         Wv[g] = wf;
         const double x = xf - vf * w1 - wf;  // (the reflector's first entry is 1)
-        X[g] = f == j + 1 ? 0.0 : x;
+        X[g] = f <= j + 2 ? 0.0 : x;
         if (f >= j + 3) part = fma(x, x, part);
         if (f == j + 2) one[1] = x;
         if (f == j + 1 && mem == 0) dout[jr + 1] = x;
