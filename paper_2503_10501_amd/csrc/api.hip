@@ -89,6 +89,10 @@ int make_plan(const tc_params* p, Plan* pl) {
     q.off_td_fail = take(B * 4);
   }
   q.off_gpart = take(gram_reserve_bytes(q));
+  q.off_gslice = take(gram_slice_reserve_bytes(q));
+  q.off_grow = take(B * Np * 4);   // per row: scale of the digits
+  q.off_gleft = take(B * Np * 16); // ... and the columns of up to eight values that are added apart
+  q.off_ginexact = take(B * 4);
   q.total = off > 0 ? off : 256;
   // A workspace also serves calls with fewer tokens (tc_info_rank on a subset of rows is one): just above the largest
   // reduction the tridiagonal route needs more than the iteration.
@@ -146,7 +150,7 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
     void* G = at<char>(ws, pl.off_G);
     void* U = at<char>(ws, pl.off_U);
     EigState* state = at<EigState>(ws, pl.off_state);
-    if ((rc = launch_gram(pl, p->dtype, p->eig_dtype, O, G, at<double>(ws, pl.off_gpart), st)) != TC_OK) return rc;
+    if ((rc = launch_gram(pl, p->dtype, p->eig_dtype, O, G, ws, 0, st)) != TC_OK) return rc;
     if ((rc = launch_jacobi(pl, p->eig_dtype, G, U, at<char>(ws, pl.off_R), at<double>(ws, pl.off_offpart), state, st)) != TC_OK)
       return rc;
     return launch_scores(pl, p->eig_dtype, G, U, state, S, p->lambda, p->norm_mode, p->sv_rtol, at<char>(ws, pl.off_sig),
@@ -175,8 +179,7 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
                             at<float>(ws, pl.off_Spart) + i0 * pl.spart_stride, streams[g]);
       if (rc != TC_OK) break;
     }
-    rc = launch_gram(sub, p->dtype, p->eig_dtype, Og, at<double>(ws, pl.off_G) + i0 * pl.Np * pl.Np,
-                     at<double>(ws, pl.off_gpart) + i0 * (gram_part_bytes(pl) / 8), streams[g]);
+    rc = launch_gram(sub, p->dtype, p->eig_dtype, Og, at<double>(ws, pl.off_G) + i0 * pl.Np * pl.Np, ws, img0, streams[g]);
     if (rc != TC_OK) break;
     // the next group's attention and Gram kernels (which fill the chip) start when this group's are done, so
     // that the groups' reductions start one after the other and their tails do not all come at the end

@@ -78,6 +78,10 @@ __device__ inline TOut* place_in_g(TOut* Gb, int Np, int ti, int tj, int r, int 
   return Gb + (size_t)(ti * 64 + 8 * r + (tid >> 5)) * Np + tj * 64 + ((2 * tid) & 63);
 }
 
+// rows without an exact slicing that are formed again one by one; with more the whole image is
+__host__ __device__ constexpr int most_inexact(int N) { return N / 16; }
+static_assert(most_inexact(MAX_NVIS) <= 1024, "the list of such rows");
+
 template <typename TOut>
 __device__ inline void store_tile(const double (*acc)[2], TOut* __restrict__ Gb, int Np, int ti, int tj, int tid) {
   typedef __attribute__((ext_vector_type(2))) TOut o2;
@@ -100,13 +104,15 @@ __device__ inline void store_tile(const double (*acc)[2], TOut* __restrict__ Gb,
 
 template <typename TIn, typename TOut>
 __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TOut* __restrict__ G, int N, int D,
-                                                   int Np, int B, int splits, double* __restrict__ part) {
+                                                   int Np, int B, int splits, double* __restrict__ part,
+                                                   const int32_t* __restrict__ inexact) {
   typedef __attribute__((ext_vector_type(2))) double d2;
   __shared__ __attribute__((aligned(16))) double As[GK][GLD];
   __shared__ __attribute__((aligned(16))) double Bs[GK][GLD];
   const int ntile = Np / 64;
   int b, t;
   if (!group_on_xcd(blockIdx.x, ntile * (ntile + 1) / 2 * splits, B, &b, &t)) return;
+  if (inexact && inexact[b] <= most_inexact(N)) return;  // the slices have formed this image's products
   const int split = t % splits;
   t /= splits;
   double* mine = part + (((size_t)b * (ntile * (ntile + 1) / 2) + t) * (splits - parts_in_g<TOut>()) + split - parts_in_g<TOut>()) * 4096;
@@ -205,6 +211,302 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict_
   store_tile<TOut>(acc, Gb, Np, ti, t, tid);
 }
 
+// ---- 16-bit rows: the products in whole numbers, exact -------------------------------------------------------------
+// The float64 matrix cores bound the kernel above (74 % busy); the 8-bit integer ones do sixty times the operations.  A row of
+// 16-bit values, scaled by a power of two that brings its largest to 31 bits, is a row of whole numbers unless one of its
+// values lies below about 2^-23 of the largest (one value in a million of attention outputs).  Four signed digits to the base
+// 256 each, sixteen digit products per product, summed in 32 bits by the weight of the digits (seven sums; D <= 16384 keeps
+// them below 2^31), joined in 64 bits and rounded once: no sum of float64 products is closer.  Values that are
+// not whole numbers are added in float64, rows with more than a few, an infinity or NaN are formed again in float64
+// (gram_rows_kernel), an image with many such rows by gram_kernel.
+// The digits lie in memory as the matrix instruction takes them: [32 rows][32 columns of O][digit][lane][16], lane l holds row
+// l % 32, columns 16 (l / 32) ..; a fragment is 1 KB in one piece, and copies to LDS and reads from it have no bank conflicts.
+typedef __attribute__((ext_vector_type(4))) int i4;
+typedef __attribute__((ext_vector_type(16))) int i16v;
+
+__device__ inline uint32_t bits16(uint16_t v) { return v; }
+__device__ inline uint32_t bits16(f16_t v) { return v.bits; }
+template <typename TIn> __device__ inline float widen1(uint32_t bits) {
+  float lo, hi;
+  unpack2<TIn>(bits, &lo, &hi);
+  return lo;
+}
+
+// Per row: the exponent of its scale and how many of its values are no whole numbers (their columns are listed and they count
+// as zero in the digits); ROW_WHOLE where they are more, or one is not finite.
+constexpr int ROW_LIST = 8, ROW_WHOLE = 15;
+__device__ inline int row_scale(int info) { return info >> 4; }
+__device__ inline int row_left(int info) { return info & 15; }
+
+// One workgroup: eight rows, read once and kept in registers until their largest value is known.  Bound by memory: 2 bytes an element in,
+// 4 out (64 images of 576 x 4096: 32 rows a workgroup, read twice, took 222 us; one image 23).
+template <typename TIn, int ITER>  // ITER: runs of 16 columns per thread, D <= 2048 ITER
+__global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict__ O, char* __restrict__ P, int32_t* __restrict__ rowinfo,
+                                                          uint16_t* __restrict__ left, int N, int D, int Np) {
+  constexpr uint32_t INF = __is_same(TIn, f16_t) ? 0x7c00u : 0x7f80u;
+  __shared__ uint32_t most[16][8];
+  __shared__ int cnt[8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.y;
+  const int r = tid & 7, row = blockIdx.x * 8 + r;
+  const TIn* src = O + ((size_t)b * N + min(row, N - 1)) * D;
+  const int runs = row < N ? D / 16 : 0;
+  uint4 in[ITER][2];
+#pragma unroll
+  for (int i = 0; i < ITER; i++) {
+    const int c = (tid >> 3) + 128 * i;
+    in[i][0] = in[i][1] = uint4{0, 0, 0, 0};
+    if (c < runs) {
+      in[i][0] = *reinterpret_cast<const uint4*>(src + c * 16);
+      in[i][1] = *reinterpret_cast<const uint4*>(src + c * 16 + 8);
+    }
+  }
+  uint32_t m = 0;
+#pragma unroll
+  for (int i = 0; i < ITER; i++) {
+    const uint32_t w[8] = {in[i][0].x, in[i][0].y, in[i][0].z, in[i][0].w, in[i][1].x, in[i][1].y, in[i][1].z, in[i][1].w};
+#pragma unroll
+    for (int k = 0; k < 8; k++) m = max(m, max(w[k] & 0x7fffu, (w[k] >> 16) & 0x7fffu));
+  }
+#pragma unroll
+  for (int o = 8; o < 64; o <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+  if (lane < 8) most[wave][lane] = m;
+  if (tid < 8) cnt[tid] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; k++) m = max(m, most[k][r]);
+  int s = 0;
+  if (m != 0 && m < INF) {
+    int ex;
+    const float mant = frexpf(widen1<TIn>(m), &ex);  // [0.5, 1): at most 11 bits, so that 2^31 of it is a whole number
+    s = (int)ldexpf(mant, 31) > 0x7f7f7f7f ? 30 - ex : 31 - ex;  // 0x7f7f7f7f: the largest number of four signed digits
+  }
+  const bool finite = m < INF;
+  uint16_t* list = left + ((size_t)b * Np + row) * ROW_LIST;
+  char* dst = P + ((size_t)b * (Np / 32) + row / 32) * (D / 32) * 4096 + (row & 31) * 16;
+#pragma unroll
+  for (int i = 0; i < ITER; i++) {
+    const int c = (tid >> 3) + 128 * i;
+    if (c >= D / 16) break;
+    const uint32_t w[8] = {in[i][0].x, in[i][0].y, in[i][0].z, in[i][0].w, in[i][1].x, in[i][1].y, in[i][1].z, in[i][1].w};
+    i4 out[4];
+    uint32_t off = 0;
+#pragma unroll
+    for (int g = 0; g < 4; g++) {  // four columns: their 16 digits, turned
+      uint32_t t[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        float lo, hi;
+        unpack2<TIn>(w[2 * g + k / 2], &lo, &hi);
+        const float x = k & 1 ? hi : lo, v = ldexpf(x, s);
+        int q = finite ? (int)v : 0;
+        if ((float)q != v || (q == 0 && x != 0.f)) {  // (a value that vanished in the scaling, too)
+          off |= 1u << (4 * g + k);
+          q = 0;
+        }
+        t[k] = ((uint32_t)q + 0x00808080u) ^ 0x00808080u;
+      }
+      const uint32_t a01 = __builtin_amdgcn_perm(t[1], t[0], 0x05010400u), b01 = __builtin_amdgcn_perm(t[1], t[0], 0x07030602u);
+      const uint32_t a23 = __builtin_amdgcn_perm(t[3], t[2], 0x05010400u), b23 = __builtin_amdgcn_perm(t[3], t[2], 0x07030602u);
+      out[0][g] = (int)__builtin_amdgcn_perm(a23, a01, 0x05040100u);
+      out[1][g] = (int)__builtin_amdgcn_perm(a23, a01, 0x07060302u);
+      out[2][g] = (int)__builtin_amdgcn_perm(b23, b01, 0x05040100u);
+      out[3][g] = (int)__builtin_amdgcn_perm(b23, b01, 0x07060302u);
+    }
+#pragma unroll
+    for (int d = 0; d < 4; d++) *reinterpret_cast<i4*>(dst + (size_t)(c >> 1) * 4096 + d * 1024 + (c & 1) * 512) = out[d];
+    while (off) {  // (rare)
+      const int k = __ffs(off) - 1;
+      off &= off - 1;
+      const int at = atomicAdd(&cnt[r], 1);
+      if (at < ROW_LIST) list[at] = (uint16_t)(c * 16 + k);
+    }
+  }
+  __syncthreads();
+  if (tid < 8) {  // (row is the thread's own)
+    const int n = cnt[tid];
+    if (n > 1 && n <= ROW_LIST)  // ascending, so that sums over the list have one order
+      for (int i = 1; i < n; i++) {
+        const uint16_t v = list[i];
+        int k = i;
+        for (; k > 0 && list[k - 1] > v; k--) list[k] = list[k - 1];
+        list[k] = v;
+      }
+    rowinfo[(size_t)b * Np + row] = s * 16 + (finite && n <= ROW_LIST ? n : ROW_WHOLE);
+  }
+}
+
+// One workgroup: a 64x64 tile (ti >= tj), mirrored; a wavefront one quadrant, its seven sums in registers.  A chunk of 64
+// columns comes to LDS without passing through registers, goes from there to registers as a whole, and the next chunk's copy
+// runs while the matrix cores work on it; two workgroups share a compute unit.
+template <typename TOut>
+__global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restrict__ P, const int32_t* __restrict__ rowinfo,
+                                                             TOut* __restrict__ G, int KB, int Np, int B) {
+  typedef __attribute__((ext_vector_type(4))) TOut o4;
+  __shared__ __attribute__((aligned(16))) char L[32768];  // [row blocks of A, of B][2 blocks of 32 columns][digit][1 KB]
+  const int ntile = Np / 64;
+  int b, t;
+  if (!group_on_xcd(blockIdx.x, ntile * (ntile + 1) / 2, B, &b, &t)) return;
+  int ti = 0;
+  while (t >= ti + 1) { t -= ti + 1; ti++; }
+  const int tj = t;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = wave >> 1, wc = wave & 1;
+  const bool diag = ti == tj, idle = diag && wave == 1;  // (the mirror of wavefront 2's quadrant)
+  const int rb = (wave < 2 ? 2 * ti : 2 * tj) + (wave & 1);  // the row block this wavefront copies
+  const char* src = P + ((size_t)b * (Np / 32) + rb) * KB * 4096 + lane * 16;
+  auto copy = [&](int kb) {
+    if (diag && wave >= 2) return;
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (size_t)kb * 4096 + i * 1024),
+                                       (__attribute__((address_space(3))) void*)(L + wave * 8192 + i * 1024), 16, 0, 0);
+  };
+  i16v acc[7];
+#pragma unroll
+  for (int c = 0; c < 7; c++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) acc[c][r] = 0;
+  const char* la = L + wr * 8192 + lane * 16;
+  const char* lb = L + (diag ? wc : 2 + wc) * 8192 + lane * 16;
+  copy(0);
+  for (int kb = 0; kb < KB; kb += 2) {  // (D is a multiple of 64)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's copies have landed ...
+    __syncthreads();                                  // ... and everyone's
+    i4 fa[2][4], fb[2][4];
+    if (!idle) {
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int d = 0; d < 4; d++) {
+          fa[h][d] = *reinterpret_cast<const i4*>(la + h * 4096 + d * 1024);
+          fb[h][d] = *reinterpret_cast<const i4*>(lb + h * 4096 + d * 1024);
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();  // the chunk is in registers: its place is free
+    if (kb + 2 < KB) copy(kb + 2);
+    if (idle) continue;
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int x = 0; x < 4; x++)
+#pragma unroll
+        for (int y = 0; y < 4; y++)
+          acc[x + y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[h][x], fb[h][y], acc[x + y], 0, 0, 0);
+  }
+  if (idle) return;
+  TOut* Gb = G + (size_t)b * Np * Np;
+  const int32_t* info = rowinfo + (size_t)b * Np;
+  const int r0 = ti * 64 + wr * 32 + 4 * (lane >> 5), col = tj * 64 + wc * 32 + (lane & 31);
+  const int sc = row_scale(info[col]);
+#pragma unroll
+  for (int g = 0; g < 4; g++) {  // four rows side by side
+    o4 v;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const int r = 4 * g + k, row = r0 + 8 * g + k;
+      const long long hi = ((long long)acc[6][r] << 16) + ((long long)acc[5][r] << 8) + acc[4][r];
+      const long long lo = ((long long)acc[3][r] << 24) + ((long long)acc[2][r] << 16) + ((long long)acc[1][r] << 8) + acc[0][r];
+      const double x = fma((double)hi, 4294967296.0, (double)lo);  // both are whole numbers below 2^53: one rounding
+      v[k] = (TOut)ldexp(x, -(sc + row_scale(info[row])));
+      Gb[(size_t)row * Np + col] = v[k];
+    }
+    if (!diag || wave == 2) *reinterpret_cast<o4*>(&Gb[(size_t)col * Np + r0 + 8 * g]) = v;
+  }
+}
+
+// What the digits leave out, in float64.  Rows with a few values left: the products of those (their columns of O: 40 KB a
+// value, where the row anew reads the whole of O; 64 images of 576 x 4096 95 us).  Rows with many: the row anew.  One
+// workgroup 64 columns; an entry of G and its mirror have one writer, the row of the two that is first in the lists.
+template <typename TIn, typename TOut>
+__global__ __launch_bounds__(1024) void gram_rows_kernel(const TIn* __restrict__ O, const int32_t* __restrict__ rowinfo,
+                                                         const uint16_t* __restrict__ left, TOut* __restrict__ G,
+                                                         int32_t* __restrict__ inexact, int N, int D, int Np) {
+  __shared__ int cnt, few, list[1024];
+  __shared__ uint16_t flist[MAX_NVIS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.y;
+  if (tid == 0) cnt = few = 0;
+  __syncthreads();
+  const int32_t* info = rowinfo + (size_t)b * Np;
+  for (int i = tid; i < N; i += 1024) {
+    const int n = row_left(info[i]);
+    if (n == ROW_WHOLE) {
+      const int at = atomicAdd(&cnt, 1);  // (any order: the rows do not depend on one another)
+      if (at < 1024) list[at] = i;
+    } else if (n > 0) {
+      flist[atomicAdd(&few, 1)] = (uint16_t)i;
+    }
+  }
+  __syncthreads();
+  const int n = cnt;
+  if (tid == 0 && blockIdx.x == 0) inexact[b] = n;
+  if (n > most_inexact(N)) return;
+  const TIn* Ob = O + (size_t)b * N * D;
+  TOut* Gb = G + (size_t)b * Np * Np;
+  const int col = blockIdx.x * 64 + lane, cinfo = col < N ? row_left(info[col]) : ROW_WHOLE;
+  if (cinfo != ROW_WHOLE)
+    for (int e = wave; e < few; e += 16) {
+      const int row = flist[e], rn = row_left(info[row]);
+      if (cinfo > 0 && col < row) continue;  // the other row's entry
+      const uint16_t* lr = left + ((size_t)b * Np + row) * ROW_LIST;
+      const uint16_t* lc = left + ((size_t)b * Np + col) * ROW_LIST;
+      double add = 0.0;
+      for (int i = 0; i < rn; i++) {
+        const int k = lr[i];
+        add = fma((double)widen1<TIn>(bits16(Ob[(size_t)row * D + k])), (double)widen1<TIn>(bits16(Ob[(size_t)col * D + k])), add);
+      }
+      for (int i = 0; i < cinfo; i++) {  // of the column's own those that the row's list does not hold
+        const int k = lc[i];
+        bool both = false;
+        for (int j = 0; j < rn; j++) both |= lr[j] == k;
+        if (!both) add = fma((double)widen1<TIn>(bits16(Ob[(size_t)row * D + k])), (double)widen1<TIn>(bits16(Ob[(size_t)col * D + k])), add);
+      }
+      const TOut v = (TOut)((double)Gb[(size_t)row * Np + col] + add);
+      Gb[(size_t)row * Np + col] = v;
+      if (row != col) Gb[(size_t)col * Np + row] = v;
+    }
+  const int c0 = blockIdx.x * 64 + wave * 4;
+  for (int e = 0; e < n; e++) {
+    const int row = list[e];
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int k = lane * 8; k < D; k += 512) {
+      double x[8], y[8];
+      widen8<TIn>(fetch8<TIn>(Ob + (size_t)row * D + k), x);
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        widen8<TIn>(fetch8<TIn>(Ob + (size_t)min(c0 + c, N - 1) * D + k), y);
+#pragma unroll
+        for (int i = 0; i < 8; i++) sum[c] = fma(x[i], y[i], sum[c]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      const double v = wave_sum(sum[c]);
+      if (lane == 0 && c0 + c < N) {  // (of two such rows both write the same value)
+        Gb[(size_t)row * Np + c0 + c] = (TOut)v;
+        Gb[(size_t)(c0 + c) * Np + row] = (TOut)v;
+      }
+    }
+  }
+}
+
+// Room for the digits of a call's images, 4 bytes an element: at most 1 GiB (or one image); more images go in turns.
+static size_t slice_bytes(const Plan& pl) { return (size_t)pl.Np * pl.D * 4; }
+// Digits for 16-bit rows of calls with work for the chip.  A tile is a chain of D / 64 chunks (0.85 us each) by one workgroup; below
+// that gram_kernel's shared tiles end sooner.  All launches of the step, float64 and digits, us: D = 4096, images of 576 tokens
+// 65 and 77 (one, 45 tiles), 111 and 79 (two, 90); of 256 tokens 52 and 75 (four, 40), 120 and 83 (sixteen, 160); 64 of 64
+// tokens 48 and 74; one of 2880 717 and 275; D = 1024, 16 of 192 tokens (96 tiles) 31 and 37, 64 of 128 (192) 40 and 40.
+// By the size of the whole call, as for the parts.
+static bool use_slices(const Plan& pl) {
+  const long long nt = pl.Np / 64, tiles = nt * (nt + 1) / 2 * pl.batch_call;
+  return pl.esize == 2 && pl.D <= 16384 && tiles >= 80 && tiles * pl.D >= 200000;
+}
+size_t gram_slice_reserve_bytes(const Plan& pl) {
+  if (!use_slices(pl)) return 0;
+  const size_t image = slice_bytes(pl), lim = (size_t)1 << 30, all = image * pl.B;
+  return all < lim ? all : (image > lim ? image : lim);
+}
+
 // Workgroups per tile: as many as keep the launch within three per compute unit, with at least eight chunks each and no more
 // than 3 MiB of parts per image: a workspace stays in proportion to the batch (one image of 576 x 4096 needs 14 MB; eight
 // workgroups per tile would add 7 to save another 0.012 ms of 2.5).  By the size of the whole call: the order of a sum
@@ -220,7 +522,7 @@ int gram_splits(const Plan& pl) {
   while (s < 8 && tiles * (s + 1) <= 768 && pl.D / GK >= 8 * (s + 1) && part_bytes(pl, s + 1) <= (3u << 20)) s++;
   return s;
 }
-size_t gram_part_bytes(const Plan& pl) { return part_bytes(pl, gram_splits(pl)); }
+static size_t gram_part_bytes(const Plan& pl) { return part_bytes(pl, gram_splits(pl)); }
 // What a plan sets aside for the parts of all its images.  The parts themselves get fewer where another tile or image takes
 // away a workgroup per tile; a workspace must not, since a smaller call has to fit it: an image has at most 3 MiB and at most as
 // many parts as D allows, a call at most a part for each of its 768 workgroups.
@@ -232,17 +534,41 @@ size_t gram_reserve_bytes(const Plan& pl) {
 }
 
 template <typename TIn, typename TOut>
-static void run_gram(const Plan& pl, const void* O, void* G, double* part, hipStream_t st) {
+static void run_gram(const Plan& pl, const void* O, void* G, void* ws, int img0, hipStream_t st) {
   const int nt = pl.Np / 64, tiles = nt * (nt + 1) / 2, splits = gram_splits(pl);
-  TC_TIMED(PK_GRAM, 0, st, (gram_kernel<TIn, TOut><<<grid_for_groups(tiles * splits, pl.B), 256, 0, st>>>((const TIn*)O, (TOut*)G, pl.N, pl.D, pl.Np, pl.B, splits, part)));
+  if constexpr (sizeof(TIn) == 2) {
+    if (use_slices(pl)) {
+      char* P = at<char>(ws, pl.off_gslice);  // (stream groups form their matrices one after the other)
+      int32_t* info = at<int32_t>(ws, pl.off_grow) + (size_t)img0 * pl.Np;
+      uint16_t* left = at<uint16_t>(ws, pl.off_gleft) + (size_t)img0 * pl.Np * ROW_LIST;
+      int32_t* inexact = at<int32_t>(ws, pl.off_ginexact) + img0;
+      const auto slice = pl.D <= 4096 ? gram_slice_kernel<TIn, 2> : (pl.D <= 8192 ? gram_slice_kernel<TIn, 4> : gram_slice_kernel<TIn, 8>);
+      const size_t fit = gram_slice_reserve_bytes(pl) / slice_bytes(pl);
+      const int turns = pl.B > 0 ? (int)((pl.B + fit - 1) / fit) : 0;
+      for (int k = 0; k < turns; k++) {
+        const int first = (int)((long long)pl.B * k / turns), n = (int)((long long)pl.B * (k + 1) / turns) - first;
+        const TIn* Ok = (const TIn*)O + (size_t)first * pl.N * pl.D;
+        TOut* Gk = (TOut*)G + (size_t)first * pl.Np * pl.Np;
+        int32_t* ik = info + (size_t)first * pl.Np;
+        TC_TIMED(PK_GRAM, 2, st, (slice<<<dim3(pl.Np / 8, n), 1024, 0, st>>>(Ok, P, ik, left + (size_t)first * pl.Np * ROW_LIST, pl.N, pl.D, pl.Np)));
+        TC_TIMED(PK_GRAM, 0, st, (gram_slices_kernel<TOut><<<grid_for_groups(tiles, n), 256, 0, st>>>(P, ik, Gk, pl.D / 32, pl.Np, n)));
+      }
+      TC_TIMED(PK_GRAM, 3, st, (gram_rows_kernel<TIn, TOut><<<dim3(nt, pl.B), 1024, 0, st>>>((const TIn*)O, info, left, (TOut*)G, inexact, pl.N, pl.D, pl.Np)));
+      TC_TIMED(PK_GRAM, 1, st, (gram_kernel<TIn, TOut><<<grid_for_groups(tiles, pl.B), 256, 0, st>>>((const TIn*)O, (TOut*)G, pl.N, pl.D, pl.Np, pl.B, 1, nullptr, inexact)));
+      return;
+    }
+  }
+  double* part = at<double>(ws, pl.off_gpart) + img0 * (gram_part_bytes(pl) / 8);
+  TC_TIMED(PK_GRAM, 0, st, (gram_kernel<TIn, TOut><<<grid_for_groups(tiles * splits, pl.B), 256, 0, st>>>((const TIn*)O, (TOut*)G, pl.N, pl.D, pl.Np, pl.B, splits, part, nullptr)));
   if (splits > 1) TC_TIMED(PK_GRAM, 1, st, (gram_sum_kernel<TOut><<<dim3(tiles, pl.B), 256, 0, st>>>(part, (TOut*)G, pl.Np, splits)));
 }
 
-int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, double* part, hipStream_t st) {
+// O and G of the images img0 .. img0 + pl.B - 1 of the call; the scratch is the call's.
+int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, void* ws, int img0, hipStream_t st) {
   const bool f64 = eig_dtype == TC_EIG_F64;
-  if (dtype == TC_BF16) f64 ? run_gram<uint16_t, double>(pl, O, G, part, st) : run_gram<uint16_t, float>(pl, O, G, part, st);
-  else if (dtype == TC_F16) f64 ? run_gram<f16_t, double>(pl, O, G, part, st) : run_gram<f16_t, float>(pl, O, G, part, st);
-  else f64 ? run_gram<float, double>(pl, O, G, part, st) : run_gram<float, float>(pl, O, G, part, st);
+  if (dtype == TC_BF16) f64 ? run_gram<uint16_t, double>(pl, O, G, ws, img0, st) : run_gram<uint16_t, float>(pl, O, G, ws, img0, st);
+  else if (dtype == TC_F16) f64 ? run_gram<f16_t, double>(pl, O, G, ws, img0, st) : run_gram<f16_t, float>(pl, O, G, ws, img0, st);
+  else f64 ? run_gram<float, double>(pl, O, G, ws, img0, st) : run_gram<float, float>(pl, O, G, ws, img0, st);
   return check_launch();
 }
 

@@ -81,7 +81,7 @@ extern "C" int tc_info_rank(const tc_params* p, const void* O, const int32_t* ro
   }
   void* G = at<char>(ws, pl.off_G);
   EigState* state = at<EigState>(ws, pl.off_state);
-  if ((rc = launch_gram(pl, p->dtype, p->eig_dtype, Osub, G, at<double>(ws, pl.off_gpart), st)) != TC_OK) return rc;
+  if ((rc = launch_gram(pl, p->dtype, p->eig_dtype, Osub, G, ws, 0, st)) != TC_OK) return rc;
   if (pl.method == TC_EIG_TRIDIAGONAL && tridiag_allowed(pl.N, st)) {  // eigenvalues only: reduction and bisection, no vectors
     if ((rc = direct_eigenvalues(pl, &q, sigma, info, ws, st)) != TC_OK) return rc;
   } else {

@@ -55,7 +55,7 @@ struct Plan {
   double tol;
   float scale;
   size_t off_O, off_S, off_Spart, off_G, off_U, off_R, off_offpart, off_state, off_sig, off_C, off_E, off_order,
-      off_rnorm, off_sim, off_mlist, off_info, off_gpart;
+      off_rnorm, off_sim, off_mlist, off_info, off_gpart, off_gslice, off_grow, off_gleft, off_ginexact;
   size_t off_td_d, off_td_e, off_td_tau, off_td_lam, off_td_blk, off_td_tnorm, off_td_rn, off_td_bad, off_td_wgt,
       off_td_W, off_td_mark, off_td_Cpart, off_td_Tf, off_td_sync, off_td_fail;  // direct eigensolver only
   size_t td_sync_bytes;  // exchange memory of the reduction, per image
@@ -79,9 +79,9 @@ inline int check_ws(const Plan& pl, const void* ws, size_t ws_bytes) {
 // ---- stage launchers (each returns a tc_status; all work is enqueued on `st`) ----------
 int launch_attention(const Plan& pl, int dtype, int causal, const void* Q, const void* K, const void* V, void* O,
                      float* S, float* Spart, hipStream_t st);
-size_t gram_part_bytes(const Plan& pl);     // partial sums of one image
-size_t gram_reserve_bytes(const Plan& pl);  // room for those of the call
-int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, double* part, hipStream_t st);
+size_t gram_reserve_bytes(const Plan& pl);        // room for the partial sums of the call
+size_t gram_slice_reserve_bytes(const Plan& pl);  // room for the digits of 16-bit rows
+int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, void* ws, int img0, hipStream_t st);
 int launch_jacobi(const Plan& pl, int eig_dtype, void* G, void* U /* nullptr: eigenvalues only */, void* R,
                   double* offpart, EigState* state, hipStream_t st);
 int launch_scores(const Plan& pl, int eig_dtype, const void* G, const void* U, const EigState* state,
