@@ -18,7 +18,7 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK = {"hbm_gbps": 8000.0, "mfma_bf16": 2500.0, "mfma_f64": 78.6, "mfma_f32": 157.3, "vec_f64": 78.6, "vec_f32": 157.3}
+PEAK = {"hbm_gbps": 8000.0, "mfma_bf16": 2500.0, "mfma_f64": 78.6, "mfma_i8": 5000.0, "mfma_f32": 157.3, "vec_f64": 78.6, "vec_f32": 157.3}
 
 
 # ---- algorithmic work per batch (what the method must move or compute) ---------------------------------------
@@ -171,7 +171,9 @@ def main():
         "a1_a2_attention": entry("attn", "mfma", attn_t, PEAK["mfma_bf16"] if w.dtype != "f32" else PEAK["vec_f32"], "TFLOP/s",
                                  ms=ms("attn"), flop_per_byte=round(attn_ai, 1),
                                  frac_of_min_mfma_hbm=None if attn_t is None else round(attn_t / attn_cap, 4)),
-        "a3_gram": entry("gram", "mfma", rate(wm["gram_flops"], "gram", "T"), PEAK["mfma_f64"], "TFLOP/s", ms=ms("gram"),
+        # 16-bit rows: sixteen products of 8-bit digits per product
+        "a3_gram": entry("gram", "mfma", rate(wm["gram_flops"] * (1 if w.dtype == "f32" else 16), "gram", "T"),
+                         PEAK["mfma_f64" if w.dtype == "f32" else "mfma_i8"], "TFLOP/s" if w.dtype == "f32" else "TOP/s", ms=ms("gram"),
                          hbm_gbps=None if not ms("gram") else round(rate(wm["gram_bytes"], "gram", "G"), 1)),
         "a8_similarity": entry("sim", "hbm", rate(wm["sim_bytes"], "sim", "G"), PEAK["hbm_gbps"], "GB/s", ms=ms("sim"),
                                mfma_tflops=None if not ms("sim") else round(rate(wm["sim_flops"], "sim", "T"), 2)),

@@ -337,7 +337,8 @@ __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict_
 
 // One workgroup: a 64x64 tile (ti >= tj), mirrored; a wavefront one quadrant, its seven sums in registers.  A chunk of 64
 // columns comes to LDS without passing through registers, goes from there to registers as a whole, and the next chunk's copy
-// runs while the matrix cores work on it; two workgroups share a compute unit.
+// runs while the matrix cores work on it; two workgroups share a compute unit.  64 images of 576 x 4096: 0.555 ms, 2.8 P operations/s
+// (three workgroups, with half of a chunk in registers at a time: 0.562; 8 images of 2880 1.64 and 1.74 ms).
 template <typename TOut>
 __global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restrict__ P, const int32_t* __restrict__ rowinfo,
                                                              TOut* __restrict__ G, int KB, int Np, int B) {
@@ -492,17 +493,21 @@ __global__ __launch_bounds__(1024) void gram_rows_kernel(const TIn* __restrict__
 
 // Room for the digits of a call's images, 4 bytes an element: at most 1 GiB (or one image); more images go in turns.
 static size_t slice_bytes(const Plan& pl) { return (size_t)pl.Np * pl.D * 4; }
-// Digits for 16-bit rows of calls with work for the chip.  A tile is a chain of D / 64 chunks (0.85 us each) by one workgroup; below
-// that gram_kernel's shared tiles end sooner.  All launches of the step, float64 and digits, us: D = 4096, images of 576 tokens
-// 65 and 77 (one, 45 tiles), 111 and 79 (two, 90); of 256 tokens 52 and 75 (four, 40), 120 and 83 (sixteen, 160); 64 of 64
-// tokens 48 and 74; one of 2880 717 and 275; D = 1024, 16 of 192 tokens (96 tiles) 31 and 37, 64 of 128 (192) 40 and 40.
-// By the size of the whole call, as for the parts.
+// Digits for 16-bit rows of calls with work for the chip.  A tile is a chain of D / 64 chunks (0.85 us each) by one workgroup, where
+// gram_kernel shares a small call's tiles, and an image of one tile has a fourth of it idle in gram_kernel but not here.  All
+// launches of the step, float64 and digits, us: D = 4096, 64 images of 64 tokens 47 and 79, 256 of them 144 and 164; 27 of 128
+// (81 tiles) 66 and 87, 48 (144) 98 and 89; 10 of 256 (100) 79 and 91; where the parts leave three workgroups or fewer to a tile, one
+// image of 576 (45) 65 and 77, two (90) 111 and 79; one of 2880 717 and 275; D = 1024, 64 of 128 (192) 40 and 40, 20 of 256 (200)
+// 49 and 41.  By the size of the whole call, as for the parts.
+int gram_splits(const Plan& pl);
 static bool use_slices(const Plan& pl) {
   const long long nt = pl.Np / 64, tiles = nt * (nt + 1) / 2 * pl.batch_call;
-  return pl.esize == 2 && pl.D <= 16384 && tiles >= 80 && tiles * pl.D >= 200000;
+  return pl.esize == 2 && pl.D <= 16384 && nt > 1 && tiles >= (gram_splits(pl) > 3 ? 128 : 80) && tiles * pl.D >= 200000;
 }
+// A workspace also serves calls of fewer tokens and images: what one that takes this way may need is set aside by the two
+// sizes alone.
 size_t gram_slice_reserve_bytes(const Plan& pl) {
-  if (!use_slices(pl)) return 0;
+  if (pl.esize != 2 || pl.D > 16384 || pl.Np <= 64) return 0;
   const size_t image = slice_bytes(pl), lim = (size_t)1 << 30, all = image * pl.B;
   return all < lim ? all : (image > lim ? image : lim);
 }

@@ -6,10 +6,10 @@ pytestmark = pytest.mark.gpu
 
 
 def _batch(n, D):
-    """So many images that the call takes this way: 80 tiles of 64, and 200 000 columns of theirs."""
+    """So many images that the call takes this way: 128 tiles of 64, and 200 000 columns of theirs."""
     nt = (n + 63) // 64
     tiles = nt * (nt + 1) // 2
-    return max(-(-80 // tiles), -(-200000 // (tiles * D)))
+    return max(-(-128 // tiles), -(-200000 // (tiles * D)))
 
 
 def _sigma(O, heads, head_dim, **kw):
@@ -41,8 +41,8 @@ def _check(O, sigma):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
-@pytest.mark.parametrize("n,heads,head_dim", [(1, 1, 64), (33, 1, 64), (64, 3, 64), (65, 1, 128), (191, 2, 128), (300, 33, 128),
-                                              (70, 65, 128), (70, 128, 128)])
+@pytest.mark.parametrize("n,heads,head_dim", [(65, 1, 64), (96, 3, 64), (128, 1, 128), (191, 2, 128), (300, 33, 128), (70, 65, 128),
+                                              (70, 128, 128)])
 def test_sizes(dtype, n, heads, head_dim):
     B = _batch(n, heads * head_dim)
     O = _rows(B, n, heads * head_dim, dtype, n)
