@@ -283,14 +283,65 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     double* Vn = (j & 1) ? Vb : Va;        // this column's reflector
     const double* Vo = (j & 1) ? Va : Vb;  // the one before
     const int jr = j + base;               // column of the matrix
+    // (with more than three elements a thread, the vectors are read again where they are wanted: no registers hold them)
+    constexpr int K = E > 3 ? 1 : E;
+    double p[E], col[E], v[K], vo[K], wo[K], dot[3] = {0.0, 0.0, 0.0};  // p^T v, w_o^T v, v_o^T v
+    double beta, tau, scal;
+    // Householder reflector that maps x[j+1:] onto beta e_1 (every workgroup and every wavefront for itself), and this
+    // thread's elements of the vectors
+    auto own_values = [&]() {
+      const double xn2 = sum8(red + 8);
+      const double alpha = one[1];
+      beta = alpha;
+      tau = scal = 0.0;
+      if (xn2 > 0.0) {
+        const double n2 = fma(alpha, alpha, xn2), rb = fast_rsq(n2);
+        double nb = n2 * rb;
+        nb = fma(0.5 * rb, fma(-nb, nb, n2), nb);          // |beta| = sqrt(n2)
+        beta = -copysign(nb, alpha);
+        tau = fma(fabs(alpha), rb, 1.0);                   // (beta - alpha) / beta
+        scal = copysign(fast_rcp(fabs(alpha) + nb), alpha);  // 1 / (alpha - beta)
+      }
+#pragma unroll
+      for (int u = 0; u < E; u++) {
+        const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
+        const int q = min(u, K - 1);
+        v[q] = vo[q] = wo[q] = 0.0;
+        if (f > j) {
+          v[q] = f == j + 1 ? 1.0 : X[g] * scal;
+          Vn[g] = v[q];
+          if (b == 0 && (MODE == 0 || ((f >> 3) % PR) == a)) vblk[(f / R * 8 + (f & 7)) * 16 + (jr & 15)] = (float)v[q];
+          if (MODE != 0) {
+            vo[q] = Vo[g];
+            wo[q] = Wv[g];
+            dot[1] = fma(wo[q], v[q], dot[1]);
+            dot[2] = fma(vo[q], v[q], dot[2]);
+          }
+        }
+      }
+      if (MODE != 0) {
+        dot[1] = wave_sum_dpp(dot[1]);
+        dot[2] = wave_sum_dpp(dot[2]);
+      }
+      if (tj == 0) {
+        Vn[tr_at(j)] = 0.0;
+        if (j > 0) Vn[tr_at(j - 1)] = 0.0;
+        if (mem == 0) {
+          eout[jr] = beta;
+          tout[jr] = (float)tau;
+        }
+      }
+    };
     // ---- A x, this workgroup's part -----------------------------------------------------------------------
     // The reflector is v = e_(j+1) + scal x with x the column below its head, so p = A v is the next column plus scal A x:
     // the sweep waits for no norm, and the chain of a square root, a reciprocal and the scaling runs while the parts are on
     // their way.  (With v in the sweep it stood before it: eight images of 2880 tokens 59.6 ms, now 55.6; four of 701 3.45,
     // now 3.39; one of 576 2.53 either way, where issuing the instructions is what takes the time.)
-    // MODE 0: the update with the column before is applied in the same sweep.  Otherwise the product is formed with the
+    // MODE 0: nothing is on its way, so the chain is issued in front of the sweep, which hides it (256 tokens: 602 us with v in
+    // the sweep, 620 with the chain behind it, 590 so).  The update with the column before is applied in the same sweep.  Otherwise the product is formed with the
     // matrix as it is and published, and the update follows while the other workgroups' parts are on their way
     // (below): p and the next column then still lack it, which costs two scalar products.
+    if (MODE == 0) own_values();
     const int kmin = (j + 1) / C;
     const bool owner = MODE != 2 || (((j + 1) >> 6) % pc) == b;
     const int l0 = (j + 1) & 63;
@@ -369,58 +420,9 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     const int slot = (j - js) & 1;
     fresh<MODE != 0>(tj);
     lj = tj & 63;
-    // (with more than three elements a thread, the vectors are read again where they are wanted: no registers hold them)
-    constexpr int K = E > 3 ? 1 : E;
-    double p[E], col[E], v[K], vo[K], wo[K], dot[3] = {0.0, 0.0, 0.0};  // p^T v, w_o^T v, v_o^T v
     auto column_sum = [&](int o) {  // over the wavefronts
       const double* c = csb + o;
       return ((c[0] + c[OWN]) + (c[2 * OWN] + c[3 * OWN])) + ((c[4 * OWN] + c[5 * OWN]) + (c[6 * OWN] + c[7 * OWN]));
-    };
-    double beta, tau, scal;
-    // Householder reflector that maps x[j+1:] onto beta e_1 (every workgroup and every wavefront for itself), and this
-    // thread's elements of the vectors
-    auto own_values = [&]() {
-      const double xn2 = sum8(red + 8);
-      const double alpha = one[1];
-      beta = alpha;
-      tau = scal = 0.0;
-      if (xn2 > 0.0) {
-        const double n2 = fma(alpha, alpha, xn2), rb = fast_rsq(n2);
-        double nb = n2 * rb;
-        nb = fma(0.5 * rb, fma(-nb, nb, n2), nb);          // |beta| = sqrt(n2)
-        beta = -copysign(nb, alpha);
-        tau = fma(fabs(alpha), rb, 1.0);                   // (beta - alpha) / beta
-        scal = copysign(fast_rcp(fabs(alpha) + nb), alpha);  // 1 / (alpha - beta)
-      }
-#pragma unroll
-      for (int u = 0; u < E; u++) {
-        const int f = F - 1 - tj - TR_THREADS * u, g = own_at(tj, u);
-        const int q = min(u, K - 1);
-        v[q] = vo[q] = wo[q] = 0.0;
-        if (f > j) {
-          v[q] = f == j + 1 ? 1.0 : X[g] * scal;
-          Vn[g] = v[q];
-          if (b == 0 && (MODE == 0 || ((f >> 3) % PR) == a)) vblk[(f / R * 8 + (f & 7)) * 16 + (jr & 15)] = (float)v[q];
-          if (MODE != 0) {
-            vo[q] = Vo[g];
-            wo[q] = Wv[g];
-            dot[1] = fma(wo[q], v[q], dot[1]);
-            dot[2] = fma(vo[q], v[q], dot[2]);
-          }
-        }
-      }
-      if (MODE != 0) {
-        dot[1] = wave_sum_dpp(dot[1]);
-        dot[2] = wave_sum_dpp(dot[2]);
-      }
-      if (tj == 0) {
-        Vn[tr_at(j)] = 0.0;
-        if (j > 0) Vn[tr_at(j - 1)] = 0.0;
-        if (mem == 0) {
-          eout[jr] = beta;
-          tout[jr] = (float)tau;
-        }
-      }
     };
     auto update = [&]() {  // A <- A - v w^T - w v^T with the column before
       fresh<true>(tj);
@@ -452,7 +454,6 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       lj = tj & 63;
     };
     if (MODE == 0) {
-      own_values();
 #pragma unroll
       for (int u = 0; u < E; u++) {
         const int f = F - 1 - tj - TR_THREADS * u;
