@@ -339,10 +339,8 @@ __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict_
 // columns comes to LDS without passing through registers, goes from there to registers as a whole, and the next chunk's copy
 // runs while the matrix cores work on it; two workgroups share a compute unit.  64 images of 576 x 4096: 0.555 ms, 2.8 P operations/s
 // (three workgroups, with half of a chunk in registers at a time: 0.562; 8 images of 2880 1.64 and 1.74 ms).
-template <typename TOut>
 __global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restrict__ P, const int32_t* __restrict__ rowinfo,
-                                                             TOut* __restrict__ G, int KB, int Np, int B) {
-  typedef __attribute__((ext_vector_type(4))) TOut o4;
+                                                             double* __restrict__ G, int KB, int Np, int B) {
   __shared__ __attribute__((aligned(16))) char L[32768];  // [row blocks of A, of B][2 blocks of 32 columns][digit][1 KB]
   const int ntile = Np / 64;
   int b, t;
@@ -396,32 +394,32 @@ __global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restr
           acc[x + y] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[h][x], fb[h][y], acc[x + y], 0, 0, 0);
   }
   if (idle) return;
-  TOut* Gb = G + (size_t)b * Np * Np;
+  double* Gb = G + (size_t)b * Np * Np;
   const int32_t* info = rowinfo + (size_t)b * Np;
   const int r0 = ti * 64 + wr * 32 + 4 * (lane >> 5), col = tj * 64 + wc * 32 + (lane & 31);
   const int sc = row_scale(info[col]);
 #pragma unroll
   for (int g = 0; g < 4; g++) {  // four rows side by side
-    o4 v;
+    d4 v;
 #pragma unroll
     for (int k = 0; k < 4; k++) {
       const int r = 4 * g + k, row = r0 + 8 * g + k;
       const long long hi = ((long long)acc[6][r] << 16) + ((long long)acc[5][r] << 8) + acc[4][r];
       const long long lo = ((long long)acc[3][r] << 24) + ((long long)acc[2][r] << 16) + ((long long)acc[1][r] << 8) + acc[0][r];
       const double x = fma((double)hi, 4294967296.0, (double)lo);  // both are whole numbers below 2^53: one rounding
-      v[k] = (TOut)ldexp(x, -(sc + row_scale(info[row])));
+      v[k] = ldexp(x, -(sc + row_scale(info[row])));
       Gb[(size_t)row * Np + col] = v[k];
     }
-    if (!diag || wave == 2) *reinterpret_cast<o4*>(&Gb[(size_t)col * Np + r0 + 8 * g]) = v;
+    if (!diag || wave == 2) *reinterpret_cast<d4*>(&Gb[(size_t)col * Np + r0 + 8 * g]) = v;
   }
 }
 
 // What the digits leave out, in float64.  Rows with a few values left: the products of those (their columns of O: 40 KB a
 // value, where the row anew reads the whole of O; 64 images of 576 x 4096 95 us).  Rows with many: the row anew.  One
 // workgroup 64 columns; an entry of G and its mirror have one writer, the row of the two that is first in the lists.
-template <typename TIn, typename TOut>
+template <typename TIn>
 __global__ __launch_bounds__(1024) void gram_rows_kernel(const TIn* __restrict__ O, const int32_t* __restrict__ rowinfo,
-                                                         const uint16_t* __restrict__ left, TOut* __restrict__ G,
+                                                         const uint16_t* __restrict__ left, double* __restrict__ G,
                                                          int32_t* __restrict__ inexact, int N, int D, int Np) {
   __shared__ int cnt, few, list[1024];
   __shared__ uint16_t flist[MAX_NVIS];
@@ -443,7 +441,7 @@ __global__ __launch_bounds__(1024) void gram_rows_kernel(const TIn* __restrict__
   if (tid == 0 && blockIdx.x == 0) inexact[b] = n;
   if (n > most_inexact(N)) return;
   const TIn* Ob = O + (size_t)b * N * D;
-  TOut* Gb = G + (size_t)b * Np * Np;
+  double* Gb = G + (size_t)b * Np * Np;
   const int col = blockIdx.x * 64 + lane, cinfo = col < N ? row_left(info[col]) : ROW_WHOLE;
   if (cinfo != ROW_WHOLE)
     for (int e = wave; e < few; e += 16) {
@@ -462,7 +460,7 @@ __global__ __launch_bounds__(1024) void gram_rows_kernel(const TIn* __restrict__
         for (int j = 0; j < rn; j++) both |= lr[j] == k;
         if (!both) add = fma((double)widen1<TIn>(bits16(Ob[(size_t)row * D + k])), (double)widen1<TIn>(bits16(Ob[(size_t)col * D + k])), add);
       }
-      const TOut v = (TOut)((double)Gb[(size_t)row * Np + col] + add);
+      const double v = Gb[(size_t)row * Np + col] + add;
       Gb[(size_t)row * Np + col] = v;
       if (row != col) Gb[(size_t)col * Np + row] = v;
     }
@@ -484,8 +482,8 @@ __global__ __launch_bounds__(1024) void gram_rows_kernel(const TIn* __restrict__
     for (int c = 0; c < 4; c++) {
       const double v = wave_sum(sum[c]);
       if (lane == 0 && c0 + c < N) {  // (of two such rows both write the same value)
-        Gb[(size_t)row * Np + c0 + c] = (TOut)v;
-        Gb[(size_t)(c0 + c) * Np + row] = (TOut)v;
+        Gb[(size_t)row * Np + c0 + c] = v;
+        Gb[(size_t)(c0 + c) * Np + row] = v;
       }
     }
   }
@@ -498,16 +496,17 @@ static size_t slice_bytes(const Plan& pl) { return (size_t)pl.Np * pl.D * 4; }
 // launches of the step, float64 and digits, us: D = 4096, 64 images of 64 tokens 47 and 79, 256 of them 144 and 164; 27 of 128
 // (81 tiles) 66 and 87, 48 (144) 98 and 89; 10 of 256 (100) 79 and 91; where the parts leave three workgroups or fewer to a tile, one
 // image of 576 (45) 65 and 77, two (90) 111 and 79; one of 2880 717 and 275; D = 1024, 64 of 128 (192) 40 and 40, 20 of 256 (200)
-// 49 and 41.  By the size of the whole call, as for the parts.
+// 49 and 41.  By the size of the whole call, as for the parts.  A float32 matrix (TC_EIG_F32) keeps gram_kernel: the values that are
+// added apart would find the digits' part already rounded to float32, and round it again.
 int gram_splits(const Plan& pl);
 static bool use_slices(const Plan& pl) {
   const long long nt = pl.Np / 64, tiles = nt * (nt + 1) / 2 * pl.batch_call;
-  return pl.esize == 2 && pl.D <= 16384 && nt > 1 && tiles >= (gram_splits(pl) > 3 ? 128 : 80) && tiles * pl.D >= 200000;
+  return pl.esize == 2 && pl.tsize == 8 && pl.D <= 16384 && nt > 1 && tiles >= (gram_splits(pl) > 3 ? 128 : 80) && tiles * pl.D >= 200000;
 }
 // A workspace also serves calls of fewer tokens and images: what one that takes this way may need is set aside by the two
 // sizes alone.
 size_t gram_slice_reserve_bytes(const Plan& pl) {
-  if (pl.esize != 2 || pl.D > 16384 || pl.Np <= 64) return 0;
+  if (pl.esize != 2 || pl.tsize != 8 || pl.D > 16384 || pl.Np <= 64) return 0;
   const size_t image = slice_bytes(pl), lim = (size_t)1 << 30, all = image * pl.B;
   return all < lim ? all : (image > lim ? image : lim);
 }
@@ -541,7 +540,7 @@ size_t gram_reserve_bytes(const Plan& pl) {
 template <typename TIn, typename TOut>
 static void run_gram(const Plan& pl, const void* O, void* G, void* ws, int img0, hipStream_t st) {
   const int nt = pl.Np / 64, tiles = nt * (nt + 1) / 2, splits = gram_splits(pl);
-  if constexpr (sizeof(TIn) == 2) {
+  if constexpr (sizeof(TIn) == 2 && sizeof(TOut) == 8) {
     if (use_slices(pl)) {
       char* P = at<char>(ws, pl.off_gslice);  // (stream groups form their matrices one after the other)
       int32_t* info = at<int32_t>(ws, pl.off_grow) + (size_t)img0 * pl.Np;
@@ -553,12 +552,12 @@ static void run_gram(const Plan& pl, const void* O, void* G, void* ws, int img0,
       for (int k = 0; k < turns; k++) {
         const int first = (int)((long long)pl.B * k / turns), n = (int)((long long)pl.B * (k + 1) / turns) - first;
         const TIn* Ok = (const TIn*)O + (size_t)first * pl.N * pl.D;
-        TOut* Gk = (TOut*)G + (size_t)first * pl.Np * pl.Np;
+        double* Gk = (double*)G + (size_t)first * pl.Np * pl.Np;
         int32_t* ik = info + (size_t)first * pl.Np;
         TC_TIMED(PK_GRAM, 2, st, (slice<<<dim3(pl.Np / 8, n), 1024, 0, st>>>(Ok, P, ik, left + (size_t)first * pl.Np * ROW_LIST, pl.N, pl.D, pl.Np)));
-        TC_TIMED(PK_GRAM, 0, st, (gram_slices_kernel<TOut><<<grid_for_groups(tiles, n), 256, 0, st>>>(P, ik, Gk, pl.D / 32, pl.Np, n)));
+        TC_TIMED(PK_GRAM, 0, st, (gram_slices_kernel<<<grid_for_groups(tiles, n), 256, 0, st>>>(P, ik, Gk, pl.D / 32, pl.Np, n)));
       }
-      TC_TIMED(PK_GRAM, 3, st, (gram_rows_kernel<TIn, TOut><<<dim3(nt, pl.B), 1024, 0, st>>>((const TIn*)O, info, left, (TOut*)G, inexact, pl.N, pl.D, pl.Np)));
+      TC_TIMED(PK_GRAM, 3, st, (gram_rows_kernel<TIn><<<dim3(nt, pl.B), 1024, 0, st>>>((const TIn*)O, info, left, (double*)G, inexact, pl.N, pl.D, pl.Np)));
       TC_TIMED(PK_GRAM, 1, st, (gram_kernel<TIn, TOut><<<grid_for_groups(tiles, pl.B), 256, 0, st>>>((const TIn*)O, (TOut*)G, pl.N, pl.D, pl.Np, pl.B, 1, nullptr, inexact)));
       return;
     }

@@ -85,6 +85,22 @@ def test_rows_that_are_not_whole_numbers(dtype, bad, left, eig):
             assert float((sigma[b] ** 2 - s ** 2).abs().max() / s.max() ** 2) < 1e-4
 
 
+def test_a_float32_matrix_is_rounded_once():
+    # A call of one image forms all products in one sum of float64, and so does a call of many: the same float32 matrix, the same
+    # iteration, the same bits.  (Added to digits that were float32 already, six small values of a row would round a second time.)
+    from paper_2503_10501_amd import binding as tc
+    g = torch.Generator().manual_seed(3)
+    O = torch.randn(_batch(130, 256), 130, 256, generator=g) * 4096
+    O[:, :, 0] = 20000
+    small = (1 + (2 * torch.randint(0, 512, (O.shape[0], 65, 6), generator=g) + 1) / 1024) * 2.0 ** -7   # odd, a quarter of the unit
+    O[:, :65].scatter_(2, torch.rand(O.shape[0], 65, 255, generator=g).argsort(2)[:, :, :6] + 1, small)
+    O = O.to(torch.float16)
+    many, _ = _sigma(O, 2, 128, eig_dtype=tc.TC_EIG_F32)
+    for b in (0, 1, O.shape[0] - 1):
+        one, _ = _sigma(O[b:b + 1], 2, 128, eig_dtype=tc.TC_EIG_F32)
+        assert torch.equal(many[b], one[0])
+
+
 def test_a_row_with_an_infinity_leaves_the_other_images_alone():
     O = _rows(_batch(130, 256), 130, 256, torch.bfloat16, 5)
     want, _ = _sigma(O, 2, 128)
