@@ -92,7 +92,7 @@ int make_plan(const tc_params* p, Plan* pl) {
   q.off_gslice = take(gram_slice_reserve_bytes(q));
   q.off_grow = take(B * Np * 4);   // per row: scale of the digits
   q.off_gleft = take(B * Np * 16); // ... and the columns of up to eight values that are added apart
-  q.off_ginexact = take(B * 4);
+  q.off_gover = take(B * (Np / 8) * 4);  // per eight rows: what the digits leave out
   q.total = off > 0 ? off : 256;
   // A workspace also serves calls with fewer tokens (tc_info_rank on a subset of rows is one): just above the largest
   // reduction the tridiagonal route needs more than the iteration.

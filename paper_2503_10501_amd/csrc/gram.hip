@@ -78,9 +78,23 @@ __device__ inline TOut* place_in_g(TOut* Gb, int Np, int ti, int tj, int r, int 
   return Gb + (size_t)(ti * 64 + 8 * r + (tid >> 5)) * Np + tj * 64 + ((2 * tid) & 63);
 }
 
-// rows without an exact slicing that are formed again one by one; with more the whole image is
-__host__ __device__ constexpr int most_inexact(int N) { return N / 16; }
-static_assert(most_inexact(MAX_NVIS) <= 1024, "the list of such rows");
+// What the digits of 16-bit rows (below) leave out of an image: single values, and rows that are formed anew, which take as long
+// as D / 128 values.  With much of it gram_kernel forms the image, and the digits' products are not begun.  The line is where
+// adding what is left (gram_rows_kernel) takes six tenths of what the products save; it is not proportional to D, since a value
+// left also costs a row of G.  us: 64 images of 576 x 4096 (1070 saved), 36 values an image 64, 576 322, 1152 490, 1536 618; 4 rows
+// anew 89, 18 256, 24 313; 8 of 2880 x 4096 (3100), 2880 values 1142, 7680 1768; 20 rows 213, 120 1169; 128 of 576 x 1024 (470),
+// 36 values 99, 144 256, 384 511; 18 rows 193, 24 237.
+struct Left { int values, anew; };
+__device__ inline bool too_much(Left l, int N, int D) {
+  return l.values + l.anew * (D / 128.f) > fmaxf((float)N * (D - 768) / 1280.f, N / 8.f);
+}
+// Of an image, from its blocks of eight rows (rows anew in the upper half of a word); every wavefront asks for itself.
+__device__ inline Left image_left(const int32_t* __restrict__ blocks, int Np) {
+  int n = 0;
+  for (int i = threadIdx.x & 63; i < Np / 8; i += 64) n += blocks[i];
+  n = wave_sum(n);
+  return {n & 0xffff, n >> 16};  // (at most 32768 values)
+}
 
 template <typename TOut>
 __device__ inline void store_tile(const double (*acc)[2], TOut* __restrict__ Gb, int Np, int ti, int tj, int tid) {
@@ -105,14 +119,14 @@ __device__ inline void store_tile(const double (*acc)[2], TOut* __restrict__ Gb,
 template <typename TIn, typename TOut>
 __global__ __launch_bounds__(256) void gram_kernel(const TIn* __restrict__ O, TOut* __restrict__ G, int N, int D,
                                                    int Np, int B, int splits, double* __restrict__ part,
-                                                   const int32_t* __restrict__ inexact) {
+                                                   const int32_t* __restrict__ left_over) {
   typedef __attribute__((ext_vector_type(2))) double d2;
   __shared__ __attribute__((aligned(16))) double As[GK][GLD];
   __shared__ __attribute__((aligned(16))) double Bs[GK][GLD];
   const int ntile = Np / 64;
   int b, t;
   if (!group_on_xcd(blockIdx.x, ntile * (ntile + 1) / 2 * splits, B, &b, &t)) return;
-  if (inexact && inexact[b] <= most_inexact(N)) return;  // the slices have formed this image's products
+  if (left_over && !too_much(image_left(left_over + (size_t)b * (Np / 8), Np), N, D)) return;  // the digits have formed this image's products
   const int split = t % splits;
   t /= splits;
   double* mine = part + (((size_t)b * (ntile * (ntile + 1) / 2) + t) * (splits - parts_in_g<TOut>()) + split - parts_in_g<TOut>()) * 4096;
@@ -217,8 +231,8 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict_
 // values lies below about 2^-23 of the largest (one value in a million of attention outputs).  Four signed digits to the base
 // 256 each, sixteen digit products per product, summed in 32 bits by the weight of the digits (seven sums; D <= 16384 keeps
 // them below 2^31), joined in 64 bits and rounded once: no sum of float64 products is closer.  Values that are
-// not whole numbers are added in float64, rows with more than a few, an infinity or NaN are formed again in float64
-// (gram_rows_kernel), an image with many such rows by gram_kernel.
+// not whole numbers are added in float64, rows with more than a few, an infinity or NaN are formed in float64
+// (gram_rows_kernel), an image with many of either by gram_kernel.
 // The digits lie in memory as the matrix instruction takes them: [32 rows][32 columns of O][digit][lane][16], lane l holds row
 // l % 32, columns 16 (l / 32) ..; a fragment is 1 KB in one piece, and copies to LDS and reads from it have no bank conflicts.
 typedef __attribute__((ext_vector_type(4))) int i4;
@@ -238,11 +252,28 @@ constexpr int ROW_LIST = 8, ROW_WHOLE = 15;
 __device__ inline int row_scale(int info) { return info >> 4; }
 __device__ inline int row_left(int info) { return info & 15; }
 
-// One workgroup: eight rows, read once and kept in registers until their largest value is known.  Bound by memory: 2 bytes an element in,
-// 4 out (64 images of 576 x 4096: 32 rows a workgroup, read twice, took 222 us; one image 23).
+// x 2^s, if it is a whole number (a value that vanishes in the scaling is none)
+__device__ inline bool whole(float x, int s, int* q) {
+  const float v = ldexpf(x, s);
+  *q = (int)v;
+  return (float)*q == v && (*q != 0 || x == 0.f);
+}
+// the bits of the power of two 2^e in storage type TIn; 0x8000 (above every value) or 0 where that has none
+template <typename TIn> __device__ inline uint32_t least_bits(int e) {
+  constexpr bool half = __is_same(TIn, f16_t);
+  constexpr int LOW = half ? -24 : -133, NORMAL = half ? -14 : -126, HIGH = half ? 15 : 127, BITS = half ? 10 : 7;
+  if (e > HIGH) return 0x8000u;
+  if (e < LOW) return 0;
+  return e < NORMAL ? 1u << (e - LOW) : (uint32_t)(e - NORMAL + 1) << BITS;
+}
+
+// One workgroup: eight rows, read once and kept in registers until their largest value is known and what they leave is listed;
+// eight that are formed anew need no digits.  Bound by memory: 2 bytes an element in, 4 out (64 images of 576 x 4096: 32 rows a
+// workgroup, read twice, took 222 us; one image 23).
 template <typename TIn, int ITER>  // ITER: runs of 16 columns per thread, D <= 2048 ITER
 __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict__ O, char* __restrict__ P, int32_t* __restrict__ rowinfo,
-                                                          uint16_t* __restrict__ left, int N, int D, int Np) {
+                                                          uint16_t* __restrict__ left, int32_t* __restrict__ left_over, int N, int D, int Np) {
+  typedef __attribute__((ext_vector_type(2))) unsigned short us2;
   constexpr uint32_t INF = __is_same(TIn, f16_t) ? 0x7c00u : 0x7f80u;
   __shared__ uint32_t most[16][8];
   __shared__ int cnt[8];
@@ -282,6 +313,58 @@ __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict_
   }
   const bool finite = m < INF;
   uint16_t* list = left + ((size_t)b * Np + row) * ROW_LIST;
+  // x 2^s of a value from here on is a whole number, whatever its last bits; the few smaller ones are looked at
+  constexpr int BITS = __is_same(TIn, f16_t) ? 10 : 7;  // of the stored significand
+  const uint32_t sure = least_bits<TIn>(BITS - s);
+  us2 least = {0xffff, 0xffff};
+#pragma unroll
+  for (int i = 0; i < ITER; i++) {
+    const uint32_t w[8] = {in[i][0].x, in[i][0].y, in[i][0].z, in[i][0].w, in[i][1].x, in[i][1].y, in[i][1].z, in[i][1].w};
+#pragma unroll
+    for (int k = 0; k < 8; k++)  // (a zero becomes the largest)
+      least = __builtin_elementwise_min(least, __builtin_bit_cast(us2, w[k] & 0x7fff7fffu) - us2{1, 1});
+  }
+  if (finite && min((uint32_t)least.x, (uint32_t)least.y) + 1 < sure) {
+#pragma unroll
+    for (int i = 0; i < ITER; i++) {
+      const uint32_t w[8] = {in[i][0].x, in[i][0].y, in[i][0].z, in[i][0].w, in[i][1].x, in[i][1].y, in[i][1].z, in[i][1].w};
+      uint32_t off = 0;
+#pragma unroll
+      for (int k = 0; k < 8; k++) {
+        float lo, hi;
+        unpack2<TIn>(w[k], &lo, &hi);
+        int q;
+        off |= (whole(lo, s, &q) ? 0u : 1u) << (2 * k) | (whole(hi, s, &q) ? 0u : 2u) << (2 * k);
+      }
+      while (off) {
+        const int k = __ffs(off) - 1, at = atomicAdd(&cnt[r], 1);
+        off &= off - 1;
+        if (at >= ROW_LIST) break;  // the row is formed anew
+        list[at] = (uint16_t)(((tid >> 3) + 128 * i) * 16 + k);
+      }
+    }
+  }
+  __syncthreads();
+  const int n = cnt[r];
+  const bool anew = !finite || n > ROW_LIST;
+  if (tid < 8) {  // (row is the thread's own)
+    if (n > 1 && n <= ROW_LIST)  // ascending, so that sums over the list have one order
+      for (int i = 1; i < n; i++) {
+        const uint16_t v = list[i];
+        int k = i;
+        for (; k > 0 && list[k - 1] > v; k--) list[k] = list[k - 1];
+        list[k] = v;
+      }
+    rowinfo[(size_t)b * Np + row] = s * 16 + (anew ? ROW_WHOLE : n);
+    int over = anew ? 1 << 16 : n;
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) over += __shfl_xor(over, o, 64);
+    if (tid == 0) left_over[(size_t)b * (Np / 8) + blockIdx.x] = over;
+  }
+  int n_anew = 0;
+#pragma unroll
+  for (int k = 0; k < 8; k++) n_anew += __shfl(anew ? 1 : 0, k, 64);
+  if (n_anew == 8) return;  // (lines of 128 bytes, filled by the eight rows together: written in part they take longer)
   char* dst = P + ((size_t)b * (Np / 32) + row / 32) * (D / 32) * 4096 + (row & 31) * 16;
 #pragma unroll
   for (int i = 0; i < ITER; i++) {
@@ -289,7 +372,6 @@ __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict_
     if (c >= D / 16) break;
     const uint32_t w[8] = {in[i][0].x, in[i][0].y, in[i][0].z, in[i][0].w, in[i][1].x, in[i][1].y, in[i][1].z, in[i][1].w};
     i4 out[4];
-    uint32_t off = 0;
 #pragma unroll
     for (int g = 0; g < 4; g++) {  // four columns: their 16 digits, turned
       uint32_t t[4];
@@ -297,12 +379,8 @@ __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict_
       for (int k = 0; k < 4; k++) {
         float lo, hi;
         unpack2<TIn>(w[2 * g + k / 2], &lo, &hi);
-        const float x = k & 1 ? hi : lo, v = ldexpf(x, s);
-        int q = finite ? (int)v : 0;
-        if ((float)q != v || (q == 0 && x != 0.f)) {  // (a value that vanished in the scaling, too)
-          off |= 1u << (4 * g + k);
-          q = 0;
-        }
+        int q;
+        if (!whole(k & 1 ? hi : lo, s, &q)) q = 0;
         t[k] = ((uint32_t)q + 0x00808080u) ^ 0x00808080u;
       }
       const uint32_t a01 = __builtin_amdgcn_perm(t[1], t[0], 0x05010400u), b01 = __builtin_amdgcn_perm(t[1], t[0], 0x07030602u);
@@ -314,24 +392,6 @@ __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict_
     }
 #pragma unroll
     for (int d = 0; d < 4; d++) *reinterpret_cast<i4*>(dst + (size_t)(c >> 1) * 4096 + d * 1024 + (c & 1) * 512) = out[d];
-    while (off) {  // (rare)
-      const int k = __ffs(off) - 1;
-      off &= off - 1;
-      const int at = atomicAdd(&cnt[r], 1);
-      if (at < ROW_LIST) list[at] = (uint16_t)(c * 16 + k);
-    }
-  }
-  __syncthreads();
-  if (tid < 8) {  // (row is the thread's own)
-    const int n = cnt[tid];
-    if (n > 1 && n <= ROW_LIST)  // ascending, so that sums over the list have one order
-      for (int i = 1; i < n; i++) {
-        const uint16_t v = list[i];
-        int k = i;
-        for (; k > 0 && list[k - 1] > v; k--) list[k] = list[k - 1];
-        list[k] = v;
-      }
-    rowinfo[(size_t)b * Np + row] = s * 16 + (finite && n <= ROW_LIST ? n : ROW_WHOLE);
   }
 }
 
@@ -340,11 +400,13 @@ __global__ __launch_bounds__(1024) void gram_slice_kernel(const TIn* __restrict_
 // runs while the matrix cores work on it; two workgroups share a compute unit.  64 images of 576 x 4096: 0.555 ms, 2.8 P operations/s
 // (three workgroups, with half of a chunk in registers at a time: 0.562; 8 images of 2880 1.64 and 1.74 ms).
 __global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restrict__ P, const int32_t* __restrict__ rowinfo,
-                                                             double* __restrict__ G, int KB, int Np, int B) {
+                                                             const int32_t* __restrict__ left_over, double* __restrict__ G, int N, int KB,
+                                                             int Np, int B) {
   __shared__ __attribute__((aligned(16))) char L[32768];  // [row blocks of A, of B][2 blocks of 32 columns][digit][1 KB]
   const int ntile = Np / 64;
   int b, t;
   if (!group_on_xcd(blockIdx.x, ntile * (ntile + 1) / 2, B, &b, &t)) return;
+  if (too_much(image_left(left_over + (size_t)b * (Np / 8), Np), N, KB * 32)) return;
   int ti = 0;
   while (t >= ti + 1) { t -= ti + 1; ti++; }
   const int tj = t;
@@ -414,78 +476,142 @@ __global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restr
   }
 }
 
-// What the digits leave out, in float64.  Rows with a few values left: the products of those (their columns of O: 40 KB a
-// value, where the row anew reads the whole of O; 64 images of 576 x 4096 95 us).  Rows with many: the row anew.  One
-// workgroup 64 columns; an entry of G and its mirror have one writer, the row of the two that is first in the lists.
+// What the digits leave out, in float64: of rows with a few values left the products of those, rows with more anew.  64 columns
+// of an image are shared by sixteen wavefronts that do not wait for one another: each takes every sixteenth of the rows with values
+// left, and four columns of the others, four of these at a time.  An entry of G and its mirror have one writer: of two rows with
+// values left the first.  The products of a value left read a column of O, 64 lines: an image stays on one XCD, and the loads of
+// a row are issued together.  (One workgroup for the 64 columns, a value's loads one after the other, the rows anew one by one:
+// 576 values 412 us, 1152 715, 18 rows 860, by the figures at too_much.)
 template <typename TIn>
-__global__ __launch_bounds__(1024) void gram_rows_kernel(const TIn* __restrict__ O, const int32_t* __restrict__ rowinfo,
-                                                         const uint16_t* __restrict__ left, double* __restrict__ G,
-                                                         int32_t* __restrict__ inexact, int N, int D, int Np) {
-  __shared__ int cnt, few, list[1024];
-  __shared__ uint16_t flist[MAX_NVIS];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.y;
-  if (tid == 0) cnt = few = 0;
-  __syncthreads();
+__global__ __launch_bounds__(256, 4) void gram_rows_kernel(const TIn* __restrict__ O, const int32_t* __restrict__ rowinfo,
+                                                        const uint16_t* __restrict__ left, double* __restrict__ G,
+                                                        const int32_t* __restrict__ left_over, int N, int D, int Np, int B) {
+  int b, t;
+  if (!group_on_xcd(blockIdx.x, Np / 64 * 4, B, &b, &t)) return;
+  const int lane = threadIdx.x & 63, col0 = t / 4 * 64, wave = __builtin_amdgcn_readfirstlane(t % 4 * 4 + (threadIdx.x >> 6));
+  const Left image = image_left(left_over + (size_t)b * (Np / 8), Np);
+  if ((image.values | image.anew) == 0 || too_much(image, N, D)) return;
   const int32_t* info = rowinfo + (size_t)b * Np;
-  for (int i = tid; i < N; i += 1024) {
-    const int n = row_left(info[i]);
-    if (n == ROW_WHOLE) {
-      const int at = atomicAdd(&cnt, 1);  // (any order: the rows do not depend on one another)
-      if (at < 1024) list[at] = i;
-    } else if (n > 0) {
-      flist[atomicAdd(&few, 1)] = (uint16_t)i;
-    }
-  }
-  __syncthreads();
-  const int n = cnt;
-  if (tid == 0 && blockIdx.x == 0) inexact[b] = n;
-  if (n > most_inexact(N)) return;
+  const uint16_t* lists = left + (size_t)b * Np * ROW_LIST;
   const TIn* Ob = O + (size_t)b * N * D;
   double* Gb = G + (size_t)b * Np * Np;
-  const int col = blockIdx.x * 64 + lane, cinfo = col < N ? row_left(info[col]) : ROW_WHOLE;
-  if (cinfo != ROW_WHOLE)
-    for (int e = wave; e < few; e += 16) {
-      const int row = flist[e], rn = row_left(info[row]);
-      if (cinfo > 0 && col < row) continue;  // the other row's entry
-      const uint16_t* lr = left + ((size_t)b * Np + row) * ROW_LIST;
-      const uint16_t* lc = left + ((size_t)b * Np + col) * ROW_LIST;
-      double add = 0.0;
-      for (int i = 0; i < rn; i++) {
-        const int k = lr[i];
-        add = fma((double)widen1<TIn>(bits16(Ob[(size_t)row * D + k])), (double)widen1<TIn>(bits16(Ob[(size_t)col * D + k])), add);
-      }
-      for (int i = 0; i < cinfo; i++) {  // of the column's own those that the row's list does not hold
-        const int k = lc[i];
-        bool both = false;
-        for (int j = 0; j < rn; j++) both |= lr[j] == k;
-        if (!both) add = fma((double)widen1<TIn>(bits16(Ob[(size_t)row * D + k])), (double)widen1<TIn>(bits16(Ob[(size_t)col * D + k])), add);
-      }
-      const double v = Gb[(size_t)row * Np + col] + add;
-      Gb[(size_t)row * Np + col] = v;
-      if (row != col) Gb[(size_t)col * Np + row] = v;
+  auto bits = [&](int row, int k) { return bits16(Ob[(size_t)row * D + k]); };
+  auto of = [](const uint32_t* list, int i) { return (list[i / 2] >> (16 * (i & 1))) & 0xffff; };
+
+  if (image.values > 0) {
+    const int col = col0 + lane, cn = col < N ? row_left(info[col]) : ROW_WHOLE;
+    const bool listed = cn > 0 && cn != ROW_WHOLE;
+    int most = 0;  // values of a column's own list
+    uint32_t lc[4] = {0, 0, 0, 0}, oc[ROW_LIST];
+#pragma unroll
+    for (int i = 0; i < ROW_LIST; i++) {
+      if (__ballot(listed && cn > i)) most = i + 1;
+      oc[i] = 0;
     }
-  const int c0 = blockIdx.x * 64 + wave * 4;
-  for (int e = 0; e < n; e++) {
-    const int row = list[e];
-    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    if (listed) {
+      const uint4 v = *reinterpret_cast<const uint4*>(lists + (size_t)col * ROW_LIST);
+      lc[0] = v.x; lc[1] = v.y; lc[2] = v.z; lc[3] = v.w;
+#pragma unroll
+      for (int i = 0; i < ROW_LIST; i++)
+        if (i < cn) oc[i] = bits(col, of(lc, i));
+    }
+    for (int r0 = wave; r0 < N; r0 += 1024) {
+      const int mine = r0 + 16 * lane, rl = mine < N ? row_left(info[mine]) : 0;
+      for (unsigned long long rows = __ballot(rl > 0 && rl != ROW_WHOLE); rows; rows &= rows - 1) {
+        const int at = __ffsll(rows) - 1, row = r0 + 16 * at, rn = __builtin_amdgcn_readlane(rl, at);
+        if (cn == ROW_WHOLE || (listed && col < row)) continue;  // formed anew, or the other row's entry
+        const uint4 v = *reinterpret_cast<const uint4*>(lists + (size_t)row * ROW_LIST);
+        const uint32_t lr[4] = {v.x, v.y, v.z, v.w};
+        const double g = Gb[(size_t)row * Np + col];
+        uint32_t x[ROW_LIST], y[ROW_LIST], z[ROW_LIST];
+        double add = 0.0;
+#pragma unroll
+        for (int i = 0; i < ROW_LIST; i++) {  // (rn and most are the same in every lane)
+          if (i < rn) {
+            x[i] = bits(row, of(lr, i));
+            y[i] = bits(col, of(lr, i));
+          }
+          if (i < most) z[i] = i < cn ? bits(row, of(lc, i)) : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < ROW_LIST; i++)
+          if (i < rn) add = fma((double)widen1<TIn>(x[i]), (double)widen1<TIn>(y[i]), add);
+#pragma unroll
+        for (int i = 0; i < ROW_LIST; i++)
+          if (i < most) {  // of the column's own those that the row's list does not hold
+            bool both = i >= cn;
+#pragma unroll
+            for (int j = 0; j < ROW_LIST; j++) both |= j < rn && of(lr, j) == of(lc, i);
+            if (!both) add = fma((double)widen1<TIn>(z[i]), (double)widen1<TIn>(oc[i]), add);
+          }
+        Gb[(size_t)row * Np + col] = g + add;
+        if (row != col) Gb[(size_t)col * Np + row] = g + add;
+      }
+    }
+  }
+
+  if (image.anew == 0) return;
+  const int c0 = col0 + wave * 4;
+  unsigned long long rows = 0;
+  for (int r0 = -64;;) {
+    int row[4] = {0, 0, 0, 0}, n = 0;
+    while (n < 4) {
+      while (!rows && r0 + 64 < N) {
+        r0 += 64;
+        rows = __ballot(r0 + lane < N && row_left(info[r0 + lane]) == ROW_WHOLE);
+      }
+      if (!rows) break;
+#pragma unroll
+      for (int i = 0; i < 4; i++) if (i == n) row[i] = r0 + __ffsll(rows) - 1;
+      rows &= rows - 1;
+      n++;
+    }
+    if (n == 0) return;
+    double sum[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int c = 0; c < 4; c++) sum[i][c] = 0.0;
     for (int k = lane * 8; k < D; k += 512) {
-      double x[8], y[8];
-      widen8<TIn>(fetch8<TIn>(Ob + (size_t)row * D + k), x);
+      uint32_t x[4][4], y[4][4];
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const uint4 v = fetch8<TIn>(Ob + (size_t)(i < n ? row[i] : row[0]) * D + k).v;
+        x[i][0] = v.x; x[i][1] = v.y; x[i][2] = v.z; x[i][3] = v.w;
+      }
 #pragma unroll
       for (int c = 0; c < 4; c++) {
-        widen8<TIn>(fetch8<TIn>(Ob + (size_t)min(c0 + c, N - 1) * D + k), y);
+        const uint4 v = fetch8<TIn>(Ob + (size_t)min(c0 + c, N - 1) * D + k).v;
+        y[c][0] = v.x; y[c][1] = v.y; y[c][2] = v.z; y[c][3] = v.w;
+      }
 #pragma unroll
-        for (int i = 0; i < 8; i++) sum[c] = fma(x[i], y[i], sum[c]);
+      for (int u = 0; u < 4; u++) {
+        float lo[4], hi[4];
+#pragma unroll
+        for (int c = 0; c < 4; c++) unpack2<TIn>(y[c][u], &lo[c], &hi[c]);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          if (i >= n) break;
+          float xl, xh;
+          unpack2<TIn>(x[i][u], &xl, &xh);
+#pragma unroll
+          for (int c = 0; c < 4; c++) {
+            sum[i][c] = fma((double)xl, (double)lo[c], sum[i][c]);
+            sum[i][c] = fma((double)xh, (double)hi[c], sum[i][c]);
+          }
+        }
       }
     }
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-      const double v = wave_sum(sum[c]);
-      if (lane == 0 && c0 + c < N) {  // (of two such rows both write the same value)
-        Gb[(size_t)row * Np + c0 + c] = v;
-        Gb[(size_t)(c0 + c) * Np + row] = v;
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        const double v = wave_sum_dpp(sum[i][c]);
+        if (lane == 0 && i < n && c0 + c < N) {  // (of two such rows both write the same value)
+          Gb[(size_t)row[i] * Np + c0 + c] = v;
+          Gb[(size_t)(c0 + c) * Np + row[i]] = v;
+        }
       }
-    }
   }
 }
 
@@ -545,8 +671,8 @@ static void run_gram(const Plan& pl, const void* O, void* G, void* ws, int img0,
       char* P = at<char>(ws, pl.off_gslice);  // (stream groups form their matrices one after the other)
       int32_t* info = at<int32_t>(ws, pl.off_grow) + (size_t)img0 * pl.Np;
       uint16_t* left = at<uint16_t>(ws, pl.off_gleft) + (size_t)img0 * pl.Np * ROW_LIST;
-      int32_t* inexact = at<int32_t>(ws, pl.off_ginexact) + img0;
-      const auto slice = pl.D <= 4096 ? gram_slice_kernel<TIn, 2> : (pl.D <= 8192 ? gram_slice_kernel<TIn, 4> : gram_slice_kernel<TIn, 8>);
+      int32_t* left_over = at<int32_t>(ws, pl.off_gover) + (size_t)img0 * (pl.Np / 8);
+      const auto slice = pl.D <= 2048 ? gram_slice_kernel<TIn, 1> : pl.D <= 4096 ? gram_slice_kernel<TIn, 2> : (pl.D <= 8192 ? gram_slice_kernel<TIn, 4> : gram_slice_kernel<TIn, 8>);
       const size_t fit = gram_slice_reserve_bytes(pl) / slice_bytes(pl);
       const int turns = pl.B > 0 ? (int)((pl.B + fit - 1) / fit) : 0;
       for (int k = 0; k < turns; k++) {
@@ -554,11 +680,12 @@ static void run_gram(const Plan& pl, const void* O, void* G, void* ws, int img0,
         const TIn* Ok = (const TIn*)O + (size_t)first * pl.N * pl.D;
         double* Gk = (double*)G + (size_t)first * pl.Np * pl.Np;
         int32_t* ik = info + (size_t)first * pl.Np;
-        TC_TIMED(PK_GRAM, 2, st, (slice<<<dim3(pl.Np / 8, n), 1024, 0, st>>>(Ok, P, ik, left + (size_t)first * pl.Np * ROW_LIST, pl.N, pl.D, pl.Np)));
-        TC_TIMED(PK_GRAM, 0, st, (gram_slices_kernel<<<grid_for_groups(tiles, n), 256, 0, st>>>(P, ik, Gk, pl.D / 32, pl.Np, n)));
+        int32_t* ok = left_over + (size_t)first * (pl.Np / 8);
+        TC_TIMED(PK_GRAM, 2, st, (slice<<<dim3(pl.Np / 8, n), 1024, 0, st>>>(Ok, P, ik, left + (size_t)first * pl.Np * ROW_LIST, ok, pl.N, pl.D, pl.Np)));
+        TC_TIMED(PK_GRAM, 0, st, (gram_slices_kernel<<<grid_for_groups(tiles, n), 256, 0, st>>>(P, ik, ok, Gk, pl.N, pl.D / 32, pl.Np, n)));
       }
-      TC_TIMED(PK_GRAM, 3, st, (gram_rows_kernel<TIn><<<dim3(nt, pl.B), 1024, 0, st>>>((const TIn*)O, info, left, (double*)G, inexact, pl.N, pl.D, pl.Np)));
-      TC_TIMED(PK_GRAM, 1, st, (gram_kernel<TIn, TOut><<<grid_for_groups(tiles, pl.B), 256, 0, st>>>((const TIn*)O, (TOut*)G, pl.N, pl.D, pl.Np, pl.B, 1, nullptr, inexact)));
+      TC_TIMED(PK_GRAM, 3, st, (gram_rows_kernel<TIn><<<grid_for_groups(nt * 4, pl.B), 256, 0, st>>>((const TIn*)O, info, left, (double*)G, left_over, pl.N, pl.D, pl.Np, pl.B)));
+      TC_TIMED(PK_GRAM, 1, st, (gram_kernel<TIn, TOut><<<grid_for_groups(tiles, pl.B), 256, 0, st>>>((const TIn*)O, (TOut*)G, pl.N, pl.D, pl.Np, pl.B, 1, nullptr, left_over)));
       return;
     }
   }

@@ -55,7 +55,7 @@ struct Plan {
   double tol;
   float scale;
   size_t off_O, off_S, off_Spart, off_G, off_U, off_R, off_offpart, off_state, off_sig, off_C, off_E, off_order,
-      off_rnorm, off_sim, off_mlist, off_info, off_gpart, off_gslice, off_grow, off_gleft, off_ginexact;
+      off_rnorm, off_sim, off_mlist, off_info, off_gpart, off_gslice, off_grow, off_gleft, off_gover;
   size_t off_td_d, off_td_e, off_td_tau, off_td_lam, off_td_blk, off_td_tnorm, off_td_rn, off_td_bad, off_td_wgt,
       off_td_W, off_td_mark, off_td_Cpart, off_td_Tf, off_td_sync, off_td_fail;  // direct eigensolver only
   size_t td_sync_bytes;  // exchange memory of the reduction, per image

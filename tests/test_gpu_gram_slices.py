@@ -85,6 +85,36 @@ def test_rows_that_are_not_whole_numbers(dtype, bad, left, eig):
             assert float((sigma[b] ** 2 - s ** 2).abs().max() / s.max() ** 2) < 1e-4
 
 
+def _gram_ms(V, **kw):
+    """Time of the Gram matrix of rows V in one image after another: keys of length far above their products make O = V."""
+    from paper_2503_10501_amd import binding as tc
+    B, n, D = V.shape
+    g = torch.Generator(device="cuda").manual_seed(0)
+    K = torch.randn(B, D // 128, n, 128, device="cuda", generator=g).bfloat16()
+    p = tc.make_params(batch=B, seq_len=n, vis_start=0, n_vis=n, n_heads=D // 128, head_dim=128, hidden_dim=D, dtype=tc.TC_BF16,
+                       k_prune=8, k_final=8, jacobi_max_sweeps=1, **kw)
+    Vh = V.view(B, n, D // 128, 128).transpose(1, 2).contiguous()
+    X_out = torch.empty(B, 8, D, dtype=V.dtype, device="cuda")
+    kept, dst = torch.empty(B, 8, dtype=torch.int32, device="cuda"), torch.empty(B, n, dtype=torch.int32, device="cuda")
+    info, ws = torch.empty(B, dtype=torch.int32, device="cuda"), tc.new_workspace(p)
+    return lambda: tc.tc_profile_compress(p, 8 * K, K, Vh, V, X_out, kept, dst, info, ws)[0]["gram"][0]
+
+
+@pytest.mark.parametrize("left", [0, 1, 4, 8, 12])   # per row; above eight the row is formed anew
+def test_rows_of_many_scales_cost_little_more_than_float64(left):
+    # The same rows through the float64 products alone (a float32 matrix takes no digits).  An image that leaves much is found before
+    # its products are begun, so a call pays for reading its rows once; with the products, and the values
+    # added one by one, it was 1.2 (four values) to 2.1 (eight).
+    from paper_2503_10501_amd import binding as tc
+    g = torch.Generator(device="cuda").manual_seed(left)
+    V = torch.randn(32, 576, 4096, device="cuda", generator=g)
+    V.scatter_(2, torch.randint(0, 4096, (32, 576, left), device="cuda", generator=g), 2.0 ** -100)
+    V = V.bfloat16()
+    digits, plain = _gram_ms(V), _gram_ms(V, eig_dtype=tc.TC_EIG_F32)
+    t = torch.tensor([[f() for f in (digits, plain)] for _ in range(12)])
+    assert float(t[:, 0].min() / t[:, 1].min()) < (0.75 if left == 0 else 1.2)
+
+
 def test_a_float32_matrix_is_rounded_once():
     # A call of one image forms all products in one sum of float64, and so does a call of many: the same float32 matrix, the same
     # iteration, the same bits.  (Added to digits that were float32 already, six small values of a row would round a second time.)
