@@ -89,10 +89,12 @@ int make_plan(const tc_params* p, Plan* pl) {
     q.off_td_fail = take(B * 4);
   }
   q.off_gpart = take(gram_reserve_bytes(q));
-  q.off_gslice = take(gram_slice_reserve_bytes(q));
-  q.off_grow = take(B * Np * 4);   // per row: scale of the digits
-  q.off_gleft = take(B * Np * 16); // ... and the columns of up to eight values that are added apart
-  q.off_gover = take(B * (Np / 8) * 4);  // per eight rows: what the digits leave out
+  size_t digits, rows;
+  gram_slice_reserve(q, &digits, &rows);
+  q.off_gslice = take(digits);
+  q.off_grow = take(rows * 4);       // per row: scale of the digits
+  q.off_gleft = take(rows * 16);     // ... and the columns of up to eight values that are added apart
+  q.off_gover = take(rows / 8 * 4);  // per eight rows: what the digits leave out
   q.total = off > 0 ? off : 256;
   // A workspace also serves calls with fewer tokens (tc_info_rank on a subset of rows is one): just above the largest
   // reduction the tridiagonal route needs more than the iteration.

@@ -615,8 +615,6 @@ __global__ __launch_bounds__(256, 4) void gram_rows_kernel(const TIn* __restrict
   }
 }
 
-// Room for the digits of a call's images, 4 bytes an element: at most 1 GiB (or one image); more images go in turns.
-static size_t slice_bytes(const Plan& pl) { return (size_t)pl.Np * pl.D * 4; }
 // Digits for 16-bit rows of calls with work for the chip.  A tile is a chain of D / 64 chunks (0.85 us each) by one workgroup, where
 // gram_kernel shares a small call's tiles, and an image of one tile has a fourth of it idle in gram_kernel but not here.  All
 // launches of the step, float64 and digits, us: D = 4096, 64 images of 64 tokens 47 and 79, 256 of them 144 and 164; 27 of 128
@@ -624,17 +622,29 @@ static size_t slice_bytes(const Plan& pl) { return (size_t)pl.Np * pl.D * 4; }
 // image of 576 (45) 65 and 77, two (90) 111 and 79; one of 2880 717 and 275; D = 1024, 64 of 128 (192) 40 and 40, 20 of 256 (200)
 // 49 and 41.  By the size of the whole call, as for the parts.  A float32 matrix (TC_EIG_F32) keeps gram_kernel: the values that are
 // added apart would find the digits' part already rounded to float32, and round it again.
+constexpr int FEWEST_TILES = 80, MANY_TILES = 128;  // (the latter where gram_kernel shares a tile among more than three)
+constexpr long long LEAST_WORK = 200000;
 int gram_splits(const Plan& pl);
-static bool use_slices(const Plan& pl) {
-  const long long nt = pl.Np / 64, tiles = nt * (nt + 1) / 2 * pl.batch_call;
-  return pl.esize == 2 && pl.tsize == 8 && pl.D <= 16384 && nt > 1 && tiles >= (gram_splits(pl) > 3 ? 128 : 80) && tiles * pl.D >= 200000;
+static long long call_tiles(const Plan& pl) {
+  const long long nt = pl.Np / 64;
+  return nt * (nt + 1) / 2 * pl.batch_call;
 }
-// A workspace also serves calls of fewer tokens and images: what one that takes this way may need is set aside by the two
-// sizes alone.
-size_t gram_slice_reserve_bytes(const Plan& pl) {
-  if (pl.esize != 2 || pl.tsize != 8 || pl.D > 16384 || pl.Np <= 64) return 0;
-  const size_t image = slice_bytes(pl), lim = (size_t)1 << 30, all = image * pl.B;
-  return all < lim ? all : (image > lim ? image : lim);
+static bool may_use_slices(const Plan& pl) {
+  return pl.esize == 2 && pl.tsize == 8 && pl.D <= 16384 && pl.Np > 64 && call_tiles(pl) >= FEWEST_TILES && call_tiles(pl) * pl.D >= LEAST_WORK;
+}
+static bool use_slices(const Plan& pl) {
+  return may_use_slices(pl) && call_tiles(pl) >= (gram_splits(pl) > 3 ? MANY_TILES : FEWEST_TILES);
+}
+// Room for the digits of the images that a turn takes, 4 bytes an element; the images of a call beyond that go in turns.
+constexpr size_t TURN_BYTES = (size_t)1 << 30;
+static size_t slice_bytes(const Plan& pl) { return (size_t)pl.Np * pl.D * 4; }
+static int turn_images(const Plan& pl) { return slice_bytes(pl) < TURN_BYTES ? (int)(TURN_BYTES / slice_bytes(pl)) : 1; }
+// A workspace also serves calls of fewer tokens and images, so it has this room where one of them may take this way (with fewer
+// tiles none does): up to a turn.
+void gram_slice_reserve(const Plan& pl, size_t* digits, size_t* rows) {
+  const size_t all = slice_bytes(pl) * pl.B, most = slice_bytes(pl) > TURN_BYTES ? slice_bytes(pl) : TURN_BYTES;
+  *digits = may_use_slices(pl) ? (all < most ? all : most) : 0;
+  *rows = may_use_slices(pl) ? (size_t)pl.B * pl.Np : 0;
 }
 
 // Workgroups per tile: as many as keep the launch within three per compute unit, with at least eight chunks each and no more
@@ -673,8 +683,7 @@ static void run_gram(const Plan& pl, const void* O, void* G, void* ws, int img0,
       uint16_t* left = at<uint16_t>(ws, pl.off_gleft) + (size_t)img0 * pl.Np * ROW_LIST;
       int32_t* left_over = at<int32_t>(ws, pl.off_gover) + (size_t)img0 * (pl.Np / 8);
       const auto slice = pl.D <= 2048 ? gram_slice_kernel<TIn, 1> : pl.D <= 4096 ? gram_slice_kernel<TIn, 2> : (pl.D <= 8192 ? gram_slice_kernel<TIn, 4> : gram_slice_kernel<TIn, 8>);
-      const size_t fit = gram_slice_reserve_bytes(pl) / slice_bytes(pl);
-      const int turns = pl.B > 0 ? (int)((pl.B + fit - 1) / fit) : 0;
+      const int turns = (pl.B + turn_images(pl) - 1) / turn_images(pl);
       for (int k = 0; k < turns; k++) {
         const int first = (int)((long long)pl.B * k / turns), n = (int)((long long)pl.B * (k + 1) / turns) - first;
         const TIn* Ok = (const TIn*)O + (size_t)first * pl.N * pl.D;

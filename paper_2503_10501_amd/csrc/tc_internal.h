@@ -80,7 +80,8 @@ inline int check_ws(const Plan& pl, const void* ws, size_t ws_bytes) {
 int launch_attention(const Plan& pl, int dtype, int causal, const void* Q, const void* K, const void* V, void* O,
                      float* S, float* Spart, hipStream_t st);
 size_t gram_reserve_bytes(const Plan& pl);        // room for the partial sums of the call
-size_t gram_slice_reserve_bytes(const Plan& pl);  // room for the digits of 16-bit rows
+// ... for the digits of 16-bit rows (bytes), and for what is noted about each of how many rows
+void gram_slice_reserve(const Plan& pl, size_t* digits, size_t* rows);
 int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G, void* ws, int img0, hipStream_t st);
 int launch_jacobi(const Plan& pl, int eig_dtype, void* G, void* U /* nullptr: eigenvalues only */, void* R,
                   double* offpart, EigState* state, hipStream_t st);

@@ -74,6 +74,26 @@ def test_a_workspace_serves_every_smaller_call(heads, head_dim, kw):
         assert all(a > 0 and a <= b for a, b in zip(sizes, sizes[1:])), n
 
 
+@pytest.mark.parametrize("batch,n,heads,digits", [(1, 576, 32, 0), (1, 700, 32, 0), (1, 768, 32, 0), (7, 256, 32, 0), (64, 64, 32, 0),
+                                                  (26, 128, 8, 0), (2, 576, 32, 2), (1, 832, 32, 1), (8, 256, 32, 8), (64, 576, 32, 64),
+                                                  (80, 576, 128, 80), (80, 576, 160, 0), (2, 3456, 128, 2)])
+def test_room_for_digits_only_where_a_call_can_use_it(batch, n, heads, digits):
+    # Workspaces of 16-bit and of 32-bit rows differ in the rows themselves and, from 80 tiles of 64 tokens on, in the digits of the Gram
+    # matrix: 4 bytes an element up to 1 GiB (`digits`: of how many images) and at most 16384 columns, and what is noted about each row
+    tc = _binding()
+
+    def need(dtype, **kw):
+        return tc.tc_workspace_bytes(tc.make_params(batch=batch, seq_len=n, vis_start=0, n_vis=n, n_heads=heads, head_dim=128,
+                                                    hidden_dim=128 * heads, dtype=dtype, k_prune=2, k_final=1, **kw))
+
+    up = lambda x: (x + 255) // 256 * 256
+    D, Np = 128 * heads, (n + 63) // 64 * 64
+    more = min(digits * Np * D * 4, 1 << 30) + (up(batch * Np * 4) + up(batch * Np * 16) + up(batch * Np // 2) if digits else 0)
+    rows = up(batch * n * D * 4) - up(batch * n * D * 2)
+    assert need(tc.TC_BF16) == need(tc.TC_F16) == need(tc.TC_F32) - rows + more
+    assert need(tc.TC_BF16, eig_dtype=tc.TC_EIG_F32) == need(tc.TC_F32, eig_dtype=tc.TC_EIG_F32) - rows
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("n_vis", 0, -2), ("n_vis", 5000, -2), ("head_dim", 96, -2), ("hidden_dim", 100, -2), ("vis_start", 600, -2),
     ("dtype", 7, -3), ("eig_dtype", 3, -3), ("lambda_", 1.5, -4), ("lambda_", -0.1, -4), ("k_final", 0, -4),
