@@ -163,6 +163,7 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
   if (profiling_active()) groups = 1;  // per-kernel timing wants kernels that run alone
   hipStream_t streams[4];
   groups = fork_streams(st, groups, streams);
+  if (groups < 1) return TC_ERR_HIP;
   int first[5];
   for (int g = 0; g <= groups; g++) first[g] = (int)((long long)pl.B * g / groups);
   int rc = TC_OK;
@@ -184,15 +185,16 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
     rc = launch_gram(sub, p->dtype, p->eig_dtype, Og, at<double>(ws, pl.off_G) + i0 * pl.Np * pl.Np, ws, img0, streams[g]);
     if (rc != TC_OK) break;
     // the next group's attention and Gram kernels (which fill the chip) start when this group's are done, so
-    // that the groups' reductions start one after the other and their tails do not all come at the end
-    stagger_streams(st, g, groups);
+    // that the groups' reductions start one after the other and their tails do not all come at the end, and because the
+    // groups share the room for the digits of the Gram step
+    if ((rc = stagger_streams(st, g, groups)) != TC_OK) break;
     float* C_ws = at<float>(ws, pl.off_C);
     rc = direct_chain(pl, sub, img0, p, true, C_ws, ics, sigma, info, ws, streams[g]);
     if (rc != TC_OK) break;
     rc = launch_combine(sub, C_ws + i0 * N, Sg, p->lambda, p->norm_mode, score + i0 * N, streams[g]);
   }
-  join_streams(st, groups);
-  return rc;
+  const int joined = join_streams(st, groups);
+  return rc != TC_OK ? rc : joined;
 }
 
 int direct_eigenvalues(const Plan& pl, const tc_params* p, float* sigma, int32_t* info, void* ws, hipStream_t st) {

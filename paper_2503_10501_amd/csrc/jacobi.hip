@@ -933,8 +933,8 @@ static StreamPool* helper_streams() {
 }
 
 // Fork: streams[0] = st, streams[1 .. n-1] = helper streams that wait for what is already enqueued on st.
-// Returns the number of streams available (1 if the helpers could not be created).  The pool's events are
-// shared by all calls on the device, so the pool stays locked until join_streams(): two host threads enqueuing
+// Returns the number of streams available (1 if the helpers could not be created, 0 if they cannot be made to wait: no join
+// then).  The pool's events are shared by all calls on the device, so the pool stays locked until join_streams(): two host threads enqueuing
 // at the same time cannot interleave their record/wait pairs.
 static std::unique_lock<std::mutex>& pool_lock() {
   static thread_local std::unique_lock<std::mutex> lock(g_pool_mutex, std::defer_lock);
@@ -946,34 +946,45 @@ int fork_streams(hipStream_t st, int groups, hipStream_t* streams) {
   StreamPool* pool = groups > 1 ? helper_streams() : nullptr;
   if (!pool) return 1;
   pool_lock().lock();
-  (void)hipEventRecord(pool->fork, st);
-  for (int g = 1; g < groups; g++) {
+  bool ok = hipEventRecord(pool->fork, st) == hipSuccess;
+  for (int g = 1; g < groups && ok; g++) {
     streams[g] = pool->s[g - 1];
-    (void)hipStreamWaitEvent(streams[g], pool->fork, 0);
+    ok = hipStreamWaitEvent(streams[g], pool->fork, 0) == hipSuccess;
   }
-  return groups;
+  if (ok) return groups;
+  (void)hipGetLastError();  // it is reported here, not by the next launch
+  pool_lock().unlock();
+  return 0;
 }
 // Between a fork and its join: what is enqueued on stream g + 1 from now on waits for what is on stream g now
-// (g = 0 is the caller's stream).  Lets the groups start one after the other instead of all at once.
-void stagger_streams(hipStream_t st, int g, int groups) {
-  if (g + 1 >= groups) return;
+// (g = 0 is the caller's stream).  Lets the groups start one after the other instead of all at once, and keeps apart what they
+// have in common (the digits of the Gram step): with an error nothing may be enqueued on stream g + 1.
+int stagger_streams(hipStream_t st, int g, int groups) {
+  if (g + 1 >= groups) return TC_OK;
   int dev = 0;
   (void)hipGetDevice(&dev);
   StreamPool& pool = g_pools[dev];
-  (void)hipEventRecord(pool.stage[g], g == 0 ? st : pool.s[g - 1]);
-  (void)hipStreamWaitEvent(pool.s[g], pool.stage[g], 0);
+  const bool ok = hipEventRecord(pool.stage[g], g == 0 ? st : pool.s[g - 1]) == hipSuccess &&
+                  hipStreamWaitEvent(pool.s[g], pool.stage[g], 0) == hipSuccess;
+  if (!ok) (void)hipGetLastError();
+  return ok ? TC_OK : TC_ERR_HIP;
 }
-// Join: st waits for everything enqueued on the helper streams since the fork.
-void join_streams(hipStream_t st, int groups) {
-  if (groups <= 1) return;
+// Join: st waits for everything enqueued on the helper streams since the fork.  Where it cannot, the host does: the caller's
+// memory is not in use any more when the call returns its error.
+int join_streams(hipStream_t st, int groups) {
+  if (groups <= 1) return TC_OK;
   int dev = 0;
   (void)hipGetDevice(&dev);
   StreamPool& pool = g_pools[dev];
-  for (int g = 0; g < groups - 1; g++) {
-    (void)hipEventRecord(pool.join[g], pool.s[g]);
-    (void)hipStreamWaitEvent(st, pool.join[g], 0);
-  }
+  int rc = TC_OK;
+  for (int g = 0; g < groups - 1; g++)
+    if (hipEventRecord(pool.join[g], pool.s[g]) != hipSuccess || hipStreamWaitEvent(st, pool.join[g], 0) != hipSuccess) {
+      (void)hipStreamSynchronize(pool.s[g]);
+      (void)hipGetLastError();
+      rc = TC_ERR_HIP;
+    }
   pool_lock().unlock();
+  return rc;
 }
 
 template <typename T>
@@ -1019,14 +1030,15 @@ static int run_jacobi(const Plan& pl, T* G, float* U, T* R, double* offpart, Eig
   if (profiling_active()) groups = 1;  // per-kernel timing wants kernels that run alone
   hipStream_t streams[MAX_GROUPS];
   groups = fork_streams(st, groups, streams);
+  if (groups < 1) return TC_ERR_HIP;
   const int per = (pl.B + groups - 1) / groups;
   for (int g = 0; g < groups; g++) {
     const int img0 = g * per, nimg = pl.B - img0 < per ? pl.B - img0 : per;
     if (nimg <= 0) continue;
     enqueue_group<T>(pl, G, U, R, offpart, state, img0, nimg, streams[g]);
   }
-  join_streams(st, groups);
-  return check_launch();
+  const int rc = join_streams(st, groups);
+  return check_launch() == TC_OK ? rc : TC_ERR_HIP;
 }
 
 int launch_jacobi(const Plan& pl, int eig_dtype, void* G, void* U, void* R, double* offpart, EigState* state,
