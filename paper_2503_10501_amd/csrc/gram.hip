@@ -468,7 +468,7 @@ __global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restr
       const int r = 4 * g + k, row = r0 + 8 * g + k;
       const long long hi = ((long long)acc[6][r] << 16) + ((long long)acc[5][r] << 8) + acc[4][r];
       const long long lo = ((long long)acc[3][r] << 24) + ((long long)acc[2][r] << 16) + ((long long)acc[1][r] << 8) + acc[0][r];
-      const double x = fma((double)hi, 4294967296.0, (double)lo);  // both are whole numbers below 2^53: one rounding
+      const double x = fma((double)hi, 4294967296.0, (double)lo);  // whole numbers below 2^44 and 2^53 (2^39.003 a column: D < 16352): one rounding
       v[k] = ldexp(x, -(sc + row_scale(info[row])));
       Gb[(size_t)row * Np + col] = v[k];
     }
@@ -713,3 +713,16 @@ int launch_gram(const Plan& pl, int dtype, int eig_dtype, const void* O, void* G
 }
 
 }  // namespace tc
+
+// For the tests, no part of the interface: the Gram step of a call on rows O by itself, G [B, Np, Np]; `digits` (host): whether
+// the call takes the digits.  Without O nothing is launched.
+extern "C" __attribute__((visibility("default"))) int tc_gram_matrix(const tc_params* p, const void* O, void* G, void* ws, size_t ws_bytes,
+                                                                     void* stream, int* digits) {
+  tc::Plan pl;
+  int rc = tc::make_plan(p, &pl);
+  if (rc != TC_OK) return rc;
+  *digits = tc::use_slices(pl) ? 1 : 0;
+  if (!O) return TC_OK;
+  if ((rc = tc::check_ws(pl, ws, ws_bytes)) != TC_OK) return rc;
+  return tc::launch_gram(pl, p->dtype, p->eig_dtype, O, G, ws, 0, (hipStream_t)stream);
+}
