@@ -167,13 +167,15 @@ def main():
     attn_t = rate(wm["attn_flops"], "attn", "T")
     attn_ai = wm["attn_flops"] / wm["attn_bytes"]
     attn_cap = min(PEAK["mfma_bf16"], attn_ai * PEAK["hbm_gbps"] / 1e3)       # TFLOP/s the HBM can feed at this intensity
+    # Gram matrix of 16-bit rows in whole numbers: sixteen products of 8-bit digits per product.  Its launches tell (digits, products, what
+    # they leave out, images left to float64); float64 takes one, or two where workgroups share a tile.
+    digits = launches.get("gram", 0) > 2
     per_row = {
         "a1_a2_attention": entry("attn", "mfma", attn_t, PEAK["mfma_bf16"] if w.dtype != "f32" else PEAK["vec_f32"], "TFLOP/s",
                                  ms=ms("attn"), flop_per_byte=round(attn_ai, 1),
                                  frac_of_min_mfma_hbm=None if attn_t is None else round(attn_t / attn_cap, 4)),
-        # 16-bit rows: sixteen products of 8-bit digits per product
-        "a3_gram": entry("gram", "mfma", rate(wm["gram_flops"] * (1 if w.dtype == "f32" else 16), "gram", "T"),
-                         PEAK["mfma_f64" if w.dtype == "f32" else "mfma_i8"], "TFLOP/s" if w.dtype == "f32" else "TOP/s", ms=ms("gram"),
+        "a3_gram": entry("gram", "mfma", rate(wm["gram_flops"] * (16 if digits else 1), "gram", "T"),
+                         PEAK["mfma_i8" if digits else "mfma_f64"], "TOP/s" if digits else "TFLOP/s", ms=ms("gram"),
                          hbm_gbps=None if not ms("gram") else round(rate(wm["gram_bytes"], "gram", "G"), 1)),
         "a8_similarity": entry("sim", "hbm", rate(wm["sim_bytes"], "sim", "G"), PEAK["hbm_gbps"], "GB/s", ms=ms("sim"),
                                mfma_tflops=None if not ms("sim") else round(rate(wm["sim_flops"], "sim", "T"), 2)),
@@ -228,7 +230,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "bf16 storage; fp32-accumulate bf16 MFMA (attention, similarity); f64 Gram + eigensolver",
+        "dtype": "bf16 storage; fp32-accumulate bf16 MFMA (attention, similarity); exact (whole numbers) or f64 Gram, f64 eigensolver",
         "data": "synthetic",
         "config": {"workload": w.name, "batch": B, "n_vis": N, "n_text": w.n_sys + w.n_prompt,
                    "hidden": w.hidden, "heads": w.n_heads, "head_dim": w.head_dim,

@@ -58,7 +58,8 @@ typedef enum {
   TC_ERR_PARAM = -4,     /* lambda, k_prune, k_final, tolerances out of range        */
   TC_ERR_WORKSPACE = -5, /* ws_bytes < tc_workspace_bytes(p)                         */
   TC_ERR_ALIGN = -6,     /* a pointer is not 16-byte aligned                         */
-  TC_ERR_HIP = -7,       /* a HIP launch failed (hipGetLastError was not hipSuccess) */
+  TC_ERR_HIP = -7,       /* a HIP launch failed (hipGetLastError was not hipSuccess), or an event
+                            that orders the stream groups: outputs are not complete        */
   TC_ERR_SCRATCH = -8    /* tc_merge_noalloc: the sizes need more than TC_NOALLOC_SCRATCH_BYTES */
 } tc_status;
 

@@ -228,7 +228,8 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double* __restrict_
 // ---- 16-bit rows: the products in whole numbers, exact -------------------------------------------------------------
 // The float64 matrix cores bound the kernel above (74 % busy); the 8-bit integer ones do sixty times the operations.  A row of
 // 16-bit values, scaled by a power of two that brings its largest to 31 bits, is a row of whole numbers unless one of its
-// values lies below about 2^-23 of the largest (one value in a million of attention outputs).  Four signed digits to the base
+// values lies below about 2^-23 of the largest (bf16, eight bits of significand; in Gaussian rows one value in two million) or
+// 2^-20 (half, eleven bits; none where the largest is below 128, since the unit of the type is 2^-24).  Four signed digits to the base
 // 256 each, sixteen digit products per product, summed in 32 bits by the weight of the digits (seven sums; D <= 16384 keeps
 // them below 2^31), joined in 64 bits and rounded once: no sum of float64 products is closer.  Values that are
 // not whole numbers are added in float64, rows with more than a few, an infinity or NaN are formed in float64
@@ -468,7 +469,8 @@ __global__ __launch_bounds__(256, 2) void gram_slices_kernel(const char* __restr
       const int r = 4 * g + k, row = r0 + 8 * g + k;
       const long long hi = ((long long)acc[6][r] << 16) + ((long long)acc[5][r] << 8) + acc[4][r];
       const long long lo = ((long long)acc[3][r] << 24) + ((long long)acc[2][r] << 16) + ((long long)acc[1][r] << 8) + acc[0][r];
-      const double x = fma((double)hi, 4294967296.0, (double)lo);  // whole numbers below 2^44 and 2^53 (2^39.003 a column: D < 16352): one rounding
+      // hi below 2^44, lo below 2^53 (2^39.003 a column at most; only from 16352 columns on it could pass): one rounding
+      const double x = fma((double)hi, 4294967296.0, (double)lo);
       v[k] = ldexp(x, -(sc + row_scale(info[row])));
       Gb[(size_t)row * Np + col] = v[k];
     }

@@ -12,7 +12,7 @@
 // column is latency: one exchange of the partial products between the workgroups of the group (about 1.1 us inside an
 // XCD), three barriers with their scalars, and the arithmetic (4 fused multiply-adds per element of the triangle, one
 // every 4.3 clocks of a SIMD).  The update runs while the partial products are on their way.  Measured at 576 tokens:
-// 2.1 ms for one image and 2.2 for 64 (5.6 and 8.8 ms with the matrix in memory), 43 ms for eight images of 2880 tokens (470 ms).
+// 2.1 ms for one image, 2.1 to 2.3 for 64 (5.6 and 8.8 ms with the matrix in memory), 40 ms for eight images of 2880 tokens (470 ms).
 //
 // Frame.  The matrix is placed at the end of a frame of F x F (row f of the frame is row f + base of the matrix).
 // Wavefront w of workgroup (a, b) owns the rows f = i R + 8 a + w (i < LI) and lane l the columns k C + 64 b + l (k < LK), R = 8 PR
@@ -338,9 +338,9 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     // their way.  (With v in the sweep it stood before it: eight images of 2880 tokens 59.6 ms, now 55.6; four of 701 3.45,
     // now 3.39; one of 576 2.53 either way, where issuing the instructions is what takes the time.)
     // MODE 0: nothing is on its way, so the chain is issued in front of the sweep, which hides it (256 tokens: 602 us with v in
-    // the sweep, 620 with the chain behind it, 590 so).  The update with the column before is applied in the same sweep.  Otherwise the product is formed with the
-    // matrix as it is and published, and the update follows while the other workgroups' parts are on their way
-    // (below): p and the next column then still lack it, which costs two scalar products.
+    // the sweep, 620 with the chain behind it, 590 so).  The update with the column before is applied in the same sweep.
+    // Otherwise the product is formed with the matrix as it is and published, and the update follows while the other workgroups'
+    // parts are on their way (below): p and the next column then still lack it, which costs two scalar products.
     if (MODE == 0) own_values();
     const int kmin = (j + 1) / C;
     const bool owner = MODE != 2 || (((j + 1) >> 6) % pc) == b;
