@@ -12,7 +12,11 @@
 // column is latency: one exchange of the partial products between the workgroups of the group (about 1.1 us inside an
 // XCD), three barriers with their scalars, and the arithmetic (4 fused multiply-adds per element of the triangle, one
 // every 4.3 clocks of a SIMD).  The update runs while the partial products are on their way.  Measured at 576 tokens:
-// 2.1 ms for one image, 2.1 to 2.3 for 64 (5.6 and 8.8 ms with the matrix in memory), 40 ms for eight images of 2880 tokens (470 ms).
+// 2.1 ms for one image, 2.1 to 2.3 for 64 (5.6 and 8.8 ms with the matrix in memory), 40 ms for eight images of 2880 tokens (470 ms), all
+// columns by this form.
+//
+// (tridiag_columns.hip does the same with whole columns, in less than half of the time a column and with twice the compute units; this
+// form is for calls whose images fill the device, for more than 2112 tokens, and for small devices.)
 //
 // Frame.  The matrix is placed at the end of a frame of F x F (row f of the frame is row f + base of the matrix).
 // Wavefront w of workgroup (a, b) owns the rows f = i R + 8 a + w (i < LI) and lane l the columns k C + 64 b + l (k < LK), R = 8 PR
@@ -40,17 +44,12 @@
 // raises the image's failure flag, its group follows, and the caller reports the image as failed.)
 // Launches of this library that would strand each other are kept apart by the host (see tr_in_order).
 #include <mutex>
-#include <utility>
 
 #include "tc_internal.h"
+#include "tridiag_device.h"
 #include "tridiag_frames.h"
 
 namespace tc {
-
-typedef unsigned long long u64;
-
-constexpr int TR_WAVES = TR_THREADS / 64;
-constexpr int TD_SPIN = 1 << 22;  // polls before a wait is given up (seconds; a wait in good order is a microsecond)
 
 // d += (value of `row` in lane n of each row of 16 lanes) * c.  `row` holds one matrix row per lane of a row of 16:
 // the multiply-add reads the broadcast lane itself, so a row's value costs no instruction of its own.
@@ -71,38 +70,6 @@ __device__ __forceinline__ void fmac_bcast_neg(double& d, double row, double c) 
 __device__ __forceinline__ void settle(double a, double b) { asm volatile("s_nop 1" : : "v"(a), "v"(b)); }
 __device__ __forceinline__ void settle(double a, double b, double c) { asm volatile("s_nop 1" : : "v"(a), "v"(b), "v"(c)); }
 __device__ __forceinline__ void settle(double a, double b, double c, double d) { asm volatile("s_nop 1" : : "v"(a), "v"(b), "v"(c), "v"(d)); }
-
-// The lowest bit makes room for the tag by rounding to nearest even, and a reader clears the tag: zero arrives as zero.
-__device__ __forceinline__ void publish(u64* p, double v, unsigned tag) {
-  const u64 y = (u64)__double_as_longlong(v);
-  __hip_atomic_store(p, ((y + ((y >> 1) & 1)) & ~1ull) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double received(u64 y) { return __longlong_as_double((long long)(y & ~1ull)); }
-__device__ __forceinline__ u64 peek(const u64* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// True when a wait has to end: it has lasted for TD_SPIN polls, or another workgroup of the image has given up.
-__device__ __forceinline__ bool tr_give_up(int spin, const int32_t* fail) {
-  return spin >= TD_SPIN ||
-         ((spin & 1023) == 1023 && __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
-}
-
-// The members of a group count themselves in.  True when the group is not complete after `patience` polls (at once where that
-// is negative): the first member to find that out sets the top bit, which nobody does once the count is whole, so all
-// members decide alike, those too that get their compute unit later.
-__device__ __forceinline__ bool tr_stranded(u64* arrived, u64 P, int patience) {
-  constexpr u64 off = 1ull << 63;
-  if (patience < 0) return true;
-  for (int spin = 0;; spin++) {
-    u64 n = peek(arrived);
-    if (n & off) return true;
-    if (n >= P) return false;
-    if (spin >= patience &&
-        __hip_atomic_compare_exchange_strong(arrived, &n, n | off, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      return true;
-  }
-}
 
 // Sums of 8 or 16 values over the 64 lanes by recursive halving (fixed order).  On return lane L holds the total of value
 // *which: the halves and the rows of 16 lanes trade with the swap instructions, then L and L^8, (16 values) L and 7-L
@@ -136,29 +103,6 @@ __device__ __forceinline__ double reduce_many(double* x, int lane, int* which) {
   return t;
 }
 
-// f(a), f(a + 1), ... f(n - 1) with the index as a constant.
-template <int a, int n, typename F>
-__device__ __forceinline__ void walk_up(F f) {
-  [&]<int... i>(std::integer_sequence<int, i...>) { (f(std::integral_constant<int, a + i>{}), ...); }(std::make_integer_sequence<int, n - a>{});
-}
-
-__device__ __forceinline__ double sum8(const double* r) {
-  return ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
-}
-
-// 1 / x and 1 / sqrt(x) to the last bit or so: hardware estimate and Newton steps (a library division is 73 cycles of
-// dependent instructions, a square root 105, and a column waits for two of them)
-__device__ __forceinline__ double fast_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
-}
-__device__ __forceinline__ double fast_rsq(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
-  return fma(0.5 * r, fma(-x * r, r, 1.0), r);
-}
-
 // Exchange memory of the launch that follows: cleared, so that no value carries the tag of its first use (1).
 __global__ __launch_bounds__(256) void tridiag_clear_kernel(u64* __restrict__ sync, size_t stride, size_t words,
                                                             int32_t* __restrict__ fail) {
@@ -177,13 +121,9 @@ __global__ __launch_bounds__(256) void tridiag_clear_kernel(u64* __restrict__ sy
 // sync                exchange memory, cleared
 __device__ __forceinline__ int tr_at(int f) { return f + (f >> 5); }
 
-// The index as a value that the compiler knows nothing about.
-template <bool on>
-__device__ __forceinline__ void fresh(int& x) { if (on) asm volatile("" : "+v"(x)); }
-
 template <int PC>  // 0: the single-workgroup frame
 __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void tridiag_kernel(
-    double* __restrict__ G, int N, int Np, int B, int first, int last, int full, double* __restrict__ dvec,
+    double* __restrict__ G, int N, int Np, int B, int first, int last, int full, int mirror, double* __restrict__ dvec,
     double* __restrict__ evec, float* __restrict__ tauv, float* __restrict__ Vc, u64* __restrict__ sync, size_t sync_stride,
     u64* __restrict__ arrived, int patience, int xcds, int32_t* __restrict__ fail) {
   typedef TrShape<PC> S;
@@ -658,6 +598,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         if (fr >= je && fc >= je && fr >= fc) {
           const double y = A[i][k] - Vo[tr_at(fr)] * Wv[tr_at(fc)] - Wv[tr_at(fr)] * Vo[tr_at(fc)];
           A0[(size_t)(fr + base) * Np + fc + base] = y;
+          if (mirror) A0[(size_t)(fc + base) * Np + fr + base] = y;
         }
       }
 }
@@ -768,8 +709,8 @@ constexpr int TR_PATIENCE = 1 << 18;
 extern "C" __attribute__((visibility("default"))) int tc_group_patience = TR_PATIENCE;
 
 namespace tc {
-bool tridiag_fits(int N) { return N <= TR_FRAMES[TR_SIZES - 1].F; }
-int tridiag_most() { return TR_FRAMES[TR_SIZES - 1].F; }
+bool tridiag_fits(int N) { return N <= TR_FRAMES[TR_TRIANGLES - 1].F; }
+int tridiag_most() { return TR_FRAMES[TR_TRIANGLES - 1].F; }
 size_t tridiag_sync_bytes(int N) { return align256(tr_sync_words(N) * 8); }
 
 static int compute_units() {  // of the current device
@@ -785,41 +726,75 @@ static bool tr_capturing(hipStream_t st) {
 
 bool tridiag_allowed(int N, hipStream_t st) { return tr_runs(N, compute_units(), tr_capturing(st)); }
 
-// Two launches of frames that span XCDs, side by side on different streams, can strand each other's groups: an XCD deals out
-// its workgroups by itself, so one may fill with the first launch and another with the second.  An event keeps them apart.
-// (A group of four lies on one XCD: a launch leaves at most three workgroups waiting there.)
-static int tr_in_order(int P, hipStream_t st, bool before) {
-  static std::mutex mx;
-  static hipEvent_t ev[64];
-  static bool used[64];
-  if (!tr_apart(P) || tr_capturing(st)) return TC_OK;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return TC_ERR_HIP;
-  if (before) {
-    mx.lock();
-    if (!used[dev] && hipEventCreateWithFlags(&ev[dev], hipEventDisableTiming) != hipSuccess) { mx.unlock(); return TC_ERR_HIP; }
-    if (used[dev] && hipStreamWaitEvent(st, ev[dev], 0) != hipSuccess) { mx.unlock(); return TC_ERR_HIP; }
-    used[dev] = true;
-    return TC_OK;  // the lock is held until the event is recorded behind the launch
+// Which launches are kept apart.  Groups that wait for members without a compute unit hold theirs, and an XCD deals out its
+// workgroups by itself, in the order of their ids: launches side by side on several streams could strand each other's groups.
+// Groups of four lie on one XCD, and a launch leaves at most three workgroups waiting there: with the four hardware queues of a
+// process twelve of 32, so these launches need no order.  All others take turns on the XCDs they use: an event per XCD, behind
+// the last launch there.  (A launch with few images of up to sixteen members uses as many XCDs as it has images, the next such
+// launch the next ones, so that small calls run side by side.)  Within a launch, the group with the lowest number that is not
+// complete finds its compute units: 15 workgroups at most wait on its XCD, and nine of the groups of four.  Captured launches
+// cannot be kept apart; tr_runs and the frames allowed there bound what a stranded group holds.
+// An event is known by the first XCD of the launch behind which it is recorded; another launch that starts there waits for it
+// first, so who waits for an event that has moved on waits for more.
+static std::mutex tr_mx;
+static hipEvent_t tr_ev[64][8];
+static bool tr_made[64];
+static unsigned char tr_last[64][8];  // event of the last launch on an XCD
+static int tr_next[64];
+
+TrTurn::TrTurn(int P, int images, int xcds_, hipStream_t st_) : xcds(xcds_ < 8 ? xcds_ : 8), st(st_) {
+  captured = tr_capturing(st);
+  apart = tr_apart(P) && !captured;
+  rc = TC_OK;
+  if (!apart) return;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { apart = false; rc = TC_ERR_HIP; return; }
+  tr_mx.lock();
+  for (int x = 0; x < 8 && !tr_made[dev]; x++)
+    if (!tr_ev[dev][x] && hipEventCreateWithFlags(&tr_ev[dev][x], hipEventDisableTiming) != hipSuccess) rc = TC_ERR_HIP;
+  if (rc == TC_OK) tr_made[dev] = true;
+  count = images < xcds ? images : xcds;
+  first = count < xcds ? tr_next[dev] % xcds : 0;
+  unsigned seen = 0;
+  for (int i = 0; i < count && rc == TC_OK; i++) {
+    const int e = tr_last[dev][(first + i) % xcds];
+    if (!(seen >> e & 1) && hipStreamWaitEvent(st, tr_ev[dev][e], 0) != hipSuccess) rc = TC_ERR_HIP;
+    seen |= 1u << e;
   }
-  const hipError_t e = hipEventRecord(ev[dev], st);
-  mx.unlock();
-  return e == hipSuccess ? TC_OK : TC_ERR_HIP;
+  if (rc != TC_OK) {
+    (void)hipGetLastError();  // it is reported here, not by the next launch
+    tr_mx.unlock();
+    apart = false;
+  }  // otherwise the lock is held until the event is recorded behind the launch
 }
 
+int TrTurn::done() {
+  if (!apart) return TC_OK;
+  const bool ok = hipEventRecord(tr_ev[dev][first], st) == hipSuccess;
+  if (!ok) {
+    (void)hipStreamSynchronize(st);  // nobody can wait for this launch, so it is over
+    (void)hipGetLastError();
+  }
+  for (int i = 0; i < count; i++) tr_last[dev][(first + i) % xcds] = (unsigned char)first;
+  tr_next[dev] = (first + count) % xcds;
+  tr_mx.unlock();
+  return ok ? TC_OK : TC_ERR_HIP;
+}
+
+int launch_columns(const Plan& pl, const TrPhase& ph, double* G, double* dvec, double* evec, float* tauv, float* Vc, u64* sync,
+                   size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st);  // tridiag_columns.hip
+
 template <int PC>
-static int tr_launch(const Plan& pl, const TrPhase& ph, double* G, double* dvec, double* evec, float* tauv, float* Vc, u64* sync,
-                     size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st) {
+static int tr_launch(const Plan& pl, const TrPhase& ph, int mirror, double* G, double* dvec, double* evec, float* tauv, float* Vc,
+                     u64* sync, size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st) {
   typedef TrShape<PC> S;
   if (S::LDS > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_kernel<PC>),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS) != hipSuccess)
     return TC_ERR_HIP;
   const int grid = (S::MODE == 1 ? (pl.B + xcds - 1) / xcds * xcds : pl.B) * S::P;
-  int rc = tr_in_order(S::P, st, true);
-  if (rc != TC_OK) return rc;
-  TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_kernel<PC><<<grid, TR_THREADS, S::LDS, st>>>(G, pl.N, pl.Np, pl.B, ph.first, ph.last, ph.first == 0, dvec, evec, tauv, Vc, sync + ph.off, stride, arrived, patience, xcds, fail)));
-  rc = check_launch();
-  const int rc2 = tr_in_order(S::P, st, false);
+  TrTurn turn(S::P, xcds, xcds, st);
+  if (turn.rc != TC_OK) return turn.rc;
+  TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_kernel<PC><<<grid, TR_THREADS, S::LDS, st>>>(G, pl.N, pl.Np, pl.B, ph.first, ph.last, ph.first == 0, mirror, dvec, evec, tauv, Vc, sync, stride, arrived, patience, xcds, fail)));
+  const int rc = check_launch(), rc2 = turn.done();
   return rc != TC_OK ? rc : rc2;
 }
 
@@ -828,24 +803,30 @@ int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float*
   const int cus = compute_units(), xcds = cus >= 64 ? cus / 32 : 1;  // (32 compute units each)
   TrPhase ph[TR_SIZES];
   size_t words;
-  const int n = tr_phases(pl.N, pl.batch_call, cus, ph, &words);
+  const int n = tr_phases(pl.N, pl.batch_call, cus, ph, &words, tr_capturing(st));
   if (n == 0) return TC_ERR_SHAPE;
   const size_t stride = sync_bytes / 8;
   if (words + TR_SIZES > stride) return TC_ERR_WORKSPACE;
   u64* sy = static_cast<u64*>(sync);
   const unsigned per = (unsigned)((words + TR_SIZES + 1023) / 1024);
   TC_TIMED(PK_TRIDIAG_UPDATE, 0, st, (tridiag_clear_kernel<<<dim3(per > 64 ? 64 : per, pl.B), 256, 0, st>>>(sy, stride, words + TR_SIZES, fail)));
+  bool alone = false;
   for (int i = 0; i < n; i++) {
     const int set = tc_group_patience, patience = set >= 0 ? set : i + 1 >= -set ? -1 : TR_PATIENCE;
-    int rc = TC_ERR_SHAPE;
-#define TR_CASE(SIZE_, PC_) case SIZE_: rc = tr_launch<PC_>(pl, ph[i], G, dvec, evec, tauv, Vc, sy, stride, sy + words + i, patience, xcds, fail, st); break;
+    const int mirror = i + 1 < n && ph[i + 1].size >= TR_TRIANGLES;  // whole columns want both triangles
+    u64* words_of = sy + ph[i].off;
+    u64* arrived = sy + words + i;
+    int rc;
+    alone |= TR_FRAMES[ph[i].size].P > 1;
+#define TR_CASE(PC_) case PC_: rc = tr_launch<PC_>(pl, ph[i], mirror, G, dvec, evec, tauv, Vc, words_of, stride, arrived, patience, xcds, fail, st); break;
     switch (ph[i].size) {
-      TR_CASE(0, 0) TR_CASE(1, 1) TR_CASE(2, 2) TR_CASE(3, 3) TR_CASE(4, 4) TR_CASE(5, 5) TR_CASE(6, 6)
+      TR_CASE(0) TR_CASE(1) TR_CASE(2) TR_CASE(3) TR_CASE(4) TR_CASE(5) TR_CASE(6)
+      default: rc = launch_columns(pl, ph[i], G, dvec, evec, tauv, Vc, words_of, stride, arrived, patience, xcds, fail, st);
     }
 #undef TR_CASE
     if (rc != TC_OK) return rc;
   }
-  if (TR_FRAMES[ph[0].size].P > 1) {
+  if (alone) {
     const size_t shm = alone_lds(pl.N);
     if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_alone_kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)

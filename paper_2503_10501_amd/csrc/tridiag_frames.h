@@ -1,5 +1,5 @@
-// Frames of the register-resident reduction to tridiagonal form (tridiag.hip): geometry, exchange memory, phases, and
-// which of them a device can hold.  Host code only.
+// Frames of the register-resident reduction to tridiagonal form (tridiag.hip, tridiag_columns.hip): geometry, exchange memory,
+// phases, and which of them a device can hold.  Host code only.
 #pragma once
 #include <stddef.h>
 
@@ -7,7 +7,7 @@ namespace tc {
 
 constexpr int TR_THREADS = 512;
 
-// Geometry of a frame.
+// Geometry of a frame that holds the lower triangle (tridiag.hip).
 template <int PC>
 struct TrShape {
   static constexpr int MODE = PC == 0 ? 0 : PC == 1 ? 1 : 2;
@@ -27,58 +27,112 @@ struct TrShape {
   static_assert(LI * R == F, "rows and columns must cover the same frame");
 };
 
-struct TrFrame { int mode, F, P; size_t words; };
-constexpr int TR_SIZES = 7;  // frames: 0 the single workgroup, n: PC = n
+// Geometry of a frame that holds whole columns (tridiag_columns.hip): P workgroups of eight wavefronts, of which four hold the
+// matrix, LK columns each with LI rows in a lane; the other four work on the vectors.
+template <int LI_, int LK_, int P_>
+struct TcShape {
+  static constexpr int LI = LI_, LK = LK_, P = P_;
+  static constexpr bool LOCAL = P <= 16;    // a group lies on one XCD
+  static constexpr int F = 64 * LI;         // rows
+  static constexpr int CW = 4 * P;          // columns of a class: one for every wavefront of the group that holds the matrix
+  static constexpr int CO = LK * CW - F;    // columns the classes have in front of the frame's first
+  static constexpr int E = (F + 255) / 256, FP = 256 * E;  // vector elements of a thread; room of a vector
+  static constexpr int RO = (F + P - 1) / P;    // rows of the reflectors that a workgroup writes
+  static constexpr size_t WORDS = (size_t)6 * F;  // exchange: two slots of products, four of next columns
+  static constexpr size_t LDS = (size_t)(5 * FP + 52) * 8 + (size_t)(RO * 16 + 16) * 4 + 16;
+  static_assert(RO <= 64, "rows of one wavefront");
+  static_assert(CO >= 0 && CO < CW, "the classes must cover the frame");
+  static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
+};
+
+constexpr int TR_LAST = 128;  // rows that one workgroup of four wavefronts reduces (tridiag_last_kernel)
+
+// least: rows a frame leaves at least (all of its workgroups must have a column to publish); us: time of a column in microseconds,
+// from which the phases are chosen.
+struct TrFrame { int mode, F, P; size_t words; int least; double us; };
+constexpr int TR_TRIANGLES = 7;  // frames: 0 the single workgroup, n: PC = n,
+constexpr int TR_LAST_SIZE = TR_TRIANGLES;  // the last columns, and whole columns from here on: (number, LI, LK, P, us)
+#define TC_FRAMES(X) \
+  X(8, 6, 12, 8, 1.4) X(9, 9, 9, 16, 1.45) X(10, 12, 6, 32, 1.75) X(11, 18, 4, 72, 1.9) X(12, 24, 3, 128, 2.2) X(13, 30, 3, 160, 2.5) X(14, 33, 3, 176, 2.7)
+constexpr int TR_SIZES = 15;
 inline const TrFrame TR_FRAMES[TR_SIZES] = {
-#define TR_ENTRY(PC_) {TrShape<PC_>::MODE, TrShape<PC_>::F, TrShape<PC_>::P, TrShape<PC_>::WORDS}
-    TR_ENTRY(0), TR_ENTRY(1), TR_ENTRY(2), TR_ENTRY(3), TR_ENTRY(4), TR_ENTRY(5), TR_ENTRY(6)
+#define TR_ENTRY(PC_, US_) {TrShape<PC_>::MODE, TrShape<PC_>::F, TrShape<PC_>::P, TrShape<PC_>::WORDS, 0, US_}
+    TR_ENTRY(0, 2.95), TR_ENTRY(1, 4.5), TR_ENTRY(2, 5.75), TR_ENTRY(3, 5.9), TR_ENTRY(4, 6.9), TR_ENTRY(5, 8.3), TR_ENTRY(6, 9.0),
+#undef TR_ENTRY
+    {3, TR_LAST, 1, 0, 0, 0.95},
+#define TR_ENTRY(N_, LI_, LK_, P_, US_) {4, TcShape<LI_, LK_, P_>::F, P_, TcShape<LI_, LK_, P_>::WORDS, TcShape<LI_, LK_, P_>::CW, US_},
+    TC_FRAMES(TR_ENTRY)
 #undef TR_ENTRY
 };
 
-// The phases of a reduction: a frame works on the columns it is worth having, then hands the trailing matrix (through G)
-// to a smaller one.  The next frame is the largest that needs fewer exchanges per column or lets more images run
-// at once, so that the launch takes fewer rounds over the device's compute units.  (Hand-overs lie at multiples of 16
-// columns: the blocks of sixteen reflectors.)
+// The smallest of the triangular frames that holds N rows (TR_TRIANGLES: none).
+inline int tr_triangle(int N) {
+  int size = 0;
+  while (size < TR_TRIANGLES && TR_FRAMES[size].F < N) size++;
+  return size;
+}
+
+// Inside a captured graph (which may be replayed on several streams, where the host cannot keep launches apart) a group that is
+// stranded (see tridiag.hip) must hold a small part of the device: up to a seventh.
+inline bool tr_holds(int P, int cus, bool captured) { return (captured ? 7 : 1) * P <= (P > 1 ? cus : 256); }
+
+// The phases of a reduction: a frame works on the columns it is worth having, then hands the trailing matrix (through G) to a
+// smaller one; the last TR_LAST rows are one workgroup's.  Chosen so that the sum over the phases is least: columns, times the
+// rounds that the call's images make over the device, times the time of a column, and TR_HAND for handing over.
+// (Hand-overs lie at multiples of 16 columns: the blocks of sixteen reflectors.)
 struct TrPhase { int size, first, last; size_t off; };  // off: where its exchange words start
-inline int tr_phases(int N, int B, int cus, TrPhase* out, size_t* words) {
-  auto rounds = [&](int s) { const int at_once = cus / TR_FRAMES[s].P > 1 ? cus / TR_FRAMES[s].P : 1; return (B + at_once - 1) / at_once; };
-  int size = 0, n = 0, first = 0;
-  while (size < TR_SIZES && TR_FRAMES[size].F < N) size++;
+constexpr double TR_HAND = 12.0;
+inline int tr_phases(int N, int B, int cus, TrPhase* out, size_t* words, bool captured = false) {
+  const int top = tr_triangle(N);
   *words = 0;
-  if (size == TR_SIZES) return 0;
-  while (true) {
-    int next = size - 1;
-    while (next >= 0 && TR_FRAMES[next].mode == TR_FRAMES[size].mode && rounds(next) >= rounds(size)) next--;
-    const int last = next >= 0 ? (N - TR_FRAMES[next].F + 15) / 16 * 16 : N;
-    out[n++] = TrPhase{size, first, last, *words};
-    *words += TR_FRAMES[size].words;
-    if (next < 0) return n;
-    size = next;
-    first = last;
+  if (top == TR_TRIANGLES) return 0;
+  const int most = TR_FRAMES[top].F > TR_FRAMES[1].F ? TR_FRAMES[top].F : TR_FRAMES[1].F;  // (what tr_sync_words counts)
+  auto from = [&](int s) { return TR_FRAMES[s].F >= N ? 0 : (N - TR_FRAMES[s].F + 15) / 16 * 16; };  // first column of a frame
+  auto rounds = [&](int P) { const int at_once = cus / P > 1 ? cus / P : 1; return (B + at_once - 1) / at_once; };
+  double best[TR_SIZES];
+  int next[TR_SIZES], start = -1;
+  for (int s = 0; s < TR_SIZES; s++) best[s] = -1;
+  best[TR_LAST_SIZE] = rounds(1) * TR_FRAMES[TR_LAST_SIZE].us * (N - from(TR_LAST_SIZE));
+  next[TR_LAST_SIZE] = -1;
+  for (int F = TR_LAST; F <= most; F += 64)  // by size
+    for (int s = 0; s < TR_SIZES; s++) {
+      const TrFrame& f = TR_FRAMES[s];
+      if (f.F != F) continue;
+      // (whether the device holds the smallest triangular frame for N is asked elsewhere: tr_runs)
+      if (s != TR_LAST_SIZE && (s == top || tr_holds(f.P, cus, captured)))
+        for (int t = 0; t < TR_SIZES; t++) {
+          if (best[t] < 0 || TR_FRAMES[t].F >= F || from(t) <= from(s) || N - from(t) < f.least) continue;
+          const double c = (from(t) - from(s)) * rounds(f.P) * f.us + TR_HAND + best[t];
+          if (best[s] < 0 || c < best[s]) { best[s] = c; next[s] = t; }
+        }
+      if (F >= N && best[s] >= 0 && (start < 0 || best[s] < best[start])) start = s;
+    }
+  if (start < 0) return 0;
+  int n = 0;
+  for (int s = start; s >= 0; s = next[s]) {
+    out[n++] = TrPhase{s, from(s), next[s] >= 0 ? from(next[s]) : N, *words};
+    *words += TR_FRAMES[s].words;
   }
+  return n;
 }
 
 // Exchange memory of one image in words of 8 bytes: that of every frame that may take part (which do depends on the number of
 // images; the size of a workspace must not fall when that or N grows), and an arrival counter per phase.
 inline size_t tr_sync_words(int N) {
   size_t words = TR_SIZES;
-  for (int size = 0; size < TR_SIZES; size++) {
-    words += TR_FRAMES[size].words;
-    if (TR_FRAMES[size].F >= N) break;
-  }
+  const int top = tr_triangle(N), F = top < 2 ? TR_FRAMES[1].F : TR_FRAMES[top < TR_TRIANGLES ? top : TR_TRIANGLES - 1].F;
+  for (const TrFrame& f : TR_FRAMES)
+    if (f.F <= F) words += f.words;
   return words;
 }
 
 // Whether the reduction of N tokens runs on a device with `cus` compute units: a group must be able to be resident at once.
-// Inside a captured graph (which may be replayed on several streams, where the host cannot keep launches apart) only where
-// a stranded group (see tridiag.hip) holds a small part of the device: up to a seventh.
 inline bool tr_runs(int N, int cus, bool captured) {
-  int size = 0;
-  while (size < TR_SIZES && TR_FRAMES[size].F < N) size++;
-  return size < TR_SIZES && (captured ? 7 : 1) * TR_FRAMES[size].P <= (TR_FRAMES[size].P > 1 ? cus : 256);
+  const int size = tr_triangle(N);
+  return size < TR_TRIANGLES && tr_holds(TR_FRAMES[size].P, cus, captured);
 }
 
-// Launches that the host keeps apart: groups of a frame that spans several XCDs.
+// Launches that the host keeps apart (see tr_in_order).
 inline bool tr_apart(int P) { return P > 4; }
 
 }  // namespace tc
