@@ -21,8 +21,11 @@
 //   vectors:  A | w_o, its sums with x | 0 | reflector v, waiting for A x, p, its product with v | B | next column
 // Measured at 576 tokens on one XCD, clocks (2.4 GHz): A x 900 - 1300, reflector 900, waiting 600, p 500, next column 350: 3500 -
 // 4000, 1.45 us (the triangle 4.5 us, one workgroup for 256 tokens 2.3 us).  The whole reduction, ms, triangle and now: 64 tokens
-// 0.097 and 0.051, 300 x 3 0.78 and 0.34, 576 x 1 2.05 and 0.80, x 16 2.07 and 0.83, x 64 2.2 and 1.9, 1152 x 1 5.4 and 2.1, 1499 x 2
+// 0.097 and 0.051, 300 x 3 0.78 and 0.34, 576 x 1 2.05 and 0.80, x 16 2.07 and 0.83, x 64 2.2 and 1.8, 1152 x 1 5.4 and 2.1, 1499 x 2
 // 7.4 and 3.2, 2880 x 1 17.5 and 11.5.
+// Batches that fill the chip take the fewest workgroups an image that the registers allow: 320 rows by four, 448 by eight (100 and
+// 98 elements a lane).  64 images of 576 tokens up to the last 128 rows, us: 192 columns of the triangle and 256 of 384 rows by
+// eight in two rounds 1091 + 736; now 128 of the triangle, 64 of 448, 64 of 384 and 192 of 320 rows 774 + 282 + 243 + 325.
 //
 // Exchange: as in tridiag.hip, a value's lowest mantissa bit carries the parity of its use of the slot.  Products have two slots
 // in turn: who publishes for column j + 2 has read all products of column j + 1, so every workgroup had published those and was
@@ -226,8 +229,15 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       // columns whose product needs the classes from K on
       constexpr int K = decltype(kc)::value, n = LK - K, i0 = (K * CW - CO > 0 ? K * CW - CO : 0) / 64, end = (K + 1) * CW - CO - 1;
       if (j >= end) return;
-      const int q = place_of_sum<n>(lane), cq = (K + q) * CW + cw;
-      const int ypl = q < 0 || cq < 0 ? 0 : 8 * cq;  // byte offset of the product that this lane publishes (0: none)
+      // Sums of M columns at a time: more take registers that the matrix needs.  ypl: byte offsets of the products that this lane
+      // publishes (0: none)
+      constexpr int M = n > 14 ? (n + 1) / 2 : n, PARTS = (n + M - 1) / M;
+      int ypl[PARTS];
+#pragma unroll
+      for (int h = 0; h < PARTS; h++) {
+        const int q = place_of_sum<M>(lane), cq = (K + h * M + q) * CW + cw;
+        ypl[h] = q < 0 || h * M + q >= n || cq < 0 ? 0 : 8 * cq;
+      }
       for (; j < min(je, end); j++) {
         int lj = lane;
         fresh<true>(lj);
@@ -239,34 +249,42 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
           constexpr int NA = n > 2 || LI - i0 < 2 ? 1 : 2;  // (few columns: two chains each)
           // (rows in turns: what is read ahead is bounded, so that the matrix stays in the registers)
           constexpr int T = LI <= 12 ? LI : 6;
-          double acc[NA][n], xr[2][T];
           auto below = [&](int i) {  // (zero up to and with the head)
             const double x = X[OFF + 64 * i + lj];
             return 64 * i <= end && 64 * i + lj <= j + 1 ? 0.0 : x;
           };
+          double xr[2][T];
 #pragma unroll
           for (int r = 0; r < T; r++)
             if (i0 + r < LI) xr[0][r] = below(i0 + r);
+          walk_up<0, PARTS>([&](auto hc) __attribute__((always_inline)) {
+            constexpr int q0 = decltype(hc)::value * M, m = n - q0 < M ? n - q0 : M;
+            static_assert(PARTS == 1 || T >= LI, "the rows are there for every part");
+            double acc[NA][M];
 #pragma unroll
-          for (int i = i0; i < LI; i++) {
-            const int r = (i - i0) % T, b = (i - i0) / T % 2;
-            if (r == 0) {
+            for (int i = i0; i < LI; i++) {
+              const int r = (i - i0) % T, b = (i - i0) / T % 2;
+              if (r == 0) {
 #pragma unroll
-              for (int s = 0; s < T; s++)
-                if (i + T + s < LI) xr[1 - b][s] = below(i + T + s);
-              if (T < LI - i0) __builtin_amdgcn_sched_barrier(0);
+                for (int s = 0; s < T; s++)
+                  if (i + T + s < LI) xr[1 - b][s] = below(i + T + s);
+                if (T < LI - i0) __builtin_amdgcn_sched_barrier(0);
+              }
+#pragma unroll
+              for (int q = 0; q < m; q++) {
+                double& a = acc[(i - i0) % NA][q];
+                a = i - i0 < NA ? A[i][K + q0 + q] * xr[b][r] : fma(A[i][K + q0 + q], xr[b][r], a);
+              }
             }
+            if (NA == 2)
 #pragma unroll
-            for (int q = 0; q < n; q++) {
-              double& a = acc[(i - i0) % NA][q];
-              a = i - i0 < NA ? A[i][K + q] * xr[b][r] : fma(A[i][K + q], xr[b][r], a);
-            }
-          }
-          if (NA == 2)
+              for (int q = 0; q < m; q++) acc[0][q] += acc[NA - 1][q];
 #pragma unroll
-            for (int q = 0; q < n; q++) acc[0][q] += acc[NA - 1][q];
-          const double t = reduce_lanes<n>(acc[0], lj);
-          if (ypl > 8 * j) publish_to(near, reinterpret_cast<u64*>(reinterpret_cast<char*>(Yj) + (unsigned)ypl), t, tag);
+            for (int q = m; q < M; q++) acc[0][q] = 0.0;
+            const double t = reduce_lanes<M>(acc[0], lj);
+            const int y = ypl[decltype(hc)::value];
+            if (y > 8 * j) publish_to(near, reinterpret_cast<u64*>(reinterpret_cast<char*>(Yj) + (unsigned)y), t, tag);
+          });
         }
         __syncthreads();
         // ---- the update with the column before ------------------------------------------------------------------
@@ -274,34 +292,38 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         // the columns' values: lane k reads those of class k, which then come from scalar registers
         const int cl = max(OFF + min(lj, LK - 1) * CW + cw, 0);
         const double vcl = -Vo[cl], wcl = -Wv[cl];
-        double vc[n], wc[n];
         constexpr int T = 3;  // rows read ahead
-        double vr[2][T], wr[2][T];
 #pragma unroll
-        for (int r = 0; r < T; r++)
-          if (i0 + r < LI) {
-            vr[0][r] = Vo[OFF + 64 * (i0 + r) + lj];
-            wr[0][r] = Wv[OFF + 64 * (i0 + r) + lj];
+        for (int q0 = 0; q0 < n; q0 += M) {  // (a column's values are four scalar registers)
+          double vc[M], wc[M], vr[2][T], wr[2][T];
+#pragma unroll
+          for (int r = 0; r < T; r++)
+            if (i0 + r < LI) {
+              vr[0][r] = Vo[OFF + 64 * (i0 + r) + lj];
+              wr[0][r] = Wv[OFF + 64 * (i0 + r) + lj];
+            }
+#pragma unroll
+          for (int k = 0; k < M; k++) {
+            vc[k] = readlane_f64(vcl, K + q0 + k);
+            wc[k] = readlane_f64(wcl, K + q0 + k);
           }
 #pragma unroll
-        for (int k = 0; k < n; k++) {
-          vc[k] = readlane_f64(vcl, K + k);
-          wc[k] = readlane_f64(wcl, K + k);
-        }
+          for (int i = i0; i < LI; i++) {
+            const int r = (i - i0) % T, b = (i - i0) / T % 2;
+            if (r == 0) {
 #pragma unroll
-        for (int i = i0; i < LI; i++) {
-          const int r = (i - i0) % T, b = (i - i0) / T % 2;
-          if (r == 0) {
+              for (int s = 0; s < T; s++)
+                if (i + T + s < LI) {
+                  vr[1 - b][s] = Vo[OFF + 64 * (i + T + s) + lj];
+                  wr[1 - b][s] = Wv[OFF + 64 * (i + T + s) + lj];
+                }
+              if (T < LI - i0) __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
-            for (int s = 0; s < T; s++)
-              if (i + T + s < LI) {
-                vr[1 - b][s] = Vo[OFF + 64 * (i + T + s) + lj];
-                wr[1 - b][s] = Wv[OFF + 64 * (i + T + s) + lj];
-              }
-            if (T < LI - i0) __builtin_amdgcn_sched_barrier(0);
+            for (int q = 0; q < M; q++)
+              if (q0 + q < n) A[i][K + q0 + q] = fma(wr[b][r], vc[q], fma(vr[b][r], wc[q], A[i][K + q0 + q]));
           }
-#pragma unroll
-          for (int q = 0; q < n; q++) A[i][K + q] = fma(wr[b][r], vc[q], fma(vr[b][r], wc[q], A[i][K + q]));
+          if (M < n) __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int i = i0; i < LI; i++)
@@ -345,16 +367,19 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     auto hand_out = [&](int j, int l) {
       const int jr = j - 1 + base;
       const double* Vo = (j & 1) ? Va : Vb;
-      if (w == 3 && l < RO) {
-        const int f = m * RO + l, r = f + base;
-        const double y = Vo[OFF + min(f, F - 1)];
-        vblk[l * 16 + (jr & 15)] = f >= j ? (float)y : 0.f;
-        if ((jr & 15) == 15 && r >= (jr & ~15) && f < F) {
-          float4* dst = reinterpret_cast<float4*>(Vc + (size_t)img * Np * Np + ((size_t)(jr >> 4) * Np + r) * 16);
+      if (w == 3)
 #pragma unroll
-          for (int u = 0; u < 4; u++) dst[u] = reinterpret_cast<const float4*>(vblk + l * 16)[u];
+        for (int s = 0; s < RO; s += 64) {
+          const int q = l + s, f = m * RO + q, r = f + base;
+          if (q >= RO) break;
+          const double y = Vo[OFF + min(f, F - 1)];
+          vblk[q * 16 + (jr & 15)] = f >= j ? (float)y : 0.f;
+          if ((jr & 15) == 15 && r >= (jr & ~15) && f < F) {
+            float4* dst = reinterpret_cast<float4*>(Vc + (size_t)img * Np * Np + ((size_t)(jr >> 4) * Np + r) * 16);
+#pragma unroll
+            for (int u = 0; u < 4; u++) dst[u] = reinterpret_cast<const float4*>(vblk + q * 16)[u];
+          }
         }
-      }
       if (w == 2 && m == 0 && (jr & 15) == 15 && l < 16) {
         const int c = (jr & ~15) + l;
         dvec[(size_t)img * Np + c] = dbuf[l];

@@ -40,7 +40,7 @@ struct TcShape {
   static constexpr int RO = (F + P - 1) / P;    // rows of the reflectors that a workgroup writes
   static constexpr size_t WORDS = (size_t)6 * F;  // exchange: two slots of products, four of next columns
   static constexpr size_t LDS = (size_t)(5 * FP + 52) * 8 + (size_t)(RO * 16 + 16) * 4 + 16;
-  static_assert(RO <= 64, "rows of one wavefront");
+  static_assert(LK <= 32, "sums and columns of one wavefront");
   static_assert(CO >= 0 && CO < CW, "the classes must cover the frame");
   static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
 };
@@ -53,13 +53,14 @@ struct TrFrame { int mode, F, P; size_t words; int least; double us; };
 constexpr int TR_TRIANGLES = 7;  // frames: 0 the single workgroup, n: PC = n,
 constexpr int TR_LAST_SIZE = TR_TRIANGLES;  // the last columns, and whole columns from here on: (number, LI, LK, P, us)
 #define TC_FRAMES(X) \
-  X(8, 6, 12, 8, 1.4) X(9, 9, 9, 16, 1.45) X(10, 12, 6, 32, 1.75) X(11, 18, 4, 72, 1.9) X(12, 24, 3, 128, 2.2) X(13, 30, 3, 160, 2.5) X(14, 33, 3, 176, 2.7)
-constexpr int TR_SIZES = 15;
+  X(8, 6, 12, 8, 1.35) X(9, 9, 9, 16, 1.75) X(10, 12, 6, 32, 2.1) X(11, 18, 4, 72, 2.5) X(12, 24, 3, 128, 2.95) X(13, 30, 3, 160, 3.3) \
+  X(14, 33, 3, 176, 3.5) X(15, 5, 20, 4, 1.45) X(16, 7, 14, 8, 1.65)
+constexpr int TR_SIZES = 17;
 inline const TrFrame TR_FRAMES[TR_SIZES] = {
 #define TR_ENTRY(PC_, US_) {TrShape<PC_>::MODE, TrShape<PC_>::F, TrShape<PC_>::P, TrShape<PC_>::WORDS, 0, US_}
-    TR_ENTRY(0, 2.95), TR_ENTRY(1, 4.5), TR_ENTRY(2, 5.75), TR_ENTRY(3, 5.9), TR_ENTRY(4, 6.9), TR_ENTRY(5, 8.3), TR_ENTRY(6, 9.0),
+    TR_ENTRY(0, 3.05), TR_ENTRY(1, 5.5), TR_ENTRY(2, 6.4), TR_ENTRY(3, 7.35), TR_ENTRY(4, 7.4), TR_ENTRY(5, 8.3), TR_ENTRY(6, 9.0),
 #undef TR_ENTRY
-    {3, TR_LAST, 1, 0, 0, 0.95},
+    {3, TR_LAST, 1, 0, 0, 0.93},
 #define TR_ENTRY(N_, LI_, LK_, P_, US_) {4, TcShape<LI_, LK_, P_>::F, P_, TcShape<LI_, LK_, P_>::WORDS, TcShape<LI_, LK_, P_>::CW, US_},
     TC_FRAMES(TR_ENTRY)
 #undef TR_ENTRY
@@ -78,7 +79,7 @@ inline bool tr_holds(int P, int cus, bool captured) { return (captured ? 7 : 1) 
 
 // The phases of a reduction: a frame works on the columns it is worth having, then hands the trailing matrix (through G) to a
 // smaller one; the last TR_LAST rows are one workgroup's.  Chosen so that the sum over the phases is least: columns, times the
-// rounds that the call's images make over the device, times the time of a column, and TR_HAND for handing over.
+// rounds that the call's images make over the device, times the time of a column, and TR_HAND a round for handing over.
 // (Hand-overs lie at multiples of 16 columns: the blocks of sixteen reflectors.)
 struct TrPhase { int size, first, last; size_t off; };  // off: where its exchange words start
 constexpr double TR_HAND = 12.0;
@@ -102,7 +103,7 @@ inline int tr_phases(int N, int B, int cus, TrPhase* out, size_t* words, bool ca
       if (s != TR_LAST_SIZE && (s == top || tr_holds(f.P, cus, captured)))
         for (int t = 0; t < TR_SIZES; t++) {
           if (best[t] < 0 || TR_FRAMES[t].F >= F || from(t) <= from(s) || N - from(t) < f.least) continue;
-          const double c = (from(t) - from(s)) * rounds(f.P) * f.us + TR_HAND + best[t];
+          const double c = (from(t) - from(s)) * rounds(f.P) * f.us + TR_HAND * rounds(f.P) + best[t];
           if (best[s] < 0 || c < best[s]) { best[s] = c; next[s] = t; }
         }
       if (F >= N && best[s] >= 0 && (start < 0 || best[s] < best[start])) start = s;

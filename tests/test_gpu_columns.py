@@ -1,5 +1,5 @@
 """GPU tests of the reduction by groups that hold whole columns, and of the last columns by one workgroup: token counts at the edges of
-their frames (128, 384, 576, 768, 1152, 1536, 1920, 2112), images that need more than one round over the device."""
+their frames (128, 320, 384, 448, 576, 768, 1152, 1536, 1920, 2112), images that need more than one round over the device."""
 import pytest
 import torch
 
@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 
 # sigma: the float32 output and a few eps ||G|| on its square; C: reflectors and vectors are held in float32, a row of U is off by
 # about sqrt(N) 2^-24 (3e-6 at 2113 tokens), and so is its weighted sum
-@pytest.mark.parametrize("n,batch", [(15, 2), (16, 1), (127, 3), (128, 1), (129, 2), (144, 1), (145, 1), (384, 33), (385, 2), (448, 17),
-                                     (560, 1), (768, 9), (769, 1), (1153, 4), (1536, 1), (1537, 2), (1921, 1), (2112, 1), (2113, 1)])
+@pytest.mark.parametrize("n,batch", [(15, 2), (16, 1), (127, 3), (128, 1), (129, 2), (144, 1), (145, 1), (200, 16), (320, 64),
+                                     (321, 65), (384, 33), (385, 2), (448, 17), (449, 40), (560, 1), (768, 9), (769, 1), (1153, 4), (1536, 1), (1537, 2), (1921, 1), (2112, 1), (2113, 1)])
 def test_singular_values_and_scores_at_the_edges_of_the_column_frames(n, batch):
     tc = _tc()
     O = _rows(batch, n, 512, 3 * n + batch)
