@@ -8,6 +8,8 @@
 // scores, forms the exact probabilities, accumulates O^T and the column sums of the probabilities
 // (the attention matrix itself is never stored).  Column sums leave the workgroup as one partial
 // row per (head, query tile) and are added in a fixed order by a second small kernel.
+#include <cfloat>
+
 #include "tc_internal.h"
 
 namespace tc {
@@ -463,86 +465,203 @@ __global__ __launch_bounds__(256) void attn_score_reduce(const float* __restrict
     S[(size_t)b * N + x] = (float)(((part[0][xl] + part[1][xl]) + (part[2][xl] + part[3][xl])) / ((double)H * (double)Nq));
 }
 
-// ---------------- float32 storage: plain-ALU correctness path ----------------
-// One wavefront per (image, head, query): two passes over the keys, float accumulation.
+// ---------------- float32 storage ----------------
+// Both products on the float32 matrix cores (16x16x4: lane i + 16 g holds A[i][g] and B[g][i], and gets D[4 g + r][i] in register
+// r; products and sums are those of a float32 multiply-add).  Tiles of 16 queries by 16 keys.  With a lane per key and a
+// wavefront per query, which this took before, every lane read rows of its own, 64 lines an instruction.  Rows and column sums, us,
+// before and now: 16 images of 300 tokens with 8 heads of 64 900 and 114, 4 of 100 with 4 of 128 110 and 26, one of 64 with 4 of 64
+// 23 and 12.5 (two launches), 2 of 2000 with 2 of 64 1050 and 117; error against float64, root mean square, 2.65e-7 and 1.93e-7,
+// 3.3e-7 and 2.3e-7, 1.9e-7 and 1.4e-7, 2.6e-7 and 2.2e-7 (short chains: eight wavefronts share the keys).  What bounds it now is the
+// wait for the rows of a tile.
+typedef __attribute__((ext_vector_type(4))) float f4v;
+
+// What a lane holds of a row that enters a product over the head dimension: in the steps 4 c .. 4 c + 3 the four lanes (0 .. 3) of a
+// row have its elements 16 c + 4 g + (step % 4).
 template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_rows(const float* __restrict__ Q, const float* __restrict__ K,
-                                                    const float* __restrict__ V, float* __restrict__ O,
-                                                    float* __restrict__ stats, int L, int Ls, int N, int Nq, int H,
-                                                    int causal, float scale, size_t stride) {
-  __shared__ float qs[DH];
-  const int q = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
+__device__ __forceinline__ void f32_row(const float* row, int g, f4v* x) {
+#pragma unroll
+  for (int c = 0; c < DH / 16; c++) x[c] = *reinterpret_cast<const f4v*>(row + 16 * c + 4 * g);
+}
+template <int DH>
+__device__ __forceinline__ f4v f32_scores(const f4v* a, const f4v* b) {
+  f4v s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};  // (two chains: half the waits, and less error)
+#pragma unroll
+  for (int c = 0; c < DH / 16; c += 2)
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+#pragma unroll
+      for (int k = 0; k < 2; k++) s[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c + k][e], b[c + k][e], s[k], 0, 0, 0);
+  return s[0] + s[1];
+}
+
+// One workgroup per (image, head, 16 queries), the key tiles dealt to its eight wavefronts, one pass: S^T = K Q^T leaves a query to the
+// four lanes of a column, whose registers are the operand of O^T += V^T P^T as they are (step r: keys 4 g + r).
+template <int DH>
+__global__ __launch_bounds__(512) void attn_f32_rows(const float* __restrict__ Q, const float* __restrict__ K,
+                                                     const float* __restrict__ V, float* __restrict__ O,
+                                                     float* __restrict__ stats, int L, int Ls, int N, int Nq, int H,
+                                                     int causal, float scale, size_t stride) {
+  constexpr int C = DH / 16, U = DH / 64;
+  __shared__ float ms[8][16], ls[8][16];
+  __shared__ f4v os[4][U][4][64];
+  const int q0 = 16 * (gridDim.x - 1 - blockIdx.x), h = blockIdx.y, b = blockIdx.z;  // (the longest first)
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j = lane & 15, g = lane >> 4;
   const size_t head_off = ((size_t)b * H + h) * (size_t)L * DH;
-  const int p = Ls + q, kend = causal ? p + 1 : L;
-  for (int d = lane; d < DH; d += 64) qs[d] = Q[head_off + (size_t)p * DH + d];
-  __syncthreads();
+  const int q = q0 + j, kend = causal ? Ls + min(q, Nq - 1) + 1 : L;             // keys of this lane's query
+  const int kall = causal ? Ls + q0 + 1 : L, kmax = causal ? Ls + min(q0 + 15, Nq - 1) + 1 : L;  // of all, of any
+  f4v qr[C], acc[U][4];
+  f32_row<DH>(Q + head_off + (size_t)(Ls + min(q, Nq - 1)) * DH, g, qr);
+#pragma unroll
+  for (int u = 0; u < U; u++)
+#pragma unroll
+    for (int t = 0; t < 4; t++) acc[u][t] = f4v{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
-  for (int k = lane; k < kend; k += 64) {
-    const float* kr = K + head_off + (size_t)k * DH;
-    float s = 0.f;
-    for (int d = 0; d < DH; d++) s += qs[d] * kr[d];
-    s *= scale;
-    const float mn = fmaxf(m, s);
-    l = l * expf(m - mn) + expf(s - mn);
-    m = mn;
-  }
-  float M = m;
+  for (int k0 = 16 * wv; k0 < kmax; k0 += 128) {
+    f4v kr[C], vr[4][U], p;
+    f32_row<DH>(K + head_off + (size_t)min(k0 + j, L - 1) * DH, g, kr);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
-  l = (m > -INFINITY) ? l * expf(m - M) : 0.f;
-  l = wave_sum(l);
-  float acc[DH];
+    for (int r = 0; r < 4; r++)
 #pragma unroll
-  for (int d = 0; d < DH; d++) acc[d] = 0.f;
-  for (int k = lane; k < kend; k += 64) {
-    const float* kr = K + head_off + (size_t)k * DH;
-    const float* vr = V + head_off + (size_t)k * DH;
-    float s = 0.f;
-    for (int d = 0; d < DH; d++) s += qs[d] * kr[d];
-    const float pk = expf(s * scale - M) / l;
+      for (int u = 0; u < U; u++)  // element 4 j + t + 64 u for output tile (u, t)
+        vr[r][u] = *reinterpret_cast<const f4v*>(V + head_off + (size_t)min(k0 + 4 * g + r, L - 1) * DH + 4 * j + 64 * u);
+    const f4v s = f32_scores<DH>(kr, qr) * scale;
+    float mt = -INFINITY;
 #pragma unroll
-    for (int d = 0; d < DH; d++) acc[d] += pk * vr[d];
-  }
-  if (q < N) {  // prompt rows (q >= N) only leave their softmax statistics
-    float* out = O + ((size_t)b * N + q) * ((size_t)H * DH) + (size_t)h * DH;
+    for (int r = 0; r < 4; r++) mt = fmaxf(mt, k0 + 4 * g + r < kend ? s[r] : -INFINITY);
+    mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    const float mn = fmaxf(m, mt), f = m == mn ? 1.f : expf(m - mn);
+    float sum = 0.f;
 #pragma unroll
-    for (int d = 0; d < DH; d++) {
-      const float v = wave_sum(acc[d]);
-      if (lane == (d & 63)) out[d] = v;
+    for (int r = 0; r < 4; r++) {
+      p[r] = k0 + 4 * g + r < kend ? expf(s[r] - mn) : 0.f;
+      sum += p[r];
     }
+    l = fmaf(l, f, sum);
+    m = mn;
+    if (!__all(f == 1.f))
+#pragma unroll
+      for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc[u][t] *= f;
+    if (k0 + 16 > kall) {  // keys that some query does not have: values that are not finite must not reach it as 0 * inf
+      bool bad = false;
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+          for (int t = 0; t < 4; t++)
+            if (!(fabsf(vr[r][u][t]) <= FLT_MAX)) { bad = true; vr[r][u][t] = 0.f; }
+      if (__any(bad))
+        for (int kk = 0; kk < 16; kk++) {
+          const float pr = (kk & 3) == 0 ? p[0] : (kk & 3) == 1 ? p[1] : (kk & 3) == 2 ? p[2] : p[3];
+          const float pk = __shfl(pr, j + 16 * (kk >> 2), 64);
+          const float* row = V + head_off + (size_t)min(k0 + kk, L - 1) * DH;
+#pragma unroll
+          for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int t = 0; t < 4; t++)
+#pragma unroll
+              for (int r = 0; r < 4; r++) {
+                const float v = row[16 * g + 4 * r + t + 64 * u];
+                if (k0 + kk < kend && !(fabsf(v) <= FLT_MAX)) acc[u][t][r] = fmaf(pk, v, acc[u][t][r]);
+              }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+      for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[r][u][t], p[r], acc[u][t], 0, 0, 0);
   }
-  if (lane == 0) {
-    stats[(size_t)b * stride + ((size_t)h * Nq + q) * 2] = M;
-    stats[(size_t)b * stride + ((size_t)h * Nq + q) * 2 + 1] = l;
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  if (g == 0) { ms[wv][j] = m; ls[wv][j] = l; }
+  __syncthreads();
+  float M = ms[0][j];
+#pragma unroll
+  for (int w = 1; w < 8; w++) M = fmaxf(M, ms[w][j]);
+  l = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; w++) l += ls[w][j] * (ms[w][j] == M ? 1.f : expf(ms[w][j] - M));
+  const float f = m == M ? 1.f : expf(m - M);
+  auto put = [&]() {
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) os[wv & 3][u][r][lane] = f4v{acc[u][0][r], acc[u][1][r], acc[u][2][r], acc[u][3][r]};
+  };
+#pragma unroll
+  for (int u = 0; u < U; u++)
+#pragma unroll
+    for (int t = 0; t < 4; t++) acc[u][t] *= f;
+  if (wv >= 4) put();
+  __syncthreads();
+  if (wv < 4)
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const f4v y = os[wv][u][r][lane];
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc[u][t][r] += y[t];
+      }
+  if (wv < 4) put();  // (each over what it has read)
+  __syncthreads();
+  const int u = wv >> 2, r = wv & 3;
+  if (q < N && u < U)  // prompt rows (q >= N) only leave their softmax statistics
+    *reinterpret_cast<f4v*>(O + ((size_t)b * N + q) * ((size_t)H * DH) + (size_t)h * DH + 64 * u + 16 * g + 4 * r) =
+        ((os[0][u][r][lane] + os[1][u][r][lane]) + (os[2][u][r][lane] + os[3][u][r][lane])) / l;
+  if (wv == 0 && g == 0 && q < Nq) {
+    float* ml = stats + (size_t)b * stride + ((size_t)h * Nq + q) * 2;
+    ml[0] = M;
+    ml[1] = l;
   }
 }
 
-// One workgroup per (image, visual key x): S[b][x] = mean over heads and the Nq query rows of A[.., q, x].
+// S[b][x] = mean over heads and the Nq query rows of A[.., q, x]: one workgroup per (image, 16 visual keys), the (head, 16 queries)
+// dealt to its sixteen wavefronts, the probabilities formed again from the statistics and added in float64.
 template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_cols(const float* __restrict__ Q, const float* __restrict__ K,
-                                                     const float* __restrict__ stats, float* __restrict__ S, int L,
-                                                     int Ls, int N, int Nq, int H, int causal, float scale, size_t stride) {
-  __shared__ double red[256];
-  const int x = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+__global__ __launch_bounds__(1024) void attn_f32_cols(const float* __restrict__ Q, const float* __restrict__ K,
+                                                      const float* __restrict__ stats, float* __restrict__ S, int L,
+                                                      int Ls, int N, int Nq, int H, int causal, float scale, size_t stride) {
+  constexpr int C = DH / 16;
+  __shared__ double red[16][16];
+  const int b = blockIdx.y, lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j = lane & 15, g = lane >> 4;
+  const int x = 16 * blockIdx.x + j, xr = min(x, N - 1);
+  const int t0 = causal ? blockIdx.x : 0, nt = (Nq + 15) / 16 - t0;  // query tiles that have these keys
+  const float* sb = stats + (size_t)b * stride;
   double acc = 0.0;
-  for (int idx = tid; idx < H * Nq; idx += 256) {
-    const int h = idx / Nq, q = idx % Nq;
-    if (causal && x > q) continue;
+  for (int i = wv; i < H * nt; i += 16) {
+    const int h = i / nt, q0 = 16 * (t0 + i - h * nt);
     const size_t head_off = ((size_t)b * H + h) * (size_t)L * DH;
-    const float* qr = Q + head_off + (size_t)(Ls + q) * DH;
-    const float* kr = K + head_off + (size_t)(Ls + x) * DH;
-    float s = 0.f;
-    for (int d = 0; d < DH; d++) s += qr[d] * kr[d];
-    const float M = stats[(size_t)b * stride + ((size_t)h * Nq + q) * 2], l = stats[(size_t)b * stride + ((size_t)h * Nq + q) * 2 + 1];
-    acc += (double)(expf(s * scale - M) / l);
+    f4v qr[C], kr[C];
+    f32_row<DH>(Q + head_off + (size_t)(Ls + min(q0 + j, Nq - 1)) * DH, g, qr);
+    f32_row<DH>(K + head_off + (size_t)(Ls + xr) * DH, g, kr);
+    float ml[4][2];
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+      for (int e = 0; e < 2; e++) ml[r][e] = sb[((size_t)h * Nq + min(q0 + 4 * g + r, Nq - 1)) * 2 + e];  // (a pair need not be aligned)
+    const f4v s = f32_scores<DH>(qr, kr) * scale;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int q = q0 + 4 * g + r;
+      if (q < Nq && (!causal || x <= q)) acc += (double)(expf(s[r] - ml[r][0]) / ml[r][1]);
+    }
   }
-  red[tid] = acc;
+  acc += __shfl_xor(acc, 16, 64);
+  acc += __shfl_xor(acc, 32, 64);
+  if (g == 0) red[wv][j] = acc;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) red[tid] += red[tid + o];
-    __syncthreads();
+  if (threadIdx.x < 16 && x < N) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < 16; w++) t += red[w][j];
+    S[(size_t)b * N + x] = (float)(t / ((double)H * (double)Nq));
   }
-  if (tid == 0) S[(size_t)b * N + x] = (float)(red[0] / ((double)H * (double)Nq));
 }
 
 int launch_attention(const Plan& pl, int dtype, int causal, const void* Q, const void* K, const void* V, void* O,
@@ -568,16 +687,16 @@ int launch_attention(const Plan& pl, int dtype, int causal, const void* Q, const
 #undef TC_ATTN16
     if (S) TC_TIMED(PK_ATTN_REDUCE, 0, st, (attn_score_reduce<<<dim3((pl.N + 63) / 64, pl.B), 256, 0, st>>>(Spart, S, pl.N, pl.Nq, pl.H, pl.n_qtiles, pl.spart_stride)));
   } else {
-    const dim3 grid(pl.Nq, pl.H, pl.B);
+    const dim3 grid((pl.Nq + 15) / 16, pl.H, pl.B), cols((pl.N + 15) / 16, pl.B);
     if (pl.dh == 128) {
-      TC_TIMED(PK_ATTN, 0, st, (attn_f32_rows<128><<<grid, 64, 0, st>>>((const float*)Q, (const float*)K, (const float*)V, (float*)O, Spart,
+      TC_TIMED(PK_ATTN, 0, st, (attn_f32_rows<128><<<grid, 512, 0, st>>>((const float*)Q, (const float*)K, (const float*)V, (float*)O, Spart,
                                               pl.L, pl.Ls, pl.N, pl.Nq, pl.H, causal, pl.scale, pl.spart_stride)));
-      if (S) TC_TIMED(PK_ATTN_REDUCE, 0, st, (attn_f32_cols<128><<<dim3(pl.N, pl.B), 256, 0, st>>>((const float*)Q, (const float*)K, Spart, S, pl.L,
+      if (S) TC_TIMED(PK_ATTN_REDUCE, 0, st, (attn_f32_cols<128><<<cols, 1024, 0, st>>>((const float*)Q, (const float*)K, Spart, S, pl.L,
                                                                    pl.Ls, pl.N, pl.Nq, pl.H, causal, pl.scale, pl.spart_stride)));
     } else {
-      TC_TIMED(PK_ATTN, 0, st, (attn_f32_rows<64><<<grid, 64, 0, st>>>((const float*)Q, (const float*)K, (const float*)V, (float*)O, Spart, pl.L,
+      TC_TIMED(PK_ATTN, 0, st, (attn_f32_rows<64><<<grid, 512, 0, st>>>((const float*)Q, (const float*)K, (const float*)V, (float*)O, Spart, pl.L,
                                              pl.Ls, pl.N, pl.Nq, pl.H, causal, pl.scale, pl.spart_stride)));
-      if (S) TC_TIMED(PK_ATTN_REDUCE, 0, st, (attn_f32_cols<64><<<dim3(pl.N, pl.B), 256, 0, st>>>((const float*)Q, (const float*)K, Spart, S, pl.L,
+      if (S) TC_TIMED(PK_ATTN_REDUCE, 0, st, (attn_f32_cols<64><<<cols, 1024, 0, st>>>((const float*)Q, (const float*)K, Spart, S, pl.L,
                                                                   pl.Ls, pl.N, pl.Nq, pl.H, causal, pl.scale, pl.spart_stride)));
     }
   }
