@@ -403,28 +403,42 @@ __global__ __launch_bounds__(256) void td_bisect_kernel(const double* __restrict
 }
 
 // ---- 2b -----------------------------------------------------------------------------------------------
-// One lane per eigenvector: T - l I = L D+ L^T from the top (pivots dp, multipliers e_i / dp_i), = U D- U^T from the bottom
-// (pivots dm, multipliers e_{i-1} / dm_i), joined at the row r with the smallest |gamma|, gamma_i = dp_i + dm_i - (d_i - l);
-// z_r = 1, upwards z_i = -(e_i / dp_i) z_{i+1}, downwards z_i = -(e_{i-1} / dm_i) z_{i-1}.
+// One lane per eigenvector: T - l I = L D+ L^T from the top (pivots dp), = U D- U^T from the bottom (pivots dm), joined at the row r
+// with the smallest |gamma|, gamma_i = dp_i + dm_i - (d_i - l); z_r = 1, upwards z_i = -(e_i / dp_i) z_{i+1}, downwards
+// z_i = -(e_{i-1} / dm_i) z_{i-1}.
+// The pivots are ratios of neighbouring minors, dp_i = P_i / P_{i-1} with P_i = (d_i - l) P_{i-1} - e_{i-1}^2 P_{i-2}, and so are the
+// steps of the vector: z_i = c_i P_{i-1} with c_r = 1 / P_{r-1} and c_i = -e_i c_{i+1} (from the bottom with Q_{i+1} the same).  A row
+// so takes a multiply-add on the chain and no division, where dp_{i+1} = d_{i+1} - l - e_i (e_i / dp_i) has a reciprocal
+// with its Newton steps there, and no pivot needs to be kept off zero.  (The error of either form is that of T's entries off by a few eps each.)
+// Divisions are left in gamma, off the chain.
+// T is scaled to ||T|| <= 1 by a power of two and the minors are brought back into range every sixteen rows, at which they have
+// fallen by 2^-850 at most (from two rows to the next two by e^2, and e > eps / 2) or grown by 3^16.  Where T is
+// split they begin anew; segments with such a row have their own instance of the walk.
 // W [B][Np][Np] float receives the unnormalised vector of slot k in column k (rows outside its block are zero); rn
 // [B][Np] its reciprocal norm (0 if the vector is not finite: weakly coupled parts of T that share an eigenvalue to the last bit;
 // that raises any[b], and td_orthogonalise_kernel makes the vector anew).
 //
 // All lanes of a wavefront walk over the same row at the same time, whatever block their eigenvalue belongs
 // to and wherever its twist index lies (a lane ignores rows that are not its own): every access to memory is one
-// contiguous run per row.  Two chains of divisions, one per wavefront, in each of three walks: pivots, gamma (four
-// wavefronts, a quarter of the segments each), vector.  With both chains in one wavefront a row took 306 clocks:
-// 0.22 -> 0.11 ms for one image of 576 tokens, 0.24 -> 0.18 for 64, 1.18 -> 0.75 for 8 of 2880.
-// Only the pivots at the ends of segments of sixteen rows are kept (cp, cm [row / 16][slot]); the later walks form the
-// others again from there.  Kept for every row they were 2 x 16 N^2 bytes of traffic per image and their latency three
-// times per row (0.34 ms for one image of 576 tokens, 0.40 for 64).
+// contiguous run per row.  Two chains, one per wavefront, in each of three walks: minors, gamma (four
+// wavefronts, a quarter of the segments each), vector.
+// Only the minors at the ends of segments of sixteen rows are kept (ck [4][row / 16][slot]: P of the segment's first row and of the one
+// before, Q of its last row and of the one behind); the later walks form the others again from there.
+// What bounds it is the instructions of a row, at 7 clocks each (one wavefront on a SIMD): minors 5, vector 8 more, gamma 35.  Before
+// (pivots by division, vectors masked row by row and stored by the wavefronts that form them) and now, us: one image of 576 tokens
+// 111 and 66, 64 images 178 and 144, two of 1499 287 and 166, one of 64 13.9 and 10.8; by walk for the first: 11, 15 and 35.
 constexpr int TW_SEG = 16;
 
-// 1 / x to the last bit or so: hardware estimate and two Newton steps (the pivots are never zero, denormal or infinite)
+// 1 / x to the last bit or so: hardware estimate and two Newton steps
 __device__ __forceinline__ double tw_rcp(double x) {
   double r = __builtin_amdgcn_rcp(x);
   r = fma(fma(-x, r, 1.0), r, r);
   return fma(fma(-x, r, 1.0), r, r);
+}
+
+static size_t td_twisted_lds(int N) {
+  const int nseg = (N + TW_SEG - 1) / TW_SEG;
+  return (size_t)(nseg * TW_SEG + 1) * 16 + (size_t)nseg * 4;
 }
 
 __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
@@ -434,159 +448,234 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
                                                         double* __restrict__ rn, int32_t* __restrict__ any, int N,
                                                         int Np) {
   extern __shared__ __attribute__((aligned(16))) unsigned char tw_smem[];
-  tb_pair* de = reinterpret_cast<tb_pair*>(tw_smem) + 1;  // [-1 .. 16 nseg - 1]: d_i, and e_i that couples rows i and i+1 (0 where T is split)
-  __shared__ double gs[4][64];
+  __shared__ double gs[4][64], ps[4][64], qs[4][64];
   __shared__ int rs[4][64];
   __shared__ double ns[64];
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, nseg = (N + TW_SEG - 1) / TW_SEG;
+  __shared__ float zs[2][2][TW_SEG * 64];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, nseg = (N + TW_SEG - 1) / TW_SEG, rows = nseg * TW_SEG;
+  tb_pair* de = reinterpret_cast<tb_pair*>(tw_smem);   // [rows + 1]: d_i, and e_{i-1} that couples rows i - 1 and i (0 where T is split)
+  int* cut = reinterpret_cast<int*>(de + rows + 1);    // [nseg]: T is split in the segment or at one of its ends
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double* db = dvec + (size_t)b * Np;
   const double* eb = evec + (size_t)b * Np;
   const double tn = tnorm[b], split = TD_EPS * tn;
-  for (int i = tid - 1; i < nseg * TW_SEG; i += 256) {  // rows behind the last stand alone (4 ||T|| is nobody's eigenvalue)
-    const double e = i >= 0 && i + 1 < N ? eb[i] : 0.0;
-    de[i] = tb_pair{i >= 0 && i < N ? db[i] : (tn > 0.0 ? 4.0 * tn : 1.0), fabs(e) > split ? e : 0.0};
+  int ex = 0;
+  if (tn > 0.0 && tn < DBL_MAX) (void)frexp(tn, &ex);
+  const double down = ldexp(1.0, -ex);
+  for (int c = tid; c < nseg; c += 256) cut[c] = 0;
+  __syncthreads();
+  for (int i = tid; i <= rows; i += 256) {  // rows behind the last stand alone (4 is nobody's eigenvalue)
+    const double e = i > 0 && i < N ? eb[i - 1] : 0.0, es = fabs(e) > split ? e * down : 0.0;
+    de[i] = tb_pair{i < N ? db[i] * down : 4.0, es};
+    if (es == 0.0 && i > 0 && i < rows) cut[(i - 1) / TW_SEG] = cut[i / TW_SEG] = 1;
   }
   __syncthreads();
-  const int k = blockIdx.x * 64 + lane, kr = min(k, N - 1);  // (lanes past the last vector repeat it and store nothing but pivots)
+  const int k = blockIdx.x * 64 + lane, kr = min(k, N - 1);  // (lanes past the last vector repeat it and store nothing but minors)
   const int2 st = blk[(size_t)b * Np + kr];
   const int s = st.x, t = st.y;
-  const double pivmin = DBL_MIN * fmax(1.0, tn * tn);
-  const double l = lam[(size_t)b * Np + kr];
-  double* cp = ckpt + (size_t)b * ckpt_stride + k;
-  double* cm = cp + (size_t)nseg * Np;
+  const double l = lam[(size_t)b * Np + kr] * down;
+  const size_t part = (size_t)nseg * Np;
+  double* ck = ckpt + (size_t)b * ckpt_stride + k;
   float* w = W + (size_t)b * Np * Np + k;
-  auto guard = [&](double p) { return fabs(p) < pivmin ? -pivmin : p; };
 
-  // pivots: dp[i + 1] = d_{i+1} - l - e_i (e_i / dp[i]);  dm[i] = d_i - l - e_i (e_i / dm[i + 1])
-  if (wv == 0) {
-    double p = guard(de[0].x - l);
-    for (int c = 0; c < nseg; c++) {
-      cp[(size_t)c * Np] = p;
-      if (c == nseg - 1) break;
-      double e = de[c * TW_SEG].y;
-#pragma unroll
-      for (int u = 0; u < TW_SEG; u++) {
-        const tb_pair a = de[c * TW_SEG + u + 1];
-        p = guard(fma(-e, e * tw_rcp(p), a.x - l));
-        e = a.y;
-      }
-    }
-  } else if (wv == 1) {
-    double q = guard(de[nseg * TW_SEG - 1].x - l);
-    for (int c = nseg - 1; c >= 0; c--) {
-      cm[(size_t)c * Np] = q;
-      if (c == 0) break;
-#pragma unroll
-      for (int u = 0; u < TW_SEG; u++) {
-        const tb_pair z = de[c * TW_SEG + TW_SEG - 2 - u];
-        q = guard(fma(-z.y, z.y * tw_rcp(q), z.x - l));
-      }
-    }
-  }
-  __syncthreads();
-  // the two pivots of the rows of a segment
-  auto segment_p = [&](int c, double p, double* f) {
-    double e = de[c * TW_SEG].y;
+  // Minors of the rows of segment c (f) and of the row before each (g), from those of its first row; then those of the row behind the
+  // segment, times 2^-k.  With `split` they begin anew where T is split.
+  auto leading = [&](auto split, int c, double& p, double& pp, double* f, double* g) __attribute__((always_inline)) {
+    const tb_pair* a = de + c * TW_SEG + 1;
 #pragma unroll
     for (int u = 0; u < TW_SEG; u++) {
       f[u] = p;
-      if (u + 1 < TW_SEG) {
-        const tb_pair a = de[c * TW_SEG + u + 1];
-        p = guard(fma(-e, e * tw_rcp(p), a.x - l));
-        e = a.y;
-      }
+      g[u] = pp;
+      const tb_pair r = a[u];
+      const double m = split && r.y == 0.0 ? 1.0 : p;
+      p = fma(r.x - l, m, -r.y * r.y * pp);
+      pp = m;
     }
+    const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));
+    p = __builtin_amdgcn_ldexp(p, -e);
+    pp = __builtin_amdgcn_ldexp(pp, -e);
+    return e;
   };
-  auto segment_m = [&](int c, double q, double* h) {
+  // The same from the last row upwards (g: of the row behind), up to the row before the segment (not for segment 0).
+  auto trailing = [&](auto split, int c, double& q, double& qq, double* f, double* g) __attribute__((always_inline)) {
+    const tb_pair* a = de + c * TW_SEG;
+    double y = a[TW_SEG - 1].y;
 #pragma unroll
     for (int u = TW_SEG - 1; u >= 0; u--) {
-      h[u] = q;
-      if (u > 0) {
-        const tb_pair z = de[c * TW_SEG + u - 1];
-        q = guard(fma(-z.y, z.y * tw_rcp(q), z.x - l));
-      }
+      f[u] = q;
+      g[u] = qq;
+      if (u == 0 && c == 0) break;
+      const tb_pair r = a[u - 1];
+      const double m = split && y == 0.0 ? 1.0 : q;
+      q = fma(r.x - l, m, -y * y * qq);
+      qq = m;
+      y = r.y;
     }
+    const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(q), fabs(qq)));
+    q = __builtin_amdgcn_ldexp(q, -e);
+    qq = __builtin_amdgcn_ldexp(qq, -e);
+    return e;
   };
+  auto segment = [&](int c, auto work) __attribute__((always_inline)) {
+    if (__builtin_amdgcn_readfirstlane(cut[c])) work(std::true_type{});
+    else work(std::false_type{});
+  };
+
+  if (wv == 0) {
+    double p = de[0].x - l, pp = 1.0;
+    for (int c = 0; c < nseg; c++) {
+      ck[(size_t)c * Np] = p;
+      ck[part + (size_t)c * Np] = pp;
+      if (c + 1 < nseg)
+        segment(c, [&](auto split) __attribute__((always_inline)) {
+          double f[TW_SEG], g[TW_SEG];
+          leading(split, c, p, pp, f, g);
+        });
+    }
+  } else if (wv == 1) {
+    double q = de[rows - 1].x - l, qq = 1.0;
+    for (int c = nseg - 1; c >= 0; c--) {
+      ck[2 * part + (size_t)c * Np] = q;
+      ck[3 * part + (size_t)c * Np] = qq;
+      if (c > 0)
+        segment(c, [&](auto split) __attribute__((always_inline)) {
+          double f[TW_SEG], g[TW_SEG];
+          trailing(split, c, q, qq, f, g);
+        });
+    }
+  }
+  __syncthreads();
   // twist index: the row with the smallest |gamma| (the last of equal ones wins); a quarter of the segments each
-  double gbest = DBL_MAX;
+  double gbest = DBL_MAX, pbest = 0.0, qbest = 0.0;
   int r = -1;
   const int c0 = nseg * wv / 4, c1 = nseg * (wv + 1) / 4;
   if (c0 < c1) {
-    double p = cp[(size_t)c0 * Np], q = cm[(size_t)c0 * Np];
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) v[u] = ck[u * part + (size_t)c0 * Np];
     for (int c = c0; c < c1; c++) {
       const int cn = min(c + 1, c1 - 1);
-      const double pn = cp[(size_t)cn * Np], qn = cm[(size_t)cn * Np];
-      double f[TW_SEG], h[TW_SEG];
-      segment_p(c, p, f);
-      segment_m(c, q, h);
+      double vn[4];
 #pragma unroll
-      for (int u = 0; u < TW_SEG; u++) {
-        const int i = c * TW_SEG + u;
-        const double g = fabs(f[u] + h[u] - (de[i].x - l));
-        const bool take = i >= s && i < t && g <= gbest;
-        gbest = take ? g : gbest;
-        r = take ? i : r;
-      }
-      p = pn;
-      q = qn;
+      for (int u = 0; u < 4; u++) vn[u] = ck[u * part + (size_t)cn * Np];
+      segment(c, [&](auto split) __attribute__((always_inline)) {
+        double f[TW_SEG], fp[TW_SEG], h[TW_SEG], hq[TW_SEG];
+        leading(split, c, v[0], v[1], f, fp);
+        trailing(split, c, v[2], v[3], h, hq);
+#pragma unroll
+        for (int u = 0; u < TW_SEG; u++) {
+          const int i = c * TW_SEG + u;
+          const double g = fabs(f[u] * tw_rcp(fp[u]) + h[u] * tw_rcp(hq[u]) - (de[i].x - l));
+          const bool take = i >= s && i < t && g <= gbest;  // (a minor of zero before or behind the row: not a number, not taken)
+          gbest = take ? g : gbest;
+          pbest = take ? fp[u] : pbest;
+          qbest = take ? hq[u] : qbest;
+          r = take ? i : r;
+        }
+      });
+#pragma unroll
+      for (int u = 0; u < 4; u++) v[u] = vn[u];
     }
   }
   gs[wv][lane] = gbest;
+  ps[wv][lane] = pbest;
+  qs[wv][lane] = qbest;
   rs[wv][lane] = r;
   __syncthreads();
   r = t - 1;
   gbest = DBL_MAX;
+  pbest = qbest = 0.0;  // (no row taken: the vector comes out not finite)
 #pragma unroll
   for (int u = 0; u < 4; u++) {
     const double g = gs[u][lane];
     const int ru = rs[u][lane];
     const bool take = ru >= 0 && g <= gbest;
     gbest = take ? g : gbest;
+    pbest = take ? ps[u][lane] : pbest;
+    qbest = take ? qs[u][lane] : qbest;
     r = take ? ru : r;
   }
-  // the vector: upwards from r over the segments from the last to the first, downwards from the first to the last
+  // The vector: wavefront 0 upwards from r over the segments from the last to the first, wavefront 1 downwards from the first to
+  // the last, and the other two store what these had a segment ago.  (A wavefront that stores waits for its stores with its next
+  // read.)  c is zero behind r and, as T is split there, outside the block: nothing is masked but what is stored.
   const bool on = k < N;
-  double z = 1.0, nrm = 0.0;
-  if (wv == 0) {
-    double p = cp[(size_t)(nseg - 1) * Np];
-    for (int c = nseg - 1; c >= 0; c--) {
-      const double pn = cp[(size_t)max(c - 1, 0) * Np];
-      double f[TW_SEG];
-      segment_p(c, p, f);
+  double nrm = 0.0, cc = 0.0, start = 0.0, p = 0.0, pp = 0.0;
+  auto couplings = [&](int c, double* y) __attribute__((always_inline)) {  // (before the selects, which would be branches around the reads)
 #pragma unroll
-      for (int u = TW_SEG - 1; u >= 0; u--) {
-        const int i = c * TW_SEG + u;
-        const double zn = -(de[i].y * tw_rcp(f[u])) * z;
-        const bool act = i >= s && i < r;
-        z = act ? zn : z;
-        nrm += act ? zn * zn : 0.0;
-        if (on && i <= r) w[(size_t)i * Np] = i < s ? 0.f : (i == r ? 1.f : (float)z);
-      }
-      p = pn;
-    }
-  } else if (wv == 1) {
-    double q = cm[0];
-    for (int c = 0; c < nseg; c++) {
-      const double qn = cm[(size_t)min(c + 1, nseg - 1) * Np];
-      double h[TW_SEG];
-      segment_m(c, q, h);
+    for (int u = 0; u < TW_SEG; u++) y[u] = de[c * TW_SEG + u].y;
 #pragma unroll
-      for (int u = 0; u < TW_SEG; u++) {
-        const int i = c * TW_SEG + u;
-        const double zn = -(de[i - 1].y * tw_rcp(h[u])) * z;
-        const bool act = i > r && i < t;
-        z = act ? zn : z;
-        nrm += act ? zn * zn : 0.0;
-        if (on && i > r && i < N) w[(size_t)i * Np] = i >= t ? 0.f : (float)z;
-      }
-      q = qn;
-    }
-    ns[lane] = nrm;
+    for (int u = 0; u < TW_SEG; u++) asm volatile("" : "+v"(y[u]));
+  };
+  if (wv < 2) {
+    start = 1.0 / (wv == 0 ? pbest : qbest);
+    const double* from = ck + (wv == 0 ? (size_t)(nseg - 1) * Np : 2 * part);
+    p = from[0];
+    pp = from[part];
   }
+  asm volatile("" : "+v"(p), "+v"(pp));
+  for (int it = 0; it <= nseg; it++) {
+    if (wv == 0 && it < nseg) {
+      const int c = nseg - 1 - it, cn = max(c - 1, 0);
+      const double pn = ck[(size_t)cn * Np], ppn = ck[part + (size_t)cn * Np];
+      float* z = zs[0][it & 1] + lane;
+      segment(c, [&](auto split) __attribute__((always_inline)) {
+        double f[TW_SEG], g[TW_SEG], en[TW_SEG];
+        couplings(c, en);
+        const double last = de[(c + 1) * TW_SEG].y;
+        const int e = leading(split, c, p, pp, f, g);
+        cc = __builtin_amdgcn_ldexp(cc, -e);  // (the minors of this segment are 2^e of the next one's)
+#pragma unroll
+        for (int u = TW_SEG - 1; u >= 0; u--) {
+          const int i = c * TW_SEG + u;
+          const double down = -(u + 1 < TW_SEG ? en[u + 1 < TW_SEG ? u + 1 : u] : last) * cc;
+          cc = i == r ? start : down;
+          const double y = g[u] * cc;
+          nrm = fma(y, y, nrm);
+          z[64 * u] = (float)y;
+        }
+      });
+      p = pn;
+      pp = ppn;
+      asm volatile("" : "+v"(p), "+v"(pp));  // (waited for here, not behind the branches, where those that store would wait too)
+    } else if (wv == 1 && it < nseg) {
+      const int c = it, cn = min(c + 1, nseg - 1);
+      const double pn = ck[2 * part + (size_t)cn * Np], ppn = ck[3 * part + (size_t)cn * Np];
+      float* z = zs[1][it & 1] + lane;
+      segment(c, [&](auto split) __attribute__((always_inline)) {
+        double f[TW_SEG], g[TW_SEG], en[TW_SEG];
+        couplings(c, en);
+        const int e = trailing(split, c, p, pp, f, g);
+        if (c > 0) cc = __builtin_amdgcn_ldexp(cc, -e);
+#pragma unroll
+        for (int u = 0; u < TW_SEG; u++) {
+          const int i = c * TW_SEG + u;
+          const double down = -en[u] * cc;
+          cc = i == r ? start : down;
+          const double y = g[u] * cc;
+          nrm = fma(y, y, nrm);
+          z[64 * u] = (float)y;
+        }
+      });
+      p = pn;
+      pp = ppn;
+      asm volatile("" : "+v"(p), "+v"(pp));  // (waited for here, not behind the branches, where those that store would wait too)
+    } else if (wv >= 2 && it > 0) {
+      const int c = wv == 2 ? nseg - it : it - 1;
+      const float* z = zs[wv - 2][(it - 1) & 1] + lane;
+      const int i0 = wv == 2 ? 0 : r + 1, i1 = !on ? 0 : wv == 2 ? r + 1 : N;  // rows this wavefront stores
+      float y[TW_SEG];
+#pragma unroll
+      for (int u = 0; u < TW_SEG; u++) y[u] = z[64 * u];
+#pragma unroll
+      for (int u = 0; u < TW_SEG; u++)
+        if (c * TW_SEG + u >= i0 && c * TW_SEG + u < i1) w[(size_t)(c * TW_SEG + u) * Np] = y[u];
+    }
+    __syncthreads();
+  }
+  if (wv == 1) ns[lane] = nrm;
   __syncthreads();
   if (wv != 0 || !on) return;
-  nrm += ns[lane] + 1.0;
+  nrm += ns[lane] - 1.0;  // (row r is in both)
   const bool fin = nrm == nrm && nrm < DBL_MAX && nrm < 1e60;  // float storage of z holds |z| < 3e38 relative to z_r = 1
   rn[(size_t)b * Np + k] = fin ? 1.0 / sqrt(nrm) : 0.0;
   if (!fin) atomicOr(&any[b], 1);
@@ -1254,7 +1343,7 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
                     double* sig, double* wgt, double* Cpart, float* Tf, float sv_rtol, bool vectors, float* C, float* C_out,
                     float* sigma_out, int32_t* info_out, hipStream_t st) {
   const int N = pl.N, Np = pl.Np, B = pl.B;
-  // The image's part of `scratch` (Np^2 doubles) holds the scaled copy of T first, the pivots of the factorisations later.
+  // The image's part of `scratch` (Np^2 doubles) holds the scaled copy of T first, the minors at the ends of segments later.
   const size_t stride = (size_t)Np * Np;
   int32_t* any = mark + (size_t)B * Np;  // (two words per image behind the marks of the group's images)
   int32_t* need = any + B;
@@ -1272,8 +1361,8 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
     return check_launch();
   }
   {
-    const size_t shm = (size_t)((N + TW_SEG - 1) / TW_SEG * TW_SEG + 1) * 16;
-    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_twisted_kernel),
+    const size_t shm = td_twisted_lds(N);
+    if (shm > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_twisted_kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
       return TC_ERR_HIP;
     TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, any, N, Np)));
