@@ -190,7 +190,7 @@ def main():
         per_row["a4_tridiagonal_reduction"] = entry("tridiag", "alu", rate(wm["tridiag_flops"], "tridiag", "T"), PEAK["vec_f64"],
                                                     "TFLOP/s", ms=ms("tridiag"))
         per_row["a4_bisection"] = {"kernel": "bisect", "bound": "alu (chain of dependent float64 multiply-adds)", "ms": ms("bisect")}
-        per_row["a4_twisted_factorisation"] = {"kernel": "twisted", "bound": "alu (chain of dependent float64 divisions)",
+        per_row["a4_twisted_factorisation"] = {"kernel": "twisted", "bound": "alu (instructions of three walks over the rows)",
                                                "ms": ms("twisted"), "hbm_gbps": rate(wm["twisted_bytes"], "twisted", "G")}
         per_row["a4_a5_backtransform_ics"] = entry("backtransform", "alu", rate(wm["backtf_flops"], "backtransform", "T"),
                                                    PEAK["vec_f32"], "TFLOP/s", ms=ms("backtransform"))
