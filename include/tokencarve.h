@@ -16,9 +16,10 @@
  *     state it keeps is up to three helper streams per device, created the first
  *     time a batch is split into stream groups (see tc_params.stream_groups) and
  *     kept until the process ends (their work is ordered after what is already on
- *     `stream` and `stream` waits for it before the next stage), and an event per
- *     device, by which reductions of more than 576 tokens that are enqueued on
- *     different streams run one after the other.
+ *     `stream` and `stream` waits for it before the next stage), and eight events
+ *     per device (one for each XCD), by which reductions of more than 128 tokens
+ *     that are enqueued on different streams take turns where they need the same
+ *     part of the device.
  *   - All scratch memory comes from `ws` (`ws_bytes` >= tc_workspace_bytes(p)).
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *     default stream) and the call returns without waiting for it.  Two calls may
@@ -104,7 +105,7 @@ typedef struct {
   int32_t eig_method;   /* tc_eig_method; TC_EIG_TRIDIAGONAL with TC_EIG_F32 or n_vis > 1024 is rejected (TC_ERR_PARAM) */
   int32_t stream_groups; /* groups of images whose eigensolver work (tridiagonal route: attention and Gram matrix
                             too) runs on helper streams and overlaps: 0 = the library chooses (Jacobi: 1, 2 or 4 by
-                            the amount of work; tridiagonal: 2 above 64 images, up to 384 tokens above 256), 1 = everything on `stream`,
+                            the amount of work; tridiagonal: 2 above 96 images, up to 384 tokens above 256), 1 = everything on `stream`,
                             2..4 = that many groups.  Results do not depend on it.                      */
   int32_t n_prompt_queries; /* P, text-guided variant of Eq. 3-7: the P query rows after the visual block (positions
                             vis_start + n_vis .. + P - 1) join the visual query rows in the column mean, which

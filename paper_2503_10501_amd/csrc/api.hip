@@ -139,11 +139,11 @@ static int direct_chain(const Plan& pl, const Plan& sub, int img0, const tc_para
 // Tridiagonal route: the batch can be cut into groups of images whose chains run on the library's helper streams, each
 // group starting when the one before it has formed its Gram matrices.  The reduction holds the registers of its compute units
 // for as long as it runs, so another group's kernels only find room where the images need more than one round over the
-// chip.  At 576 tokens (four compute units an image) that is above 64 images: one group and two, 5.49 and 6.20 ms for 64
-// images, 7.52 and 6.71 for 72, 8.48 and 7.90 for 96, 9.89 and 9.98 for 128; 701 tokens, 72 images 10.1 and 9.5; 1152 to 2000
-// tokens, 66 to 72 images 1 % slower with two.  Up to 256 tokens (one compute unit an image) and not far above (the last 256
-// columns of every reduction) it is above 256 images: 256 tokens, 128 images 2.38 and 2.61, 257 images 2.43 and 2.12; 300 tokens,
-// 128 images 1.99 and 2.20; 400 tokens, 96 images 4.94 and 4.91.
+// chip several times over.  ms, one group and two (heads of 128: 16, 8 above 576 tokens): 576 tokens, 64 images 3.34 and 3.55, 72 4.73 and
+// 4.93, 96 5.18 and 5.50, 112 5.75 and 5.32, 128 6.17 and 6.12; 700 tokens, 72 images 7.62 and 8.27, 96 9.49 and 9.86; 1000, 72
+// 18.6 and 20.1; 450, 72 3.30 and 3.08 (the one case against), 96 3.44 and 3.57.  Where four or fewer compute units hold an image
+// for most columns it is above 256 images: 384 tokens, 128 images 2.69 and 2.74; 320 tokens, 256 3.23 and 3.40; 256 tokens, 256
+// 1.97 and 2.14, 300 2.73 and 2.47.
 static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const void* K, const void* V, void* O,
                        float* S, float* score, float* ics, float* sigma, int32_t* info, void* ws, hipStream_t st) {
   if (pl.method != TC_EIG_TRIDIAGONAL || !tridiag_allowed(pl.N, st)) {
@@ -158,7 +158,7 @@ static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const 
     return launch_scores(pl, p->eig_dtype, G, U, state, S, p->lambda, p->norm_mode, p->sv_rtol, at<char>(ws, pl.off_sig),
                          at<float>(ws, pl.off_C), score, ics, sigma, info, st);
   }
-  int groups = pl.groups > 0 ? pl.groups : (pl.B > (pl.N <= 384 ? 256 : 64) ? 2 : 1);
+  int groups = pl.groups > 0 ? pl.groups : (pl.B > (pl.N <= 384 ? 256 : 96) ? 2 : 1);
   if (groups > pl.B) groups = pl.B;
   if (profiling_active()) groups = 1;  // per-kernel timing wants kernels that run alone
   hipStream_t streams[4];

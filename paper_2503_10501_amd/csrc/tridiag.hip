@@ -42,7 +42,7 @@
 // compute units back before it has written anything; tridiag_alone_kernel then reduces the image by one workgroup.  A
 // group that is complete stays resident and its waits end.  (They are bounded all the same, TD_SPIN polls: a workgroup that gives up
 // raises the image's failure flag, its group follows, and the caller reports the image as failed.)
-// Launches of this library that would strand each other are kept apart by the host (see tr_in_order).
+// Launches of this library that would strand each other are kept apart by the host (see TrTurn).
 #include <mutex>
 
 #include "tc_internal.h"

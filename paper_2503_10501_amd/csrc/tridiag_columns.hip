@@ -700,7 +700,7 @@ static int launch_shape(const Plan& pl, const TrPhase& ph, double* G, double* dv
   if (S::LDS > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_columns_kernel<S>),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS) != hipSuccess)
     return TC_ERR_HIP;
-  // Captured launches cannot be kept apart.  Up to eight members on one XCD do no harm then (see tr_in_order); sixteen are spread
+  // Captured launches cannot be kept apart.  Up to eight members on one XCD do no harm then (see TrTurn); sixteen are spread
   // over the XCDs like larger groups.
   TrTurn turn(S::P, S::LOCAL ? pl.B : xcds, xcds, st);
   if (turn.rc != TC_OK) return turn.rc;

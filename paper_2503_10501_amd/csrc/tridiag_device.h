@@ -9,7 +9,7 @@ namespace tc {
 
 typedef unsigned long long u64;
 
-// The turn of a launch whose groups have P members and lie on `images` XCDs (tr_in_order in tridiag.hip): taken before the launch,
+// The turn of a launch whose groups have P members and lie on `images` XCDs (tridiag.hip): taken before the launch,
 // over with done(), which is called after it in any case.
 struct TrTurn {
   int rc, first = 0;      // status; number of the first XCD

@@ -133,7 +133,7 @@ inline bool tr_runs(int N, int cus, bool captured) {
   return size < TR_TRIANGLES && tr_holds(TR_FRAMES[size].P, cus, captured);
 }
 
-// Launches that the host keeps apart (see tr_in_order).
+// Launches that the host keeps apart (see TrTurn).
 inline bool tr_apart(int P) { return P > 4; }
 
 }  // namespace tc
