@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
   __syncthreads();
   r = t - 1;
   gbest = DBL_MAX;
-  pbest = qbest = 0.0;  // (no row taken: the vector comes out not finite)
+  pbest = qbest = 0.0;  // (no row taken, each having a minor of zero before or behind it: the vector comes out not finite)
 #pragma unroll
   for (int u = 0; u < 4; u++) {
     const double g = gs[u][lane];
@@ -597,7 +597,8 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
   }
   // The vector: wavefront 0 upwards from r over the segments from the last to the first, wavefront 1 downwards from the first to
   // the last, and the other two store what these had a segment ago.  (A wavefront that stores waits for its stores with its next
-  // read.)  c is zero behind r and, as T is split there, outside the block: nothing is masked but what is stored.
+  // read.)  c is zero behind r and, as T is split there, outside the block: nothing is masked but what is stored.  (A vector that is not
+  // finite stays so across the split: see the end.)
   const bool on = k < N;
   double nrm = 0.0, cc = 0.0, start = 0.0, p = 0.0, pp = 0.0;
   auto couplings = [&](int c, double* y) __attribute__((always_inline)) {  // (before the selects, which would be branches around the reads)
@@ -678,7 +679,11 @@ __global__ __launch_bounds__(256) void td_twisted_kernel(const double* __restric
   nrm += ns[lane] - 1.0;  // (row r is in both)
   const bool fin = nrm == nrm && nrm < DBL_MAX && nrm < 1e60;  // float storage of z holds |z| < 3e38 relative to z_r = 1
   rn[(size_t)b * Np + k] = fin ? 1.0 / sqrt(nrm) : 0.0;
-  if (!fin) atomicOr(&any[b], 1);
+  if (!fin) {  // made anew in its block only; the back-transformation reads all rows, also of a vector without weight
+    atomicOr(&any[b], 1);
+    for (int i = 0; i < s; i++) w[(size_t)i * Np] = 0.f;
+    for (int i = t; i < N; i++) w[(size_t)i * Np] = 0.f;
+  }
 }
 
 // ---- close eigenvalues inside one block -----------------------------------------------------------------
