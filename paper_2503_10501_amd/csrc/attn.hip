@@ -495,7 +495,8 @@ __device__ __forceinline__ f4v f32_scores(const f4v* a, const f4v* b) {
 }
 
 // One workgroup per (image, head, 16 queries), the key tiles dealt to its eight wavefronts, one pass: S^T = K Q^T leaves a query to the
-// four lanes of a column, whose registers are the operand of O^T += V^T P^T as they are (step r: keys 4 g + r).
+// four lanes of a column, whose registers are the operand of O^T += V^T P^T as they are (step r: keys 4 g + r).  There the weights
+// are exp(s - m) over the power of two between 2 L and 4 L: the sums stay within the range of the values.
 template <int DH>
 __global__ __launch_bounds__(512) void attn_f32_rows(const float* __restrict__ Q, const float* __restrict__ K,
                                                      const float* __restrict__ V, float* __restrict__ O,
@@ -509,6 +510,7 @@ __global__ __launch_bounds__(512) void attn_f32_rows(const float* __restrict__ Q
   const size_t head_off = ((size_t)b * H + h) * (size_t)L * DH;
   const int q = q0 + j, kend = causal ? Ls + min(q, Nq - 1) + 1 : L;             // keys of this lane's query
   const int kall = causal ? Ls + q0 + 1 : L, kmax = causal ? Ls + min(q0 + 15, Nq - 1) + 1 : L;  // of all, of any
+  const float part = ldexpf(1.f, __clz(L) - 33);
   f4v qr[C], acc[U][4];
   f32_row<DH>(Q + head_off + (size_t)(Ls + min(q, Nq - 1)) * DH, g, qr);
 #pragma unroll
@@ -537,6 +539,7 @@ __global__ __launch_bounds__(512) void attn_f32_rows(const float* __restrict__ Q
       p[r] = k0 + 4 * g + r < kend ? expf(s[r] - mn) : 0.f;
       sum += p[r];
     }
+    p *= part;
     l = fmaf(l, f, sum);
     m = mn;
     if (!__all(f == 1.f))
@@ -613,7 +616,7 @@ __global__ __launch_bounds__(512) void attn_f32_rows(const float* __restrict__ Q
   const int u = wv >> 2, r = wv & 3;
   if (q < N && u < U)  // prompt rows (q >= N) only leave their softmax statistics
     *reinterpret_cast<f4v*>(O + ((size_t)b * N + q) * ((size_t)H * DH) + (size_t)h * DH + 64 * u + 16 * g + 4 * r) =
-        ((os[0][u][r][lane] + os[1][u][r][lane]) + (os[2][u][r][lane] + os[3][u][r][lane])) / l;
+        ((os[0][u][r][lane] + os[1][u][r][lane]) + (os[2][u][r][lane] + os[3][u][r][lane])) / (l * part);
   if (wv == 0 && g == 0 && q < Nq) {
     float* ml = stats + (size_t)b * stride + ((size_t)h * Nq + q) * 2;
     ml[0] = M;

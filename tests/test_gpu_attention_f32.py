@@ -1,5 +1,5 @@
 """GPU tests of the attention over float32 storage: query and key counts around its tiles of sixteen, both head sizes, odd strides of the
-statistics, and values that are not finite behind the causal line."""
+statistics, values that are not finite behind the causal line, and values near the ends of the float32 range."""
 import math
 
 import pytest
@@ -64,3 +64,36 @@ def test_what_is_not_finite_reaches_only_the_queries_that_have_the_key(dh):
     fin = o.isfinite()
     assert float((O - o)[fin].abs().max() / o[fin].abs().max()) < 4 * dh * 2.0 ** -24
     assert float((S - s).abs().max() / s.abs().max()) < 4 * dh * 2.0 ** -24
+
+
+# An output is a mean of values, so it has their range: sums of the products before the division must not leave it.  (L 2^-24: a sum of L
+# terms; below 2^-126 the storage has steps of 2^-149, of which every product and the result lose half, and their sum is within L halves.)
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("n,causal", [(40, 1), (300, 0)])
+@pytest.mark.parametrize("size", [3.0e38, 1.0e30, 1.0e-30, 1.0e-37])
+def test_values_of_any_size(dh, n, causal, size):
+    Q, K, V = _inputs(1, n, 3, 2, 2, dh, dh + n)
+    L = n + 5
+    V = ((0.75 + 0.25 * V.tanh()) * size).float()
+    O, S = _attention(_tc(), 1, n, 3, 2, 2, dh, causal, 0, Q.cuda(), K.cuda(), V.cuda())
+    o, s = _reference(n, 3, causal, 0, Q, K, V)
+    assert bool(O.isfinite().all())
+    assert float((O - o).abs().max()) < (4 * dh + L) * 2.0 ** -24 * size + L * 2.0 ** -149
+    assert float((S - s).abs().max() / s.abs().max()) < 4 * dh * 2.0 ** -24
+
+
+# One key that all queries have, at a score far below the others', with the only value that is not zero: the output is that value times a
+# probability near the ends of what float32 holds.  (exp of a score of size m is off by m 2^-24 and what the score is off by, 4 m 2^-24; the
+# probability has steps of 2^-149 below 2^-126.)
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("n", [20, 400])
+@pytest.mark.parametrize("below", [40, 80, 86, 90])
+def test_a_small_probability_of_a_large_value(dh, n, below):
+    L, key = n + 4, 2
+    Q, K, V = torch.zeros(1, 1, L, dh), torch.zeros(1, 1, L, dh), torch.zeros(1, 1, L, dh)
+    Q[..., 0] = math.sqrt(dh)
+    K[0, 0, key, 0] = -below
+    V[0, 0, key] = torch.linspace(-1e38, 1e38, dh)
+    O, S = _attention(_tc(), 1, n, 3, 1, 1, dh, 0, 0, Q.cuda(), K.cuda(), V.cuda())
+    o, s = _reference(n, 3, 0, 0, Q, K, V)
+    assert float((O - o).abs().max()) < 5 * below * 2.0 ** -24 * float(o.abs().max()) + 2.0 ** -149 * 1e38
