@@ -16,10 +16,11 @@
  *     state it keeps is up to three helper streams per device, created the first
  *     time a batch is split into stream groups (see tc_params.stream_groups) and
  *     kept until the process ends (their work is ordered after what is already on
- *     `stream` and `stream` waits for it before the next stage), and eight events
- *     per device (one for each XCD), by which reductions of more than 128 tokens
- *     that are enqueued on different streams take turns where they need the same
- *     part of the device.
+ *     `stream` and `stream` waits for it before the next stage), and events
+ *     (153 per device, made with the first reduction of more than 128 tokens), by
+ *     which reductions that are enqueued on different streams take turns where
+ *     their workgroups could otherwise fill a part of the device and wait there
+ *     for each other.
  *   - All scratch memory comes from `ws` (`ws_bytes` >= tc_workspace_bytes(p)).
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *     default stream) and the call returns without waiting for it.  Two calls may

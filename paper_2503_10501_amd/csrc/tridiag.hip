@@ -727,39 +727,65 @@ static bool tr_capturing(hipStream_t st) {
 bool tridiag_allowed(int N, hipStream_t st) { return tr_runs(N, compute_units(), tr_capturing(st)); }
 
 // Which launches are kept apart.  Groups that wait for members without a compute unit hold theirs, and an XCD deals out its
-// workgroups by itself, in the order of their ids: launches side by side on several streams could strand each other's groups.
-// Groups of four lie on one XCD, and a launch leaves at most three workgroups waiting there: with the four hardware queues of a
-// process twelve of 32, so these launches need no order.  All others take turns on the XCDs they use: an event per XCD, behind
-// the last launch there.  (A launch with few images of up to sixteen members uses as many XCDs as it has images, the next such
-// launch the next ones, so that small calls run side by side.)  Within a launch, the group with the lowest number that is not
-// complete finds its compute units: 15 workgroups at most wait on its XCD, and nine of the groups of four.  Captured launches
-// cannot be kept apart; tr_runs and the frames allowed there bound what a stranded group holds.
-// An event is known by the first XCD of the launch behind which it is recorded; another launch that starts there waits for it
-// first, so who waits for an event that has moved on waits for more.
+// workgroups by itself, in the order of their ids: launches side by side on several streams could strand each other's groups,
+// where all 32 compute units of an XCD are held by workgroups that wait.  So what may wait there at once has to be
+// less: of a launch whose groups lie on one XCD, the one group that is not complete, less a member; of a launch whose groups are
+// spread over the XCDs, any of its workgroups.  A process has four hardware queues, so with three waiting in each, 19 more may.  An
+// XCD has as many places, and a launch takes one for each workgroup above three (tr_places) on each XCD that it uses, behind the
+// last launches there.  Groups of four take none and need no order.  A launch that could fill the XCD takes all: it is alone but for groups
+// of four, and the image with the lowest number that is not complete finds its compute units, at most 22 of the 23 that are left.
+// Which places and XCDs a launch takes depends on its shape and its stream only (the streams are counted as they come, which matters for
+// nothing else).  Groups of sixteen have twelve places, and the other launches of their calls share the other seven: the groups of eight of
+// one call run beside the groups of sixteen of another.  In calls without groups of sixteen each of four streams has places of its own.
+// Launches with few images of groups on one XCD use as many XCDs as they have images, each stream its own.
+// ms a call on two and on four streams, each with a hardware queue, when a launch took whole XCDs and now: 576 tokens, 2 images 0.62 and 0.62,
+// 0.36 and 0.35; 8 images 0.73 and 0.74, 0.72 and 0.50; 701 tokens, 1 image 0.96 and 0.77, 0.96 and 0.41; 2 images 0.97 and 0.80, 0.96 and 0.47;
+// 1152 tokens, 1 image 2.05 and 1.48, 2.04 and 1.37; 300 tokens, 8 images 0.35 and 0.34, 0.26 and 0.21.  (16 images of 576 tokens: 1.14 and 1.15, 1.05
+// and 1.06; 32 images 1.81 and 1.81, 1.84 and 1.84: a call fills the device.  Two such calls side by side, 32 images on four streams: 1.96.)
+// Captured launches cannot be kept apart; tr_runs and the frames allowed there bound what a stranded group holds.
+// An event is known by the first place of the launch behind which it is recorded; every launch waits for the event it is going to
+// record, so who waits for an event that has moved on waits for more.  (And for those of launches that take all, and of groups of sixteen
+// where it needs a place of theirs: which events a call waits for does not depend on calls before it.)
+constexpr int TR_STREAMS = 64, TR_ALL = 8 * TR_PLACES, TR_EVENTS = TR_ALL + 1;
+struct TrDevice {
+  hipEvent_t ev[TR_EVENTS];               // XCD x, place p: TR_PLACES x + p; TR_ALL: launches that take all
+  unsigned char last[8 * TR_PLACES];      // event of the last launch there, and one (0: none)
+  bool made;
+  hipStream_t streams[TR_STREAMS];        // the last ones that were new
+  unsigned seen;
+};
 static std::mutex tr_mx;
-static hipEvent_t tr_ev[64][8];
-static bool tr_made[64];
-static unsigned char tr_last[64][8];  // event of the last launch on an XCD
-static int tr_next[64];
+static TrDevice tr_devices[64];
 
-TrTurn::TrTurn(int P, int images, int xcds_, hipStream_t st_) : xcds(xcds_ < 8 ? xcds_ : 8), st(st_) {
+TrTurn::TrTurn(int P, bool local, int images, bool sixteen, int xcds_, hipStream_t st_) : xcds(xcds_ < 8 ? xcds_ : 8), st(st_) {
   captured = tr_capturing(st);
   apart = tr_apart(P) && !captured;
   rc = TC_OK;
   if (!apart) return;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) { apart = false; rc = TC_ERR_HIP; return; }
   tr_mx.lock();
-  for (int x = 0; x < 8 && !tr_made[dev]; x++)
-    if (!tr_ev[dev][x] && hipEventCreateWithFlags(&tr_ev[dev][x], hipEventDisableTiming) != hipSuccess) rc = TC_ERR_HIP;
-  if (rc == TC_OK) tr_made[dev] = true;
-  count = images < xcds ? images : xcds;
-  first = count < xcds ? tr_next[dev] % xcds : 0;
-  unsigned seen = 0;
-  for (int i = 0; i < count && rc == TC_OK; i++) {
-    const int e = tr_last[dev][(first + i) % xcds];
-    if (!(seen >> e & 1) && hipStreamWaitEvent(st, tr_ev[dev][e], 0) != hipSuccess) rc = TC_ERR_HIP;
-    seen |= 1u << e;
+  TrDevice& d = tr_devices[dev];
+  for (int u = 0; u < TR_EVENTS && !d.made; u++)
+    if (!d.ev[u] && hipEventCreateWithFlags(&d.ev[u], hipEventDisableTiming) != hipSuccess) rc = TC_ERR_HIP;
+  if (rc == TC_OK) d.made = true;
+  unsigned slot = 0;
+  while (slot < d.seen && slot < TR_STREAMS && d.streams[slot] != st) slot++;
+  if (slot == d.seen || slot == TR_STREAMS) {
+    slot = d.seen++ % TR_STREAMS;
+    d.streams[slot] = st;
   }
+  places = tr_places(P, local, images, xcds);
+  count = local && images < xcds ? images : xcds;
+  first = count < xcds ? (int)(slot * count % xcds) : 0;
+  from = tr_first_place(places, local, count == xcds, sixteen, slot);
+  event = places == TR_PLACES && count == xcds ? TR_ALL : unit(0);
+  bool waits[TR_EVENTS] = {};
+  waits[event] = waits[TR_ALL] = true;
+  if (from < TR_SIXTEEN) waits[unit(0) - from] = true;
+  for (int i = 0; i < count * places; i++)
+    if (d.last[unit(i)]) waits[d.last[unit(i)] - 1] = true;
+  for (int e = 0; e < TR_EVENTS && rc == TC_OK; e++)
+    if (waits[e] && hipStreamWaitEvent(st, d.ev[e], 0) != hipSuccess) rc = TC_ERR_HIP;
   if (rc != TC_OK) {
     (void)hipGetLastError();  // it is reported here, not by the next launch
     tr_mx.unlock();
@@ -769,29 +795,29 @@ TrTurn::TrTurn(int P, int images, int xcds_, hipStream_t st_) : xcds(xcds_ < 8 ?
 
 int TrTurn::done() {
   if (!apart) return TC_OK;
-  const bool ok = hipEventRecord(tr_ev[dev][first], st) == hipSuccess;
+  TrDevice& d = tr_devices[dev];
+  const bool ok = hipEventRecord(d.ev[event], st) == hipSuccess;
   if (!ok) {
     (void)hipStreamSynchronize(st);  // nobody can wait for this launch, so it is over
     (void)hipGetLastError();
   }
-  for (int i = 0; i < count; i++) tr_last[dev][(first + i) % xcds] = (unsigned char)first;
-  tr_next[dev] = (first + count) % xcds;
+  for (int i = 0; i < count * places; i++) d.last[unit(i)] = (unsigned char)(event + 1);
   tr_mx.unlock();
   return ok ? TC_OK : TC_ERR_HIP;
 }
 
 int launch_columns(const Plan& pl, const TrPhase& ph, double* G, double* dvec, double* evec, float* tauv, float* Vc, u64* sync,
-                   size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st);  // tridiag_columns.hip
+                   size_t stride, u64* arrived, int patience, bool sixteen, int xcds, int32_t* fail, hipStream_t st);  // tridiag_columns.hip
 
 template <int PC>
 static int tr_launch(const Plan& pl, const TrPhase& ph, int mirror, double* G, double* dvec, double* evec, float* tauv, float* Vc,
-                     u64* sync, size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st) {
+                     u64* sync, size_t stride, u64* arrived, int patience, bool sixteen, int xcds, int32_t* fail, hipStream_t st) {
   typedef TrShape<PC> S;
   if (S::LDS > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_kernel<PC>),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS) != hipSuccess)
     return TC_ERR_HIP;
   const int grid = (S::MODE == 1 ? (pl.B + xcds - 1) / xcds * xcds : pl.B) * S::P;
-  TrTurn turn(S::P, xcds, xcds, st);
+  TrTurn turn(S::P, false, pl.B, sixteen, xcds, st);
   if (turn.rc != TC_OK) return turn.rc;
   TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_kernel<PC><<<grid, TR_THREADS, S::LDS, st>>>(G, pl.N, pl.Np, pl.B, ph.first, ph.last, ph.first == 0, mirror, dvec, evec, tauv, Vc, sync, stride, arrived, patience, xcds, fail)));
   const int rc = check_launch(), rc2 = turn.done();
@@ -810,7 +836,8 @@ int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float*
   u64* sy = static_cast<u64*>(sync);
   const unsigned per = (unsigned)((words + TR_SIZES + 1023) / 1024);
   TC_TIMED(PK_TRIDIAG_UPDATE, 0, st, (tridiag_clear_kernel<<<dim3(per > 64 ? 64 : per, pl.B), 256, 0, st>>>(sy, stride, words + TR_SIZES, fail)));
-  bool alone = false;
+  bool alone = false, sixteen = false;
+  for (int i = 0; i < n; i++) sixteen |= tr_local(ph[i].size) && TR_FRAMES[ph[i].size].P == 16;
   for (int i = 0; i < n; i++) {
     const int set = tc_group_patience, patience = set >= 0 ? set : i + 1 >= -set ? -1 : TR_PATIENCE;
     const int mirror = i + 1 < n && ph[i + 1].size >= TR_TRIANGLES;  // whole columns want both triangles
@@ -818,10 +845,10 @@ int launch_tridiag(const Plan& pl, double* G, double* dvec, double* evec, float*
     u64* arrived = sy + words + i;
     int rc;
     alone |= TR_FRAMES[ph[i].size].P > 1;
-#define TR_CASE(PC_) case PC_: rc = tr_launch<PC_>(pl, ph[i], mirror, G, dvec, evec, tauv, Vc, words_of, stride, arrived, patience, xcds, fail, st); break;
+#define TR_CASE(PC_) case PC_: rc = tr_launch<PC_>(pl, ph[i], mirror, G, dvec, evec, tauv, Vc, words_of, stride, arrived, patience, sixteen, xcds, fail, st); break;
     switch (ph[i].size) {
       TR_CASE(0) TR_CASE(1) TR_CASE(2) TR_CASE(3) TR_CASE(4) TR_CASE(5) TR_CASE(6)
-      default: rc = launch_columns(pl, ph[i], G, dvec, evec, tauv, Vc, words_of, stride, arrived, patience, xcds, fail, st);
+      default: rc = launch_columns(pl, ph[i], G, dvec, evec, tauv, Vc, words_of, stride, arrived, patience, sixteen, xcds, fail, st);
     }
 #undef TR_CASE
     if (rc != TC_OK) return rc;

@@ -696,13 +696,13 @@ __global__ __launch_bounds__(256) void tridiag_last_kernel(double* __restrict__ 
 
 template <class S>
 static int launch_shape(const Plan& pl, const TrPhase& ph, double* G, double* dvec, double* evec, float* tauv, float* Vc, u64* sync,
-                        size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st) {
+                        size_t stride, u64* arrived, int patience, bool sixteen, int xcds, int32_t* fail, hipStream_t st) {
   if (S::LDS > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(tridiag_columns_kernel<S>),
                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS) != hipSuccess)
     return TC_ERR_HIP;
   // Captured launches cannot be kept apart.  Up to eight members on one XCD do no harm then (see TrTurn); sixteen are spread
   // over the XCDs like larger groups.
-  TrTurn turn(S::P, S::LOCAL ? pl.B : xcds, xcds, st);
+  TrTurn turn(S::P, S::LOCAL, pl.B, sixteen, xcds, st);
   if (turn.rc != TC_OK) return turn.rc;
   const int shift = turn.captured && S::P > 8 ? -1 : turn.first;
   const int grid = (S::LOCAL ? (pl.B + xcds - 1) / xcds * xcds : pl.B) * S::P;
@@ -712,12 +712,12 @@ static int launch_shape(const Plan& pl, const TrPhase& ph, double* G, double* dv
 }
 
 int launch_columns(const Plan& pl, const TrPhase& ph, double* G, double* dvec, double* evec, float* tauv, float* Vc, u64* sync,
-                   size_t stride, u64* arrived, int patience, int xcds, int32_t* fail, hipStream_t st) {
+                   size_t stride, u64* arrived, int patience, bool sixteen, int xcds, int32_t* fail, hipStream_t st) {
   switch (ph.size) {
     case TR_LAST_SIZE:
       TC_TIMED(PK_TRIDIAG, 0, st, (tridiag_last_kernel<<<pl.B, 256, 0, st>>>(G, pl.N, pl.Np, ph.first, dvec, evec, tauv, Vc, fail)));
       return check_launch();
-#define TC_CASE(N_, LI_, LK_, P_, US_) case N_: return launch_shape<TcShape<LI_, LK_, P_>>(pl, ph, G, dvec, evec, tauv, Vc, sync, stride, arrived, patience, xcds, fail, st);
+#define TC_CASE(N_, LI_, LK_, P_, US_) case N_: return launch_shape<TcShape<LI_, LK_, P_>>(pl, ph, G, dvec, evec, tauv, Vc, sync, stride, arrived, patience, sixteen, xcds, fail, st);
     TC_FRAMES(TC_CASE)
 #undef TC_CASE
   }

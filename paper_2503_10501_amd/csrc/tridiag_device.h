@@ -4,20 +4,22 @@
 #include <utility>
 
 #include "tc_internal.h"
+#include "tridiag_frames.h"
 
 namespace tc {
 
 typedef unsigned long long u64;
 
-// The turn of a launch whose groups have P members and lie on `images` XCDs (tridiag.hip): taken before the launch,
-// over with done(), which is called after it in any case.
+// The turn of a launch with groups of P, each on one XCD (local) or spread over them, in a call that has groups of sixteen or not
+// (tridiag.hip): taken before the launch, over with done(), which is called after it in any case.
 struct TrTurn {
   int rc, first = 0;      // status; number of the first XCD
   bool captured, apart;   // the stream is being captured; the launch is kept apart from others
-  TrTurn(int P, int images, int xcds, hipStream_t st);
+  TrTurn(int P, bool local, int images, bool sixteen, int xcds, hipStream_t st);
   int done();
  private:
-  int count = 0, dev = 0, xcds;
+  int unit(int i) const { return TR_PLACES * ((first + i / places) % xcds) + from + i % places; }
+  int count = 0, places = 1, from = 0, event = 0, dev = 0, xcds;
   hipStream_t st;
 };
 

@@ -133,7 +133,23 @@ inline bool tr_runs(int N, int cus, bool captured) {
   return size < TR_TRIANGLES && tr_holds(TR_FRAMES[size].P, cus, captured);
 }
 
-// Launches that the host keeps apart (see TrTurn).
+// Launches that the host keeps apart (see TrTurn): most workgroups of one that may wait on an XCD at once, and how many of its
+// places the launch takes there; all, too, where its workgroups would fill the XCD anyway.
+constexpr int TR_PLACES = 19;
 inline bool tr_apart(int P) { return P > 4; }
+inline bool tr_local(int size) { return TR_FRAMES[size].mode == 4 && TR_FRAMES[size].P <= 16; }
+inline int tr_places(int P, bool local, int images, int xcds) {
+  const long long all = ((long long)P * images + xcds - 1) / xcds, waiting = local ? P - 1 : all;
+  return all >= 32 || waiting - 3 > TR_PLACES ? TR_PLACES : waiting > 4 ? (int)waiting - 3 : 1;
+}
+// The first of these places.  Groups of sixteen take TR_SIXTEEN from 0 on; launches of their calls (sixteen) with groups that are spread make
+// do with the rest, and so do groups of eight behind them on all XCDs.
+constexpr int TR_SIXTEEN = 12;
+inline int tr_first_place(int places, bool local, bool all, bool sixteen, unsigned slot) {
+  constexpr int rest = TR_PLACES - TR_SIXTEEN;
+  if (places > rest) return sixteen || 2 * places > TR_PLACES ? 0 : places * (int)(slot % 2);
+  if (sixteen) return !local ? TR_SIXTEEN + places * (int)(slot % (rest / places)) : all ? TR_PLACES - places : 0;
+  return TR_PLACES - places * (1 + (int)(slot % (TR_PLACES / places)));
+}
 
 }  // namespace tc
