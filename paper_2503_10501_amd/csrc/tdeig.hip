@@ -436,6 +436,12 @@ __device__ __forceinline__ double tw_rcp(double x) {
   return fma(fma(-x, r, 1.0), r, r);
 }
 
+// LDS beyond 64 KB, what the kernel itself declares (fixed) and what its launch adds, has to be asked for.
+static bool td_lds(const void* kernel, size_t fixed, size_t added) {
+  return fixed + added <= 64 * 1024 || hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)added) == hipSuccess;
+}
+
+constexpr size_t TW_FIXED = 3 * 4 * 64 * 8 + 4 * 64 * 4 + 64 * 8 + 2 * 2 * TW_SEG * 64 * 4;
 static size_t td_twisted_lds(int N) {
   const int nseg = (N + TW_SEG - 1) / TW_SEG;
   return (size_t)(nseg * TW_SEG + 1) * 16 + (size_t)nseg * 4;
@@ -899,6 +905,7 @@ __global__ __launch_bounds__(256) void td_pairs_kernel(const double* __restrict_
 // finite) gets bad[b], and the caller's info turns negative.
 constexpr int TO_THREADS = 512, TO_WAVES = TO_THREADS / 64;
 constexpr int TO_SLOTS = 16;  // of a workgroup (288 pairs in one image of 577 tokens: a chain of 0.4 ms each)
+constexpr size_t TO_FIXED = TO_WAVES * 8;
 static size_t td_orthogonalise_lds(int N) { return (size_t)N * 5 * 8 + (TO_WAVES + 1) * 64 * 8 + round_up(N, 16) + (size_t)N * 4; }
 
 __global__ __launch_bounds__(TO_THREADS) void td_orthogonalise_kernel(const double* __restrict__ dvec, const double* __restrict__ evec,
@@ -1367,9 +1374,7 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
   }
   {
     const size_t shm = td_twisted_lds(N);
-    if (shm > 48 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_twisted_kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
-      return TC_ERR_HIP;
+    if (!td_lds(reinterpret_cast<const void*>(td_twisted_kernel), TW_FIXED, shm)) return TC_ERR_HIP;
     TC_TIMED(PK_TWISTED, 0, st, (td_twisted_kernel<<<dim3((N + 63) / 64, B), 256, shm, st>>>(dvec, evec, lam, blk, tnorm, scratch, stride, W, rn, any, N, Np)));
   }
   const int nt = (N + 63) / 64;
@@ -1382,9 +1387,7 @@ int launch_td_eigen(const Plan& pl, const double* dvec, const double* evec, cons
   TC_TIMED(PK_TWISTED, 1, st, (td_pairs_kernel<<<dim3(nt * (nt + 1) / 2, B), 256, 0, st>>>(lam, blk, tnorm, W, rn, mark, any, probe ? need : nullptr, N, Np)));
   {
     const size_t shm = td_orthogonalise_lds(N);
-    if (shm > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(td_orthogonalise_kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
-      return TC_ERR_HIP;
+    if (!td_lds(reinterpret_cast<const void*>(td_orthogonalise_kernel), TO_FIXED, shm)) return TC_ERR_HIP;
     TC_TIMED(PK_TWISTED, 2, st, (td_orthogonalise_kernel<<<dim3((N + TO_SLOTS - 1) / TO_SLOTS, B), TO_THREADS, shm, st>>>(dvec, evec, lam, blk, tnorm, mark, any, W, rn, bad, N, Np)));
   }
   TC_TIMED(PK_BISECT, 1, st, (td_weights_kernel<<<B, 256, shm_sig, st>>>(lam, rn, tnorm, bad, sv_rtol, sig, wgt, sigma_out, info_out, N, Np)));
