@@ -519,6 +519,13 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   }
 }
 
+// What lanes of this wavefront have written to LDS before is there for its other lanes after (no instruction: it keeps the compiler
+// from moving accesses across).
+__device__ __forceinline__ void between_lanes() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---- the last columns -------------------------------------------------------------------------------------------
 // Up to 128 rows by one workgroup of four wavefronts, one per SIMD: wavefront w owns the columns 16 k + 4 w + (lane & 3), a lane of
 // them the rows 16 i + (lane >> 2).  The vectors' part is done by every wavefront for itself, bit for bit the same, with copies of
@@ -663,6 +670,7 @@ __global__ __launch_bounds__(256) void tridiag_last_kernel(double* __restrict__ 
           tb[q] = (float)tau;
           db[(jr + 1) & 31] = d;
         }
+        between_lanes();
         if (q == 15 || j == F - 2) {
 #pragma unroll
           for (int u = 0; u < 2; u++) {
@@ -685,6 +693,7 @@ __global__ __launch_bounds__(256) void tridiag_last_kernel(double* __restrict__ 
           }
         }
       }
+      between_lanes();  // (X, V, W to the next column; sixteen results before the next overwrites them)
     }
   });
   if (tid == 3 * 64) {
