@@ -126,8 +126,11 @@ __device__ __forceinline__ void walk_down(int least, F f) {
     }
 }
 
-// A store that the other members can poll.  Members on one XCD share its L2: a plain store ends there and the polls find it.
-// Elsewhere it has to go on to memory (one way from store to poll, measured with 64 lanes: 800 clocks and 1300 to 1700).
+// A store that the other members can poll.  Members on one XCD (known from XCC_ID, not assumed) share its L2: the store ends there and
+// the polls find it.  Elsewhere it has to go on to memory (one way from store to poll, measured with 64 lanes: 800 clocks and 1300 to
+// 1700).  The near store stands on the machine, not on the memory model, which promises a store of workgroup scope to its own workgroup
+// only: L1 writes through, so global_store with sc0 and without sc1 ends in the L2 of the XCD, and a load with sc1 passes L1 by.  The value
+// carries its own tag, so nothing else has to be ordered with it.
 __device__ __forceinline__ void publish_to(bool near, u64* p, double v, unsigned tag) {
   const u64 y = tagged(v, tag);
   if (near) __hip_atomic_store(p, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

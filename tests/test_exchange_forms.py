@@ -29,3 +29,16 @@ def test_lanes_that_exchange_through_lds_are_kept_in_order(kernels):
     last = [code for name, code in kernels.items() if "tridiag_last_kernel" in name]
     assert len(last) == 1
     assert last[0].count("; wave barrier") >= 16
+
+
+def test_near_and_far_stores_have_the_forms_that_the_polls_find(kernels):
+    columns = [code for name, code in kernels.items() if "tridiag_columns_kernel" in name]
+    assert len(columns) == 9
+    for code in columns:
+        flags = [line.split(";")[0].split() for line in code.splitlines() if re.match(r"\s(global|flat)_(store|load)_dwordx2 ", line)]
+        flags = [(f[0], {x for x in f if x in ("sc0", "sc1", "nt")}) for f in flags]
+        stores = [x for op, x in flags if op == "global_store_dwordx2"]
+        near, far = stores.count({"sc0"}), stores.count({"sc1"})
+        assert far > 0 and all(not x or x in ({"sc0"}, {"sc1"}) for x in stores) and not any(op.startswith("flat") for op, _ in flags)
+        assert near == far
+        assert sum(x == {"sc1"} for op, x in flags if op == "global_load_dwordx2") > 0
