@@ -118,9 +118,11 @@ inline int tr_phases(int N, int B, int cus, TrPhase* out, size_t* words, bool ca
 }
 
 // Exchange memory of one image in words of 8 bytes: that of every frame that may take part (which do depends on the number of
-// images; the size of a workspace must not fall when that or N grows), and an arrival counter per phase.
+// images; the size of a workspace must not fall when that or N grows), and an arrival counter per phase.  (Up to TR_LAST tokens one
+// workgroup does all columns.)
 inline size_t tr_sync_words(int N) {
   size_t words = TR_SIZES;
+  if (N <= TR_LAST) return words;
   const int top = tr_triangle(N), F = top < 2 ? TR_FRAMES[1].F : TR_FRAMES[top < TR_TRIANGLES ? top : TR_TRIANGLES - 1].F;
   for (const TrFrame& f : TR_FRAMES)
     if (f.F <= F) words += f.words;

@@ -75,3 +75,31 @@ def test_a_group_fits_the_device(ask, cus, most, captured):
 
 def test_the_end_of_the_frames(ask):
     assert [bool(r[4]) for r in ask([(3456, 1, 256), (3457, 1, 256)])] == [True, False]
+
+
+# The same for captured streams too, with the rows that a frame has to leave to the next one.
+CAPTURED = PROGRAM.replace("int N, B, cus;", "int N, B, cus, captured;").replace('"%d %d %d", &N, &B, &cus) == 3', '"%d %d %d %d", &N, &B, &cus, &captured) == 4')
+CAPTURED = CAPTURED.replace("&words);", "&words, captured != 0);").replace("tr_apart(TR_FRAMES[ph[i].size].P)", "TR_FRAMES[ph[i].size].least")
+
+
+@pytest.fixture(scope="module")
+def ask_captured(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("captured")
+    (d / "frames.cpp").write_text(CAPTURED)
+    subprocess.run([gxx, "-std=c++20", "-O1", "-I", CSRC, str(d / "frames.cpp"), "-o", str(d / "frames")], check=True)
+
+    def run(questions):
+        out = subprocess.run([str(d / "frames")], input="\n".join("%d %d %d %d" % q for q in questions), capture_output=True, text=True, check=True)
+        rows = [[int(x) for x in line.split()] for line in out.stdout.splitlines()]
+        assert len(rows) == len(questions)
+        return [(r[0], r[1], r[2], r[3], [tuple(r[5 + 5 * i:10 + 5 * i]) for i in range(r[4])]) for r in rows]
+    return run
+
+
+def test_the_room_for_exchanges_never_falls_and_is_small_where_there_are_none(ask_captured):
+    rooms = [r[3] for r in ask_captured([(n, 1, 256, 0) for n in range(1, 3457)])]
+    assert rooms == sorted(rooms)
+    assert rooms[127] * 8 <= 256   # up to 128 tokens: one workgroup
