@@ -77,9 +77,11 @@ typedef enum { TC_EIG_F64 = 0, TC_EIG_F32 = 1 } tc_eig_dtype;
    TC_EIG_AUTO         the tridiagonal route for float64 and n_vis <= 3456 (1728 while the stream is
                        being captured into a graph), else Jacobi; less on a partition of the GPU with fewer than 256
                        compute units (1152 on one with 32).
-   Above 256 tokens the tridiagonal route shares an image between workgroups that must be resident together.  Where the
+   Above 128 tokens the tridiagonal route shares an image between workgroups that must be resident together.  Where the
    compute units are taken (by other processes, say) for a quarter of a second, the image is reduced by one workgroup
-   instead: the result is the same but for rounding, and late (18 ms for 576 tokens, 2.6 s for 2880). */
+   instead: the result is the same but for rounding, and late (18 ms for 576 tokens, 2.6 s for 2880).  While the stream is being
+   captured, above 768 tokens smaller groups are used than otherwise (on a partition of 128, 64 or 32 compute units above
+   576, 448 or 128): a replay and a call that is not captured differ by rounding there, and agree in every bit below. */
 typedef enum { TC_EIG_AUTO = 0, TC_EIG_JACOBI = 1, TC_EIG_TRIDIAGONAL = 2 } tc_eig_method;
 
 typedef struct {

@@ -103,3 +103,30 @@ def test_the_room_for_exchanges_never_falls_and_is_small_where_there_are_none(as
     rooms = [r[3] for r in ask_captured([(n, 1, 256, 0) for n in range(1, 3457)])]
     assert rooms == sorted(rooms)
     assert rooms[127] * 8 <= 256   # up to 128 tokens: one workgroup
+
+
+# first and last size of every frame, and where that of the last 128 rows ends
+EDGES = sorted({n + d for n in (128, 256, 320, 384, 448, 576, 768, 1152, 1536, 1728, 1920, 2112, 2304, 2880, 3456) for d in (-1, 0, 1, 2)} - {3457, 3458})
+
+
+@pytest.mark.parametrize("captured", [0, 1])
+@pytest.mark.parametrize("cus", [256, 128, 64, 32])
+def test_phases_at_the_edges_of_the_frames(ask_captured, cus, captured):
+    questions = [(n, b, cus, captured) for n in EDGES for b in (1, 2, 8, 16, 33, 64, 97, 300)]
+    for (n, b, _, _), (runs, in_graph, words, room, phases) in zip(questions, ask_captured(questions)):
+        if not (in_graph if captured else runs):
+            continue
+        assert phases[0][2] == 0 and phases[-1][3] == n and words + len(phases) <= room
+        for (F, P, first, last, least), nxt in zip(phases, phases[1:]):
+            assert last == nxt[2] and last % 16 == 0 and first < last and n - first <= F
+            assert n - last >= least, (n, b)   # whole columns: every workgroup has one to publish up to the last
+        assert n - phases[-1][2] <= phases[-1][0]
+        assert all((7 if captured else 1) * P <= cus or P == 1 for _, P, _, _, _ in phases), (n, b)
+
+
+def test_captured_phases_are_the_same_as_far_as_the_header_says(ask_captured):
+    for cus, same in ((256, 768), (128, 576), (64, 448), (32, 128)):
+        sizes = [n for n in range(1, 3457) if n <= same + 1]
+        one, other = (ask_captured([(n, b, cus, c) for n in sizes for b in (1, 3, 16, 64, 300)]) for c in (0, 1))
+        differ = [n for (n, _), x, y in zip(((n, b) for n in sizes for b in (1, 3, 16, 64, 300)), one, other) if x[4] != y[4]]
+        assert differ and min(differ) == same + 1, cus
