@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void tridiag_clear_kernel(u64* __restrict__ sy
 }
 
 // G      [B][Np][Np]  in: the Gram matrix (full != 0: stored in full, else the lower triangle of the trailing matrix that the
-//                     phase before left); out: the trailing matrix from column last on, lower triangle
+//                     phase before left); out: the trailing matrix from column last on, lower triangle (mirror != 0: both)
 // dvec   [B][Np]      out: diagonal of T
 // evec   [B][Np]      out: evec[j] = T[j+1][j], j < N-1
 // tauv   [B][Np]      out: tau_j (0 for a reflector that is the identity)

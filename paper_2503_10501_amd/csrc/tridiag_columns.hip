@@ -108,24 +108,6 @@ __device__ __forceinline__ double sum_lanes(double x, double y, double z, int la
   return lanes_of_blocks(d);
 }
 
-// f(n) with n as a constant, lo <= n < hi.
-template <int lo, int hi, typename F>
-__device__ __forceinline__ void with_constant(int n, F f) {
-  if constexpr (hi - lo == 1) f(std::integral_constant<int, lo>{});
-  else if (n < (lo + hi) / 2) with_constant<lo, (lo + hi) / 2>(n, f);
-  else with_constant<(lo + hi) / 2, hi>(n, f);
-}
-
-// f(n - 1), f(n - 2), ... with the index as a constant, as long as it is at least `least`.
-template <int n, typename F>
-__device__ __forceinline__ void walk_down(int least, F f) {
-  if constexpr (n > 0)
-    if (n - 1 >= least) {
-      f(std::integral_constant<int, n - 1>{});
-      walk_down<n - 1>(least, f);
-    }
-}
-
 // A store that the other members can poll.  Members on one XCD (known from XCC_ID, not assumed) share its L2: the store ends there and
 // the polls find it.  Elsewhere it has to go on to memory (one way from store to poll, measured with 64 lanes: 800 clocks and 1300 to
 // 1700).  The near store stands on the machine, not on the memory model, which promises a store of workgroup scope to its own workgroup
@@ -142,7 +124,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     double* __restrict__ G, int N, int Np, int B, int first, int last, double* __restrict__ dvec, double* __restrict__ evec,
     float* __restrict__ tauv, float* __restrict__ Vc, u64* __restrict__ sync, size_t sync_stride, u64* __restrict__ arrived,
     int patience, int xcds, int shift, int32_t* __restrict__ fail) {
-  constexpr int LI = S::LI, LK = S::LK, P = S::P, F = S::F, CW = S::CW, CO = S::CO, E = S::E, RO = S::RO;
+  constexpr int LI = S::LI, LK = S::LK, P = S::P, F = S::F, CW = S::CW, E = S::E, RO = S::RO;
   constexpr int OT = 256, FP = S::FP, OFF = FP - F;   // the vectors have room for elements that no row belongs to
   extern __shared__ __attribute__((aligned(16))) unsigned char tc_smem[];
   double* Va = reinterpret_cast<double*>(tc_smem);  // [FP] reflector of the even columns
@@ -195,7 +177,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   for (int f = js + tid; f < F; f += TR_THREADS) X[OFF + f] = A0[(size_t)first * Np + f + base];
 
   if (w >= 4) {  // ==== a wavefront of the matrix =========================================================================
-    const int cw = m * 4 + w - 4 - CO;  // column of class k: cw + k CW
+    const int cw = m * 4 + w - 4;  // column of class k: cw + k CW
     double A[LI][LK];
 #pragma unroll
     for (int k = 0; k < LK; k++)
@@ -208,8 +190,8 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     // from c on).
     auto publish_column = [&](auto kc, int c) __attribute__((always_inline)) {
       constexpr int K = decltype(kc)::value;
-      const int k = (c + CO) / CW;
-      if ((c + CO) - k * CW != m * 4 + w - 4) return;
+      const int k = c / CW;
+      if (c - k * CW != cw) return;
       const int n = c - 1 - js;  // use of the slots
       const unsigned tag = ((n >> 2) & 1) ^ 1;
       u64* dst = Cn + (size_t)(n & 3) * F;
@@ -223,14 +205,14 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         }
     };
     walk_up<0, LK>([&](auto kc) __attribute__((always_inline)) {
-      if ((js + 1 + CO) / CW == decltype(kc)::value) publish_column(kc, js + 1);
+      if ((js + 1) / CW == decltype(kc)::value) publish_column(kc, js + 1);
     });
     __builtin_amdgcn_s_waitcnt(0);  // (the matrix is there: no wait for it inside the loop)
     __syncthreads();
     int j = js;
     walk_up<0, LK>([&](auto kc) __attribute__((always_inline)) {
       // columns whose product needs the classes from K on
-      constexpr int K = decltype(kc)::value, n = LK - K, i0 = (K * CW - CO > 0 ? K * CW - CO : 0) / 64, end = (K + 1) * CW - CO - 1;
+      constexpr int K = decltype(kc)::value, n = LK - K, i0 = K * CW / 64, end = (K + 1) * CW - 1;
       if (j >= end) return;
       // Sums of M columns at a time: more take registers that the matrix needs.  ypl: byte offsets of the products that this lane
       // publishes (0: none)
@@ -238,8 +220,8 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       int ypl[PARTS];
 #pragma unroll
       for (int h = 0; h < PARTS; h++) {
-        const int q = place_of_sum<M>(lane), cq = (K + h * M + q) * CW + cw;
-        ypl[h] = q < 0 || h * M + q >= n || cq < 0 ? 0 : 8 * cq;
+        const int q = place_of_sum<M>(lane);
+        ypl[h] = q < 0 || h * M + q >= n ? 0 : 8 * ((K + h * M + q) * CW + cw);
       }
       for (; j < min(je, end); j++) {
         int lj = lane;
@@ -293,7 +275,7 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         // ---- the update with the column before ------------------------------------------------------------------
         fresh<true>(lj);
         // the columns' values: lane k reads those of class k, which then come from scalar registers
-        const int cl = max(OFF + min(lj, LK - 1) * CW + cw, 0);
+        const int cl = OFF + min(lj, LK - 1) * CW + cw;
         const double vcl = -Vo[cl], wcl = -Wv[cl];
         constexpr int T = 3;  // rows read ahead
 #pragma unroll

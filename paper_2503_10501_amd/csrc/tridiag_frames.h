@@ -35,18 +35,18 @@ struct TcShape {
   static constexpr bool LOCAL = P <= 16;    // a group lies on one XCD
   static constexpr int F = 64 * LI;         // rows
   static constexpr int CW = 4 * P;          // columns of a class: one for every wavefront of the group that holds the matrix
-  static constexpr int CO = LK * CW - F;    // columns the classes have in front of the frame's first
   static constexpr int E = (F + 255) / 256, FP = 256 * E;  // vector elements of a thread; room of a vector
   static constexpr int RO = (F + P - 1) / P;    // rows of the reflectors that a workgroup writes
   static constexpr size_t WORDS = (size_t)6 * F;  // exchange: two slots of products, four of next columns
   static constexpr size_t LDS = (size_t)(5 * FP + 52) * 8 + (size_t)(RO * 16 + 16) * 4 + 16;
   static_assert(LK <= 32, "sums and columns of one wavefront");
-  static_assert(CO >= 0 && CO < CW, "the classes must cover the frame");
+  static_assert(LK * CW == F, "the classes must cover the frame");
   static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
 };
 
 constexpr int TR_LAST = 128;  // rows that one workgroup of four wavefronts reduces (tridiag_last_kernel)
 
+// mode: TrShape::MODE of a triangle, 3 the last columns, 4 whole columns;
 // least: rows a frame leaves at least (all of its workgroups must have a column to publish); us: time of a column in microseconds,
 // from which the phases are chosen.
 struct TrFrame { int mode, F, P; size_t words; int least; double us; };
