@@ -1,4 +1,4 @@
-"""GPU tests of the contribution score on attention outputs in hand: the frames of the reduction to tridiagonal form
+"""GPU tests of the contribution score on attention outputs in hand: the triangular frames of the reduction to tridiagonal form
 (256, 576 and multiples of 576 tokens), the split contraction of the Gram matrix, captured graphs and concurrent calls."""
 import ctypes
 
@@ -99,7 +99,8 @@ def test_a_captured_call_replays_to_the_eager_result(n, batch):
 
 
 def test_captured_calls_replay_on_two_streams_at_once():
-    # groups of 16 that nothing keeps apart: 160 workgroups each.  An image whose group gave up differs by rounding
+    # groups of 32 and of 16, spread over the XCDs, that nothing keeps apart: 320 and 160 workgroups each.  An image whose group gave up
+    # differs by rounding
     tc = _tc()
     calls, graphs, want = [], [], []
     for i in range(2):
@@ -143,8 +144,8 @@ def test_the_rank_of_some_rows_fits_the_workspace_of_all(n, rows):
     assert abs(int(rank) - int((s > 1e-3 * s.max()).sum())) <= 1   # a value at the threshold
 
 
-# (calls, tokens, images): workgroups that wait for each other, all calls together: 192 of 64 (which fit the chip at once), 320 of
-# 16, 384 of 36, 576 of 64, 176 of 4 beside 128 of 16
+# (calls, tokens, images): workgroups of the widest groups, all calls together: 480 of 160 (one image a call); 640 of 32, then 320 of 16; 180
+# of 36 beside 512 and 160 of 128 and 160; 576 of 64 (the triangle); 704 of 16 beside 128 of 16 (the triangle)
 @pytest.mark.parametrize("shapes", [[(1729, 1)] * 3, [(701, 10)] * 2, [(1400, 5), (1153, 4), (1729, 1)], [(2200, 3)] * 3,
                                     [(576, 22), (576, 22), (900, 8)]])
 def test_calls_on_several_streams_at_once(shapes):
@@ -182,9 +183,9 @@ def test_groups_of_images_give_what_one_group_gives(n, batch):
 
 
 @pytest.mark.parametrize("n,batch,phase", [(257, 1, 0), (300, 9, 0), (576, 2, 0), (577, 2, 0), (577, 2, 1), (1000, 1, 1), (1153, 2, 0),
-                                           (1153, 2, 1), (1729, 1, 2)])
+                                           (1153, 2, 1), (1729, 1, 2), (576, 64, 1), (576, 64, 3), (901, 8, 1), (1729, 3, 1)])
 def test_images_whose_groups_are_not_resident_at_once(n, batch, phase):
-    # the groups give up from this phase on: one workgroup per image does the rest
+    # the groups give up from this phase on: one workgroup per image does the rest.  (The last four: columns behind a triangle)
     tc = _tc()
     patience = ctypes.c_int.in_dll(tc.load_library(), "tc_group_patience")
     O = _rows(batch, n, 512, 7 * n)
