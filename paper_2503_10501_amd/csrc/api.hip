@@ -139,11 +139,12 @@ static int direct_chain(const Plan& pl, const Plan& sub, int img0, const tc_para
 // Tridiagonal route: the batch can be cut into groups of images whose chains run on the library's helper streams, each
 // group starting when the one before it has formed its Gram matrices.  The reduction holds the registers of its compute units
 // for as long as it runs, so another group's kernels only find room where the images need more than one round over the
-// chip several times over.  ms, one group and two (heads of 128: 16, 8 above 576 tokens): 576 tokens, 64 images 3.34 and 3.55, 72 4.73 and
-// 4.93, 96 5.18 and 5.50, 112 5.75 and 5.32, 128 6.17 and 6.12; 700 tokens, 72 images 7.62 and 8.27, 96 9.49 and 9.86; 1000, 72
-// 18.6 and 20.1; 450, 72 3.30 and 3.08 (the one case against), 96 3.44 and 3.57.  Where four or fewer compute units hold an image
-// for most columns it is above 256 images: 384 tokens, 128 images 2.69 and 2.74; 320 tokens, 256 3.23 and 3.40; 256 tokens, 256
-// 1.97 and 2.14, 300 2.73 and 2.47.
+// chip several times over.  ms, one group and two (heads of 128: 16, 8 above 576 tokens): 576 tokens, 64 images 3.34 and 3.55, 72 4.74 and
+// 4.88, 96 5.18 and 5.56, 97 5.49 and 4.84, 112 5.74 and 5.38, 128 6.17 and 6.12; 700 tokens, 72 images 7.58 and 8.27, 96 9.49 and 9.86; 1000,
+// 72 18.6 and 20.1; 450, 96 3.41 and 3.58.  Against the line: 65 images (576 tokens 4.37 and 4.14, 400 2.49 and 2.13), 80 up to 450 tokens
+// (400 2.75 and 2.64, 450 3.22 and 2.97), 72 of 450 (3.30 and 3.08; but 400 2.48 and 2.61, 550 4.21 and 4.66).  Where four or fewer compute
+// units hold an image for most columns it is above 256 images: 384 tokens, 128 images 2.69 and 2.74, 257 5.63 and 5.11; 320 tokens, 256 3.23 and
+// 3.40, 257 3.88 and 3.46; 256 tokens, 256 1.97 and 2.14, 257 2.51 and 2.23.
 static int front_chain(const Plan& pl, const tc_params* p, const void* Q, const void* K, const void* V, void* O,
                        float* S, float* score, float* ics, float* sigma, int32_t* info, void* ws, hipStream_t st) {
   if (pl.method != TC_EIG_TRIDIAGONAL || !tridiag_allowed(pl.N, st)) {

@@ -472,7 +472,7 @@ __global__ __launch_bounds__(256) void attn_score_reduce(const float* __restrict
 // before and now: 16 images of 300 tokens with 8 heads of 64 900 and 114, 4 of 100 with 4 of 128 110 and 26, one of 64 with 4 of 64
 // 23 and 12.5 (two launches), 2 of 2000 with 2 of 64 1050 and 117; error against float64, root mean square, 2.65e-7 and 1.93e-7,
 // 3.3e-7 and 2.3e-7, 1.9e-7 and 1.4e-7, 2.6e-7 and 2.2e-7 (short chains: eight wavefronts share the keys).  What bounds it now is the
-// wait for the rows of a tile.
+// wait for the rows of a tile.  (Heads of 128: 27 scalars wait in vector registers; nothing goes through scratch.)
 typedef __attribute__((ext_vector_type(4))) float f4v;
 
 // What a lane holds of a row that enters a product over the head dimension: in the steps 4 c .. 4 c + 3 the four lanes (0 .. 3) of a

@@ -20,7 +20,8 @@
 //   matrix:   A | A x, published | 0 | A <- A - v_o w_o^T - w_o v_o^T, next column published | B
 //   vectors:  A | w_o, its sums with x | 0 | reflector v, waiting for A x, p, its product with v | B | next column
 // Measured at 576 tokens on one XCD, clocks (2.4 GHz): A x 900 - 1300, reflector 900, waiting 600, p 500, next column 350: 3500 -
-// 4000, 1.45 us (the triangle 4.5 us, one workgroup for 256 tokens 2.3 us).  The whole reduction, ms, triangle and now: 64 tokens
+// 4000; with the loads and stores at the ends of a phase 1.7 us a column of the 576 frame and 1.3 of the 384 frame (the triangle 4.5 us, one
+// workgroup for 256 tokens 2.3 us).  The whole reduction, ms, triangle and now: 64 tokens
 // 0.097 and 0.051, 300 x 3 0.78 and 0.34, 576 x 1 2.05 and 0.80, x 16 2.07 and 0.83, x 64 2.2 and 1.8, 1152 x 1 5.4 and 2.1, 1499 x 2
 // 7.4 and 3.2, 2880 x 1 17.5 and 11.5.
 // Batches that fill the chip take the fewest workgroups an image that the registers allow: 320 rows by four, 448 by eight (100 and
@@ -232,7 +233,8 @@ __global__ __launch_bounds__(TR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         // ---- A x, this wavefront's columns --------------------------------------------------------------------
         {
           constexpr int NA = n > 2 || LI - i0 < 2 ? 1 : 2;  // (few columns: two chains each)
-          // (rows in turns: what is read ahead is bounded, so that the matrix stays in the registers)
+          // (rows in turns: what is read ahead is bounded, so that the matrix stays in the registers; the 1920 and 2112 frames
+          // have 2 and 40 registers too few: the compiler puts one store to scratch into the kernel, and twenty)
           constexpr int T = LI <= 12 ? LI : 6;
           auto below = [&](int i) {  // (zero up to and with the head)
             const double x = X[OFF + 64 * i + lj];
